@@ -59,14 +59,19 @@ bf_status bf_op_gemm_gelu_bwd_colsum(int dtype, int kernels, int M, int N, int K
 bf_status bf_op_gemm_splitk(int dtype, int kernels, int layout, int epilogue, int M, int N, int K, const void* A,
                             const void* B, void* C, const float* bias, const void* R, float* planes,
                             size_t planes_elems, void* stream);
-/* Slices that call would use for this shape (1: the contraction is not split). */
+/* Slices that call would use for this shape (1: the contraction is not split), and what its scratch is sized by.  A
+ * product of at most 512 tiles of 64 x 64 fills the chip with those and runs unsplit all the same. */
 int bf_op_gemm_splitk_slices(int layout, int epilogue, int M, int N, int K);
-/* 1 if the MFMA kernel takes this problem in bf16 mode, 0 if the plain kernel would run. */
+/* 1 if the problem is whole tiles of the bf16 MFMA kernel, 0 if not.  Other bf16 problems run on the same kernel with
+ * partly empty tiles where their rows are whole 16-byte chunks (N % 8 == 0, and K % 8 == 0 or, weight gradient, M % 8
+ * == 0), on the fp32 matrix instructions where they are not. */
 int bf_op_gemm_uses_mfma(int layout, int epilogue, int M, int N, int K);
 /* The tile of C (rows x columns per workgroup) that the MFMA kernel runs an unsplit product of this shape on by itself:
  * 256 x 256, 256 x 128, 128 x 128, or 256 x 192 (forward and dgrad layouts with the epilogues none, bias, bias + residual
  * and N a multiple of 192, where that fills the rounds of the grid better: 2048 x 6144 outputs are 256 such tiles).  A
- * step that runs two chains of micro-batches does not take the last shape.  Host arithmetic only.  Returns 1 and the tile in tile_m / tile_n (host ints), or 0
+ * step that runs two chains of micro-batches does not take the last shape.  Products of few tiles (at most 512 of 64 x 64,
+ * weight gradients 256) run on 64 x 64 tiles instead, and weight gradients with an odd multiple of 128 on partly empty
+ * 256 x 256 ones where that is faster; the shape given is the whole tile they would otherwise take.  Host arithmetic only.  Returns 1 and the tile in tile_m / tile_n (host ints), or 0
  * (and 0 x 0) where bf_op_gemm_uses_mfma is 0. */
 int bf_op_gemm_tile(int layout, int epilogue, int M, int N, int K, int* tile_m, int* tile_n);
 

@@ -81,6 +81,14 @@ bf_status gemm_plain(int dtype, int layout, int epi, const GemmArgs& a, hipStrea
 // true if the MFMA kernel covers this problem (bf16, sizes multiples of its tiles)
 bool gemm_mfma_supported(int layout, int epi, int M, int N, int K);
 bf_status gemm_mfma(int layout, int epi, const GemmArgs& a, hipStream_t st);
+// The same kernel on tiles that may reach past the product (bf16): any M, N % 8 == 0, and whole 16-byte chunks along
+// the fast dimension of the operands (K % 8 == 0, in the weight-gradient layout M % 8 == 0 with any K).
+bool gemm_mfma_edge_supported(int layout, int epi, int M, int N, int K);
+// true where a product of whole tiles runs faster in the edge form: on 64 x 64 tiles (few_tiles) or on partly empty
+// 256 x 256 ones
+bool gemm_mfma_edge_better(int layout, int M, int N);
+bool gemm_mfma_few_tiles(int layout, int M, int N);
+bf_status gemm_mfma_edge(int layout, int epi, const GemmArgs& a, hipStream_t st);
 // tile (rows x columns of C per workgroup) the MFMA kernel runs an unsplit product of this shape on; 0 x 0 if none fits
 void gemm_mfma_tile(int layout, int epi, int M, int N, int* bm, int* bn);
 // Slices the matrix-core path would cut the contraction of this forward / dgrad product into (1: no split).

@@ -81,8 +81,10 @@ struct Stager {
   u32x4 v[CHUNKS];
   uint32_t goff;  // byte offset of chunk 0 from the tile's first element
   int loff;       // element offset of chunk 0 inside the LDS tile
+  int kcol;       // first k of the thread's chunks inside the k-tile (K-contiguous operands)
 
   __device__ __forceinline__ void init(size_t ld, int tid) {
+    kcol = (tid & 7) * 8;
     if (KCONTIG) {
       const int row = tid >> 3, kc = tid & 7;  // 8 chunks per row of BK = 64
       goff = (uint32_t)(((size_t)row * ld + kc * 8) * sizeof(bf16_t));
@@ -92,6 +94,22 @@ struct Stager {
       goff = (uint32_t)(((size_t)krow * ld + rc * 8) * sizeof(bf16_t));
       loff = krow * (R + TPAD) + ((rc ^ tkey(krow)) << 3);
     }
+  }
+  // The same for a tile that may reach past the matrix (R_ext rows / columns, K long): the descriptor ends where the
+  // matrix ends, and loads past its end return zero.  That covers rows past R_ext of a K-contiguous operand and rows
+  // past K of the other kind; chunks past K of a K-contiguous row are sent past the end; columns past R_ext of a
+  // K-slow operand pick up values of the next row, which only reach outputs that are not stored.  The whole offset
+  // goes through the lane register: a scalar offset would take part in the range check by subtraction.
+  __device__ __forceinline__ void load_edge(const bf16_t* __restrict__ g, size_t ld, int r0, int k0, int R_ext, int K) {
+    const bf16_t* base = KCONTIG ? g + (size_t)r0 * ld + k0 : g + (size_t)k0 * ld + r0;
+    const size_t left = KCONTIG ? (size_t)(R_ext - r0) * ld - k0 : (size_t)(K - k0) * ld - r0;  // elements to the end
+    const size_t cap = (size_t)0x7fffff00 / sizeof(bf16_t);
+    __amdgpu_buffer_rsrc_t rsrc =
+        __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, (int)((left < cap ? left : cap) * sizeof(bf16_t)), 0x00020000);
+    const uint32_t step = (uint32_t)((size_t)ROWSTEP * ld * sizeof(bf16_t));
+    const uint32_t off = KCONTIG && kcol >= K - k0 ? 0x7fffff00u : goff;
+#pragma unroll
+    for (int i = 0; i < CHUNKS; ++i) v[i] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, off + i * step, 0, 0);
   }
   // g: operand base (uniform); r0: first row/col of the tile; k0: first k.  Buffer loads: the
   // descriptor carries the tile's base address, the lane offset is a VGPR, the chunk step an SGPR.
@@ -191,7 +209,9 @@ __device__ __forceinline__ bf16x8 load_frag(const bf16_t* lds, int r16, int kk, 
 // SEG_POW2: the k-tiles per segment are a power of two (weight gradient only; true for every
 // sequence length that is one): the segment of a k-tile is then a shift, not a division, which
 // takes 40 scalar instructions out of the loop (0.7-1 % of the product)
-template <typename TL, bool AK, bool BKC, int EPI, typename TO, bool SEG_POW2>
+// EDGE: the tiles may reach past M, N and K (K-contiguous rows a multiple of 8 long, outputs N % 8 == 0): guarded loads
+// (Stager::load_edge) and stores, everything else the same.
+template <typename TL, bool AK, bool BKC, int EPI, typename TO, bool SEG_POW2, bool EDGE>
 __global__ __launch_bounds__(TL::NT) void gemm_mfma_kernel(int M, int N, int K, const bf16_t* __restrict__ A,
                                                            const bf16_t* __restrict__ B, TO* __restrict__ C,
                                                            const float* __restrict__ bias, const TO* __restrict__ R,
@@ -260,7 +280,7 @@ __global__ __launch_bounds__(TL::NT) void gemm_mfma_kernel(int M, int N, int K, 
           for (int r = 0; r < 4; ++r) {
             const size_t row = m0 + wm * TL::TM + i * 16 + (lane >> 4) * 4 + r;
             const size_t col = n0 + wn * TL::TN + j * 16 + (lane & 15);
-            acc[i][j][r] = C[row * (size_t)N + col];
+            if (!EDGE || (row < (size_t)M && col < (size_t)N)) acc[i][j][r] = C[row * (size_t)N + col];
           }
     }
   }
@@ -285,11 +305,16 @@ __global__ __launch_bounds__(TL::NT) void gemm_mfma_kernel(int M, int N, int K, 
 #pragma unroll
         for (int q = 0; q < NQ; ++q) {
           const int c = tid + q * NT, lr = c / (BN / 8), lc = (c % (BN / 8)) * 8;
+          if (EDGE && (m0 + p * PR + lr >= M || n0 + lc >= N)) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) rpre[p][q][e] = (__bf16)0.f;
+            continue;
+          }
           rpre[p][q] = *reinterpret_cast<const bf16x8*>(reinterpret_cast<const bf16_t*>(R) + (size_t)(m0 + p * PR + lr) * N + n0 + lc);
         }
     }
   };
-  const int nk_seg = K / BK, nk = nk_seg * n_seg;
+  const int nk_seg = EDGE ? (K + BK - 1) / BK : K / BK, nk = nk_seg * n_seg;
   // k-tile kt lives in segment kt / nk_seg (one segment unless this is a multi-micro-batch weight gradient)
   // (only the weight-gradient product is launched with segments: the others skip the division)
   constexpr bool SEGS = EPI == E_ACCUM;
@@ -298,6 +323,14 @@ __global__ __launch_bounds__(TL::NT) void gemm_mfma_kernel(int M, int N, int K, 
   auto seg_a_of = [&](int kt) { return SEGS ? A + (size_t)seg_of(kt) * seg_a : A; };
   auto seg_b_of = [&](int kt) { return SEGS ? B + (size_t)seg_of(kt) * seg_b : B; };
   auto k0_of = [&](int kt) { return !SEGS ? kt * BK : SEG_POW2 ? (kt & (nk_seg - 1)) * BK : (kt % nk_seg) * BK; };
+  auto load_a = [&](int kt) {
+    if constexpr (EDGE) sa.load_edge(seg_a_of(kt), lda, m0, k0_of(kt), M, K);
+    else sa.load(seg_a_of(kt), lda, m0, k0_of(kt));
+  };
+  auto load_b = [&](int kt) {
+    if constexpr (EDGE) sb.load_edge(seg_b_of(kt), ldb, n0, k0_of(kt), N, K);
+    else sb.load(seg_b_of(kt), ldb, n0, k0_of(kt));
+  };
   {
     // A k-tile is two k-steps of 32; a k-step runs in two phases, one per half of the wave's A
     // fragments (MI / 2 x NI MFMAs each), so that only half of them are live at a time.  Phase p uses
@@ -364,13 +397,13 @@ __global__ __launch_bounds__(TL::NT) void gemm_mfma_kernel(int M, int N, int K, 
     typedef std::integral_constant<int, 0> H0;
     typedef std::integral_constant<int, 1> H1;
 
-    sa.load(A, lda, m0, 0);
-    sb.load(B, ldb, n0, 0);
+    load_a(0);
+    load_b(0);
     sa.store(smem);
     sb.store(smem + A_ST);
     if (nk > 1) {
-      sa.load(seg_a_of(1), lda, m0, k0_of(1));
-      sb.load(seg_b_of(1), ldb, n0, k0_of(1));
+      load_a(1);
+      load_b(1);
     }
     __syncthreads();
     ldA(0, smem, 0, 0);
@@ -394,8 +427,8 @@ __global__ __launch_bounds__(TL::NT) void gemm_mfma_kernel(int M, int N, int K, 
       // the registers are free again as soon as their LDS store has issued: the loads of tile kt+2
       // follow at once, a full k-tile ahead of their use
       if constexpr (decltype(do_load)::value) {
-        if constexpr (!SPLIT) sa.load(seg_a_of(kt + 2), lda, m0, k0_of(kt + 2));
-        sb.load(seg_b_of(kt + 2), ldb, n0, k0_of(kt + 2));
+        if constexpr (!SPLIT) load_a(kt + 2);
+        load_b(kt + 2);
       }
       mma(0, 0, H0{});
       if constexpr (decltype(do_load)::value) interleave2(RA{}, MW{}, NC0{}, MG{}, NC0{});
@@ -409,7 +442,7 @@ __global__ __launch_bounds__(TL::NT) void gemm_mfma_kernel(int M, int N, int K, 
       // phase 2
       ldA(1, as, 1, 1);
       if constexpr (SPLIT && decltype(do_store)::value) sa.store(smem + (cur ^ 1) * STAGE);
-      if constexpr (SPLIT && decltype(do_load)::value) sa.load(seg_a_of(kt + 2), lda, m0, k0_of(kt + 2));
+      if constexpr (SPLIT && decltype(do_load)::value) load_a(kt + 2);
       mma(0, 1, H0{});
       if constexpr (SPLIT && decltype(do_load)::value) interleave2(RA{}, MW{}, NC2{}, MG{}, NC2{});
       else if constexpr (SPLIT && decltype(do_store)::value) interleave2(RA{}, MW{}, NC2{}, MW{}, N0{});
@@ -440,7 +473,7 @@ __global__ __launch_bounds__(TL::NT) void gemm_mfma_kernel(int M, int N, int K, 
         for (int r = 0; r < 4; ++r) {
           const size_t row = m0 + wm * TL::TM + i * 16 + (lane >> 4) * 4 + r;
           const size_t col = n0 + wn * TL::TN + j * 16 + (lane & 15);
-          C[row * (size_t)N + col] = acc[i][j][r];
+          if (!EDGE || (row < (size_t)M && col < (size_t)N)) C[row * (size_t)N + col] = acc[i][j][r];
         }
   } else {
     // bf16 outputs: the fp32 accumulators pass through LDS, 64 tile rows at a time, so that every
@@ -470,6 +503,7 @@ __global__ __launch_bounds__(TL::NT) void gemm_mfma_kernel(int M, int N, int K, 
       for (int q = 0; q < NQ; ++q) {
         const int c = tid + q * NT, lr = c / (BN / 8), lc = (c % (BN / 8)) * 8;
         const size_t row = m0 + p * PR + lr, col = n0 + lc, idx = row * (size_t)N + col;
+        if (EDGE && (row >= (size_t)M || col >= (size_t)N)) continue;
         float v[8];
         *reinterpret_cast<f32x4*>(v) = *reinterpret_cast<const f32x4*>(cs + lr * LDC + lc);
         *reinterpret_cast<f32x4*>(v + 4) = *reinterpret_cast<const f32x4*>(cs + lr * LDC + lc + 4);
@@ -515,6 +549,7 @@ __global__ __launch_bounds__(TL::NT) void gemm_mfma_kernel(int M, int N, int K, 
         for (int e = 0; e < 8; ++e) cs[rg * BN + g * 8 + e] = csum[e];
         __syncthreads();
         for (int c = tid; c < BN; c += NT) {
+          if (EDGE && n0 + c >= N) break;
           float t = 0.f;
 #pragma unroll 8
           for (int r = 0; r < RG; ++r) t += cs[r * BN + c];
@@ -534,16 +569,19 @@ typedef Tile<128, 128, 2, 2> TileSmall;  // 4 waves, 64 x 64 per wave
 // tile's 24 column groups and keeps the other shapes.
 typedef Tile<256, 192, 4, 2> TileWide;
 
+// 4 waves, 32 x 32 per wave, for products of few tiles (edge form only)
+typedef Tile<64, 64, 2, 2> TileTiny;
+
 template <typename TL, bool AK, bool BKC>
 constexpr size_t lds_bytes() { return 2 * (size_t)(stage_elems<AK, TL::BM>() + stage_elems<BKC, TL::BN>()) * sizeof(bf16_t); }
 
-template <typename TL, bool AK, bool BKC, int EPI, typename TO, bool SEG_POW2 = false>
+template <typename TL, bool AK, bool BKC, int EPI, typename TO, bool EDGE = false, bool SEG_POW2 = false>
 bf_status launch(const GemmArgs& a, hipStream_t st) {
-  if constexpr (EPI == E_ACCUM && !SEG_POW2) {
+  if constexpr (EPI == E_ACCUM && !SEG_POW2 && !EDGE) {
     const int nk_seg = a.K / ((AK && a.k_slices > 1) ? a.k_slices : 1) / BK;
-    if ((nk_seg & (nk_seg - 1)) == 0) return launch<TL, AK, BKC, EPI, TO, true>(a, st);
+    if ((nk_seg & (nk_seg - 1)) == 0) return launch<TL, AK, BKC, EPI, TO, false, true>(a, st);
   }
-  auto kern = gemm_mfma_kernel<TL, AK, BKC, EPI, TO, SEG_POW2>;
+  auto kern = gemm_mfma_kernel<TL, AK, BKC, EPI, TO, SEG_POW2, EDGE>;
   constexpr size_t lds = lds_bytes<TL, AK, BKC>();
   // The LDS reservation is a per-device attribute of the kernel: one bit per device and instantiation,
   // set after the call has succeeded (two threads racing here both make the call, which is harmless).
@@ -556,7 +594,7 @@ bf_status launch(const GemmArgs& a, hipStream_t st) {
     if (e != hipSuccess) { set_error("gemm_mfma: cannot reserve %zu bytes of LDS: %s", lds, hipGetErrorString(e)); return BF_EDEVICE; }
     if (dev < 64) attr_set.fetch_or(bit, std::memory_order_release);
   }
-  const int tiles_m = a.M / TL::BM, tiles_n = a.N / TL::BN;
+  const int tiles_m = (a.M + TL::BM - 1) / TL::BM, tiles_n = (a.N + TL::BN - 1) / TL::BN;  // exact without EDGE
   const int remap = (tiles_m * tiles_n) % 8 == 0 ? 1 : 0;
   // split-K (fp32 planes of partial results, forward / dgrad layouts only): a.K is the whole contraction, the kernel
   // gets the slice length and the row length of the K-contiguous operands separately
@@ -571,30 +609,32 @@ bf_status launch(const GemmArgs& a, hipStream_t st) {
   return BF_OK;
 }
 
-template <typename TL, bool AK, bool BKC>
+template <typename TL, bool AK, bool BKC, bool EDGE>
 bf_status by_epilogue(int epi, const GemmArgs& a, hipStream_t st) {
   switch (epi) {
-    case E_NONE: return launch<TL, AK, BKC, E_NONE, bf16_t>(a, st);
-    case E_BIAS: return launch<TL, AK, BKC, E_BIAS, bf16_t>(a, st);
-    case E_BIAS_RES: return launch<TL, AK, BKC, E_BIAS_RES, bf16_t>(a, st);
-    case E_BIAS_GELU: return launch<TL, AK, BKC, E_BIAS_GELU, bf16_t>(a, st);
-    case E_GELU_BWD: return launch<TL, AK, BKC, E_GELU_BWD, bf16_t>(a, st);
+    case E_NONE: return launch<TL, AK, BKC, E_NONE, bf16_t, EDGE>(a, st);
+    case E_BIAS: return launch<TL, AK, BKC, E_BIAS, bf16_t, EDGE>(a, st);
+    case E_BIAS_RES: return launch<TL, AK, BKC, E_BIAS_RES, bf16_t, EDGE>(a, st);
+    case E_BIAS_GELU: return launch<TL, AK, BKC, E_BIAS_GELU, bf16_t, EDGE>(a, st);
+    case E_GELU_BWD: return launch<TL, AK, BKC, E_GELU_BWD, bf16_t, EDGE>(a, st);
     default: break;
   }
   set_error("gemm_mfma: epilogue %d not available for this layout", epi);
   return BF_EINVAL;
 }
 
-template <typename TL>
+template <typename TL, bool EDGE = false>
 bf_status by_layout(int layout, int epi, const GemmArgs& a, hipStream_t st) {
-  if (epi == E_ACCUM && layout != L_TN) {  // fp32 planes of a split contraction
-    if (layout == L_NN) return launch<TL, true, false, E_ACCUM, float>(a, st);
-    return launch<TL, true, true, E_ACCUM, float>(a, st);
+  if constexpr (!EDGE) {
+    if (epi == E_ACCUM && layout != L_TN) {  // fp32 planes of a split contraction
+      if (layout == L_NN) return launch<TL, true, false, E_ACCUM, float>(a, st);
+      return launch<TL, true, true, E_ACCUM, float>(a, st);
+    }
   }
-  if (layout == L_NN) return by_epilogue<TL, true, false>(epi, a, st);
-  if (layout == L_NT) return by_epilogue<TL, true, true>(epi, a, st);
+  if (layout == L_NN) return by_epilogue<TL, true, false, EDGE>(epi, a, st);
+  if (layout == L_NT) return by_epilogue<TL, true, true, EDGE>(epi, a, st);
   if (epi != E_ACCUM) { set_error("gemm_mfma: the weight-gradient layout stores fp32 with E_ACCUM only"); return BF_EINVAL; }
-  return launch<TL, false, false, E_ACCUM, float>(a, st);
+  return launch<TL, false, false, E_ACCUM, float, EDGE>(a, st);
 }
 
 inline bool small_fits(int M, int N) { return M % 128 == 0 && N % 128 == 0; }
@@ -629,7 +669,64 @@ inline int choose_tile(int M, int N, bool wide = false) {
   return best;
 }
 
+// Products of few tiles run on 64 x 64 ones, whole or not: a workgroup that has a compute unit to itself takes 1.2, 0.72,
+// 0.6-0.7 and 0.3 us per k-tile on 256 x 256, 256 x 128, 128 x 128 and 64 x 64 (two of the last: 0.5), so up to two of
+// them per compute unit the smallest tile is the fastest.  Measured (forward / dgrad layout, the best whole tile
+// against 64 x 64): 128 x 1024 x 1024 12.3 / 7.2 us, 1024 x 1024 x 2048 24.4 / 12.9, 1024 x 2048 x 2048 24.9 / 17.9; 1024 x
+// 3072 x 1024 (768 tiles) 14.3 / 14.0, 2048 x 2048 x 2048 (1024) 25.6 / 27.7.  Weight-gradient layout, whose transpose
+// loads make more of the smaller tile: 1024 x 1024 x 2048 (256 tiles) 21.3 / 16.7, 1024 x 2048 x 2048 (512) 22.4 / 23.0.
+inline bool few_tiles(int layout, int M, int N) {
+  return (long)((M + 63) / 64) * ((N + 63) / 64) <= (layout == L_TN ? 256 : 512);
+}
+
+// Tile of the edge form: 0: 256 x 256, 1: 128 x 128 (by the estimate of choose_tile, the last tiles partly empty), 2: 64 x 64.
+inline int choose_edge_tile(int layout, int M, int N) {
+  if (few_tiles(layout, M, N)) return 2;
+  const int e[2] = {256, 128};
+  const long slots[2] = {256, 512};
+  const double rate[2] = {1.0, TILE_RATE_SMALL / 2};
+  double t[2];
+  for (int i = 0; i < 2; ++i) {
+    const long tiles = (long)((M + e[i] - 1) / e[i]) * ((N + e[i] - 1) / e[i]), full = tiles / slots[i], rest = tiles % slots[i];
+    t[i] = ((double)full + (rest ? 0.5 + 0.5 * (double)rest / slots[i] : 0.0)) * e[i] * e[i] / rate[i];
+  }
+  return t[0] < t[1] ? 0 : 1;
+}
+
 }  // namespace
+
+bool gemm_mfma_edge_supported(int layout, int epi, int M, int N, int K) {
+  if (layout < L_NN || layout > L_TN || (layout == L_TN) != (epi == E_ACCUM) || epi < E_NONE || epi > E_ACCUM) return false;
+  if (M < 1 || N < 1 || K < 1 || N % 8) return false;
+  const long ldmax = 1l << 21;  // 32-bit lane offsets over 256 rows
+  if (M > ldmax || N > ldmax || K > ldmax) return false;
+  return layout == L_TN ? M % 8 == 0 : K % 8 == 0;
+}
+
+bool gemm_mfma_few_tiles(int layout, int M, int N) { return few_tiles(layout, M, N); }
+
+// Weight gradients of odd multiples of 128 (a 50304-word vocabulary: 393 x 128) on 256 x 256 tiles whose last row is half
+// empty: 50304 x 2048 over 2048 tokens 603 -> 451 us.  The other layouts have the 256 x 192 and 256 x 128 tiles there.
+bool gemm_mfma_edge_better(int layout, int M, int N) {
+  if (few_tiles(layout, M, N)) return true;
+  if (layout != L_TN || !(M % 256 || N % 256) || choose_tile(M, N) != 2) return false;
+  return choose_edge_tile(layout, M, N) == 0;
+}
+
+bf_status gemm_mfma_edge(int layout, int epi, const GemmArgs& a, hipStream_t st) {
+  if (!gemm_mfma_edge_supported(layout, epi, a.M, a.N, a.K)) { set_error("gemm_mfma: shape not supported"); return BF_EINVAL; }
+  if (a.n_seg > 1 && (layout != L_TN || ((a.seg_stride_a | a.seg_stride_b) & 7))) {
+    set_error("gemm_mfma: segments go with the weight-gradient layout and 16-byte aligned strides");
+    return BF_EINVAL;
+  }
+  const uintptr_t al = (uintptr_t)a.A | (uintptr_t)a.B | (uintptr_t)a.C | (uintptr_t)a.R | (uintptr_t)a.C2 | (uintptr_t)a.bias;
+  if (al & 15) { set_error("gemm_mfma: operands must be 16-byte aligned"); return BF_EINVAL; }
+  switch (choose_edge_tile(layout, a.M, a.N)) {
+    case 0: return by_layout<TileBig, true>(layout, epi, a, st);
+    case 1: return by_layout<TileSmall, true>(layout, epi, a, st);
+    default: return by_layout<TileTiny, true>(layout, epi, a, st);
+  }
+}
 
 bool gemm_mfma_supported(int layout, int epi, int M, int N, int K) {
   if (layout < L_NN || layout > L_TN) return false;

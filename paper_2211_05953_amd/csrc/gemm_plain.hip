@@ -1,6 +1,6 @@
 // Plain GEMM: LDS-tiled fp32 FMA, any shape, any of the three operand layouts, both
-// storage types.  It is the fp32-mode GEMM and the fallback for shapes the MFMA kernel
-// does not take; it is not meant to be fast.
+// storage types.  It is what BF_KERNELS_PLAIN asks for (the matrix-core kernels are checked against it) and the
+// fallback for sizes past their 32-bit offsets; it is not meant to be fast.
 #include "common.h"
 #include "epilogue.h"
 
@@ -133,21 +133,25 @@ bf_status gemm(int dtype, int kernels, int layout, int epi, const GemmArgs& a, h
   const uintptr_t al = (uintptr_t)a.A | (uintptr_t)a.B | (uintptr_t)a.C | (uintptr_t)a.R | (uintptr_t)a.C2 | (uintptr_t)a.bias;
   bf_status s;
   const bool seg_ok = a.n_seg <= 1 || ((a.seg_stride_a | a.seg_stride_b) & 7) == 0;  // 16-byte aligned segments
-  if (dtype == BF_BF16 && kernels == BF_KERNELS_AUTO && (al & 15) == 0 && seg_ok && gemm_mfma_supported(layout, epi, a.M, a.N, a.K)) {
+  const bool mfma = dtype == BF_BF16 && kernels == BF_KERNELS_AUTO && (al & 15) == 0 && seg_ok;
+  const bool whole = mfma && gemm_mfma_supported(layout, epi, a.M, a.N, a.K) && !gemm_mfma_edge_better(layout, a.M, a.N);
+  if (whole || (mfma && gemm_mfma_edge_supported(layout, epi, a.M, a.N, a.K))) {
     s = gemm_check(layout, epi, a);
     if (s != BF_OK) return s;
-    if (layout != L_TN && a.colsum && a.colsum_part) {
+    // (not on 64 x 64 tiles: colsum_part has a row per 128, and a second pass over so small an output takes no longer
+    // than adding up the rows)
+    if (layout != L_TN && a.colsum && a.colsum_part && !gemm_mfma_few_tiles(layout, a.M, a.N)) {
       // the epilogue leaves one row of partial column sums per row of tiles; add them up
       int rows = 0;
       GemmArgs b = a;
       b.colsum_rows = &rows;
-      s = gemm_mfma(layout, epi, b, st);
+      s = whole ? gemm_mfma(layout, epi, b, st) : gemm_mfma_edge(layout, epi, b, st);
       if (s != BF_OK) return s;
       return colsum_finish(a.colsum_part, rows, a.N, a.colsum, a.accumulate, st);
     }
     GemmArgs b = a;
     b.colsum_part = nullptr;
-    const int slices = a.splitk_ws ? gemm_splitk_slices(layout, epi, a.M, a.N, a.K) : 1;
+    const int slices = whole && a.splitk_ws ? gemm_splitk_slices(layout, epi, a.M, a.N, a.K) : 1;
     if (slices > 1 && a.splitk_ws_elems >= (size_t)slices * a.M * a.N && ((uintptr_t)a.splitk_ws & 15) == 0) {
       // few tiles, long contraction: slices of K on more workgroups into fp32 planes, then the planes added in order
       b.C = a.splitk_ws;
@@ -160,7 +164,7 @@ bf_status gemm(int dtype, int kernels, int layout, int epi, const GemmArgs& a, h
       if (s != BF_OK) return s;
       return gemm_splitk_finish(epi, a.M, a.N, slices, a.splitk_ws, a.bias, a.R, a.C, st);
     }
-    s = gemm_mfma(layout, epi, b, st);
+    s = whole ? gemm_mfma(layout, epi, b, st) : gemm_mfma_edge(layout, epi, b, st);
   } else {
     s = gemm_plain(dtype, layout, epi, a, st);
   }

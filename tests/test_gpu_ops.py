@@ -401,3 +401,60 @@ def test_op_argument_errors():
         bf.bf_op_layernorm_fwd(bf.BF_FP32, 0, 4, t, t, t, 1e-5, t, t)
     with pytest.raises(bf.BfError):
         bf.bf_op_attention_fwd(bf.BF_FP32, 0, 1, 5000, 1, 4, 1, t, t, t)
+
+
+def _guarded(a, b16):
+    """A device copy of `a` with NaN on both sides: a read outside the operand that reaches a result shows."""
+    flat = torch.full((a.size + 128,), float("nan"), dtype=_dt(b16), device="cuda")
+    flat[64:64 + a.size] = to_dev(a, b16).reshape(-1)
+    return flat[64:64 + a.size]
+
+
+@pytest.mark.parametrize("mode,dtype", MODES)
+@pytest.mark.parametrize("M,N,K", [(1, 8, 8), (100, 72, 64), (127, 136, 200), (129, 264, 72), (1000, 8200, 72), (300, 1000, 24), (520, 264, 1000),
+                                   (33, 35, 37), (1, 1, 1), (130, 66, 101), (2048, 392, 40)])
+def test_gemm_on_partly_empty_tiles(mode, dtype, M, N, K):
+    """Sizes around the tiles' edges, down to one element and with rows that are not 16-byte chunks: every layout and
+    epilogue, operands between NaNs, outputs that must not be written outside.  fp32: a chain of K products, error
+    under 2^-24 sqrt(K) of the sum's scale, far below the bar of 1e-5, and the same chain as the plain kernel's: the same
+    bits; bf16: one rounding of such a sum, 2^-8, below 2e-2."""
+    b16 = dtype == bf.BF_BF16
+    A = bf_inputs.normal(21, 0, (M, K), bf16=b16)
+    B = bf_inputs.normal(21, 1, (K, N), 0.05, bf16=b16)
+    bias = bf_inputs.normal(21, 2, (N,), 0.5)
+    R = bf_inputs.normal(21, 3, (M, N), bf16=b16)
+    R64 = R.astype(np.float64)
+    acc = A.astype(np.float64) @ B.astype(np.float64)
+    gA, gB, gBt, gR, gbias = _guarded(A, b16), _guarded(B, b16), _guarded(np.ascontiguousarray(B.T), b16), _guarded(R, b16), to_dev(bias, False)
+    gAt = _guarded(np.ascontiguousarray(A.T), b16)
+
+    def outbuf(td):
+        return torch.full((M * N + 128,), 7.0, dtype=td, device="cuda")
+
+    def taken(buf):
+        assert bool((buf[:64] == 7.0).all()) and bool((buf[64 + M * N:] == 7.0).all())
+        return to_host(buf[64:64 + M * N].reshape(M, N))
+    for layout, op in ((bf.BF_NN, gB), (bf.BF_NT, gBt)):
+        for epi, ref in ((bf.BF_EPI_NONE, acc), (bf.BF_EPI_BIAS, acc + bias), (bf.BF_EPI_BIAS_RES, acc + bias + R64),
+                         (bf.BF_EPI_BIAS_GELU, acc + bias), (bf.BF_EPI_GELU_BWD, acc * L.gelu_grad(R64))):
+            out, out2 = outbuf(_dt(b16)), outbuf(_dt(b16))
+            bf.bf_op_gemm(dtype, 0, layout, epi, M, N, K, gA, op, out[64:], bias=gbias, R=gR, C2=out2[64:])
+            assert rel_err(taken(out), ref) <= TOL[mode], (layout, epi)
+            if epi == bf.BF_EPI_BIAS_GELU:
+                assert rel_err(taken(out2), L.gelu(acc + bias)) <= TOL[mode]
+            if not b16:
+                plain, plain2 = outbuf(_dt(b16)), outbuf(_dt(b16))
+                bf.bf_op_gemm(dtype, bf.BF_KERNELS_PLAIN, layout, epi, M, N, K, gA, op, plain[64:], bias=gbias, R=gR, C2=plain2[64:])
+                assert torch.equal(out, plain) and torch.equal(out2, plain2), (layout, epi)
+    G = outbuf(torch.float32)
+    for accumulate in (0, 1):
+        bf.bf_op_gemm(dtype, 0, bf.BF_TN, bf.BF_EPI_ACCUM, M, N, K, gAt, gB, G[64:], accumulate=accumulate)
+        assert rel_err(taken(G), (1 + accumulate) * acc) <= 1e-5
+    # the column sums that go with the GeLU backward, through the scratch rows and without
+    if M >= 100:
+        ref = (acc * L.gelu_grad(R64)).sum(axis=0)
+        for part in (torch.full(((M + 127) // 128, N), float("nan"), device="cuda"), None):
+            out, db = outbuf(_dt(b16)), torch.full((N,), float("nan"), device="cuda")
+            bf.bf_op_gemm_gelu_bwd_colsum(dtype, 0, M, N, K, gA, gBt, out[64:], gR, db, part)
+            taken(out)
+            assert rel_err(to_host(db), ref) <= TOL[mode]
