@@ -89,6 +89,9 @@ bool gemm_mfma_edge_supported(int layout, int epi, int M, int N, int K);
 bool gemm_mfma_edge_better(int layout, int M, int N);
 bool gemm_mfma_few_tiles(int layout, int M, int N);
 bf_status gemm_mfma_edge(int layout, int epi, const GemmArgs& a, hipStream_t st);
+// fp32 matrix-core product: any shape, both storage types (operands widened), all layouts and epilogues
+bool gemm_f32_supported(int layout, int epi, const GemmArgs& a);
+bf_status gemm_f32(int dtype, int layout, int epi, const GemmArgs& a, hipStream_t st);
 // tile (rows x columns of C per workgroup) the MFMA kernel runs an unsplit product of this shape on; 0 x 0 if none fits
 void gemm_mfma_tile(int layout, int epi, int M, int N, int* bm, int* bn);
 // Slices the matrix-core path would cut the contraction of this forward / dgrad product into (1: no split).

@@ -165,6 +165,10 @@ bf_status gemm(int dtype, int kernels, int layout, int epi, const GemmArgs& a, h
       return gemm_splitk_finish(epi, a.M, a.N, slices, a.splitk_ws, a.bias, a.R, a.C, st);
     }
     s = whole ? gemm_mfma(layout, epi, b, st) : gemm_mfma_edge(layout, epi, b, st);
+  } else if (kernels == BF_KERNELS_AUTO && (dtype == BF_FP32 || dtype == BF_BF16) && gemm_f32_supported(layout, epi, a)) {
+    s = gemm_check(layout, epi, a);
+    if (s != BF_OK) return s;
+    s = gemm_f32(dtype, layout, epi, a, st);
   } else {
     s = gemm_plain(dtype, layout, epi, a, st);
   }
