@@ -1,11 +1,13 @@
 // Plain attention, forward and backward: one wavefront per query (or key) row, fp32
 // arithmetic, scores staged in LDS.  Any head size, S_seq up to 4096, both storage
-// types.  It is the fp32-mode attention and the fallback for shapes the MFMA kernels
-// do not take.  All reductions run in a fixed order.
+// types.  It is what BF_KERNELS_PLAIN asks for (the matrix-core kernels are checked against it) and
+// the fallback for shapes those do not take.  All reductions run in a fixed order.
 //
 // Layout: qkv [S_mb, S_seq, 3 S_hidden] packed [Q | K | V], head a at columns
 // a*S_head..; ctx [S_mb, S_seq, S_hidden]; lse [S_mb, N_heads, S_seq] = log sum exp of the
 // scaled, masked scores of a row.
+#include <type_traits>
+
 #include "common.h"
 
 namespace bf {
@@ -221,9 +223,13 @@ bf_status fwd_t(int S_mb, int S_seq, int N_heads, int d, int causal, const void*
 
 template <typename T>
 bf_status bwd_t(int S_mb, int S_seq, int N_heads, int d, int causal, const void* qkv, const void* ctx, const float* lse,
-                const void* dctx, void* dqkv, float* delta, hipStream_t st) {
+                const void* dctx, void* dqkv, float* delta, hipStream_t st, bool matrix) {
   dim3 grid((S_seq + ROWS - 1) / ROWS, N_heads, S_mb);
   const float scale = 1.0f / sqrtf((float)d);
+  if (matrix) {
+    attn_delta_kernel<T><<<grid, ROWS * 64, 0, st>>>((const T*)ctx, (const T*)dctx, delta, S_seq, N_heads, d);
+    return attention_bwd_f32(std::is_same<T, float>::value ? BF_FP32 : BF_BF16, S_mb, S_seq, N_heads, d, causal, qkv, lse, delta, dctx, dqkv, st);
+  }
   if (!allow_lds(attn_bwd_dq_plain_kernel<T>, (size_t)ROWS * (S_seq + 2 * d) * sizeof(float))) return BF_EDEVICE;
   if (!allow_lds(attn_bwd_dkv_plain_kernel<T>, (size_t)ROWS * (2 * S_seq + 2 * d) * sizeof(float))) return BF_EDEVICE;
   attn_delta_kernel<T><<<grid, ROWS * 64, 0, st>>>((const T*)ctx, (const T*)dctx, delta, S_seq, N_heads, d);
@@ -248,11 +254,11 @@ bf_status attention_fwd_plain(int dtype, int S_mb, int S_seq, int N_heads, int S
 
 bf_status attention_bwd_plain(int dtype, int S_mb, int S_seq, int N_heads, int S_head, int causal, const void* qkv,
                               const void* ctx, const float* lse, const void* dctx, void* dqkv, float* delta,
-                              hipStream_t st) {
+                              hipStream_t st, bool matrix) {
   if (!qkv || !ctx || !lse || !dctx || !dqkv || !delta) { set_error("attention_bwd: null pointer"); return BF_EINVAL; }
   if (!plain_ok(S_mb, S_seq, N_heads, S_head)) return BF_EINVAL;
-  if (dtype == BF_BF16) return bwd_t<bf16_t>(S_mb, S_seq, N_heads, S_head, causal, qkv, ctx, lse, dctx, dqkv, delta, st);
-  return bwd_t<float>(S_mb, S_seq, N_heads, S_head, causal, qkv, ctx, lse, dctx, dqkv, delta, st);
+  if (dtype == BF_BF16) return bwd_t<bf16_t>(S_mb, S_seq, N_heads, S_head, causal, qkv, ctx, lse, dctx, dqkv, delta, st, matrix);
+  return bwd_t<float>(S_mb, S_seq, N_heads, S_head, causal, qkv, ctx, lse, dctx, dqkv, delta, st, matrix);
 }
 
 bf_status attention_fwd(int dtype, int kernels, int S_mb, int S_seq, int N_heads, int S_head, int causal,
@@ -260,6 +266,10 @@ bf_status attention_fwd(int dtype, int kernels, int S_mb, int S_seq, int N_heads
   if (dtype == BF_BF16 && kernels == BF_KERNELS_AUTO && attention_mfma_supported(S_seq, S_head)) {
     if (!qkv || !ctx || !lse) { set_error("attention_fwd: null pointer"); return BF_EINVAL; }
     return attention_fwd_mfma(S_mb, S_seq, N_heads, S_head, causal, qkv, ctx, lse, st);
+  }
+  if (kernels == BF_KERNELS_AUTO && attention_fwd_f32_supported(S_mb, S_seq, N_heads, S_head)) {
+    if (!qkv || !ctx || !lse) { set_error("attention_fwd: null pointer"); return BF_EINVAL; }
+    return attention_fwd_f32(dtype, S_mb, S_seq, N_heads, S_head, causal, qkv, ctx, lse, st);
   }
   return attention_fwd_plain(dtype, S_mb, S_seq, N_heads, S_head, causal, qkv, ctx, lse, st);
 }
@@ -285,7 +295,8 @@ bf_status attention_bwd(int dtype, int kernels, int S_mb, int S_seq, int N_heads
       return attn_bias_finish(use, (int)rq, use + rq * h, (int)rkv, h, db_qkv, accumulate, st);
     }
   } else {
-    r = attention_bwd_plain(dtype, S_mb, S_seq, N_heads, S_head, causal, qkv, ctx, lse, dctx, dqkv, delta, st);
+    r = attention_bwd_plain(dtype, S_mb, S_seq, N_heads, S_head, causal, qkv, ctx, lse, dctx, dqkv, delta, st,
+                            kernels == BF_KERNELS_AUTO && attention_f32_supported(S_mb, S_seq, N_heads, S_head));
     if (r != BF_OK || !db_qkv) return r;
   }
   return colsum(dtype, S_mb * S_seq, 3 * h, dqkv, db_qkv, accumulate, st);

@@ -120,7 +120,7 @@ bf_status attention_fwd_plain(int dtype, int S_mb, int S_seq, int N_heads, int S
                               const void* qkv, void* ctx, float* lse, hipStream_t st);
 bf_status attention_bwd_plain(int dtype, int S_mb, int S_seq, int N_heads, int S_head, int causal,
                               const void* qkv, const void* ctx, const float* lse, const void* dctx,
-                              void* dqkv, float* delta, hipStream_t st);
+                              void* dqkv, float* delta, hipStream_t st, bool matrix = false);
 bool attention_mfma_supported(int S_seq, int S_head);
 bf_status attention_fwd_mfma(int S_mb, int S_seq, int N_heads, int S_head, int causal,
                              const void* qkv, void* ctx, float* lse, hipStream_t st);
@@ -132,6 +132,14 @@ bf_status attention_bwd_mfma(int S_mb, int S_seq, int N_heads, int S_head, int c
                              void* dqkv, float* delta, hipStream_t st, float* part = nullptr);
 size_t attention_bwd_mfma_part_q_rows(int S_mb, int S_seq);
 size_t attention_bwd_mfma_part_kv_rows(int S_mb, int S_seq);
+// The plain kernels' results, bit for bit, on the fp32 matrix instructions (both storage types, head sizes up to 128; the
+// forward pass keeps the scores of its rows in LDS, which bounds S_seq)
+bool attention_f32_supported(int S_mb, int S_seq, int N_heads, int S_head);
+bool attention_fwd_f32_supported(int S_mb, int S_seq, int N_heads, int S_head);
+bf_status attention_fwd_f32(int dtype, int S_mb, int S_seq, int N_heads, int S_head, int causal, const void* qkv, void* ctx, float* lse,
+                            hipStream_t st);
+bf_status attention_bwd_f32(int dtype, int S_mb, int S_seq, int N_heads, int S_head, int causal, const void* qkv, const float* lse,
+                            const float* delta, const void* dctx, void* dqkv, hipStream_t st);
 bf_status attention_fwd(int dtype, int kernels, int S_mb, int S_seq, int N_heads, int S_head, int causal,
                         const void* qkv, void* ctx, float* lse, hipStream_t st);
 // db_qkv (may be null): also db_qkv[3 S_hidden] = (accumulate ? db_qkv : 0) + column sums of dqkv, the bias

@@ -458,3 +458,30 @@ def test_gemm_on_partly_empty_tiles(mode, dtype, M, N, K):
             bf.bf_op_gemm_gelu_bwd_colsum(dtype, 0, M, N, K, gA, gBt, out[64:], gR, db, part)
             taken(out)
             assert rel_err(to_host(db), ref) <= TOL[mode]
+
+
+@pytest.mark.parametrize("mode,dtype", MODES)
+@pytest.mark.parametrize("causal", [1, 0])
+@pytest.mark.parametrize("poison", [False, True])
+@pytest.mark.parametrize("S_mb,S_seq,a,d", [(1, 1, 1, 8), (1, 128, 4, 60), (2, 65, 2, 33), (2, 100, 3, 40), (1, 200, 20, 128), (3, 129, 30, 64), (1, 1900, 1, 16)])
+def test_attention_on_the_fp32_matrix_instructions(mode, dtype, causal, poison, S_mb, S_seq, a, d):
+    """The same bits as the plain kernels (ascending chains, the same order of every sum): tiles of 64 with remainders,
+    16 and 32 rows per workgroup, odd head sizes, and infinities and NaN that the mask keeps from earlier rows."""
+    b16 = dtype == bf.BF_BF16
+    if b16 and d in (64, 128):
+        pytest.skip("bf16 heads of 64 and 128 run on the bf16 matrix instructions")
+    h = a * d
+    qkv, dctx = (bf_inputs.normal(31, i, (S_mb, S_seq, n * h), bf16=b16) for i, n in ((0, 3), (1, 1)))
+    if poison and S_seq > 2:
+        qkv[:, 2 * S_seq // 3, 2 * h + 3], qkv[:, 2 * S_seq // 3 + 1, h + 1] = np.inf, np.nan
+        qkv[:, S_seq // 3, 5], dctx[:, S_seq // 2, 2] = -np.inf, np.nan
+    dQKV, dDC = to_dev(qkv, b16), to_dev(dctx, b16)
+    got = []
+    for kernels in (bf.BF_KERNELS_AUTO, bf.BF_KERNELS_PLAIN):
+        ctx, dqkv = (torch.full((S_mb, S_seq, n * h), 7.0, dtype=_dt(b16), device="cuda") for n in (1, 3))
+        lse, delta = (torch.full((S_mb, a, S_seq), 7.0, device="cuda") for _ in range(2))
+        bf.bf_op_attention_fwd(dtype, kernels, S_mb, S_seq, a, d, causal, dQKV, ctx, lse)
+        bf.bf_op_attention_bwd(dtype, kernels, S_mb, S_seq, a, d, causal, dQKV, ctx, lse, dDC, dqkv, delta)
+        got.append((ctx, lse, dqkv))
+    for x, y in zip(*got):
+        assert torch.equal(torch.nan_to_num(x.float(), 123.0), torch.nan_to_num(y.float(), 123.0))
