@@ -758,6 +758,9 @@ bf_status gemm_mfma(int layout, int epi, const GemmArgs& a, hipStream_t st) {
   }
   const uintptr_t al = (uintptr_t)a.A | (uintptr_t)a.B | (uintptr_t)a.C | (uintptr_t)a.R | (uintptr_t)a.C2 | (uintptr_t)a.bias;
   if (al & 15) { set_error("gemm_mfma: operands must be 16-byte aligned"); return BF_EINVAL; }
+  // slices of a product of few tiles: on 64 x 64 as well, as long as both slices' workgroups find room
+  if (planes && (long)(a.M / 64) * (a.N / 64) <= 256)
+    return layout == L_NN ? launch<TileTiny, true, false, E_ACCUM, float>(a, st) : launch<TileTiny, true, true, E_ACCUM, float>(a, st);
   switch (planes ? SPLITK_TILE : choose_tile(a.M, a.N, !a.shared_chip && wide_fits(layout, epi, a.M, a.N))) {
     case 0: return by_layout<TileBig>(layout, epi, a, st);
     case 1: return by_layout<TileMid>(layout, epi, a, st);

@@ -485,3 +485,21 @@ def test_attention_on_the_fp32_matrix_instructions(mode, dtype, causal, poison, 
         got.append((ctx, lse, dqkv))
     for x, y in zip(*got):
         assert torch.equal(torch.nan_to_num(x.float(), 123.0), torch.nan_to_num(y.float(), 123.0))
+
+
+@pytest.mark.parametrize("M,N,K", [(256, 128, 4608), (1024, 1024, 4608), (1024, 2048, 8192)])
+def test_split_contraction_of_few_tiles(M, N, K):
+    """Long contractions of at most 512 tiles of 64 x 64: two slices on 64 x 64 tiles (up to 256 of them) or 256 x 128 ones,
+    with the epilogue in the second pass.  The sums associate differently from the unsplit product's: fp32 rounding of
+    the sum, then one bf16 rounding on either side, 2^-7."""
+    A, B = bf_inputs.normal(16, 0, (M, K), bf16=True), bf_inputs.normal(16, 1, (K, N), 0.05, bf16=True)
+    bias, R = bf_inputs.normal(16, 2, (N,), 0.5), bf_inputs.normal(16, 3, (M, N), bf16=True)
+    dA, dB, dBt, dR, dbias = to_dev(A, True), to_dev(B, True), to_dev(np.ascontiguousarray(B.T), True), to_dev(R, True), to_dev(bias, False)
+    planes = torch.full((2 * M * N,), float("nan"), dtype=torch.float32, device="cuda")
+    want = A.astype(np.float64) @ B.astype(np.float64) + bias + R
+    for layout, op in ((bf.BF_NN, dB), (bf.BF_NT, dBt)):
+        out, ref = (torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+        bf.bf_op_gemm_splitk(bf.BF_BF16, 0, layout, bf.BF_EPI_BIAS_RES, M, N, K, dA, op, out, bias=dbias, R=dR, planes=planes)
+        bf.bf_op_gemm(bf.BF_BF16, 0, layout, bf.BF_EPI_BIAS_RES, M, N, K, dA, op, ref, bias=dbias, R=dR)
+        assert bool(torch.isfinite(planes).all())   # both slices were run
+        assert rel_err(to_host(out), want) <= TOL["bf16"] and rel_err(to_host(out), to_host(ref).astype(np.float64)) <= 2.0 ** -7
