@@ -66,12 +66,29 @@ struct TileRegs {
       v[i] = *reinterpret_cast<const u32x4*>(g + (size_t)row * ld + ch * 8);
     }
   }
+  // rows from `valid` on (the sequence ends inside the tile) are zero
+  __device__ __forceinline__ void load_edge(const bf16_t* __restrict__ g, size_t ld, int tid, int valid) {
+#pragma unroll
+    for (int i = 0; i < CH; ++i) {
+      const int c = tid + i * NT, row = c / (D / 8), ch = c % (D / 8);
+      v[i] = row < valid ? *reinterpret_cast<const u32x4*>(g + (size_t)row * ld + ch * 8) : u32x4{0, 0, 0, 0};
+    }
+  }
   __device__ __forceinline__ void store(bf16_t* lds, int tid) const {
 #pragma unroll
     for (int i = 0; i < CH; ++i) {
       const int c = tid + i * NT, row = c / (D / 8), ch = c % (D / 8);
       *reinterpret_cast<u32x4*>(lds + row * D + ((ch ^ row_key<D>(row)) << 3)) = v[i];
     }
+  }
+  // an infinity or a NaN among the thread's values
+  __device__ __forceinline__ bool non_finite() const {
+    bool bad = false;
+#pragma unroll
+    for (int i = 0; i < CH; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) bad |= (v[i][j] & 0x7f80u) == 0x7f80u || (v[i][j] & 0x7f800000u) == 0x7f800000u;
+    return bad;
   }
 };
 
@@ -102,6 +119,49 @@ __device__ __forceinline__ bf16x8 pack8(const f32x16& a, int kk) {
   return o;
 }
 
+// what pack8 rounds away, as a second B operand: together they carry 16 bits of a probability
+__device__ __forceinline__ bf16x8 pack8_low(const f32x16& a, int kk) {
+  bf16x8 o;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) o[e] = (__bf16)(a[8 * kk + e] - (float)(__bf16)a[8 * kk + e]);
+  return o;
+}
+
+// ---- Sequences of any length (the EDGE forms of the kernels below).  Tiles past the end are filled with zeros and masked,
+// and probabilities and their gradients enter the products as two bf16 operands, value and remainder: these lengths used
+// to run on fp32 kernels, and the results are no further from the exact ones than those kernels' were.  2 x 1000 tokens, 16
+// heads of 128, causal, forward / dQ / dK dV: 422 / 395 / 516 us on fp32 matrix instructions, 53 / 51 / 113 here (bound by the
+// chain score -> exponential -> two-part product of one or two waves per SIMD; the longest key block sets the last).
+// A zero times an infinity is a NaN in a matrix instruction, but a masked pair must not touch its row: where a tile that
+// the mask cuts holds non-finite values, its 64 rows are added element by element, allowed pairs only.
+// acc (rows = head dims, column = this lane's row) += sum over the tile's rows of s (rows = tile rows) x tile.
+constexpr int DUMP = 16 * 32;  // fp32 words of LDS a wave needs for it
+template <int D, int NTT, typename F>
+__device__ __forceinline__ void accumulate_allowed(f32x16 (&acc)[D / 32], const f32x16 (&s)[NTT], int t0, const bf16_t* tile, float* dump, int lane, F allowed) {
+#pragma unroll 1
+  for (int q = 0; q < 2 * NTT; ++q) {  // 16 tile rows at a time: registers 8 (q & 1) .. of s[q / 2]
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      float v = s[0][e];
+#pragma unroll
+      for (int u = 1; u < 2 * NTT; ++u) v = u == q ? s[u / 2][8 * (u & 1) + e] : v;
+      dump[((e >> 2) * 8 + (lane >> 5) * 4 + (e & 3)) * 32 + (lane & 31)] = v;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll 1
+    for (int k = 0; k < 16; ++k) {
+      const int row = 32 * t0 + 16 * q + k;
+      if (!allowed(row)) continue;
+      const float p = dump[k * 32 + (lane & 31)];
+#pragma unroll
+      for (int dt = 0; dt < D / 32; ++dt)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[dt][r] = fmaf(p, (float)tile[swz<D>(row, 32 * dt + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3))], acc[dt][r]);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  }
+}
+
 // B operand straight from global memory: lane holds row[16kk + 8(l/32) .. +7] of its own token row
 template <int D>
 __device__ __forceinline__ void load_rowfrags(const bf16_t* __restrict__ row, int lane, bf16x8 (&f)[D / 16]) {
@@ -122,6 +182,22 @@ __device__ __forceinline__ void mfma_lds_pipeline() {
   }
   __builtin_amdgcn_sched_group_barrier(0x008, AHEAD, 0);
   __builtin_amdgcn_sched_barrier(0);
+}
+
+// acc += tile^T s over the 32 tile rows from row0 on, s (fp32 accumulator layout) as value and remainder
+template <int D, typename FA>
+__device__ __forceinline__ void accumulate_split(f32x16 (&acc)[D / 32], const f32x16& s, const bf16_t* tile, int row0, const FA& fa) {
+  const bf16x8 lo[2] = {pack8_low(s, 0), pack8_low(s, 1)}, hi[2] = {pack8(s, 0), pack8(s, 1)};
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int k2 = 0; k2 < 2; ++k2)
+#pragma unroll
+    for (int dt = 0; dt < D / 32; ++dt) {
+      const bf16x8 tf = fa.frag_t(tile, row0 + 16 * k2, dt);
+      acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tf, lo[k2], acc[dt], 0, 0, 0);
+      acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tf, hi[k2], acc[dt], 0, 0, 0);
+    }
+  mfma_lds_pipeline<4 * (D / 32), 1, 4>();
 }
 
 __device__ __forceinline__ int acc_row(int r, int lane) { return (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3); }
@@ -263,8 +339,8 @@ struct NextSetOf<DEPTH, std::integral_constant<int, V>> { static constexpr int v
 // (accumulators in AGPRs, one wavefront per SIMD): built and measured level with this form (100 against
 // 98 us at 64 heads of 128, S_seq 2048): a lone wavefront issues in order, so each of its LDS, barrier
 // and softmax waits stops its MFMAs too, and there is no partner on the SIMD to fill the gap.
-template <int D, int ROWS>
-__global__ __launch_bounds__(2 * ROWS, ROWS == 128 ? 2 : 1) void attn_fwd_kernel(const bf16_t* __restrict__ qkv,
+template <int D, int ROWS, bool EDGE = false>
+__global__ __launch_bounds__(2 * ROWS, ROWS == 128 && !(EDGE && D == 128) ? 2 : 1) void attn_fwd_kernel(const bf16_t* __restrict__ qkv,
                                                                                  bf16_t* __restrict__ ctx, float* __restrict__ lse,
                                                                                  int S_seq, int N_heads, int S_mb, int causal,
                                                                                  float scale) {
@@ -273,35 +349,50 @@ __global__ __launch_bounds__(2 * ROWS, ROWS == 128 ? 2 : 1) void attn_fwd_kernel
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   // 1-D grid ordered by work: the last (longest) query block of every head first, then the next ...
   const int nhb = N_heads * S_mb;
-  const int qblk = S_seq / ROWS - 1 - blockIdx.x / nhb;
+  const int qblk = (EDGE ? (S_seq + ROWS - 1) / ROWS : S_seq / ROWS) - 1 - blockIdx.x / nhb;
   const int head = (blockIdx.x % nhb) % N_heads, b = (blockIdx.x % nhb) / N_heads;
   const int h = N_heads * D;
   const size_t ld = 3 * (size_t)h;
   const bf16_t* base = qkv + (size_t)b * S_seq * ld + head * D;
   const int q0 = qblk * ROWS, qw = q0 + 32 * w, q = qw + (lane & 31);
+  const int ql = EDGE ? min(q, S_seq - 1) : q;  // the row that is read in the place of q
+  __shared__ float dump[EDGE ? ROWS / 32 * DUMP : 1];
+  __shared__ int bad_tile[2];  // per LDS stage: 1 + the last tile staged there with a non-finite V
+  if (EDGE && tid < 2) bad_tile[tid] = 0;
 
   FragAddr<D> fa;
   fa.init(lane);
   bf16x8 qf[D / 16];
-  load_rowfrags<D>(base + (size_t)q * ld, lane, qf);
+  load_rowfrags<D>(base + (size_t)ql * ld, lane, qf);
   f32x16 o[D / 32];
 #pragma unroll
   for (int dt = 0; dt < D / 32; ++dt) o[dt] = zero16();
   float m = -INFINITY, l = 0.f;
   const float c2 = scale * LOG2E;
 
-  const int nblk = causal ? (q0 + ROWS) / BLK : S_seq / BLK;
+  const int nblk = EDGE ? ((causal ? min(q0 + ROWS, S_seq) : S_seq) + BLK - 1) / BLK : causal ? (q0 + ROWS) / BLK : S_seq / BLK;
   TileRegs<BLK, D, NT> kr[DEPTH], vr[DEPTH];  // set (j % DEPTH) carries tile j
   auto fetch = [&](auto setc, int j) {
     constexpr int SET = decltype(setc)::value;
+    if constexpr (EDGE) {
+      kr[SET].load_edge(base + (size_t)j * BLK * ld + h, ld, tid, S_seq - j * BLK);
+      vr[SET].load_edge(base + (size_t)j * BLK * ld + 2 * h, ld, tid, S_seq - j * BLK);
+      return;
+    }
     kr[SET].load(base + (size_t)j * BLK * ld + h, ld, tid);
     vr[SET].load(base + (size_t)j * BLK * ld + 2 * h, ld, tid);
   };
   typedef std::integral_constant<int, 0> I0;
   typedef std::integral_constant<int, 1> I1;
   fetch(I0{}, 0);
+  // tile j goes to an LDS stage: does the mask cut it, and does it hold what must not meet a masked zero
+  auto note = [&](int j, int stage, const TileRegs<BLK, D, NT>& v) {
+    if (EDGE && causal && j * BLK + BLK - 1 > q0 && v.non_finite()) bad_tile[stage] = j + 1;
+  };
+  if (EDGE) __syncthreads();  // bad_tile is clear
   kr[0].store(KVs[0][0], tid);
   vr[0].store(KVs[0][1], tid);
+  note(0, 0, vr[0]);
   if (nblk > 1) fetch(std::integral_constant<int, 1 % DEPTH>{}, 1);
   if (DEPTH > 1 && nblk > 2) fetch(I0{}, 2);
   __syncthreads();
@@ -315,10 +406,12 @@ __global__ __launch_bounds__(2 * ROWS, ROWS == 128 ? 2 : 1) void attn_fwd_kernel
     if (j + 1 < nblk) {
       kr[NextSet::value].store(KVs[PAR ^ 1][0], tid);
       vr[NextSet::value].store(KVs[PAR ^ 1][1], tid);
+      note(j + 1, PAR ^ 1, vr[NextSet::value]);
     }
     if (j + 1 + DEPTH < nblk) fetch(NextSet{}, j + 1 + DEPTH);
     const int kb = j * BLK;
-    if (causal && kb > qw + 31) { __syncthreads(); return; }  // the whole tile is above this wave's diagonal
+    // the whole tile is above this wave's diagonal, or the wave's rows are past the end
+    if ((causal && kb > qw + 31) || (EDGE && qw >= S_seq)) { __syncthreads(); return; }
     f32x16 s[2] = {zero16(), zero16()};
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -337,6 +430,13 @@ __global__ __launch_bounds__(2 * ROWS, ROWS == 128 ? 2 : 1) void attn_fwd_kernel
         for (int r = 0; r < 16; ++r)
           if (kb + 32 * t + acc_row(r, lane) > q) s[t][r] = -INFINITY;
     }
+    if (EDGE && kb + BLK > S_seq) {
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          if (kb + 32 * t + acc_row(r, lane) >= S_seq) s[t][r] = -INFINITY;
+    }
     float mx = m;
 #pragma unroll
     for (int t = 0; t < 2; ++t)
@@ -349,12 +449,13 @@ __global__ __launch_bounds__(2 * ROWS, ROWS == 128 ? 2 : 1) void attn_fwd_kernel
     for (int t = 0; t < 2; ++t)
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const float p = __builtin_amdgcn_exp2f(fmaf(s[t][r], c2, nmx));
+        // (EDGE: the difference first, so that no rounding of the maximum enters every term and the log-sum-exp)
+        const float p = __builtin_amdgcn_exp2f(EDGE ? (s[t][r] - mx) * c2 : fmaf(s[t][r], c2, nmx));
         s[t][r] = p;
         sum += p;
       }
     if (__builtin_amdgcn_ballot_w64(mx > m) != 0) {  // some row's max moved: rescale (rare after the first tiles)
-      const float alpha = __builtin_amdgcn_exp2f(fmaf(m, c2, nmx));
+      const float alpha = __builtin_amdgcn_exp2f(EDGE ? (m - mx) * c2 : fmaf(m, c2, nmx));
       l *= alpha;
 #pragma unroll
       for (int dt = 0; dt < D / 32; ++dt)
@@ -363,6 +464,17 @@ __global__ __launch_bounds__(2 * ROWS, ROWS == 128 ? 2 : 1) void attn_fwd_kernel
       m = mx;
     }
     l += sum;
+    if constexpr (EDGE) {
+      if (bad_tile[PAR] == j + 1) {
+        accumulate_allowed<D, 2>(o, s, 0, Vs, dump + w * DUMP, lane, [&](int row) { return kb + row <= q && kb + row < S_seq; });
+        __syncthreads();
+        return;
+      }
+#pragma unroll
+      for (int t = 0; t < 2; ++t) accumulate_split<D>(o, s[t], Vs, 32 * t, fa);
+      __syncthreads();
+      return;
+    }
     bf16x8 pb[2][2];
 #pragma unroll
     for (int t = 0; t < 2; ++t)
@@ -384,6 +496,7 @@ __global__ __launch_bounds__(2 * ROWS, ROWS == 128 ? 2 : 1) void attn_fwd_kernel
     if (j + 1 < nblk) body(j + 1, I1{});
   }
   l += __shfl_xor(l, 32, 64);
+  if (EDGE && q >= S_seq) return;
   store_rows<D>(o, ctx + ((size_t)b * S_seq + q) * h + head * D, lane, 1.0f / l);
   if (lane < 32) lse[((size_t)b * N_heads + head) * S_seq + q] = m * scale + logf(l);
 }
@@ -392,8 +505,8 @@ __global__ __launch_bounds__(2 * ROWS, ROWS == 128 ? 2 : 1) void attn_fwd_kernel
 // Also takes delta[b, head, i] = sum_c dctx[i, c] ctx[i, c] of its queries (each lane already holds
 // half of its query's dctx row) and leaves it in `delta` for the dK/dV pass.
 // ROWS queries per workgroup and K/V tiles DEPTH tiles ahead, as in the forward kernel.
-template <int D, int ROWS>
-__global__ __launch_bounds__(2 * ROWS, ROWS == 128 ? 2 : 1) void attn_bwd_dq_kernel(
+template <int D, int ROWS, bool EDGE = false>
+__global__ __launch_bounds__(2 * ROWS, ROWS == 128 && !EDGE ? 2 : 1) void attn_bwd_dq_kernel(
     const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ ctx, const bf16_t* __restrict__ dctx,
     const float* __restrict__ lse, float* __restrict__ delta, bf16_t* __restrict__ dqkv, int S_seq, int N_heads, int S_mb,
     int causal, float scale, float* __restrict__ colpart) {
@@ -401,48 +514,62 @@ __global__ __launch_bounds__(2 * ROWS, ROWS == 128 ? 2 : 1) void attn_bwd_dq_ker
   __shared__ __attribute__((aligned(16))) bf16_t KVs[2][2][BLK * D];  // double-buffered, one barrier per tile
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int nhb = N_heads * S_mb;
-  const int qblk = S_seq / ROWS - 1 - blockIdx.x / nhb;  // longest query blocks of every head first
+  const int qblk = (EDGE ? (S_seq + ROWS - 1) / ROWS : S_seq / ROWS) - 1 - blockIdx.x / nhb;  // longest query blocks of every head first
   const int head = (blockIdx.x % nhb) % N_heads, b = (blockIdx.x % nhb) / N_heads;
   const int h = N_heads * D;
   const size_t ld = 3 * (size_t)h;
   const bf16_t* base = qkv + (size_t)b * S_seq * ld + head * D;
   const int q0 = qblk * ROWS, qw = q0 + 32 * w, q = qw + (lane & 31);
+  const int ql = EDGE ? min(q, S_seq - 1) : q;  // the row that is read in the place of q
+  __shared__ float dump[EDGE ? ROWS / 32 * DUMP : 1];
+  __shared__ int bad_tile[2];  // per LDS stage: 1 + the last tile staged there with a non-finite K
+  if (EDGE && tid < 2) bad_tile[tid] = 0;
 
   // precomputed offsets where the registers allow (the 128-query form at S_head 128 would spill)
-  typename std::conditional<(ROWS == 256 || D == 64), FragAddr<D>, FragAddrLive<D>>::type fa;
+  typename std::conditional<(ROWS == 256 || D == 64 || EDGE), FragAddr<D>, FragAddrLive<D>>::type fa;
   fa.init(lane);
   bf16x8 qf[D / 16], dof[D / 16];
-  load_rowfrags<D>(base + (size_t)q * ld, lane, qf);
-  load_rowfrags<D>(dctx + ((size_t)b * S_seq + q) * h + head * D, lane, dof);
-  const size_t st = ((size_t)b * N_heads + head) * S_seq + q;
+  load_rowfrags<D>(base + (size_t)ql * ld, lane, qf);
+  load_rowfrags<D>(dctx + ((size_t)b * S_seq + ql) * h + head * D, lane, dof);
+  const size_t st = ((size_t)b * N_heads + head) * S_seq + ql;
   float dl = 0.f;
   {
     bf16x8 cf[D / 16];
-    load_rowfrags<D>(ctx + ((size_t)b * S_seq + q) * h + head * D, lane, cf);
+    load_rowfrags<D>(ctx + ((size_t)b * S_seq + ql) * h + head * D, lane, cf);
 #pragma unroll
     for (int kk = 0; kk < D / 16; ++kk)
 #pragma unroll
       for (int e = 0; e < 8; ++e) dl = fmaf((float)dof[kk][e], (float)cf[kk][e], dl);
     dl += __shfl_xor(dl, 32, 64);  // lanes l and l + 32 hold the two halves of the row
-    if (lane < 32) delta[st] = dl;
+    if (lane < 32 && (!EDGE || q < S_seq)) delta[st] = dl;
   }
   const float lse2 = lse[st] * LOG2E, c2 = scale * LOG2E;
   f32x16 dq[D / 32];
 #pragma unroll
   for (int dt = 0; dt < D / 32; ++dt) dq[dt] = zero16();
 
-  const int nblk = causal ? (q0 + ROWS) / BLK : S_seq / BLK;
+  const int nblk = EDGE ? ((causal ? min(q0 + ROWS, S_seq) : S_seq) + BLK - 1) / BLK : causal ? (q0 + ROWS) / BLK : S_seq / BLK;
   TileRegs<BLK, D, NT> kr[DEPTH], vr[DEPTH];  // set (j % DEPTH) carries tile j
   auto fetch = [&](auto setc, int j) {
     constexpr int SET = decltype(setc)::value;
+    if constexpr (EDGE) {
+      kr[SET].load_edge(base + (size_t)j * BLK * ld + h, ld, tid, S_seq - j * BLK);
+      vr[SET].load_edge(base + (size_t)j * BLK * ld + 2 * h, ld, tid, S_seq - j * BLK);
+      return;
+    }
     kr[SET].load(base + (size_t)j * BLK * ld + h, ld, tid);
     vr[SET].load(base + (size_t)j * BLK * ld + 2 * h, ld, tid);
   };
   typedef std::integral_constant<int, 0> I0;
   typedef std::integral_constant<int, 1> I1;
   fetch(I0{}, 0);
+  auto note = [&](int j, int stage, const TileRegs<BLK, D, NT>& k) {
+    if (EDGE && causal && j * BLK + BLK - 1 > q0 && k.non_finite()) bad_tile[stage] = j + 1;
+  };
+  if (EDGE) __syncthreads();  // bad_tile is clear
   kr[0].store(KVs[0][0], tid);
   vr[0].store(KVs[0][1], tid);
+  note(0, 0, kr[0]);
   if (nblk > 1) fetch(std::integral_constant<int, 1 % DEPTH>{}, 1);
   if (DEPTH > 1 && nblk > 2) fetch(I0{}, 2);
   __syncthreads();
@@ -455,10 +582,11 @@ __global__ __launch_bounds__(2 * ROWS, ROWS == 128 ? 2 : 1) void attn_bwd_dq_ker
     if (j + 1 < nblk) {
       kr[NextSet::value].store(KVs[p ^ 1][0], tid);
       vr[NextSet::value].store(KVs[p ^ 1][1], tid);
+      note(j + 1, p ^ 1, kr[NextSet::value]);
     }
     if (j + 1 + DEPTH < nblk) fetch(NextSet{}, j + 1 + DEPTH);
     const int kb = j * BLK;
-    if (causal && kb > qw + 31) { __syncthreads(); return; }
+    if ((causal && kb > qw + 31) || (EDGE && qw >= S_seq)) { __syncthreads(); return; }
     const bool diag = causal && kb + BLK - 1 > qw;
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
@@ -478,6 +606,20 @@ __global__ __launch_bounds__(2 * ROWS, ROWS == 128 ? 2 : 1) void attn_bwd_dq_ker
         for (int r = 0; r < 16; ++r)
           if (kb + 32 * t + acc_row(r, lane) > q) s[r] = 0.f;
       }
+      if constexpr (EDGE) {
+        if (kb + BLK > S_seq) {
+#pragma unroll
+          for (int r = 0; r < 16; ++r)
+            if (kb + 32 * t + acc_row(r, lane) >= S_seq) s[r] = 0.f;
+        }
+        if (bad_tile[p] == j + 1) {
+          const f32x16 s1[1] = {s};
+          accumulate_allowed<D, 1>(dq, s1, t, Ks, dump + w * DUMP, lane, [&](int row) { return kb + row <= q && kb + row < S_seq; });
+          continue;
+        }
+        accumulate_split<D>(dq, s, Ks, 32 * t, fa);
+        continue;
+      }
       const bf16x8 dsb[2] = {pack8(s, 0), pack8(s, 1)};
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -489,7 +631,7 @@ __global__ __launch_bounds__(2 * ROWS, ROWS == 128 ? 2 : 1) void attn_bwd_dq_ker
     }
     __syncthreads();
   };
-  if constexpr (ROWS == 256 || D == 64) {
+  if constexpr (ROWS == 256 || D == 64 || EDGE) {
     // unrolled by two: the LDS stage (and with it every fragment address) is a compile-time constant
     for (int j = 0; j < nblk; j += 2) {
       body(j, I0{});
@@ -499,6 +641,7 @@ __global__ __launch_bounds__(2 * ROWS, ROWS == 128 ? 2 : 1) void attn_bwd_dq_ker
     static_assert(DEPTH == 1, "a run-time stage goes with one tile in flight");
     for (int j = 0; j < nblk; ++j) body(j, j & 1);
   }
+  if (EDGE && q >= S_seq) return;
   store_rows<D>(dq, dqkv + ((size_t)b * S_seq + q) * ld + head * D, lane, scale);
   if (colpart) {
     // row (b, query block) of the partial column sums of dQ, [S_mb * S_seq / ROWS][N_heads * D]; the tile
@@ -521,7 +664,7 @@ __global__ __launch_bounds__(2 * ROWS, ROWS == 128 ? 2 : 1) void attn_bwd_dq_ker
 // role's exponentials overlap the other's MFMAs.
 constexpr int NTHR_DKV = 512;
 
-template <int D>
+template <int D, bool EDGE = false>
 __global__ __launch_bounds__(NTHR_DKV) void attn_bwd_dkv_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dctx,
                                                                 const float* __restrict__ lse, const float* __restrict__ delta,
                                                                 bf16_t* __restrict__ dqkv, int S_seq, int N_heads, int S_mb, int causal,
@@ -529,7 +672,11 @@ __global__ __launch_bounds__(NTHR_DKV) void attn_bwd_dkv_kernel(const bf16_t* __
   __shared__ __attribute__((aligned(16))) bf16_t QOs[2][2][BLK * D];  // Q and dO tiles, double-buffered
   __shared__ __attribute__((aligned(16))) float stat_s[2][2][BLK];    // lse * log2(e) and delta of the tile's queries
   __shared__ __attribute__((aligned(16))) bf16_t Ps[2][4][2][64 * 8]; // P of a sub-tile: [sub-tile][key group][register half][lane]
+  __shared__ __attribute__((aligned(16))) bf16_t Pl[EDGE ? 2 : 1][EDGE ? 4 : 1][EDGE ? 2 : 1][EDGE ? 64 * 8 : 8];  // what P's rounding left
+  __shared__ float dump[EDGE ? 8 * DUMP : 1];
+  __shared__ int bad_tile[2];  // per LDS stage: 1 + the last tile staged there with a non-finite Q or dO
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  if (EDGE && tid < 2) bad_tile[tid] = 0;
   const int kg = w & 3;
   const bool dk_role = w >= 4;  // wave-uniform
   const int nhb = N_heads * S_mb;
@@ -546,26 +693,38 @@ __global__ __launch_bounds__(NTHR_DKV) void attn_bwd_dkv_kernel(const bf16_t* __
   FragAddr<D> fa;
   fa.init(lane);
   bf16x8 kvf[D / 16];  // this wave's K rows (dV role) or V rows (dK role): the B operand of its score-sized product
-  load_rowfrags<D>(base + (size_t)key * ld + (dk_role ? 2 * h : h), lane, kvf);
+  load_rowfrags<D>(base + (size_t)(EDGE ? min(key, S_seq - 1) : key) * ld + (dk_role ? 2 * h : h), lane, kvf);
   const float c2 = scale * LOG2E;
   f32x16 acc[D / 32];  // dV (waves 0-3) or dK (waves 4-7), transposed: rows = head dims, column = key
 #pragma unroll
   for (int dt = 0; dt < D / 32; ++dt) acc[dt] = zero16();
 
-  const int jbeg = causal ? k0 / BLK : 0, nblk = S_seq / BLK;
+  const int jbeg = causal ? k0 / BLK : 0, nblk = EDGE ? (S_seq + BLK - 1) / BLK : S_seq / BLK;
   TileRegs<BLK, D, NTHR_DKV> qr, dor;
-  qr.load(base + (size_t)jbeg * BLK * ld, ld, tid);
-  dor.load(dob + (size_t)jbeg * BLK * h, h, tid);
   float lnext = 0.f, dnext = 0.f;
-  if (tid < BLK) { lnext = lrow[jbeg * BLK + tid] * LOG2E; dnext = drow[jbeg * BLK + tid]; }
+  auto fetch = [&](int j) {
+    const int i = j * BLK + tid;
+    if constexpr (EDGE) {
+      qr.load_edge(base + (size_t)j * BLK * ld, ld, tid, S_seq - j * BLK);
+      dor.load_edge(dob + (size_t)j * BLK * h, h, tid, S_seq - j * BLK);
+      // past the end: exp2(0 - inf) = 0, no probability
+      if (tid < BLK) { lnext = i < S_seq ? lrow[i] * LOG2E : INFINITY; dnext = i < S_seq ? drow[i] : 0.f; }
+    } else {
+      qr.load(base + (size_t)j * BLK * ld, ld, tid);
+      dor.load(dob + (size_t)j * BLK * h, h, tid);
+      if (tid < BLK) { lnext = lrow[i] * LOG2E; dnext = drow[i]; }
+    }
+  };
+  auto note = [&](int j, int stage) {
+    if (EDGE && causal && j * BLK < k0 + WG_ROWS - 1 && (qr.non_finite() || dor.non_finite())) bad_tile[stage] = j + 1;
+  };
+  fetch(jbeg);
+  if (EDGE) __syncthreads();  // bad_tile is clear
   qr.store(QOs[0][0], tid);
   dor.store(QOs[0][1], tid);
+  note(jbeg, 0);
   if (tid < BLK) { stat_s[0][0][tid] = lnext; stat_s[0][1][tid] = dnext; }
-  if (jbeg + 1 < nblk) {
-    qr.load(base + (size_t)(jbeg + 1) * BLK * ld, ld, tid);
-    dor.load(dob + (size_t)(jbeg + 1) * BLK * h, h, tid);
-    if (tid < BLK) { lnext = lrow[(jbeg + 1) * BLK + tid] * LOG2E; dnext = drow[(jbeg + 1) * BLK + tid]; }
-  }
+  if (jbeg + 1 < nblk) fetch(jbeg + 1);
   __syncthreads();
   // Every wave passes the same barriers per query tile: one per hand-over of P and one at the end
   // (the other LDS stage is complete, this one may be overwritten).
@@ -579,15 +738,12 @@ __global__ __launch_bounds__(NTHR_DKV) void attn_bwd_dkv_kernel(const bf16_t* __
       qr.store(QOs[cur ^ 1][0], tid);
       dor.store(QOs[cur ^ 1][1], tid);
       if (tid < BLK) { stat_s[cur ^ 1][0][tid] = lnext; stat_s[cur ^ 1][1][tid] = dnext; }
+      note(j + 1, cur ^ 1);
     }
-    if (j + 2 < nblk) {
-      qr.load(base + (size_t)(j + 2) * BLK * ld, ld, tid);
-      dor.load(dob + (size_t)(j + 2) * BLK * h, h, tid);
-      if (tid < BLK) { lnext = lrow[(j + 2) * BLK + tid] * LOG2E; dnext = drow[(j + 2) * BLK + tid]; }
-    }
+    if (j + 2 < nblk) fetch(j + 2);
     const int qb = j * BLK;
     // every query of the tile is before this pair's keys: nothing to add (the partner skips as well)
-    const bool skip = causal && qb + BLK - 1 < kw;
+    const bool skip = (causal && qb + BLK - 1 < kw) || (EDGE && kw >= S_seq);
     const bool diag = causal && qb < kw + 31;
     // Sub-tiles T0 .. T1-1 (32 queries each) go through the two stages together; every wave passes the
     // hand-over barrier between the stages, whether it has work or not.
@@ -621,6 +777,10 @@ __global__ __launch_bounds__(NTHR_DKV) void attn_bwd_dkv_kernel(const bf16_t* __
             pb[u][1] = pack8(s[u], 1);
             *reinterpret_cast<bf16x8*>(&Ps[t][kg][0][lane * 8]) = pb[u][0];
             *reinterpret_cast<bf16x8*>(&Ps[t][kg][1][lane * 8]) = pb[u][1];
+            if constexpr (EDGE) {
+              *reinterpret_cast<bf16x8*>(&Pl[t][kg][0][lane * 8]) = pack8_low(s[u], 0);
+              *reinterpret_cast<bf16x8*>(&Pl[t][kg][1][lane * 8]) = pack8_low(s[u], 1);
+            }
           }
         } else {
           // dP = dO V^T
@@ -633,6 +793,37 @@ __global__ __launch_bounds__(NTHR_DKV) void attn_bwd_dkv_kernel(const bf16_t* __
         }
       }
       __syncthreads();
+      if constexpr (EDGE) {
+        if (!skip) {
+          if (dk_role) {
+            // dS = P (dP - delta), P from its two parts; masked pairs by selection (dP may be anything there)
+#pragma unroll
+            for (int u = 0; u < NTT; ++u) {
+              const int t = T0 + u;
+              bf16x8 hi[2], lo[2];
+#pragma unroll
+              for (int k2 = 0; k2 < 2; ++k2) {
+                hi[k2] = *reinterpret_cast<const bf16x8*>(&Ps[t][kg][k2][lane * 8]);
+                lo[k2] = *reinterpret_cast<const bf16x8*>(&Pl[t][kg][k2][lane * 8]);
+              }
+#pragma unroll
+              for (int r = 0; r < 16; ++r) {
+                const float p = (float)hi[r >> 3][r & 7] + (float)lo[r >> 3][r & 7];
+                const int i = qb + 32 * t + acc_row(r, lane);
+                s[u][r] = (causal && key > i) || i >= S_seq ? 0.f : p * (s[u][r] - delta_s[32 * t + acc_row(r, lane)]);
+              }
+            }
+          }
+          const bf16_t* tile = dk_role ? Qs : dOs;
+          if (bad_tile[cur] == j + 1) {
+            accumulate_allowed<D, NTT>(acc, s, T0, tile, dump + w * DUMP, lane, [&](int row) { return key <= qb + row && qb + row < S_seq; });
+          } else {
+#pragma unroll
+            for (int u = 0; u < NTT; ++u) accumulate_split<D>(acc, s[u], tile, 32 * (T0 + u), fa);
+          }
+        }
+        return;
+      }
       if (!skip) {
         if (!dk_role) {
           // dV += dO^T P
@@ -673,7 +864,7 @@ __global__ __launch_bounds__(NTHR_DKV) void attn_bwd_dkv_kernel(const bf16_t* __
     typedef std::integral_constant<int, 0> T_0;
     typedef std::integral_constant<int, 1> T_1;
     typedef std::integral_constant<int, 2> T_2;
-    if constexpr (D == 128) {
+    if constexpr (D == 128 && !EDGE) {
       // both sub-tiles together: two independent accumulators in the score-sized products, one
       // hand-over barrier per tile (measured: 2 % faster than one sub-tile at a time at S_head 128,
       // 7 % slower at S_head 64)
@@ -684,6 +875,7 @@ __global__ __launch_bounds__(NTHR_DKV) void attn_bwd_dkv_kernel(const bf16_t* __
     }
     __syncthreads();
   }
+  if (EDGE && key >= S_seq) return;
   bf16_t* out = dqkv + ((size_t)b * S_seq + key) * ld + head * D;
   if (dk_role) store_rows<D>(acc, out + h, lane, scale);
   else store_rows<D>(acc, out + 2 * h, lane, 1.0f);
@@ -731,6 +923,28 @@ bf_status bwd_d(int S_mb, int S_seq, int N_heads, int causal, const void* qkv, c
   return BF_OK;
 }
 
+// The EDGE forms: 128 rows per workgroup, the last ones partly empty; no partial column sums.
+template <int D>
+bf_status fwd_edge(int S_mb, int S_seq, int N_heads, int causal, const void* qkv, void* ctx, float* lse, hipStream_t st) {
+  const unsigned grid = (unsigned)((S_seq + 127) / 128) * N_heads * S_mb;
+  attn_fwd_kernel<D, 128, true><<<grid, 256, 0, st>>>((const bf16_t*)qkv, (bf16_t*)ctx, lse, S_seq, N_heads, S_mb, causal, 1.0f / sqrtf((float)D));
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) { set_error("attention_fwd_mfma launch failed: %s", hipGetErrorString(e)); return BF_EDEVICE; }
+  return BF_OK;
+}
+
+template <int D>
+bf_status bwd_edge(int S_mb, int S_seq, int N_heads, int causal, const void* qkv, const void* ctx, const float* lse,
+                   const void* dctx, void* dqkv, float* delta, hipStream_t st) {
+  const float scale = 1.0f / sqrtf((float)D);
+  const unsigned grid = (unsigned)((S_seq + 127) / 128) * N_heads * S_mb;
+  attn_bwd_dq_kernel<D, 128, true><<<grid, NTHR, 0, st>>>((const bf16_t*)qkv, (const bf16_t*)ctx, (const bf16_t*)dctx, lse, delta, (bf16_t*)dqkv, S_seq, N_heads, S_mb, causal, scale, nullptr);
+  attn_bwd_dkv_kernel<D, true><<<grid, NTHR_DKV, 0, st>>>((const bf16_t*)qkv, (const bf16_t*)dctx, lse, delta, (bf16_t*)dqkv, S_seq, N_heads, S_mb, causal, scale, nullptr);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) { set_error("attention_bwd_mfma launch failed: %s", hipGetErrorString(e)); return BF_EDEVICE; }
+  return BF_OK;
+}
+
 bool args_ok(int S_mb, int S_seq, int N_heads, int S_head, const void* a, const void* b2) {
   if (!attention_mfma_supported(S_seq, S_head)) { set_error("attention_mfma: needs S_head 64 or 128 and S_seq a multiple of 128"); return false; }
   if (S_mb < 1 || N_heads < 1 || S_mb > 65535 || N_heads > 65535) { set_error("attention_mfma: bad S_mb / N_heads"); return false; }
@@ -742,6 +956,22 @@ bool args_ok(int S_mb, int S_seq, int N_heads, int S_head, const void* a, const 
 
 bool attention_mfma_supported(int S_seq, int S_head) {
   return (S_head == 64 || S_head == 128) && S_seq >= WG_ROWS && S_seq % WG_ROWS == 0;
+}
+
+bool attention_mfma_edge_supported(int S_mb, int S_seq, int N_heads, int S_head) {
+  return (S_head == 64 || S_head == 128) && S_seq >= 1 && S_seq <= 4096 && S_mb >= 1 && N_heads >= 1 && S_mb <= 65535 && N_heads <= 65535 &&
+         (long)((S_seq + 127) / 128) * N_heads * S_mb < (1l << 31);
+}
+
+bf_status attention_fwd_mfma_edge(int S_mb, int S_seq, int N_heads, int S_head, int causal, const void* qkv, void* ctx, float* lse,
+                                  hipStream_t st) {
+  return S_head == 128 ? fwd_edge<128>(S_mb, S_seq, N_heads, causal, qkv, ctx, lse, st) : fwd_edge<64>(S_mb, S_seq, N_heads, causal, qkv, ctx, lse, st);
+}
+
+bf_status attention_bwd_mfma_edge(int S_mb, int S_seq, int N_heads, int S_head, int causal, const void* qkv, const void* ctx,
+                                  const float* lse, const void* dctx, void* dqkv, float* delta, hipStream_t st) {
+  return S_head == 128 ? bwd_edge<128>(S_mb, S_seq, N_heads, causal, qkv, ctx, lse, dctx, dqkv, delta, st)
+                       : bwd_edge<64>(S_mb, S_seq, N_heads, causal, qkv, ctx, lse, dctx, dqkv, delta, st);
 }
 
 bf_status attention_fwd_mfma(int S_mb, int S_seq, int N_heads, int S_head, int causal, const void* qkv, void* ctx,

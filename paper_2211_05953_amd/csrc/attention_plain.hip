@@ -267,6 +267,11 @@ bf_status attention_fwd(int dtype, int kernels, int S_mb, int S_seq, int N_heads
     if (!qkv || !ctx || !lse) { set_error("attention_fwd: null pointer"); return BF_EINVAL; }
     return attention_fwd_mfma(S_mb, S_seq, N_heads, S_head, causal, qkv, ctx, lse, st);
   }
+  if (dtype == BF_BF16 && kernels == BF_KERNELS_AUTO && attention_mfma_edge_supported(S_mb, S_seq, N_heads, S_head) &&
+      (((uintptr_t)qkv | (uintptr_t)ctx) & 15) == 0) {
+    if (!qkv || !ctx || !lse) { set_error("attention_fwd: null pointer"); return BF_EINVAL; }
+    return attention_fwd_mfma_edge(S_mb, S_seq, N_heads, S_head, causal, qkv, ctx, lse, st);
+  }
   if (kernels == BF_KERNELS_AUTO && attention_fwd_f32_supported(S_mb, S_seq, N_heads, S_head)) {
     if (!qkv || !ctx || !lse) { set_error("attention_fwd: null pointer"); return BF_EINVAL; }
     return attention_fwd_f32(dtype, S_mb, S_seq, N_heads, S_head, causal, qkv, ctx, lse, st);
@@ -294,6 +299,11 @@ bf_status attention_bwd(int dtype, int kernels, int S_mb, int S_seq, int N_heads
       const size_t rq = attention_bwd_mfma_part_q_rows(S_mb, S_seq), rkv = attention_bwd_mfma_part_kv_rows(S_mb, S_seq);
       return attn_bias_finish(use, (int)rq, use + rq * h, (int)rkv, h, db_qkv, accumulate, st);
     }
+  } else if (dtype == BF_BF16 && kernels == BF_KERNELS_AUTO && attention_mfma_edge_supported(S_mb, S_seq, N_heads, S_head) &&
+             (((uintptr_t)qkv | (uintptr_t)ctx | (uintptr_t)dctx | (uintptr_t)dqkv) & 15) == 0) {
+    if (!qkv || !ctx || !lse || !dctx || !dqkv || !delta) { set_error("attention_bwd: null pointer"); return BF_EINVAL; }
+    r = attention_bwd_mfma_edge(S_mb, S_seq, N_heads, S_head, causal, qkv, ctx, lse, dctx, dqkv, delta, st);
+    if (r != BF_OK || !db_qkv) return r;
   } else {
     r = attention_bwd_plain(dtype, S_mb, S_seq, N_heads, S_head, causal, qkv, ctx, lse, dctx, dqkv, delta, st,
                             kernels == BF_KERNELS_AUTO && attention_f32_supported(S_mb, S_seq, N_heads, S_head));

@@ -124,6 +124,12 @@ bf_status attention_bwd_plain(int dtype, int S_mb, int S_seq, int N_heads, int S
 bool attention_mfma_supported(int S_seq, int S_head);
 bf_status attention_fwd_mfma(int S_mb, int S_seq, int N_heads, int S_head, int causal,
                              const void* qkv, void* ctx, float* lse, hipStream_t st);
+// The same for sequences of any length up to 4096 (16-byte aligned tensors), probabilities kept to 16 bits and more
+bool attention_mfma_edge_supported(int S_mb, int S_seq, int N_heads, int S_head);
+bf_status attention_fwd_mfma_edge(int S_mb, int S_seq, int N_heads, int S_head, int causal, const void* qkv, void* ctx, float* lse,
+                                  hipStream_t st);
+bf_status attention_bwd_mfma_edge(int S_mb, int S_seq, int N_heads, int S_head, int causal, const void* qkv, const void* ctx,
+                                  const float* lse, const void* dctx, void* dqkv, float* delta, hipStream_t st);
 // part (may be null): the kernels also leave partial column sums of dqkv, attention_bwd_mfma_part_q_rows rows of
 // [S_hidden] for dQ (one per sequence and query block) followed by attention_bwd_mfma_part_kv_rows rows of
 // [2 S_hidden] for [dK | dV] (one per sequence and block of 128 keys).

@@ -503,3 +503,38 @@ def test_split_contraction_of_few_tiles(M, N, K):
         bf.bf_op_gemm(bf.BF_BF16, 0, layout, bf.BF_EPI_BIAS_RES, M, N, K, dA, op, ref, bias=dbias, R=dR)
         assert bool(torch.isfinite(planes).all())   # both slices were run
         assert rel_err(to_host(out), want) <= TOL["bf16"] and rel_err(to_host(out), to_host(ref).astype(np.float64)) <= 2.0 ** -7
+
+
+@pytest.mark.parametrize("causal", [1, 0])
+@pytest.mark.parametrize("S_mb,S_seq,a,d", [(1, 2, 2, 64), (2, 63, 2, 64), (1, 65, 2, 128), (1, 129, 2, 128), (2, 300, 2, 64), (1, 255, 3, 128)])
+def test_attention_of_any_length_in_bf16(causal, S_mb, S_seq, a, d):
+    """Sequences that are not whole blocks of 128 on the bf16 matrix instructions, probabilities in two parts: no further
+    from the oracle than the fp32 kernels that served them (2 % of the rounding of the outputs, which both share, for
+    the chance of single roundings), nothing written outside, and finite wherever those are finite when infinities
+    and NaN lie behind the mask."""
+    h = a * d
+    for poison in (False, True):
+        qkv, dctx = (bf_inputs.normal(33, i, (S_mb, S_seq, n * h), bf16=True) for i, n in ((0, 3), (1, 1)))
+        if poison:
+            qkv[:, S_seq - 1, 2 * h + 3], qkv[:, 2 * S_seq // 3, h + 1] = np.inf, np.nan
+            qkv[:, S_seq // 3, 5], dctx[:, S_seq // 2, 2] = -np.inf, np.nan
+        dQKV, dDC = to_dev(qkv, True), to_dev(dctx, True)
+        got = []
+        for kernels in (bf.BF_KERNELS_AUTO, bf.BF_KERNELS_PLAIN):
+            ctx, dqkv = (torch.full((S_mb * S_seq * n * h + 64,), 7.0, dtype=torch.bfloat16, device="cuda") for n in (1, 3))
+            lse, delta = (torch.full((S_mb * a * S_seq + 64,), 7.0, device="cuda") for _ in range(2))
+            bf.bf_op_attention_fwd(bf.BF_BF16, kernels, S_mb, S_seq, a, d, causal, dQKV, ctx, lse)
+            bf.bf_op_attention_bwd(bf.BF_BF16, kernels, S_mb, S_seq, a, d, causal, dQKV, ctx, lse, dDC, dqkv, delta)
+            for t in (ctx, dqkv, lse, delta):
+                assert bool((t[-64:] == 7.0).all())
+            got.append([to_host(ctx[:-64].reshape(S_mb, S_seq, h)), to_host(dqkv[:-64].reshape(S_mb, S_seq, 3 * h)), to_host(lse[:-64])])
+        if poison:
+            for x, y in zip(*got):
+                assert np.array_equal(np.isfinite(x), np.isfinite(y))
+            continue
+        ctx_ref, saved = L.attention_fwd(qkv.astype(np.float64), a, bool(causal))
+        dqkv_ref = L.attention_bwd(dctx.astype(np.float64), saved, a)
+        for x, y, ref in ((got[0][0], got[1][0], ctx_ref), (got[0][1], got[1][1], dqkv_ref)):
+            off = [np.linalg.norm(t - ref) / np.linalg.norm(ref) for t in (x, y)]
+            assert off[0] <= 1.02 * off[1] + 1e-6, off
+        assert np.abs(got[0][2] - got[1][2]).max() <= 4e-6
