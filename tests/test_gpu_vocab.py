@@ -200,3 +200,50 @@ def test_lm_step_argument_errors():
     with pytest.raises(bf.BfError):
         st.bf_get_params(0, bf.VOCAB_TENSOR_IDS["w_out"])       # the vocabulary tensors live in pseudo-layer N_layers
     st.close()
+
+
+@pytest.mark.parametrize("dtype,bar", [(bf.BF_FP32, 1e-5), (bf.BF_BF16, 2e-2)])
+@pytest.mark.parametrize("V", [8, 1000, 2048, 2056, 8192, 8200, 32768, 50304, 57344, 57352])
+def test_ce_loss_row_kept_in_registers(dtype, bar, V):
+    """Vocabularies around the sizes at which a thread's share of the row grows (256 or 1024 threads, 1 to 13 vectors each)
+    and past the largest, with a row half masked (by -inf where the row stays in registers) and labels out of range;
+    bars as for every kernel."""
+    n = 5
+    td = torch.bfloat16 if dtype == bf.BF_BF16 else torch.float32
+    z = torch.from_numpy(np.random.default_rng(V).standard_normal((n, V)).astype(np.float32) * 3).to(td)
+    z[1, : V // 2] = float("-inf") if V <= (57344 if dtype == bf.BF_BF16 else 53248) else -1e30
+    labels = torch.tensor([0, V - 1, V // 2, -1, V], dtype=torch.int32)
+    z64 = z.double()
+    lse = torch.logsumexp(z64, -1)
+    want, loss = torch.softmax(z64, -1), torch.zeros(n, dtype=torch.float64)
+    for r in range(3):
+        loss[r] = (lse[r] - z64[r, labels[r]]) * 0.25
+        want[r, labels[r]] -= 1.0
+    want[3:] = 0.0
+    buf = torch.full((n * V + 64,), 7.0, dtype=td, device="cuda")
+    buf[: n * V] = z.cuda().reshape(-1)
+    rl, total = torch.empty(n, device="cuda"), torch.empty(1, device="cuda")
+    bf.bf_op_ce_loss(dtype, n, V, buf, labels.cuda(), 0.25, rl, total)
+    got = buf[: n * V].reshape(n, V).double().cpu()
+    assert bool((buf[n * V:] == 7.0).all())
+    assert (got - want * 0.25).abs().max() <= bar * (want * 0.25).abs().max()
+    assert (rl.double().cpu() - loss).abs().max() <= 1e-5 * loss.abs().max() and abs(total.item() - loss.sum().item()) <= 1e-5 * loss.abs().sum()
+
+
+@pytest.mark.parametrize("S_mb,S_seq,V,h", [(1, 1, 3, 8), (3, 700, 5, 40), (1, 2049, 2, 1028), (2, 1500, 40, 33)])
+def test_embedding_bwd_of_frequent_tokens(S_mb, S_seq, V, h):
+    """Many uses of few ids: more than 16 rows in flight, more than one window of 2048 positions, ids out of range, odd
+    widths.  fp32 sums in ascending position: against 64 bits within n 2^-24 of the sum of magnitudes."""
+    rng = np.random.default_rng(S_seq)
+    tok = rng.integers(-1, V + 1, (S_mb, S_seq)).astype(np.int32)
+    d = rng.standard_normal((S_mb, S_seq, h)).astype(np.float32)
+    g_tok = torch.ones((V, h), device="cuda")
+    g_pos = torch.full((S_seq, h), 2.0, device="cuda")
+    bf.bf_op_embedding_bwd(bf.BF_FP32, S_mb, S_seq, V, h, torch.from_numpy(tok).cuda(), torch.from_numpy(d).cuda(), g_tok, g_pos, 1)
+    want, size = np.ones((V, h)), np.ones((V, h))
+    for v in range(V):
+        want[v] += d[tok == v].astype(np.float64).sum(0)
+        size[v] += np.abs(d[tok == v]).sum(0)
+    n = S_mb * S_seq
+    assert (np.abs(g_tok.cpu().numpy() - want) <= (n + 1) * 2.0 ** -24 * size).all()
+    assert np.abs(g_pos.cpu().numpy() - (2.0 + d.astype(np.float64).sum(0))).max() <= 1e-5
