@@ -685,38 +685,42 @@ bf_status colsum(int dtype, int T, int N, const void* dY, float* out, int accumu
   return BF_OK;
 }
 
-__global__ __launch_bounds__(256) void colsum_finish_kernel(const float* __restrict__ part, int rows, int N, float* __restrict__ out,
+__global__ __launch_bounds__(64) void colsum_finish_kernel(const float* __restrict__ part, int rows, int N, float* __restrict__ out,
                                                             int accumulate) {
-  const int n = blockIdx.x * 256 + threadIdx.x;
+  const int n = blockIdx.x * 64 + threadIdx.x;
   if (n >= N) return;
   float t = accumulate ? out[n] : 0.f;
+#pragma unroll 8  // eight loads in flight: the launch is a chain of them
   for (int r = 0; r < rows; ++r) t += part[(size_t)r * N + n];
   out[n] = t;
 }
 
 bf_status colsum_finish(const float* part, int rows, int N, float* out, int accumulate, hipStream_t st) {
   if (!part || !out || rows < 1 || N < 1) { set_error("colsum_finish: bad argument"); return BF_EINVAL; }
-  colsum_finish_kernel<<<(N + 255) / 256, 256, 0, st>>>(part, rows, N, out, accumulate);
+  colsum_finish_kernel<<<(N + 63) / 64, 64, 0, st>>>(part, rows, N, out, accumulate);
   BF_LAUNCH_CHECK();
   return BF_OK;
 }
 
-__global__ __launch_bounds__(256) void attn_bias_finish_kernel(const float* __restrict__ pq, int rows_q, const float* __restrict__ pkv,
+__global__ __launch_bounds__(64) void attn_bias_finish_kernel(const float* __restrict__ pq, int rows_q, const float* __restrict__ pkv,
                                                                int rows_kv, int h, float* __restrict__ out, int accumulate) {
-  const int n = blockIdx.x * 256 + threadIdx.x;
+  const int n = blockIdx.x * 64 + threadIdx.x;
   if (n >= 3 * h) return;
   float t = accumulate ? out[n] : 0.f;
-  if (n < h)
-    for (int r = 0; r < rows_q; ++r) t += pq[(size_t)r * h + n];
-  else
-    for (int r = 0; r < rows_kv; ++r) t += pkv[(size_t)r * 2 * h + (n - h)];
+  // one loop for both kinds of column, eight loads in flight (the launch is a chain of them: 9.0 -> 4.6 us at 32 rows,
+  // 6.5 -> 4.8 at 16)
+  const float* p = n < h ? pq + n : pkv + (n - h);
+  const size_t pitch = n < h ? h : 2 * (size_t)h;
+  const int rows = n < h ? rows_q : rows_kv;
+#pragma unroll 8
+  for (int r = 0; r < rows; ++r) t += p[r * pitch];
   out[n] = t;
 }
 
 bf_status attn_bias_finish(const float* pq, int rows_q, const float* pkv, int rows_kv, int h, float* out, int accumulate,
                            hipStream_t st) {
   if (!pq || !pkv || !out || rows_q < 1 || rows_kv < 1 || h < 1) { set_error("attn_bias_finish: bad argument"); return BF_EINVAL; }
-  attn_bias_finish_kernel<<<(3 * h + 255) / 256, 256, 0, st>>>(pq, rows_q, pkv, rows_kv, h, out, accumulate);
+  attn_bias_finish_kernel<<<(3 * h + 63) / 64, 64, 0, st>>>(pq, rows_q, pkv, rows_kv, h, out, accumulate);
   BF_LAUNCH_CHECK();
   return BF_OK;
 }
