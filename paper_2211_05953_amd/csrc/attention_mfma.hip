@@ -330,7 +330,8 @@ struct NextSetOf<DEPTH, std::integral_constant<int, V>> { static constexpr int v
 // their use and are double-buffered in LDS: tile j+1 is written to the idle stage while tile j is
 // consumed, so an iteration has a single barrier.  The 256-query form reads each tile from HBM / L2
 // once for twice as many queries and keeps two tiles in flight; it needs enough (head, block) pairs
-// to fill the chip.
+// to fill the chip.  KG = 2: two groups of waves take every other key tile of the same rows (tiles staged in pairs) and
+// merge their maxima, sums and outputs in LDS at the end, for launches of few rows.
 // Measured at S_seq 1024-2048, 64 heads of 128: timed without softmax, P V and K/V refetch, the bare
 // S = K Q^T loop (one 1 KB LDS fragment read per MFMA, Q from registers) reaches 44 % of the MFMA
 // rate; without P V 70 % of the full time remains, without the softmax arithmetic 84 %, without the
@@ -339,14 +340,15 @@ struct NextSetOf<DEPTH, std::integral_constant<int, V>> { static constexpr int v
 // (accumulators in AGPRs, one wavefront per SIMD): built and measured level with this form (100 against
 // 98 us at 64 heads of 128, S_seq 2048): a lone wavefront issues in order, so each of its LDS, barrier
 // and softmax waits stops its MFMAs too, and there is no partner on the SIMD to fill the gap.
-template <int D, int ROWS, bool EDGE = false>
-__global__ __launch_bounds__(2 * ROWS, ROWS == 128 && !(EDGE && D == 128) ? 2 : 1) void attn_fwd_kernel(const bf16_t* __restrict__ qkv,
+template <int D, int ROWS, bool EDGE = false, int KG = 1>
+__global__ __launch_bounds__(2 * ROWS * KG, ROWS == 128 && !(EDGE && D == 128) ? 2 : 1) void attn_fwd_kernel(const bf16_t* __restrict__ qkv,
                                                                                  bf16_t* __restrict__ ctx, float* __restrict__ lse,
                                                                                  int S_seq, int N_heads, int S_mb, int causal,
                                                                                  float scale) {
-  constexpr int NT = 2 * ROWS, DEPTH = ROWS == 128 ? 1 : 2;
-  __shared__ __attribute__((aligned(16))) bf16_t KVs[2][2][BLK * D];
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  constexpr int NT = 2 * ROWS * KG, DEPTH = ROWS == 256 ? 2 : 1, BT = BLK * KG;
+  __shared__ __attribute__((aligned(16))) bf16_t KVs[2][2][BT * D];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int grp = KG == 1 ? 0 : (tid >> 6) / (ROWS / 32), w = KG == 1 ? tid >> 6 : (tid >> 6) % (ROWS / 32);  // key group, rows
   // 1-D grid ordered by work: the last (longest) query block of every head first, then the next ...
   const int nhb = N_heads * S_mb;
   const int qblk = (EDGE ? (S_seq + ROWS - 1) / ROWS : S_seq / ROWS) - 1 - blockIdx.x / nhb;
@@ -370,8 +372,8 @@ __global__ __launch_bounds__(2 * ROWS, ROWS == 128 && !(EDGE && D == 128) ? 2 : 
   float m = -INFINITY, l = 0.f;
   const float c2 = scale * LOG2E;
 
-  const int nblk = EDGE ? ((causal ? min(q0 + ROWS, S_seq) : S_seq) + BLK - 1) / BLK : causal ? (q0 + ROWS) / BLK : S_seq / BLK;
-  TileRegs<BLK, D, NT> kr[DEPTH], vr[DEPTH];  // set (j % DEPTH) carries tile j
+  const int nblk = EDGE ? ((causal ? min(q0 + ROWS, S_seq) : S_seq) + BLK - 1) / BLK : causal ? (q0 + ROWS + (KG - 1) * BLK) / BT : S_seq / BT;
+  TileRegs<BT, D, NT> kr[DEPTH], vr[DEPTH];  // set (j % DEPTH) carries tile j
   auto fetch = [&](auto setc, int j) {
     constexpr int SET = decltype(setc)::value;
     if constexpr (EDGE) {
@@ -379,14 +381,14 @@ __global__ __launch_bounds__(2 * ROWS, ROWS == 128 && !(EDGE && D == 128) ? 2 : 
       vr[SET].load_edge(base + (size_t)j * BLK * ld + 2 * h, ld, tid, S_seq - j * BLK);
       return;
     }
-    kr[SET].load(base + (size_t)j * BLK * ld + h, ld, tid);
-    vr[SET].load(base + (size_t)j * BLK * ld + 2 * h, ld, tid);
+    kr[SET].load(base + (size_t)j * BT * ld + h, ld, tid);
+    vr[SET].load(base + (size_t)j * BT * ld + 2 * h, ld, tid);
   };
   typedef std::integral_constant<int, 0> I0;
   typedef std::integral_constant<int, 1> I1;
   fetch(I0{}, 0);
   // tile j goes to an LDS stage: does the mask cut it, and does it hold what must not meet a masked zero
-  auto note = [&](int j, int stage, const TileRegs<BLK, D, NT>& v) {
+  auto note = [&](int j, int stage, const TileRegs<BT, D, NT>& v) {
     if (EDGE && causal && j * BLK + BLK - 1 > q0 && v.non_finite()) bad_tile[stage] = j + 1;
   };
   if (EDGE) __syncthreads();  // bad_tile is clear
@@ -401,15 +403,15 @@ __global__ __launch_bounds__(2 * ROWS, ROWS == 128 && !(EDGE && D == 128) ? 2 : 
   auto body = [&](int j, auto parc) {
     constexpr int PAR = decltype(parc)::value;
     typedef std::integral_constant<int, (PAR + 1) % DEPTH> NextSet;
-    const bf16_t* Ks = KVs[PAR][0];
-    const bf16_t* Vs = KVs[PAR][1];
+    const bf16_t* Ks = KVs[PAR][0] + grp * BLK * D;
+    const bf16_t* Vs = KVs[PAR][1] + grp * BLK * D;
     if (j + 1 < nblk) {
       kr[NextSet::value].store(KVs[PAR ^ 1][0], tid);
       vr[NextSet::value].store(KVs[PAR ^ 1][1], tid);
       note(j + 1, PAR ^ 1, vr[NextSet::value]);
     }
     if (j + 1 + DEPTH < nblk) fetch(NextSet{}, j + 1 + DEPTH);
-    const int kb = j * BLK;
+    const int kb = j * BT + grp * BLK;
     // the whole tile is above this wave's diagonal, or the wave's rows are past the end
     if ((causal && kb > qw + 31) || (EDGE && qw >= S_seq)) { __syncthreads(); return; }
     f32x16 s[2] = {zero16(), zero16()};
@@ -495,6 +497,31 @@ __global__ __launch_bounds__(2 * ROWS, ROWS == 128 && !(EDGE && D == 128) ? 2 : 
     body(j, I0{});
     if (j + 1 < nblk) body(j + 1, I1{});
   }
+  if constexpr (KG == 2) {
+    // the second key group hands its rows over, lane to lane (the loop ended on a barrier: the tiles are free); it may
+    // have seen no key (maximum -inf, sums 0)
+    constexpr int NV = D / 2 + 2;
+    static_assert(NV * 64 * (ROWS / 32) * 4 <= sizeof(KVs), "the hand-over does not fit");
+    float* hb = reinterpret_cast<float*>(&KVs[0][0][0]) + w * NV * 64 + lane;
+    if (grp == 1) {
+#pragma unroll
+      for (int dt = 0; dt < D / 32; ++dt)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) hb[(dt * 16 + r) * 64] = o[dt][r];
+      hb[(NV - 2) * 64] = m;
+      hb[(NV - 1) * 64] = l;
+    }
+    __syncthreads();
+    if (grp == 1) return;
+    const float m1 = hb[(NV - 2) * 64], M = fmaxf(m, m1);
+    const float a0 = __builtin_amdgcn_exp2f((m - M) * c2), a1 = __builtin_amdgcn_exp2f((m1 - M) * c2);
+    l = l * a0 + hb[(NV - 1) * 64] * a1;
+#pragma unroll
+    for (int dt = 0; dt < D / 32; ++dt)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) o[dt][r] = o[dt][r] * a0 + hb[(dt * 16 + r) * 64] * a1;
+    m = M;
+  }
   l += __shfl_xor(l, 32, 64);
   if (EDGE && q >= S_seq) return;
   store_rows<D>(o, ctx + ((size_t)b * S_seq + q) * h + head * D, lane, 1.0f / l);
@@ -505,14 +532,15 @@ __global__ __launch_bounds__(2 * ROWS, ROWS == 128 && !(EDGE && D == 128) ? 2 : 
 // Also takes delta[b, head, i] = sum_c dctx[i, c] ctx[i, c] of its queries (each lane already holds
 // half of its query's dctx row) and leaves it in `delta` for the dK/dV pass.
 // ROWS queries per workgroup and K/V tiles DEPTH tiles ahead, as in the forward kernel.
-template <int D, int ROWS, bool EDGE = false>
-__global__ __launch_bounds__(2 * ROWS, ROWS == 128 && !EDGE ? 2 : 1) void attn_bwd_dq_kernel(
+template <int D, int ROWS, bool EDGE = false, int KG = 1>
+__global__ __launch_bounds__(2 * ROWS * KG, ROWS == 128 && !EDGE ? 2 : 1) void attn_bwd_dq_kernel(
     const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ ctx, const bf16_t* __restrict__ dctx,
     const float* __restrict__ lse, float* __restrict__ delta, bf16_t* __restrict__ dqkv, int S_seq, int N_heads, int S_mb,
     int causal, float scale, float* __restrict__ colpart) {
-  constexpr int NT = 2 * ROWS, DEPTH = ROWS == 128 ? 1 : 2;
-  __shared__ __attribute__((aligned(16))) bf16_t KVs[2][2][BLK * D];  // double-buffered, one barrier per tile
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  constexpr int NT = 2 * ROWS * KG, DEPTH = ROWS == 256 ? 2 : 1, BT = BLK * KG;
+  __shared__ __attribute__((aligned(16))) bf16_t KVs[2][2][BT * D];  // double-buffered, one barrier per tile
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int grp = KG == 1 ? 0 : (tid >> 6) / (ROWS / 32), w = KG == 1 ? tid >> 6 : (tid >> 6) % (ROWS / 32);  // key group, rows
   const int nhb = N_heads * S_mb;
   const int qblk = (EDGE ? (S_seq + ROWS - 1) / ROWS : S_seq / ROWS) - 1 - blockIdx.x / nhb;  // longest query blocks of every head first
   const int head = (blockIdx.x % nhb) % N_heads, b = (blockIdx.x % nhb) / N_heads;
@@ -526,7 +554,7 @@ __global__ __launch_bounds__(2 * ROWS, ROWS == 128 && !EDGE ? 2 : 1) void attn_b
   if (EDGE && tid < 2) bad_tile[tid] = 0;
 
   // precomputed offsets where the registers allow (the 128-query form at S_head 128 would spill)
-  typename std::conditional<(ROWS == 256 || D == 64 || EDGE), FragAddr<D>, FragAddrLive<D>>::type fa;
+  typename std::conditional<(ROWS != 128 || KG == 2 || D == 64 || EDGE), FragAddr<D>, FragAddrLive<D>>::type fa;
   fa.init(lane);
   bf16x8 qf[D / 16], dof[D / 16];
   load_rowfrags<D>(base + (size_t)ql * ld, lane, qf);
@@ -541,15 +569,15 @@ __global__ __launch_bounds__(2 * ROWS, ROWS == 128 && !EDGE ? 2 : 1) void attn_b
 #pragma unroll
       for (int e = 0; e < 8; ++e) dl = fmaf((float)dof[kk][e], (float)cf[kk][e], dl);
     dl += __shfl_xor(dl, 32, 64);  // lanes l and l + 32 hold the two halves of the row
-    if (lane < 32 && (!EDGE || q < S_seq)) delta[st] = dl;
+    if (lane < 32 && grp == 0 && (!EDGE || q < S_seq)) delta[st] = dl;
   }
   const float lse2 = lse[st] * LOG2E, c2 = scale * LOG2E;
   f32x16 dq[D / 32];
 #pragma unroll
   for (int dt = 0; dt < D / 32; ++dt) dq[dt] = zero16();
 
-  const int nblk = EDGE ? ((causal ? min(q0 + ROWS, S_seq) : S_seq) + BLK - 1) / BLK : causal ? (q0 + ROWS) / BLK : S_seq / BLK;
-  TileRegs<BLK, D, NT> kr[DEPTH], vr[DEPTH];  // set (j % DEPTH) carries tile j
+  const int nblk = EDGE ? ((causal ? min(q0 + ROWS, S_seq) : S_seq) + BLK - 1) / BLK : causal ? (q0 + ROWS + (KG - 1) * BLK) / BT : S_seq / BT;
+  TileRegs<BT, D, NT> kr[DEPTH], vr[DEPTH];  // set (j % DEPTH) carries tile j
   auto fetch = [&](auto setc, int j) {
     constexpr int SET = decltype(setc)::value;
     if constexpr (EDGE) {
@@ -557,13 +585,13 @@ __global__ __launch_bounds__(2 * ROWS, ROWS == 128 && !EDGE ? 2 : 1) void attn_b
       vr[SET].load_edge(base + (size_t)j * BLK * ld + 2 * h, ld, tid, S_seq - j * BLK);
       return;
     }
-    kr[SET].load(base + (size_t)j * BLK * ld + h, ld, tid);
-    vr[SET].load(base + (size_t)j * BLK * ld + 2 * h, ld, tid);
+    kr[SET].load(base + (size_t)j * BT * ld + h, ld, tid);
+    vr[SET].load(base + (size_t)j * BT * ld + 2 * h, ld, tid);
   };
   typedef std::integral_constant<int, 0> I0;
   typedef std::integral_constant<int, 1> I1;
   fetch(I0{}, 0);
-  auto note = [&](int j, int stage, const TileRegs<BLK, D, NT>& k) {
+  auto note = [&](int j, int stage, const TileRegs<BT, D, NT>& k) {
     if (EDGE && causal && j * BLK + BLK - 1 > q0 && k.non_finite()) bad_tile[stage] = j + 1;
   };
   if (EDGE) __syncthreads();  // bad_tile is clear
@@ -577,15 +605,15 @@ __global__ __launch_bounds__(2 * ROWS, ROWS == 128 && !EDGE ? 2 : 1) void attn_b
   auto body = [&](int j, auto par) {
     typedef std::integral_constant<int, NextSetOf<DEPTH, decltype(par)>::value> NextSet;
     const int p = par;
-    const bf16_t* Ks = KVs[p][0];
-    const bf16_t* Vs = KVs[p][1];
+    const bf16_t* Ks = KVs[p][0] + grp * BLK * D;
+    const bf16_t* Vs = KVs[p][1] + grp * BLK * D;
     if (j + 1 < nblk) {
       kr[NextSet::value].store(KVs[p ^ 1][0], tid);
       vr[NextSet::value].store(KVs[p ^ 1][1], tid);
       note(j + 1, p ^ 1, kr[NextSet::value]);
     }
     if (j + 1 + DEPTH < nblk) fetch(NextSet{}, j + 1 + DEPTH);
-    const int kb = j * BLK;
+    const int kb = j * BT + grp * BLK;
     if ((causal && kb > qw + 31) || (EDGE && qw >= S_seq)) { __syncthreads(); return; }
     const bool diag = causal && kb + BLK - 1 > qw;
 #pragma unroll
@@ -631,7 +659,7 @@ __global__ __launch_bounds__(2 * ROWS, ROWS == 128 && !EDGE ? 2 : 1) void attn_b
     }
     __syncthreads();
   };
-  if constexpr (ROWS == 256 || D == 64 || EDGE) {
+  if constexpr (ROWS != 128 || KG == 2 || D == 64 || EDGE) {
     // unrolled by two: the LDS stage (and with it every fragment address) is a compile-time constant
     for (int j = 0; j < nblk; j += 2) {
       body(j, I0{});
@@ -641,15 +669,35 @@ __global__ __launch_bounds__(2 * ROWS, ROWS == 128 && !EDGE ? 2 : 1) void attn_b
     static_assert(DEPTH == 1, "a run-time stage goes with one tile in flight");
     for (int j = 0; j < nblk; ++j) body(j, j & 1);
   }
+  if constexpr (KG == 2) {
+    // the second key group's share, lane to lane
+    constexpr int NV = D / 2;
+    static_assert(NV * 64 * (ROWS / 32) * 4 <= sizeof(KVs), "the hand-over does not fit");
+    float* hb = reinterpret_cast<float*>(&KVs[0][0][0]) + w * NV * 64 + lane;
+    if (grp == 1) {
+#pragma unroll
+      for (int dt = 0; dt < D / 32; ++dt)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) hb[(dt * 16 + r) * 64] = dq[dt][r];
+    }
+    __syncthreads();
+    if (grp == 0) {
+#pragma unroll
+      for (int dt = 0; dt < D / 32; ++dt)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) dq[dt][r] += hb[(dt * 16 + r) * 64];
+    }
+    __syncthreads();  // the hand-over has been read: the column sums below use the same LDS
+  }
   if (EDGE && q >= S_seq) return;
-  store_rows<D>(dq, dqkv + ((size_t)b * S_seq + q) * ld + head * D, lane, scale);
+  if (grp == 0) store_rows<D>(dq, dqkv + ((size_t)b * S_seq + q) * ld + head * D, lane, scale);
   if (colpart) {
     // row (b, query block) of the partial column sums of dQ, [S_mb * S_seq / ROWS][N_heads * D]; the tile
     // buffers are free: the loop ended on a barrier
     float* red = reinterpret_cast<float*>(&KVs[0][0][0]);
-    wave_colsum<D>(dq, scale, red + (size_t)w * 4 * (D / 2), lane);
+    if (grp == 0) wave_colsum<D>(dq, scale, red + (size_t)w * 4 * (D / 2), lane);
     __syncthreads();
-    if (tid < D) colpart[((size_t)b * (S_seq / ROWS) + qblk) * h + head * D + tid] = colsum_of<D>(red, 0, NT / 64, tid);
+    if (tid < D) colpart[((size_t)b * (S_seq / ROWS) + qblk) * h + head * D + tid] = colsum_of<D>(red, 0, ROWS / 32, tid);
   }
 }
 
@@ -895,6 +943,18 @@ __global__ __launch_bounds__(NTHR_DKV, D == 64 && !EDGE ? 4 : 2) void attn_bwd_d
 
 template <int D>
 bf_status fwd_d(int S_mb, int S_seq, int N_heads, int causal, const void* qkv, void* ctx, float* lse, hipStream_t st) {
+  const long blocks = (long)(S_seq / WG_ROWS) * N_heads * S_mb;
+  const float scale = 1.0f / sqrtf((float)D);
+  // Two key groups per workgroup halve the chain of key tiles of a row, which is the time of a launch that leaves compute
+  // units idle (all of them but those of the longest rows, if causal).  Measured, one group / two on 64 rows / two on 128
+  // rows, us: S_head 128, S_seq 2048 causal, 8 heads 50 / 45 / 42, 16 heads 52 / 53 / 44, 32 heads 68 / 106 / 57, 64 heads
+  // 88 / 206 / 111; bidirectional, 16 heads 53 / 87 / 49, 32 heads 76 / 199 / 93; S_seq 512, 16 heads 16.5 / 14.9 / 16.2;
+  // S_head 64, S_seq 2048 causal, 16 heads 36 / 30 / 27, 32 heads 46 / 43 / 35, 64 heads 62 / 85 / 76.
+  if (S_seq >= 1024 && blocks <= (causal ? 512 : 256)) {
+    attn_fwd_kernel<D, 128, false, 2><<<(unsigned)blocks, 512, 0, st>>>((const bf16_t*)qkv, (bf16_t*)ctx, lse, S_seq, N_heads, S_mb, causal, scale);
+  } else if (S_seq >= 256 && S_seq < 1024 && blocks <= 128) {
+    attn_fwd_kernel<D, 64, false, 2><<<(unsigned)(2 * blocks), 256, 0, st>>>((const bf16_t*)qkv, (bf16_t*)ctx, lse, S_seq, N_heads, S_mb, causal, scale);
+  } else
   // the 256-query form when there are enough (head, block) pairs to give every compute unit one
   if (S_seq % 256 == 0 && (long)(S_seq / 256) * N_heads * S_mb >= 256) {
     const unsigned grid = (unsigned)(S_seq / 256) * N_heads * S_mb;
@@ -908,6 +968,16 @@ bf_status fwd_d(int S_mb, int S_seq, int N_heads, int causal, const void* qkv, v
   return BF_OK;
 }
 
+// out[r][n] = sum of rows fold * r .. fold * r + fold - 1 of in, in order
+__global__ __launch_bounds__(64) void fold_rows_kernel(const float* __restrict__ in, float* __restrict__ out, int fold, int h) {
+  const int n = blockIdx.x * 64 + threadIdx.x;
+  if (n >= h) return;
+  const float* p = in + (size_t)blockIdx.y * fold * h + n;
+  float t = p[0];
+  for (int k = 1; k < fold; ++k) t += p[(size_t)k * h];
+  out[(size_t)blockIdx.y * h + n] = t;
+}
+
 template <int D>
 bf_status bwd_d(int S_mb, int S_seq, int N_heads, int causal, const void* qkv, const void* ctx, const float* lse,
                 const void* dctx, void* dqkv, float* delta, float* part, hipStream_t st) {
@@ -915,7 +985,17 @@ bf_status bwd_d(int S_mb, int S_seq, int N_heads, int causal, const void* qkv, c
   const unsigned grid = (unsigned)(S_seq / WG_ROWS) * N_heads * S_mb;
   // partial column sums: dQ's rows first, then those of [dK | dV]
   float* part_kv = part ? part + attention_bwd_mfma_part_q_rows(S_mb, S_seq) * (size_t)N_heads * D : nullptr;
-  if (S_seq % 256 == 0)  // measured faster than the 128-query form also on grids that do not fill the chip
+  // Two key groups on 64 rows, as in the forward pass (S_head 128, S_seq 2048 causal, 8 / 16 / 32 heads: 81 -> 53, 83 -> 66,
+  // 88 -> 125 us; bidirectional, 8 / 16 heads 81 -> 53, 84 -> 104; S_head 64, causal, 16 / 32 heads 47 -> 31, 50 -> 49; on 128
+  // rows it spills).  Its partial column sums, one row per 64 queries, go where those of [dK | dV] will be and are folded
+  // into the rows per 256 (or 128) queries that the scratch has (4 us).
+  if (S_seq >= 256 && 2 * (long)grid <= (causal ? 512 : 256)) {
+    attn_bwd_dq_kernel<D, 64, false, 2><<<grid * 2, 256, 0, st>>>((const bf16_t*)qkv, (const bf16_t*)ctx, (const bf16_t*)dctx, lse, delta, (bf16_t*)dqkv, S_seq, N_heads, S_mb, causal, scale, part_kv);
+    if (part) {
+      const int h = N_heads * D, rows = (int)attention_bwd_mfma_part_q_rows(S_mb, S_seq);
+      fold_rows_kernel<<<dim3((h + 63) / 64, rows), 64, 0, st>>>(part_kv, part, S_mb * (S_seq / 64) / rows, h);
+    }
+  } else if (S_seq % 256 == 0)  // measured faster than the 128-query form also on grids that do not fill the chip
     attn_bwd_dq_kernel<D, 256><<<grid / 2, 512, 0, st>>>((const bf16_t*)qkv, (const bf16_t*)ctx, (const bf16_t*)dctx, lse, delta, (bf16_t*)dqkv, S_seq, N_heads, S_mb, causal, scale, part);
   else
     attn_bwd_dq_kernel<D, 128><<<grid, NTHR, 0, st>>>((const bf16_t*)qkv, (const bf16_t*)ctx, (const bf16_t*)dctx, lse, delta, (bf16_t*)dqkv, S_seq, N_heads, S_mb, causal, scale, part);

@@ -538,3 +538,29 @@ def test_attention_of_any_length_in_bf16(causal, S_mb, S_seq, a, d):
             off = [np.linalg.norm(t - ref) / np.linalg.norm(ref) for t in (x, y)]
             assert off[0] <= 1.02 * off[1] + 1e-6, off
         assert np.abs(got[0][2] - got[1][2]).max() <= 4e-6
+
+
+@pytest.mark.parametrize("causal", [1, 0])
+@pytest.mark.parametrize("S_mb,S_seq,a,d", [(1, 256, 2, 64), (1, 384, 1, 128), (2, 640, 1, 64), (1, 1024, 1, 128), (2, 1152, 1, 64)])
+def test_attention_with_two_key_groups(causal, S_mb, S_seq, a, d):
+    """Launches of few rows: two groups of waves share a row's key tiles and merge; odd and even numbers of tiles per block,
+    rows that only one group sees a key of, and the folded partial column sums of dQ (4 and 2 rows into one)."""
+    h = a * d
+    qkv, dctx = (bf_inputs.normal(35, i, (S_mb, S_seq, n * h), bf16=True) for i, n in ((0, 3), (1, 1)))
+    qkv[..., :h] *= 3.0  # peaked rows: the two groups' maxima differ
+    qkv = bf_inputs.round_bf16(qkv)
+    ctx_ref, saved = L.attention_fwd(qkv.astype(np.float64), a, bool(causal))
+    dqkv_ref = L.attention_bwd(dctx.astype(np.float64), saved, a)
+    dQKV, dDC = to_dev(qkv, True), to_dev(dctx, True)
+    ctx, dqkv = (torch.full((S_mb, S_seq, n * h), float("nan"), dtype=torch.bfloat16, device="cuda") for n in (1, 3))
+    lse, delta = (torch.full((S_mb, a, S_seq), float("nan"), device="cuda") for _ in range(2))
+    part = torch.full((bf.bf_op_attention_bwd_part_elems(S_mb, S_seq, a, d) + 64,), float("nan"), device="cuda")
+    db = torch.full((3 * h,), float("nan"), device="cuda")
+    bf.bf_op_attention_fwd(bf.BF_BF16, 0, S_mb, S_seq, a, d, causal, dQKV, ctx, lse)
+    bf.bf_op_attention_bwd_bias(bf.BF_BF16, 0, S_mb, S_seq, a, d, causal, dQKV, ctx, lse, dDC, dqkv, delta, db, part, 0)
+    assert bool(torch.isnan(part[-64:]).all())
+    assert rel_err(to_host(ctx), ctx_ref) <= TOL["bf16"]
+    for i in range(3):
+        assert rel_err(to_host(dqkv)[..., i * h:(i + 1) * h], dqkv_ref[..., i * h:(i + 1) * h]) <= TOL["bf16"]
+    assert rel_err(to_host(db), dqkv_ref.reshape(-1, 3 * h).sum(0)) <= TOL["bf16"]
+    assert rel_err(to_host(db), to_host(dqkv).astype(np.float64).reshape(-1, 3 * h).sum(0)) <= 2.0 ** -8
