@@ -341,7 +341,7 @@ struct NextSetOf<DEPTH, std::integral_constant<int, V>> { static constexpr int v
 // 98 us at 64 heads of 128, S_seq 2048): a lone wavefront issues in order, so each of its LDS, barrier
 // and softmax waits stops its MFMAs too, and there is no partner on the SIMD to fill the gap.
 template <int D, int ROWS, bool EDGE = false, int KG = 1>
-__global__ __launch_bounds__(2 * ROWS * KG, ROWS == 128 && !(EDGE && D == 128) ? 2 : 1) void attn_fwd_kernel(const bf16_t* __restrict__ qkv,
+__global__ __launch_bounds__(2 * ROWS * KG, ROWS == 128 && !(EDGE && D == 128 && KG == 1) ? 2 : 1) void attn_fwd_kernel(const bf16_t* __restrict__ qkv,
                                                                                  bf16_t* __restrict__ ctx, float* __restrict__ lse,
                                                                                  int S_seq, int N_heads, int S_mb, int causal,
                                                                                  float scale) {
@@ -358,7 +358,7 @@ __global__ __launch_bounds__(2 * ROWS * KG, ROWS == 128 && !(EDGE && D == 128) ?
   const bf16_t* base = qkv + (size_t)b * S_seq * ld + head * D;
   const int q0 = qblk * ROWS, qw = q0 + 32 * w, q = qw + (lane & 31);
   const int ql = EDGE ? min(q, S_seq - 1) : q;  // the row that is read in the place of q
-  __shared__ float dump[EDGE ? ROWS / 32 * DUMP : 1];
+  __shared__ float dump[EDGE ? NT / 64 * DUMP : 1];
   __shared__ int bad_tile[2];  // per LDS stage: 1 + the last tile staged there with a non-finite V
   if (EDGE && tid < 2) bad_tile[tid] = 0;
 
@@ -372,13 +372,13 @@ __global__ __launch_bounds__(2 * ROWS * KG, ROWS == 128 && !(EDGE && D == 128) ?
   float m = -INFINITY, l = 0.f;
   const float c2 = scale * LOG2E;
 
-  const int nblk = EDGE ? ((causal ? min(q0 + ROWS, S_seq) : S_seq) + BLK - 1) / BLK : causal ? (q0 + ROWS + (KG - 1) * BLK) / BT : S_seq / BT;
+  const int nblk = EDGE ? ((causal ? min(q0 + ROWS, S_seq) : S_seq) + BT - 1) / BT : causal ? (q0 + ROWS + (KG - 1) * BLK) / BT : S_seq / BT;
   TileRegs<BT, D, NT> kr[DEPTH], vr[DEPTH];  // set (j % DEPTH) carries tile j
   auto fetch = [&](auto setc, int j) {
     constexpr int SET = decltype(setc)::value;
     if constexpr (EDGE) {
-      kr[SET].load_edge(base + (size_t)j * BLK * ld + h, ld, tid, S_seq - j * BLK);
-      vr[SET].load_edge(base + (size_t)j * BLK * ld + 2 * h, ld, tid, S_seq - j * BLK);
+      kr[SET].load_edge(base + (size_t)j * BT * ld + h, ld, tid, S_seq - j * BT);
+      vr[SET].load_edge(base + (size_t)j * BT * ld + 2 * h, ld, tid, S_seq - j * BT);
       return;
     }
     kr[SET].load(base + (size_t)j * BT * ld + h, ld, tid);
@@ -389,7 +389,7 @@ __global__ __launch_bounds__(2 * ROWS * KG, ROWS == 128 && !(EDGE && D == 128) ?
   fetch(I0{}, 0);
   // tile j goes to an LDS stage: does the mask cut it, and does it hold what must not meet a masked zero
   auto note = [&](int j, int stage, const TileRegs<BT, D, NT>& v) {
-    if (EDGE && causal && j * BLK + BLK - 1 > q0 && v.non_finite()) bad_tile[stage] = j + 1;
+    if (EDGE && causal && j * BT + BT - 1 > q0 && v.non_finite()) bad_tile[stage] = j + 1;
   };
   if (EDGE) __syncthreads();  // bad_tile is clear
   kr[0].store(KVs[0][0], tid);
@@ -413,7 +413,7 @@ __global__ __launch_bounds__(2 * ROWS * KG, ROWS == 128 && !(EDGE && D == 128) ?
     if (j + 1 + DEPTH < nblk) fetch(NextSet{}, j + 1 + DEPTH);
     const int kb = j * BT + grp * BLK;
     // the whole tile is above this wave's diagonal, or the wave's rows are past the end
-    if ((causal && kb > qw + 31) || (EDGE && qw >= S_seq)) { __syncthreads(); return; }
+    if ((causal && kb > qw + 31) || (EDGE && (qw >= S_seq || kb >= S_seq))) { __syncthreads(); return; }
     f32x16 s[2] = {zero16(), zero16()};
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -468,7 +468,7 @@ __global__ __launch_bounds__(2 * ROWS * KG, ROWS == 128 && !(EDGE && D == 128) ?
     l += sum;
     if constexpr (EDGE) {
       if (bad_tile[PAR] == j + 1) {
-        accumulate_allowed<D, 2>(o, s, 0, Vs, dump + w * DUMP, lane, [&](int row) { return kb + row <= q && kb + row < S_seq; });
+        accumulate_allowed<D, 2>(o, s, 0, Vs, dump + (tid >> 6) * DUMP, lane, [&](int row) { return kb + row <= q && kb + row < S_seq; });
         __syncthreads();
         return;
       }
@@ -549,7 +549,7 @@ __global__ __launch_bounds__(2 * ROWS * KG, ROWS == 128 && !EDGE ? 2 : 1) void a
   const bf16_t* base = qkv + (size_t)b * S_seq * ld + head * D;
   const int q0 = qblk * ROWS, qw = q0 + 32 * w, q = qw + (lane & 31);
   const int ql = EDGE ? min(q, S_seq - 1) : q;  // the row that is read in the place of q
-  __shared__ float dump[EDGE ? ROWS / 32 * DUMP : 1];
+  __shared__ float dump[EDGE ? NT / 64 * DUMP : 1];
   __shared__ int bad_tile[2];  // per LDS stage: 1 + the last tile staged there with a non-finite K
   if (EDGE && tid < 2) bad_tile[tid] = 0;
 
@@ -576,13 +576,13 @@ __global__ __launch_bounds__(2 * ROWS * KG, ROWS == 128 && !EDGE ? 2 : 1) void a
 #pragma unroll
   for (int dt = 0; dt < D / 32; ++dt) dq[dt] = zero16();
 
-  const int nblk = EDGE ? ((causal ? min(q0 + ROWS, S_seq) : S_seq) + BLK - 1) / BLK : causal ? (q0 + ROWS + (KG - 1) * BLK) / BT : S_seq / BT;
+  const int nblk = EDGE ? ((causal ? min(q0 + ROWS, S_seq) : S_seq) + BT - 1) / BT : causal ? (q0 + ROWS + (KG - 1) * BLK) / BT : S_seq / BT;
   TileRegs<BT, D, NT> kr[DEPTH], vr[DEPTH];  // set (j % DEPTH) carries tile j
   auto fetch = [&](auto setc, int j) {
     constexpr int SET = decltype(setc)::value;
     if constexpr (EDGE) {
-      kr[SET].load_edge(base + (size_t)j * BLK * ld + h, ld, tid, S_seq - j * BLK);
-      vr[SET].load_edge(base + (size_t)j * BLK * ld + 2 * h, ld, tid, S_seq - j * BLK);
+      kr[SET].load_edge(base + (size_t)j * BT * ld + h, ld, tid, S_seq - j * BT);
+      vr[SET].load_edge(base + (size_t)j * BT * ld + 2 * h, ld, tid, S_seq - j * BT);
       return;
     }
     kr[SET].load(base + (size_t)j * BT * ld + h, ld, tid);
@@ -592,7 +592,7 @@ __global__ __launch_bounds__(2 * ROWS * KG, ROWS == 128 && !EDGE ? 2 : 1) void a
   typedef std::integral_constant<int, 1> I1;
   fetch(I0{}, 0);
   auto note = [&](int j, int stage, const TileRegs<BT, D, NT>& k) {
-    if (EDGE && causal && j * BLK + BLK - 1 > q0 && k.non_finite()) bad_tile[stage] = j + 1;
+    if (EDGE && causal && j * BT + BT - 1 > q0 && k.non_finite()) bad_tile[stage] = j + 1;
   };
   if (EDGE) __syncthreads();  // bad_tile is clear
   kr[0].store(KVs[0][0], tid);
@@ -614,7 +614,7 @@ __global__ __launch_bounds__(2 * ROWS * KG, ROWS == 128 && !EDGE ? 2 : 1) void a
     }
     if (j + 1 + DEPTH < nblk) fetch(NextSet{}, j + 1 + DEPTH);
     const int kb = j * BT + grp * BLK;
-    if ((causal && kb > qw + 31) || (EDGE && qw >= S_seq)) { __syncthreads(); return; }
+    if ((causal && kb > qw + 31) || (EDGE && (qw >= S_seq || kb >= S_seq))) { __syncthreads(); return; }
     const bool diag = causal && kb + BLK - 1 > qw;
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
@@ -642,7 +642,7 @@ __global__ __launch_bounds__(2 * ROWS * KG, ROWS == 128 && !EDGE ? 2 : 1) void a
         }
         if (bad_tile[p] == j + 1) {
           const f32x16 s1[1] = {s};
-          accumulate_allowed<D, 1>(dq, s1, t, Ks, dump + w * DUMP, lane, [&](int row) { return kb + row <= q && kb + row < S_seq; });
+          accumulate_allowed<D, 1>(dq, s1, t, Ks, dump + (tid >> 6) * DUMP, lane, [&](int row) { return kb + row <= q && kb + row < S_seq; });
           continue;
         }
         accumulate_split<D>(dq, s, Ks, 32 * t, fa);
@@ -1005,11 +1005,19 @@ bf_status bwd_d(int S_mb, int S_seq, int N_heads, int causal, const void* qkv, c
   return BF_OK;
 }
 
-// The EDGE forms: 128 rows per workgroup, the last ones partly empty; no partial column sums.
+// The EDGE forms, the last block of rows partly empty; no partial column sums.  Two key groups for launches of few rows,
+// as in fwd_d and bwd_d (S_head 128 on 64 rows: on 128 they spill).  Forward, one group / two, us: S_head 128, causal, 1000
+// tokens, 16 heads 47 / 34, twice that 51 / 48 (bidirectional 51 / 70), 2 x 1900 tokens 90 / 126; S_head 64, 1900 tokens, 16
+// heads 51 / 36, 4 x 1000 tokens 33 / 31.
 template <int D>
 bf_status fwd_edge(int S_mb, int S_seq, int N_heads, int causal, const void* qkv, void* ctx, float* lse, hipStream_t st) {
-  const unsigned grid = (unsigned)((S_seq + 127) / 128) * N_heads * S_mb;
-  attn_fwd_kernel<D, 128, true><<<grid, 256, 0, st>>>((const bf16_t*)qkv, (bf16_t*)ctx, lse, S_seq, N_heads, S_mb, causal, 1.0f / sqrtf((float)D));
+  const long blocks = (long)((S_seq + 127) / 128) * N_heads * S_mb;
+  const float scale = 1.0f / sqrtf((float)D);
+  constexpr int EDGE_ROWS = D == 64 ? 128 : 64;
+  if (S_seq > 256 && blocks <= (causal ? 256 : 128) * (D == 64 ? 2 : 1))
+    attn_fwd_kernel<D, EDGE_ROWS, true, 2><<<(unsigned)((S_seq + EDGE_ROWS - 1) / EDGE_ROWS) * N_heads * S_mb, 4 * EDGE_ROWS, 0, st>>>((const bf16_t*)qkv, (bf16_t*)ctx, lse, S_seq, N_heads, S_mb, causal, scale);
+  else
+    attn_fwd_kernel<D, 128, true><<<(unsigned)blocks, 256, 0, st>>>((const bf16_t*)qkv, (bf16_t*)ctx, lse, S_seq, N_heads, S_mb, causal, scale);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) { set_error("attention_fwd_mfma launch failed: %s", hipGetErrorString(e)); return BF_EDEVICE; }
   return BF_OK;
@@ -1020,7 +1028,10 @@ bf_status bwd_edge(int S_mb, int S_seq, int N_heads, int causal, const void* qkv
                    const void* dctx, void* dqkv, float* delta, hipStream_t st) {
   const float scale = 1.0f / sqrtf((float)D);
   const unsigned grid = (unsigned)((S_seq + 127) / 128) * N_heads * S_mb;
-  attn_bwd_dq_kernel<D, 128, true><<<grid, NTHR, 0, st>>>((const bf16_t*)qkv, (const bf16_t*)ctx, (const bf16_t*)dctx, lse, delta, (bf16_t*)dqkv, S_seq, N_heads, S_mb, causal, scale, nullptr);
+  if (S_seq > 128 && 2 * (long)grid <= (causal && D == 64 ? 512 : 256))
+    attn_bwd_dq_kernel<D, 64, true, 2><<<(unsigned)((S_seq + 63) / 64) * N_heads * S_mb, 256, 0, st>>>((const bf16_t*)qkv, (const bf16_t*)ctx, (const bf16_t*)dctx, lse, delta, (bf16_t*)dqkv, S_seq, N_heads, S_mb, causal, scale, nullptr);
+  else
+    attn_bwd_dq_kernel<D, 128, true><<<grid, NTHR, 0, st>>>((const bf16_t*)qkv, (const bf16_t*)ctx, (const bf16_t*)dctx, lse, delta, (bf16_t*)dqkv, S_seq, N_heads, S_mb, causal, scale, nullptr);
   attn_bwd_dkv_kernel<D, true><<<grid, NTHR_DKV, 0, st>>>((const bf16_t*)qkv, (const bf16_t*)dctx, lse, delta, (bf16_t*)dqkv, S_seq, N_heads, S_mb, causal, scale, nullptr);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) { set_error("attention_bwd_mfma launch failed: %s", hipGetErrorString(e)); return BF_EDEVICE; }

@@ -506,7 +506,8 @@ def test_split_contraction_of_few_tiles(M, N, K):
 
 
 @pytest.mark.parametrize("causal", [1, 0])
-@pytest.mark.parametrize("S_mb,S_seq,a,d", [(1, 2, 2, 64), (2, 63, 2, 64), (1, 65, 2, 128), (1, 129, 2, 128), (2, 300, 2, 64), (1, 255, 3, 128)])
+@pytest.mark.parametrize("S_mb,S_seq,a,d", [(1, 2, 2, 64), (2, 63, 2, 64), (1, 65, 2, 128), (1, 129, 2, 128), (2, 300, 2, 64), (1, 255, 3, 128),
+                                           (1, 451, 2, 128), (1, 257, 70, 64)])
 def test_attention_of_any_length_in_bf16(causal, S_mb, S_seq, a, d):
     """Sequences that are not whole blocks of 128 on the bf16 matrix instructions, probabilities in two parts: no further
     from the oracle than the fp32 kernels that served them (2 % of the rounding of the outputs, which both share, for
