@@ -980,7 +980,7 @@ __global__ __launch_bounds__(64) void fold_rows_kernel(const float* __restrict__
 
 template <int D>
 bf_status bwd_d(int S_mb, int S_seq, int N_heads, int causal, const void* qkv, const void* ctx, const float* lse,
-                const void* dctx, void* dqkv, float* delta, float* part, hipStream_t st) {
+                const void* dctx, void* dqkv, float* delta, float* part, hipStream_t st, bool shared_chip) {
   const float scale = 1.0f / sqrtf((float)D);
   const unsigned grid = (unsigned)(S_seq / WG_ROWS) * N_heads * S_mb;
   // partial column sums: dQ's rows first, then those of [dK | dV]
@@ -989,7 +989,9 @@ bf_status bwd_d(int S_mb, int S_seq, int N_heads, int causal, const void* qkv, c
   // 88 -> 125 us; bidirectional, 8 / 16 heads 81 -> 53, 84 -> 104; S_head 64, causal, 16 / 32 heads 47 -> 31, 50 -> 49; on 128
   // rows it spills).  Its partial column sums, one row per 64 queries, go where those of [dK | dV] will be and are folded
   // into the rows per 256 (or 128) queries that the scratch has (4 us).
-  if (S_seq >= 256 && 2 * (long)grid <= (causal ? 512 : 256)) {
+  // Beside another stream's kernels the longest rows' units are not the only busy ones, and from 257 workgroups on the
+  // second group costs more than it hides (a 2048-wide step on two chains: attention backward 8.9 -> 9.9 ms, step 36.5 -> 37.6, with two).
+  if (S_seq >= 256 && 2 * (long)grid <= (causal && !shared_chip ? 512 : 256)) {
     attn_bwd_dq_kernel<D, 64, false, 2><<<grid * 2, 256, 0, st>>>((const bf16_t*)qkv, (const bf16_t*)ctx, (const bf16_t*)dctx, lse, delta, (bf16_t*)dqkv, S_seq, N_heads, S_mb, causal, scale, part_kv);
     if (part) {
       const int h = N_heads * D, rows = (int)attention_bwd_mfma_part_q_rows(S_mb, S_seq);
@@ -1080,10 +1082,10 @@ size_t attention_bwd_mfma_part_q_rows(int S_mb, int S_seq) { return (size_t)S_mb
 size_t attention_bwd_mfma_part_kv_rows(int S_mb, int S_seq) { return (size_t)S_mb * (S_seq / WG_ROWS); }
 
 bf_status attention_bwd_mfma(int S_mb, int S_seq, int N_heads, int S_head, int causal, const void* qkv, const void* ctx,
-                             const float* lse, const void* dctx, void* dqkv, float* delta, hipStream_t st, float* part) {
+                             const float* lse, const void* dctx, void* dqkv, float* delta, hipStream_t st, float* part, bool shared_chip) {
   if (!args_ok(S_mb, S_seq, N_heads, S_head, qkv, dqkv) || !args_ok(S_mb, S_seq, N_heads, S_head, ctx, dctx)) return BF_EINVAL;
-  if (S_head == 128) return bwd_d<128>(S_mb, S_seq, N_heads, causal, qkv, ctx, lse, dctx, dqkv, delta, part, st);
-  return bwd_d<64>(S_mb, S_seq, N_heads, causal, qkv, ctx, lse, dctx, dqkv, delta, part, st);
+  if (S_head == 128) return bwd_d<128>(S_mb, S_seq, N_heads, causal, qkv, ctx, lse, dctx, dqkv, delta, part, st, shared_chip);
+  return bwd_d<64>(S_mb, S_seq, N_heads, causal, qkv, ctx, lse, dctx, dqkv, delta, part, st, shared_chip);
 }
 
 }  // namespace bf

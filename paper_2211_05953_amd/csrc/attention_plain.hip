@@ -287,13 +287,13 @@ size_t attention_bwd_part_elems(int S_mb, int S_seq, int N_heads, int S_head) {
 
 bf_status attention_bwd(int dtype, int kernels, int S_mb, int S_seq, int N_heads, int S_head, int causal,
                         const void* qkv, const void* ctx, const float* lse, const void* dctx, void* dqkv, float* delta,
-                        hipStream_t st, float* db_qkv, float* part, int accumulate) {
+                        hipStream_t st, float* db_qkv, float* part, int accumulate, bool shared_chip) {
   const int h = N_heads * S_head;
   bf_status r;
   if (dtype == BF_BF16 && kernels == BF_KERNELS_AUTO && attention_mfma_supported(S_seq, S_head)) {
     if (!qkv || !ctx || !lse || !dctx || !dqkv || !delta) { set_error("attention_bwd: null pointer"); return BF_EINVAL; }
     float* use = db_qkv ? part : nullptr;
-    r = attention_bwd_mfma(S_mb, S_seq, N_heads, S_head, causal, qkv, ctx, lse, dctx, dqkv, delta, st, use);
+    r = attention_bwd_mfma(S_mb, S_seq, N_heads, S_head, causal, qkv, ctx, lse, dctx, dqkv, delta, st, use, shared_chip);
     if (r != BF_OK || !db_qkv) return r;
     if (use) {
       const size_t rq = attention_bwd_mfma_part_q_rows(S_mb, S_seq), rkv = attention_bwd_mfma_part_kv_rows(S_mb, S_seq);

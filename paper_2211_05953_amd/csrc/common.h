@@ -135,7 +135,7 @@ bf_status attention_bwd_mfma_edge(int S_mb, int S_seq, int N_heads, int S_head, 
 // [2 S_hidden] for [dK | dV] (one per sequence and block of 128 keys).
 bf_status attention_bwd_mfma(int S_mb, int S_seq, int N_heads, int S_head, int causal,
                              const void* qkv, const void* ctx, const float* lse, const void* dctx,
-                             void* dqkv, float* delta, hipStream_t st, float* part = nullptr);
+                             void* dqkv, float* delta, hipStream_t st, float* part = nullptr, bool shared_chip = false);
 size_t attention_bwd_mfma_part_q_rows(int S_mb, int S_seq);
 size_t attention_bwd_mfma_part_kv_rows(int S_mb, int S_seq);
 // The plain kernels' results, bit for bit, on the fp32 matrix instructions (both storage types, head sizes up to 128; the
@@ -151,11 +151,11 @@ bf_status attention_fwd(int dtype, int kernels, int S_mb, int S_seq, int N_heads
 // db_qkv (may be null): also db_qkv[3 S_hidden] = (accumulate ? db_qkv : 0) + column sums of dqkv, the bias
 // gradient of the QKV projection.  With `part` (attention_bwd_part_elems floats) the matrix-core kernels take the
 // sums on their way out and a small kernel adds their partial rows in fixed order; without it, or on the plain
-// path, dqkv is read a second time.
+// path, dqkv is read a second time.  shared_chip: another stream's kernels run beside these.
 bf_status attention_bwd(int dtype, int kernels, int S_mb, int S_seq, int N_heads, int S_head, int causal,
                         const void* qkv, const void* ctx, const float* lse, const void* dctx,
                         void* dqkv, float* delta, hipStream_t st, float* db_qkv = nullptr, float* part = nullptr,
-                        int accumulate = 0);
+                        int accumulate = 0, bool shared_chip = false);
 size_t attention_bwd_part_elems(int S_mb, int S_seq, int N_heads, int S_head);
 // out[n] = (accumulate ? out[n] : 0) + sum_r pq[r][n] for n < h, + sum_r pkv[r][n - h] for h <= n < 3 h
 bf_status attn_bias_finish(const float* pq, int rows_q, const float* pkv, int rows_kv, int h, float* out, int accumulate,

@@ -475,7 +475,7 @@ bf_status p_attn_bwd(bf_stack* s, int S_mb, const void* qkv, const void* ctx, co
   // algorithmic backward = 2.5 x forward (five score-sized products); the two-pass kernels run seven
   return timed(s, BF_K_ATTN_BWD, 2.5 * (c.causal ? full / 2 : full), 0.0, st, [&] {
     return attention_bwd(c.dtype, c.kernels, S_mb, c.S_seq, c.N_heads, c.S_head, c.causal, qkv, ctx, lse, dctx, dqkv, delta, st,
-                         db_qkv, part, acc);
+                         db_qkv, part, acc, s->chains_active == 2);
   });
 }
 
