@@ -330,8 +330,7 @@ struct NextSetOf<DEPTH, std::integral_constant<int, V>> { static constexpr int v
 // their use and are double-buffered in LDS: tile j+1 is written to the idle stage while tile j is
 // consumed, so an iteration has a single barrier.  The 256-query form reads each tile from HBM / L2
 // once for twice as many queries and keeps two tiles in flight; it needs enough (head, block) pairs
-// to fill the chip.  KG = 2: two groups of waves take every other key tile of the same rows (tiles staged in pairs) and
-// merge their maxima, sums and outputs in LDS at the end, for launches of few rows.
+// to fill the chip.
 // Measured at S_seq 1024-2048, 64 heads of 128: timed without softmax, P V and K/V refetch, the bare
 // S = K Q^T loop (one 1 KB LDS fragment read per MFMA, Q from registers) reaches 44 % of the MFMA
 // rate; without P V 70 % of the full time remains, without the softmax arithmetic 84 %, without the
@@ -340,12 +339,143 @@ struct NextSetOf<DEPTH, std::integral_constant<int, V>> { static constexpr int v
 // (accumulators in AGPRs, one wavefront per SIMD): built and measured level with this form (100 against
 // 98 us at 64 heads of 128, S_seq 2048): a lone wavefront issues in order, so each of its LDS, barrier
 // and softmax waits stops its MFMAs too, and there is no partner on the SIMD to fill the gap.
-template <int D, int ROWS, bool EDGE = false, int KG = 1>
-__global__ __launch_bounds__(2 * ROWS * KG, ROWS == 128 && !(EDGE && D == 128 && KG == 1) ? 2 : 1) void attn_fwd_kernel(const bf16_t* __restrict__ qkv,
+template <int D, int ROWS>
+__global__ __launch_bounds__(2 * ROWS, ROWS == 128 ? 2 : 1) void attn_fwd_kernel(const bf16_t* __restrict__ qkv,
                                                                                  bf16_t* __restrict__ ctx, float* __restrict__ lse,
                                                                                  int S_seq, int N_heads, int S_mb, int causal,
                                                                                  float scale) {
-  constexpr int NT = 2 * ROWS * KG, DEPTH = ROWS == 256 ? 2 : 1, BT = BLK * KG;
+  constexpr int NT = 2 * ROWS, DEPTH = ROWS == 128 ? 1 : 2;
+  __shared__ __attribute__((aligned(16))) bf16_t KVs[2][2][BLK * D];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  // 1-D grid ordered by work: the last (longest) query block of every head first, then the next ...
+  const int nhb = N_heads * S_mb;
+  const int qblk = S_seq / ROWS - 1 - blockIdx.x / nhb;
+  const int head = (blockIdx.x % nhb) % N_heads, b = (blockIdx.x % nhb) / N_heads;
+  const int h = N_heads * D;
+  const size_t ld = 3 * (size_t)h;
+  const bf16_t* base = qkv + (size_t)b * S_seq * ld + head * D;
+  const int q0 = qblk * ROWS, qw = q0 + 32 * w, q = qw + (lane & 31);
+
+  FragAddr<D> fa;
+  fa.init(lane);
+  bf16x8 qf[D / 16];
+  load_rowfrags<D>(base + (size_t)q * ld, lane, qf);
+  f32x16 o[D / 32];
+#pragma unroll
+  for (int dt = 0; dt < D / 32; ++dt) o[dt] = zero16();
+  float m = -INFINITY, l = 0.f;
+  const float c2 = scale * LOG2E;
+
+  const int nblk = causal ? (q0 + ROWS) / BLK : S_seq / BLK;
+  TileRegs<BLK, D, NT> kr[DEPTH], vr[DEPTH];  // set (j % DEPTH) carries tile j
+  auto fetch = [&](auto setc, int j) {
+    constexpr int SET = decltype(setc)::value;
+    kr[SET].load(base + (size_t)j * BLK * ld + h, ld, tid);
+    vr[SET].load(base + (size_t)j * BLK * ld + 2 * h, ld, tid);
+  };
+  typedef std::integral_constant<int, 0> I0;
+  typedef std::integral_constant<int, 1> I1;
+  fetch(I0{}, 0);
+  kr[0].store(KVs[0][0], tid);
+  vr[0].store(KVs[0][1], tid);
+  if (nblk > 1) fetch(std::integral_constant<int, 1 % DEPTH>{}, 1);
+  if (DEPTH > 1 && nblk > 2) fetch(I0{}, 2);
+  __syncthreads();
+  // one key tile; PAR = j & 1 is a compile-time constant (the loop is unrolled by two) so that the
+  // LDS stage and the register set are too
+  auto body = [&](int j, auto parc) {
+    constexpr int PAR = decltype(parc)::value;
+    typedef std::integral_constant<int, (PAR + 1) % DEPTH> NextSet;
+    const bf16_t* Ks = KVs[PAR][0];
+    const bf16_t* Vs = KVs[PAR][1];
+    if (j + 1 < nblk) {
+      kr[NextSet::value].store(KVs[PAR ^ 1][0], tid);
+      vr[NextSet::value].store(KVs[PAR ^ 1][1], tid);
+    }
+    if (j + 1 + DEPTH < nblk) fetch(NextSet{}, j + 1 + DEPTH);
+    const int kb = j * BLK;
+    if (causal && kb > qw + 31) { __syncthreads(); return; }  // the whole tile is above this wave's diagonal
+    f32x16 s[2] = {zero16(), zero16()};
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int kk = 0; kk < D / 16; ++kk)
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+        s[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa.frag_k(Ks, 32 * t, kk), qf[kk], s[t], 0, 0, 0);
+    mfma_lds_pipeline<2 * (D / 16), 1, 4>();
+    // Online softmax on the raw scores: m is the running max of the unscaled scores, the scale
+    // 1/sqrt(S_head) log2(e) enters through one fma per element, the exponentials are the
+    // hardware exp2 (arguments <= 0; masked scores are -inf and give exactly 0).
+    if (causal && kb + BLK - 1 > qw) {  // only tiles that touch the diagonal pay for the mask
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          if (kb + 32 * t + acc_row(r, lane) > q) s[t][r] = -INFINITY;
+    }
+    float mx = m;
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[t][r]);
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    const float nmx = -mx * c2;
+    float sum = 0.f;
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const float p = __builtin_amdgcn_exp2f(fmaf(s[t][r], c2, nmx));
+        s[t][r] = p;
+        sum += p;
+      }
+    if (__builtin_amdgcn_ballot_w64(mx > m) != 0) {  // some row's max moved: rescale (rare after the first tiles)
+      const float alpha = __builtin_amdgcn_exp2f(fmaf(m, c2, nmx));
+      l *= alpha;
+#pragma unroll
+      for (int dt = 0; dt < D / 32; ++dt)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o[dt][r] *= alpha;
+      m = mx;
+    }
+    l += sum;
+    bf16x8 pb[2][2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int k2 = 0; k2 < 2; ++k2) pb[t][k2] = pack8(s[t], k2);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int k2 = 0; k2 < 2; ++k2)
+#pragma unroll
+        for (int dt = 0; dt < D / 32; ++dt)
+          o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa.frag_t(Vs, 32 * t + 16 * k2, dt), pb[t][k2], o[dt], 0, 0, 0);
+    mfma_lds_pipeline<4 * (D / 32), 2, 4>();
+    __syncthreads();
+  };
+  for (int j = 0; j < nblk; j += 2) {
+    body(j, I0{});
+    if (j + 1 < nblk) body(j + 1, I1{});
+  }
+  l += __shfl_xor(l, 32, 64);
+  store_rows<D>(o, ctx + ((size_t)b * S_seq + q) * h + head * D, lane, 1.0f / l);
+  if (lane < 32) lse[((size_t)b * N_heads + head) * S_seq + q] = m * scale + logf(l);
+}
+
+// The forward kernel's other forms: any length (EDGE: the last tile and the last rows partly empty), and two groups of waves
+// that take every other key tile of the same rows (KG = 2, tiles staged in pairs) and merge their maxima, sums and outputs
+// in LDS at the end, for launches of few rows.  A kernel of its own: as parameters of the one above the two changed the
+// schedule of its common form (S_head 64, S_seq 512, 100 heads, causal 13.0 -> 14.5 us; 128, 1152, 64 heads, bidirectional
+// 70.8 -> 75.2), which is why their bodies, alike as they are, stay apart.
+template <int D, int ROWS, bool EDGE, int KG>
+__global__ __launch_bounds__(2 * ROWS * KG, ROWS == 128 && !(EDGE && D == 128 && KG == 1) ? 2 : 1) void attn_fwd_general_kernel(const bf16_t* __restrict__ qkv,
+                                                                                 bf16_t* __restrict__ ctx, float* __restrict__ lse,
+                                                                                 int S_seq, int N_heads, int S_mb, int causal,
+                                                                                 float scale) {
+  static_assert((EDGE || KG == 2) && ROWS <= 128, "whole lengths with one key group have a kernel of their own");
+  constexpr int NT = 2 * ROWS * KG, BT = BLK * KG;
   __shared__ __attribute__((aligned(16))) bf16_t KVs[2][2][BT * D];
   const int tid = threadIdx.x, lane = tid & 63;
   const int grp = KG == 1 ? 0 : (tid >> 6) / (ROWS / 32), w = KG == 1 ? tid >> 6 : (tid >> 6) % (ROWS / 32);  // key group, rows
@@ -373,44 +503,40 @@ __global__ __launch_bounds__(2 * ROWS * KG, ROWS == 128 && !(EDGE && D == 128 &&
   const float c2 = scale * LOG2E;
 
   const int nblk = EDGE ? ((causal ? min(q0 + ROWS, S_seq) : S_seq) + BT - 1) / BT : causal ? (q0 + ROWS + (KG - 1) * BLK) / BT : S_seq / BT;
-  TileRegs<BT, D, NT> kr[DEPTH], vr[DEPTH];  // set (j % DEPTH) carries tile j
-  auto fetch = [&](auto setc, int j) {
-    constexpr int SET = decltype(setc)::value;
+  TileRegs<BT, D, NT> kr, vr;
+  auto fetch = [&](int j) {
     if constexpr (EDGE) {
-      kr[SET].load_edge(base + (size_t)j * BT * ld + h, ld, tid, S_seq - j * BT);
-      vr[SET].load_edge(base + (size_t)j * BT * ld + 2 * h, ld, tid, S_seq - j * BT);
+      kr.load_edge(base + (size_t)j * BT * ld + h, ld, tid, S_seq - j * BT);
+      vr.load_edge(base + (size_t)j * BT * ld + 2 * h, ld, tid, S_seq - j * BT);
       return;
     }
-    kr[SET].load(base + (size_t)j * BT * ld + h, ld, tid);
-    vr[SET].load(base + (size_t)j * BT * ld + 2 * h, ld, tid);
+    kr.load(base + (size_t)j * BT * ld + h, ld, tid);
+    vr.load(base + (size_t)j * BT * ld + 2 * h, ld, tid);
   };
   typedef std::integral_constant<int, 0> I0;
   typedef std::integral_constant<int, 1> I1;
-  fetch(I0{}, 0);
+  fetch(0);
   // tile j goes to an LDS stage: does the mask cut it, and does it hold what must not meet a masked zero
   auto note = [&](int j, int stage, const TileRegs<BT, D, NT>& v) {
     if (EDGE && causal && j * BT + BT - 1 > q0 && v.non_finite()) bad_tile[stage] = j + 1;
   };
   if (EDGE) __syncthreads();  // bad_tile is clear
-  kr[0].store(KVs[0][0], tid);
-  vr[0].store(KVs[0][1], tid);
-  note(0, 0, vr[0]);
-  if (nblk > 1) fetch(std::integral_constant<int, 1 % DEPTH>{}, 1);
-  if (DEPTH > 1 && nblk > 2) fetch(I0{}, 2);
+  kr.store(KVs[0][0], tid);
+  vr.store(KVs[0][1], tid);
+  note(0, 0, vr);
+  if (nblk > 1) fetch(1);
   __syncthreads();
-  // one key tile; PAR = j & 1 is a compile-time constant (the loop is unrolled by two) so that the
-  // LDS stage and the register set are too
+  // one key tile; PAR = j & 1, the LDS stage, is a compile-time constant (the loop is unrolled by two)
   auto body = [&](int j, auto parc) {
     constexpr int PAR = decltype(parc)::value;
-    typedef std::integral_constant<int, (PAR + 1) % DEPTH> NextSet;
     const bf16_t* Ks = KVs[PAR][0] + grp * BLK * D;
     const bf16_t* Vs = KVs[PAR][1] + grp * BLK * D;
     if (j + 1 < nblk) {
-      kr[NextSet::value].store(KVs[PAR ^ 1][0], tid);
-      vr[NextSet::value].store(KVs[PAR ^ 1][1], tid);
-      note(j + 1, PAR ^ 1, vr[NextSet::value]);
+      kr.store(KVs[PAR ^ 1][0], tid);
+      vr.store(KVs[PAR ^ 1][1], tid);
+      note(j + 1, PAR ^ 1, vr);
     }
-    if (j + 1 + DEPTH < nblk) fetch(NextSet{}, j + 1 + DEPTH);
+    if (j + 2 < nblk) fetch(j + 2);
     const int kb = j * BT + grp * BLK;
     // the whole tile is above this wave's diagonal, or the wave's rows are past the end
     if ((causal && kb > qw + 31) || (EDGE && (qw >= S_seq || kb >= S_seq))) { __syncthreads(); return; }
@@ -532,12 +658,132 @@ __global__ __launch_bounds__(2 * ROWS * KG, ROWS == 128 && !(EDGE && D == 128 &&
 // Also takes delta[b, head, i] = sum_c dctx[i, c] ctx[i, c] of its queries (each lane already holds
 // half of its query's dctx row) and leaves it in `delta` for the dK/dV pass.
 // ROWS queries per workgroup and K/V tiles DEPTH tiles ahead, as in the forward kernel.
-template <int D, int ROWS, bool EDGE = false, int KG = 1>
-__global__ __launch_bounds__(2 * ROWS * KG, ROWS == 128 && !EDGE ? 2 : 1) void attn_bwd_dq_kernel(
+template <int D, int ROWS>
+__global__ __launch_bounds__(2 * ROWS, ROWS == 128 ? 2 : 1) void attn_bwd_dq_kernel(
     const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ ctx, const bf16_t* __restrict__ dctx,
     const float* __restrict__ lse, float* __restrict__ delta, bf16_t* __restrict__ dqkv, int S_seq, int N_heads, int S_mb,
     int causal, float scale, float* __restrict__ colpart) {
-  constexpr int NT = 2 * ROWS * KG, DEPTH = ROWS == 256 ? 2 : 1, BT = BLK * KG;
+  constexpr int NT = 2 * ROWS, DEPTH = ROWS == 128 ? 1 : 2;
+  __shared__ __attribute__((aligned(16))) bf16_t KVs[2][2][BLK * D];  // double-buffered, one barrier per tile
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int nhb = N_heads * S_mb;
+  const int qblk = S_seq / ROWS - 1 - blockIdx.x / nhb;  // longest query blocks of every head first
+  const int head = (blockIdx.x % nhb) % N_heads, b = (blockIdx.x % nhb) / N_heads;
+  const int h = N_heads * D;
+  const size_t ld = 3 * (size_t)h;
+  const bf16_t* base = qkv + (size_t)b * S_seq * ld + head * D;
+  const int q0 = qblk * ROWS, qw = q0 + 32 * w, q = qw + (lane & 31);
+
+  // precomputed offsets where the registers allow (the 128-query form at S_head 128 would spill)
+  typename std::conditional<(ROWS == 256 || D == 64), FragAddr<D>, FragAddrLive<D>>::type fa;
+  fa.init(lane);
+  bf16x8 qf[D / 16], dof[D / 16];
+  load_rowfrags<D>(base + (size_t)q * ld, lane, qf);
+  load_rowfrags<D>(dctx + ((size_t)b * S_seq + q) * h + head * D, lane, dof);
+  const size_t st = ((size_t)b * N_heads + head) * S_seq + q;
+  float dl = 0.f;
+  {
+    bf16x8 cf[D / 16];
+    load_rowfrags<D>(ctx + ((size_t)b * S_seq + q) * h + head * D, lane, cf);
+#pragma unroll
+    for (int kk = 0; kk < D / 16; ++kk)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) dl = fmaf((float)dof[kk][e], (float)cf[kk][e], dl);
+    dl += __shfl_xor(dl, 32, 64);  // lanes l and l + 32 hold the two halves of the row
+    if (lane < 32) delta[st] = dl;
+  }
+  const float lse2 = lse[st] * LOG2E, c2 = scale * LOG2E;
+  f32x16 dq[D / 32];
+#pragma unroll
+  for (int dt = 0; dt < D / 32; ++dt) dq[dt] = zero16();
+
+  const int nblk = causal ? (q0 + ROWS) / BLK : S_seq / BLK;
+  TileRegs<BLK, D, NT> kr[DEPTH], vr[DEPTH];  // set (j % DEPTH) carries tile j
+  auto fetch = [&](auto setc, int j) {
+    constexpr int SET = decltype(setc)::value;
+    kr[SET].load(base + (size_t)j * BLK * ld + h, ld, tid);
+    vr[SET].load(base + (size_t)j * BLK * ld + 2 * h, ld, tid);
+  };
+  typedef std::integral_constant<int, 0> I0;
+  typedef std::integral_constant<int, 1> I1;
+  fetch(I0{}, 0);
+  kr[0].store(KVs[0][0], tid);
+  vr[0].store(KVs[0][1], tid);
+  if (nblk > 1) fetch(std::integral_constant<int, 1 % DEPTH>{}, 1);
+  if (DEPTH > 1 && nblk > 2) fetch(I0{}, 2);
+  __syncthreads();
+  // one key tile; par = j & 1 selects the LDS stage
+  auto body = [&](int j, auto par) {
+    typedef std::integral_constant<int, NextSetOf<DEPTH, decltype(par)>::value> NextSet;
+    const int p = par;
+    const bf16_t* Ks = KVs[p][0];
+    const bf16_t* Vs = KVs[p][1];
+    if (j + 1 < nblk) {
+      kr[NextSet::value].store(KVs[p ^ 1][0], tid);
+      vr[NextSet::value].store(KVs[p ^ 1][1], tid);
+    }
+    if (j + 1 + DEPTH < nblk) fetch(NextSet{}, j + 1 + DEPTH);
+    const int kb = j * BLK;
+    if (causal && kb > qw + 31) { __syncthreads(); return; }
+    const bool diag = causal && kb + BLK - 1 > qw;
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      f32x16 s = zero16(), dp = zero16();
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int kk = 0; kk < D / 16; ++kk) {
+        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa.frag_k(Ks, 32 * t, kk), qf[kk], s, 0, 0, 0);
+        dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa.frag_k(Vs, 32 * t, kk), dof[kk], dp, 0, 0, 0);
+      }
+      mfma_lds_pipeline<2 * (D / 16), 1, 4>();
+      // p = exp(s/sqrt(d) - lse); dS = p (dP - delta) (the factor 1/sqrt(d) is applied once, to dQ)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) s[r] = __builtin_amdgcn_exp2f(fmaf(s[r], c2, -lse2)) * (dp[r] - dl);
+      if (diag) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          if (kb + 32 * t + acc_row(r, lane) > q) s[r] = 0.f;
+      }
+      const bf16x8 dsb[2] = {pack8(s, 0), pack8(s, 1)};
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int k2 = 0; k2 < 2; ++k2)
+#pragma unroll
+        for (int dt = 0; dt < D / 32; ++dt)
+          dq[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa.frag_t(Ks, 32 * t + 16 * k2, dt), dsb[k2], dq[dt], 0, 0, 0);
+      mfma_lds_pipeline<2 * (D / 32), 2, 4>();
+    }
+    __syncthreads();
+  };
+  if constexpr (ROWS == 256 || D == 64) {
+    // unrolled by two: the LDS stage (and with it every fragment address) is a compile-time constant
+    for (int j = 0; j < nblk; j += 2) {
+      body(j, I0{});
+      if (j + 1 < nblk) body(j + 1, I1{});
+    }
+  } else {
+    static_assert(DEPTH == 1, "a run-time stage goes with one tile in flight");
+    for (int j = 0; j < nblk; ++j) body(j, j & 1);
+  }
+  store_rows<D>(dq, dqkv + ((size_t)b * S_seq + q) * ld + head * D, lane, scale);
+  if (colpart) {
+    // row (b, query block) of the partial column sums of dQ, [S_mb * S_seq / ROWS][N_heads * D]; the tile
+    // buffers are free: the loop ended on a barrier
+    float* red = reinterpret_cast<float*>(&KVs[0][0][0]);
+    wave_colsum<D>(dq, scale, red + (size_t)w * 4 * (D / 2), lane);
+    __syncthreads();
+    if (tid < D) colpart[((size_t)b * (S_seq / ROWS) + qblk) * h + head * D + tid] = colsum_of<D>(red, 0, NT / 64, tid);
+  }
+}
+
+// The dQ kernel's other forms, as in the forward pass.
+template <int D, int ROWS, bool EDGE, int KG>
+__global__ __launch_bounds__(2 * ROWS * KG, ROWS == 128 && !EDGE ? 2 : 1) void attn_bwd_dq_general_kernel(
+    const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ ctx, const bf16_t* __restrict__ dctx,
+    const float* __restrict__ lse, float* __restrict__ delta, bf16_t* __restrict__ dqkv, int S_seq, int N_heads, int S_mb,
+    int causal, float scale, float* __restrict__ colpart) {
+  static_assert((EDGE || KG == 2) && ROWS <= 128, "whole lengths with one key group have a kernel of their own");
+  constexpr int NT = 2 * ROWS * KG, BT = BLK * KG;
   __shared__ __attribute__((aligned(16))) bf16_t KVs[2][2][BT * D];  // double-buffered, one barrier per tile
   const int tid = threadIdx.x, lane = tid & 63;
   const int grp = KG == 1 ? 0 : (tid >> 6) / (ROWS / 32), w = KG == 1 ? tid >> 6 : (tid >> 6) % (ROWS / 32);  // key group, rows
@@ -553,8 +799,7 @@ __global__ __launch_bounds__(2 * ROWS * KG, ROWS == 128 && !EDGE ? 2 : 1) void a
   __shared__ int bad_tile[2];  // per LDS stage: 1 + the last tile staged there with a non-finite K
   if (EDGE && tid < 2) bad_tile[tid] = 0;
 
-  // precomputed offsets where the registers allow (the 128-query form at S_head 128 would spill)
-  typename std::conditional<(ROWS != 128 || KG == 2 || D == 64 || EDGE), FragAddr<D>, FragAddrLive<D>>::type fa;
+  FragAddr<D> fa;
   fa.init(lane);
   bf16x8 qf[D / 16], dof[D / 16];
   load_rowfrags<D>(base + (size_t)ql * ld, lane, qf);
@@ -577,42 +822,39 @@ __global__ __launch_bounds__(2 * ROWS * KG, ROWS == 128 && !EDGE ? 2 : 1) void a
   for (int dt = 0; dt < D / 32; ++dt) dq[dt] = zero16();
 
   const int nblk = EDGE ? ((causal ? min(q0 + ROWS, S_seq) : S_seq) + BT - 1) / BT : causal ? (q0 + ROWS + (KG - 1) * BLK) / BT : S_seq / BT;
-  TileRegs<BT, D, NT> kr[DEPTH], vr[DEPTH];  // set (j % DEPTH) carries tile j
-  auto fetch = [&](auto setc, int j) {
-    constexpr int SET = decltype(setc)::value;
+  TileRegs<BT, D, NT> kr, vr;
+  auto fetch = [&](int j) {
     if constexpr (EDGE) {
-      kr[SET].load_edge(base + (size_t)j * BT * ld + h, ld, tid, S_seq - j * BT);
-      vr[SET].load_edge(base + (size_t)j * BT * ld + 2 * h, ld, tid, S_seq - j * BT);
+      kr.load_edge(base + (size_t)j * BT * ld + h, ld, tid, S_seq - j * BT);
+      vr.load_edge(base + (size_t)j * BT * ld + 2 * h, ld, tid, S_seq - j * BT);
       return;
     }
-    kr[SET].load(base + (size_t)j * BT * ld + h, ld, tid);
-    vr[SET].load(base + (size_t)j * BT * ld + 2 * h, ld, tid);
+    kr.load(base + (size_t)j * BT * ld + h, ld, tid);
+    vr.load(base + (size_t)j * BT * ld + 2 * h, ld, tid);
   };
   typedef std::integral_constant<int, 0> I0;
   typedef std::integral_constant<int, 1> I1;
-  fetch(I0{}, 0);
+  fetch(0);
   auto note = [&](int j, int stage, const TileRegs<BT, D, NT>& k) {
     if (EDGE && causal && j * BT + BT - 1 > q0 && k.non_finite()) bad_tile[stage] = j + 1;
   };
   if (EDGE) __syncthreads();  // bad_tile is clear
-  kr[0].store(KVs[0][0], tid);
-  vr[0].store(KVs[0][1], tid);
-  note(0, 0, kr[0]);
-  if (nblk > 1) fetch(std::integral_constant<int, 1 % DEPTH>{}, 1);
-  if (DEPTH > 1 && nblk > 2) fetch(I0{}, 2);
+  kr.store(KVs[0][0], tid);
+  vr.store(KVs[0][1], tid);
+  note(0, 0, kr);
+  if (nblk > 1) fetch(1);
   __syncthreads();
-  // one key tile; par = j & 1 selects the LDS stage
-  auto body = [&](int j, auto par) {
-    typedef std::integral_constant<int, NextSetOf<DEPTH, decltype(par)>::value> NextSet;
-    const int p = par;
+  // one key tile; p = j & 1, the LDS stage, is a compile-time constant (the loop is unrolled by two)
+  auto body = [&](int j, auto parc) {
+    constexpr int p = decltype(parc)::value;
     const bf16_t* Ks = KVs[p][0] + grp * BLK * D;
     const bf16_t* Vs = KVs[p][1] + grp * BLK * D;
     if (j + 1 < nblk) {
-      kr[NextSet::value].store(KVs[p ^ 1][0], tid);
-      vr[NextSet::value].store(KVs[p ^ 1][1], tid);
-      note(j + 1, p ^ 1, kr[NextSet::value]);
+      kr.store(KVs[p ^ 1][0], tid);
+      vr.store(KVs[p ^ 1][1], tid);
+      note(j + 1, p ^ 1, kr);
     }
-    if (j + 1 + DEPTH < nblk) fetch(NextSet{}, j + 1 + DEPTH);
+    if (j + 2 < nblk) fetch(j + 2);
     const int kb = j * BT + grp * BLK;
     if ((causal && kb > qw + 31) || (EDGE && (qw >= S_seq || kb >= S_seq))) { __syncthreads(); return; }
     const bool diag = causal && kb + BLK - 1 > qw;
@@ -659,15 +901,9 @@ __global__ __launch_bounds__(2 * ROWS * KG, ROWS == 128 && !EDGE ? 2 : 1) void a
     }
     __syncthreads();
   };
-  if constexpr (ROWS != 128 || KG == 2 || D == 64 || EDGE) {
-    // unrolled by two: the LDS stage (and with it every fragment address) is a compile-time constant
-    for (int j = 0; j < nblk; j += 2) {
-      body(j, I0{});
-      if (j + 1 < nblk) body(j + 1, I1{});
-    }
-  } else {
-    static_assert(DEPTH == 1, "a run-time stage goes with one tile in flight");
-    for (int j = 0; j < nblk; ++j) body(j, j & 1);
+  for (int j = 0; j < nblk; j += 2) {
+    body(j, I0{});
+    if (j + 1 < nblk) body(j + 1, I1{});
   }
   if constexpr (KG == 2) {
     // the second key group's share, lane to lane
@@ -951,9 +1187,9 @@ bf_status fwd_d(int S_mb, int S_seq, int N_heads, int causal, const void* qkv, v
   // 88 / 206 / 111; bidirectional, 16 heads 53 / 87 / 49, 32 heads 76 / 199 / 93; S_seq 512, 16 heads 16.5 / 14.9 / 16.2;
   // S_head 64, S_seq 2048 causal, 16 heads 36 / 30 / 27, 32 heads 46 / 43 / 35, 64 heads 62 / 85 / 76.
   if (S_seq >= 1024 && blocks <= (causal ? 512 : 256)) {
-    attn_fwd_kernel<D, 128, false, 2><<<(unsigned)blocks, 512, 0, st>>>((const bf16_t*)qkv, (bf16_t*)ctx, lse, S_seq, N_heads, S_mb, causal, scale);
+    attn_fwd_general_kernel<D, 128, false, 2><<<(unsigned)blocks, 512, 0, st>>>((const bf16_t*)qkv, (bf16_t*)ctx, lse, S_seq, N_heads, S_mb, causal, scale);
   } else if (S_seq >= 256 && S_seq < 1024 && blocks <= 128) {
-    attn_fwd_kernel<D, 64, false, 2><<<(unsigned)(2 * blocks), 256, 0, st>>>((const bf16_t*)qkv, (bf16_t*)ctx, lse, S_seq, N_heads, S_mb, causal, scale);
+    attn_fwd_general_kernel<D, 64, false, 2><<<(unsigned)(2 * blocks), 256, 0, st>>>((const bf16_t*)qkv, (bf16_t*)ctx, lse, S_seq, N_heads, S_mb, causal, scale);
   } else
   // the 256-query form when there are enough (head, block) pairs to give every compute unit one
   if (S_seq % 256 == 0 && (long)(S_seq / 256) * N_heads * S_mb >= 256) {
@@ -992,7 +1228,7 @@ bf_status bwd_d(int S_mb, int S_seq, int N_heads, int causal, const void* qkv, c
   // Beside another stream's kernels the longest rows' units are not the only busy ones, and from 257 workgroups on the
   // second group costs more than it hides (a 2048-wide step on two chains: attention backward 8.9 -> 9.9 ms, step 36.5 -> 37.6, with two).
   if (S_seq >= 256 && 2 * (long)grid <= (causal && !shared_chip ? 512 : 256)) {
-    attn_bwd_dq_kernel<D, 64, false, 2><<<grid * 2, 256, 0, st>>>((const bf16_t*)qkv, (const bf16_t*)ctx, (const bf16_t*)dctx, lse, delta, (bf16_t*)dqkv, S_seq, N_heads, S_mb, causal, scale, part_kv);
+    attn_bwd_dq_general_kernel<D, 64, false, 2><<<grid * 2, 256, 0, st>>>((const bf16_t*)qkv, (const bf16_t*)ctx, (const bf16_t*)dctx, lse, delta, (bf16_t*)dqkv, S_seq, N_heads, S_mb, causal, scale, part_kv);
     if (part) {
       const int h = N_heads * D, rows = (int)attention_bwd_mfma_part_q_rows(S_mb, S_seq);
       fold_rows_kernel<<<dim3((h + 63) / 64, rows), 64, 0, st>>>(part_kv, part, S_mb * (S_seq / 64) / rows, h);
@@ -1017,9 +1253,9 @@ bf_status fwd_edge(int S_mb, int S_seq, int N_heads, int causal, const void* qkv
   const float scale = 1.0f / sqrtf((float)D);
   constexpr int EDGE_ROWS = D == 64 ? 128 : 64;
   if (S_seq > 256 && blocks <= (causal ? 256 : 128) * (D == 64 ? 2 : 1))
-    attn_fwd_kernel<D, EDGE_ROWS, true, 2><<<(unsigned)((S_seq + EDGE_ROWS - 1) / EDGE_ROWS) * N_heads * S_mb, 4 * EDGE_ROWS, 0, st>>>((const bf16_t*)qkv, (bf16_t*)ctx, lse, S_seq, N_heads, S_mb, causal, scale);
+    attn_fwd_general_kernel<D, EDGE_ROWS, true, 2><<<(unsigned)((S_seq + EDGE_ROWS - 1) / EDGE_ROWS) * N_heads * S_mb, 4 * EDGE_ROWS, 0, st>>>((const bf16_t*)qkv, (bf16_t*)ctx, lse, S_seq, N_heads, S_mb, causal, scale);
   else
-    attn_fwd_kernel<D, 128, true><<<(unsigned)blocks, 256, 0, st>>>((const bf16_t*)qkv, (bf16_t*)ctx, lse, S_seq, N_heads, S_mb, causal, scale);
+    attn_fwd_general_kernel<D, 128, true, 1><<<(unsigned)blocks, 256, 0, st>>>((const bf16_t*)qkv, (bf16_t*)ctx, lse, S_seq, N_heads, S_mb, causal, scale);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) { set_error("attention_fwd_mfma launch failed: %s", hipGetErrorString(e)); return BF_EDEVICE; }
   return BF_OK;
@@ -1031,9 +1267,9 @@ bf_status bwd_edge(int S_mb, int S_seq, int N_heads, int causal, const void* qkv
   const float scale = 1.0f / sqrtf((float)D);
   const unsigned grid = (unsigned)((S_seq + 127) / 128) * N_heads * S_mb;
   if (S_seq > 128 && 2 * (long)grid <= (causal && D == 64 ? 512 : 256))
-    attn_bwd_dq_kernel<D, 64, true, 2><<<(unsigned)((S_seq + 63) / 64) * N_heads * S_mb, 256, 0, st>>>((const bf16_t*)qkv, (const bf16_t*)ctx, (const bf16_t*)dctx, lse, delta, (bf16_t*)dqkv, S_seq, N_heads, S_mb, causal, scale, nullptr);
+    attn_bwd_dq_general_kernel<D, 64, true, 2><<<(unsigned)((S_seq + 63) / 64) * N_heads * S_mb, 256, 0, st>>>((const bf16_t*)qkv, (const bf16_t*)ctx, (const bf16_t*)dctx, lse, delta, (bf16_t*)dqkv, S_seq, N_heads, S_mb, causal, scale, nullptr);
   else
-    attn_bwd_dq_kernel<D, 128, true><<<grid, NTHR, 0, st>>>((const bf16_t*)qkv, (const bf16_t*)ctx, (const bf16_t*)dctx, lse, delta, (bf16_t*)dqkv, S_seq, N_heads, S_mb, causal, scale, nullptr);
+    attn_bwd_dq_general_kernel<D, 128, true, 1><<<grid, NTHR, 0, st>>>((const bf16_t*)qkv, (const bf16_t*)ctx, (const bf16_t*)dctx, lse, delta, (bf16_t*)dqkv, S_seq, N_heads, S_mb, causal, scale, nullptr);
   attn_bwd_dkv_kernel<D, true><<<grid, NTHR_DKV, 0, st>>>((const bf16_t*)qkv, (const bf16_t*)dctx, lse, delta, (bf16_t*)dqkv, S_seq, N_heads, S_mb, causal, scale, nullptr);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) { set_error("attention_bwd_mfma launch failed: %s", hipGetErrorString(e)); return BF_EDEVICE; }
