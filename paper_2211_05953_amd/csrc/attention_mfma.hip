@@ -17,6 +17,8 @@
 // LDS tiles are [row][S_head] with the 16-byte chunk index XOR-swizzled by row bits; the
 // layout serves both the K-contiguous 16-byte fragment reads and the transpose loads without
 // bank conflicts.
+#include <float.h>
+
 #include <type_traits>
 
 #include "common.h"
@@ -363,7 +365,9 @@ __global__ __launch_bounds__(2 * ROWS, ROWS == 128 ? 2 : 1) void attn_fwd_kernel
   f32x16 o[D / 32];
 #pragma unroll
   for (int dt = 0; dt < D / 32; ++dt) o[dt] = zero16();
-  float m = -INFINITY, l = 0.f;
+  // The running maximum starts at the lowest finite value: while a row has met only scores of -inf, from
+  // -inf or overflowing keys, their difference to it is -inf and adds exactly 0, where -inf - -inf would be a NaN.
+  float m = -FLT_MAX, l = 0.f;
   const float c2 = scale * LOG2E;
 
   const int nblk = causal ? (q0 + ROWS) / BLK : S_seq / BLK;
@@ -499,7 +503,9 @@ __global__ __launch_bounds__(2 * ROWS * KG, ROWS == 128 && !(EDGE && D == 128 &&
   f32x16 o[D / 32];
 #pragma unroll
   for (int dt = 0; dt < D / 32; ++dt) o[dt] = zero16();
-  float m = -INFINITY, l = 0.f;
+  // The running maximum starts at the lowest finite value: while a row (or a key group's share of it) has met only scores of -inf, from
+  // -inf or overflowing keys, their difference to it is -inf and adds exactly 0, where -inf - -inf would be a NaN.
+  float m = -FLT_MAX, l = 0.f;
   const float c2 = scale * LOG2E;
 
   const int nblk = EDGE ? ((causal ? min(q0 + ROWS, S_seq) : S_seq) + BT - 1) / BT : causal ? (q0 + ROWS + (KG - 1) * BLK) / BT : S_seq / BT;
@@ -625,7 +631,7 @@ __global__ __launch_bounds__(2 * ROWS * KG, ROWS == 128 && !(EDGE && D == 128 &&
   }
   if constexpr (KG == 2) {
     // the second key group hands its rows over, lane to lane (the loop ended on a barrier: the tiles are free); it may
-    // have seen no key (maximum -inf, sums 0)
+    // have seen no finite score (maximum -FLT_MAX, sums 0)
     constexpr int NV = D / 2 + 2;
     static_assert(NV * 64 * (ROWS / 32) * 4 <= sizeof(KVs), "the hand-over does not fit");
     float* hb = reinterpret_cast<float*>(&KVs[0][0][0]) + w * NV * 64 + lane;

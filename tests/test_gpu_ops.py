@@ -565,3 +565,41 @@ def test_attention_with_two_key_groups(causal, S_mb, S_seq, a, d):
         assert rel_err(to_host(dqkv)[..., i * h:(i + 1) * h], dqkv_ref[..., i * h:(i + 1) * h]) <= TOL["bf16"]
     assert rel_err(to_host(db), dqkv_ref.reshape(-1, 3 * h).sum(0)) <= TOL["bf16"]
     assert rel_err(to_host(db), to_host(dqkv).astype(np.float64).reshape(-1, 3 * h).sum(0)) <= 2.0 ** -8
+
+
+def _attention_by_both(S_mb, S_seq, a, d, causal, qkv, dctx):
+    """ctx, lse, dqkv of a bf16 call by the kernels the sizes choose, and by the plain ones."""
+    h = a * d
+    dQKV, dDC = to_dev(qkv, True), to_dev(dctx, True)
+    got = []
+    for kernels in (bf.BF_KERNELS_AUTO, bf.BF_KERNELS_PLAIN):
+        ctx, dqkv = (torch.full((S_mb, S_seq, n * h), 7.0, dtype=torch.bfloat16, device="cuda") for n in (1, 3))
+        lse, delta = (torch.full((S_mb, a, S_seq), 7.0, device="cuda") for _ in range(2))
+        bf.bf_op_attention_fwd(bf.BF_BF16, kernels, S_mb, S_seq, a, d, causal, dQKV, ctx, lse)
+        bf.bf_op_attention_bwd(bf.BF_BF16, kernels, S_mb, S_seq, a, d, causal, dQKV, ctx, lse, dDC, dqkv, delta)
+        got.append([to_host(t) for t in (ctx, lse, dqkv)])
+    return got
+
+
+# one and two key groups, whole lengths (128 and 256 rows per workgroup) and others
+ATTENTION_FORMS = [(1, 128, 2, 128), (1, 256, 2, 64), (1, 384, 50, 128), (1, 256, 256, 64), (1, 1024, 2, 128), (1, 200, 2, 128), (1, 300, 2, 128),
+                   (1, 300, 2, 64), (1, 451, 70, 128), (1, 451, 200, 64)]
+
+
+@pytest.mark.parametrize("causal", [1, 0])
+@pytest.mark.parametrize("keys", [(64, 65), (64, 128), (0, 64)])
+@pytest.mark.parametrize("value", [-np.inf, -3.3895313892515355e38])
+@pytest.mark.parametrize("S_mb,S_seq,a,d", ATTENTION_FORMS)
+def test_attention_keys_without_a_finite_score(causal, keys, value, S_mb, S_seq, a, d):
+    """Keys that hold -inf, or bf16's lowest value against a query component above 1 (the product overflows), score -inf: one
+    key, a whole tile of 64, the first tile.  Results are finite exactly where the plain kernels' are (rows with no other
+    key have none), and there within the bf16 bar of them."""
+    h = a * d
+    qkv, dctx = (bf_inputs.normal(37, i, (S_mb, S_seq, n * h), bf16=True) for i, n in ((0, 3), (1, 1)))
+    qkv[..., 5:h:d] = bf_inputs.round_bf16(np.abs(qkv[..., 5:h:d]) + np.float32(1.5))
+    qkv[:, keys[0]:keys[1], h + 5:2 * h:d] = value
+    got = _attention_by_both(S_mb, S_seq, a, d, causal, qkv, dctx)
+    for name, x, y in list(zip(("ctx", "lse"), *got)):
+        there = np.isfinite(y)
+        assert np.array_equal(np.isfinite(x), there), (name, int((~np.isfinite(x)).sum()), int((~there).sum()))
+        assert there.any() and np.abs(np.where(there, x, 0) - np.where(there, y, 0)).max() <= TOL["bf16"] * np.abs(y[there]).max(), name
