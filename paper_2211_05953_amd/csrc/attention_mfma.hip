@@ -83,14 +83,14 @@ struct TileRegs {
       *reinterpret_cast<u32x4*>(lds + row * D + ((ch ^ row_key<D>(row)) << 3)) = v[i];
     }
   }
-  // an infinity or a NaN among the thread's values
+  // an infinity or a NaN among the thread's values: an exponent of all ones carries into the sign's place
   __device__ __forceinline__ bool non_finite() const {
-    bool bad = false;
+    uint32_t carry = 0;
 #pragma unroll
     for (int i = 0; i < CH; ++i)
 #pragma unroll
-      for (int j = 0; j < 4; ++j) bad |= (v[i][j] & 0x7f80u) == 0x7f80u || (v[i][j] & 0x7f800000u) == 0x7f800000u;
-    return bad;
+      for (int j = 0; j < 4; ++j) carry |= (v[i][j] & 0x7f807f80u) + 0x00800080u;
+    return (carry & 0x80008000u) != 0;
   }
 };
 
@@ -134,8 +134,9 @@ __device__ __forceinline__ bf16x8 pack8_low(const f32x16& a, int kk) {
 // to run on fp32 kernels, and the results are no further from the exact ones than those kernels' were.  2 x 1000 tokens, 16
 // heads of 128, causal, forward / dQ / dK dV: 422 / 395 / 516 us on fp32 matrix instructions, 53 / 51 / 113 here (bound by the
 // chain score -> exponential -> two-part product of one or two waves per SIMD; the longest key block sets the last).
-// A zero times an infinity is a NaN in a matrix instruction, but a masked pair must not touch its row: where a tile that
-// the mask cuts holds non-finite values, its 64 rows are added element by element, allowed pairs only.
+// A zero times an infinity is a NaN in a matrix instruction, but a masked pair must not touch its row, and neither must the
+// remainder of a probability (zero or negative) take an infinity's sign: where a tile holds non-finite values, or a score
+// gradient is past what bf16 holds, the tile's rows are added element by element, allowed pairs only.
 // acc (rows = head dims, column = this lane's row) += sum over the tile's rows of s (rows = tile rows) x tile.
 constexpr int DUMP = 16 * 32;  // fp32 words of LDS a wave needs for it
 template <int D, int NTT, typename F>
@@ -162,6 +163,17 @@ __device__ __forceinline__ void accumulate_allowed(f32x16 (&acc)[D / 32], const 
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   }
+}
+
+// a value of the wave's that would round to an infinity (a NaN stays one either way)
+template <int NTT>
+__device__ __forceinline__ bool past_bf16(const f32x16 (&s)[NTT]) {
+  float m = 0.f;
+#pragma unroll
+  for (int u = 0; u < NTT; ++u)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) m = fmaxf(m, fabsf(s[u][r]));
+  return __builtin_amdgcn_ballot_w64(m > 0x1.fep127f) != 0;
 }
 
 // B operand straight from global memory: lane holds row[16kk + 8(l/32) .. +7] of its own token row
@@ -522,9 +534,9 @@ __global__ __launch_bounds__(2 * ROWS * KG, ROWS == 128 && !(EDGE && D == 128 &&
   typedef std::integral_constant<int, 0> I0;
   typedef std::integral_constant<int, 1> I1;
   fetch(0);
-  // tile j goes to an LDS stage: does the mask cut it, and does it hold what must not meet a masked zero
+  // tile j goes to an LDS stage: does it hold what must not meet a masked zero or a remainder
   auto note = [&](int j, int stage, const TileRegs<BT, D, NT>& v) {
-    if (EDGE && causal && j * BT + BT - 1 > q0 && v.non_finite()) bad_tile[stage] = j + 1;
+    if (EDGE && v.non_finite()) bad_tile[stage] = j + 1;
   };
   if (EDGE) __syncthreads();  // bad_tile is clear
   kr.store(KVs[0][0], tid);
@@ -600,7 +612,7 @@ __global__ __launch_bounds__(2 * ROWS * KG, ROWS == 128 && !(EDGE && D == 128 &&
     l += sum;
     if constexpr (EDGE) {
       if (bad_tile[PAR] == j + 1) {
-        accumulate_allowed<D, 2>(o, s, 0, Vs, dump + (tid >> 6) * DUMP, lane, [&](int row) { return kb + row <= q && kb + row < S_seq; });
+        accumulate_allowed<D, 2>(o, s, 0, Vs, dump + (tid >> 6) * DUMP, lane, [&](int row) { return (!causal || kb + row <= q) && kb + row < S_seq; });
         __syncthreads();
         return;
       }
@@ -842,7 +854,7 @@ __global__ __launch_bounds__(2 * ROWS * KG, ROWS == 128 && !EDGE ? 2 : 1) void a
   typedef std::integral_constant<int, 1> I1;
   fetch(0);
   auto note = [&](int j, int stage, const TileRegs<BT, D, NT>& k) {
-    if (EDGE && causal && j * BT + BT - 1 > q0 && k.non_finite()) bad_tile[stage] = j + 1;
+    if (EDGE && k.non_finite()) bad_tile[stage] = j + 1;
   };
   if (EDGE) __syncthreads();  // bad_tile is clear
   kr.store(KVs[0][0], tid);
@@ -888,9 +900,9 @@ __global__ __launch_bounds__(2 * ROWS * KG, ROWS == 128 && !EDGE ? 2 : 1) void a
           for (int r = 0; r < 16; ++r)
             if (kb + 32 * t + acc_row(r, lane) >= S_seq) s[r] = 0.f;
         }
-        if (bad_tile[p] == j + 1) {
-          const f32x16 s1[1] = {s};
-          accumulate_allowed<D, 1>(dq, s1, t, Ks, dump + (tid >> 6) * DUMP, lane, [&](int row) { return kb + row <= q && kb + row < S_seq; });
+        const f32x16 s1[1] = {s};
+        if (bad_tile[p] == j + 1 || past_bf16(s1)) {
+          accumulate_allowed<D, 1>(dq, s1, t, Ks, dump + (tid >> 6) * DUMP, lane, [&](int row) { return (!causal || kb + row <= q) && kb + row < S_seq; });
           continue;
         }
         accumulate_split<D>(dq, s, Ks, 32 * t, fa);
@@ -1008,7 +1020,7 @@ __global__ __launch_bounds__(NTHR_DKV, D == 64 && !EDGE ? 4 : 2) void attn_bwd_d
     }
   };
   auto note = [&](int j, int stage) {
-    if (EDGE && causal && j * BLK < k0 + WG_ROWS - 1 && (qr.non_finite() || dor.non_finite())) bad_tile[stage] = j + 1;
+    if (EDGE && (qr.non_finite() || dor.non_finite())) bad_tile[stage] = j + 1;
   };
   fetch(jbeg);
   if (EDGE) __syncthreads();  // bad_tile is clear
@@ -1107,8 +1119,8 @@ __global__ __launch_bounds__(NTHR_DKV, D == 64 && !EDGE ? 4 : 2) void attn_bwd_d
             }
           }
           const bf16_t* tile = dk_role ? Qs : dOs;
-          if (bad_tile[cur] == j + 1) {
-            accumulate_allowed<D, NTT>(acc, s, T0, tile, dump + w * DUMP, lane, [&](int row) { return key <= qb + row && qb + row < S_seq; });
+          if (bad_tile[cur] == j + 1 || past_bf16(s)) {
+            accumulate_allowed<D, NTT>(acc, s, T0, tile, dump + w * DUMP, lane, [&](int row) { return (!causal || key <= qb + row) && qb + row < S_seq; });
           } else {
 #pragma unroll
             for (int u = 0; u < NTT; ++u) accumulate_split<D>(acc, s[u], tile, 32 * (T0 + u), fa);

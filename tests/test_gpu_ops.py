@@ -603,3 +603,22 @@ def test_attention_keys_without_a_finite_score(causal, keys, value, S_mb, S_seq,
         there = np.isfinite(y)
         assert np.array_equal(np.isfinite(x), there), (name, int((~np.isfinite(x)).sum()), int((~there).sum()))
         assert there.any() and np.abs(np.where(there, x, 0) - np.where(there, y, 0)).max() <= TOL["bf16"] * np.abs(y[there]).max(), name
+
+
+@pytest.mark.parametrize("causal", [1, 0])
+@pytest.mark.parametrize("where", ["q", "k", "v", "dctx"])
+@pytest.mark.parametrize("S_mb,S_seq,a,d", [f for f in ATTENTION_FORMS if f[1] % 128])
+def test_attention_of_any_length_keeps_infinities(causal, where, S_mb, S_seq, a, d):
+    """One infinite component per head: every output is an infinity of the same sign, a NaN or finite where the plain
+    kernels' is (value and remainder of a probability must not both meet it, nor a masked pair)."""
+    h = a * d
+    qkv, dctx = (bf_inputs.normal(39, i, (S_mb, S_seq, n * h), bf16=True) for i, n in ((0, 3), (1, 1)))
+    if where == "dctx":
+        dctx[:, S_seq // 3, 3::d] = np.inf
+    else:
+        part = "qkv".index(where)
+        qkv[:, S_seq // 3, part * h + 3:(part + 1) * h:d] = np.inf
+    got = _attention_by_both(S_mb, S_seq, a, d, causal, qkv, dctx)
+    for name, x, y in zip(("ctx", "lse", "dqkv"), *got):
+        kind = [np.where(np.isnan(t), 2, np.where(np.isinf(t), np.sign(t), 0)) for t in (x, y)]
+        assert np.array_equal(*kind), (name, [[int((k == c).sum()) for c in (-1, 1, 2)] for k in kind])
