@@ -68,12 +68,12 @@ struct TileRegs {
       v[i] = *reinterpret_cast<const u32x4*>(g + (size_t)row * ld + ch * 8);
     }
   }
-  // rows from `valid` on (the sequence ends inside the tile) are zero
+  // rows from `valid` >= 1 on (the sequence ends inside the tile) repeat the last valid one
   __device__ __forceinline__ void load_edge(const bf16_t* __restrict__ g, size_t ld, int tid, int valid) {
 #pragma unroll
     for (int i = 0; i < CH; ++i) {
-      const int c = tid + i * NT, row = c / (D / 8), ch = c % (D / 8);
-      v[i] = row < valid ? *reinterpret_cast<const u32x4*>(g + (size_t)row * ld + ch * 8) : u32x4{0, 0, 0, 0};
+      const int c = tid + i * NT, row = min(c / (D / 8), valid - 1), ch = c % (D / 8);
+      v[i] = *reinterpret_cast<const u32x4*>(g + (size_t)row * ld + ch * 8);
     }
   }
   __device__ __forceinline__ void store(bf16_t* lds, int tid) const {
@@ -129,11 +129,13 @@ __device__ __forceinline__ bf16x8 pack8_low(const f32x16& a, int kk) {
   return o;
 }
 
-// ---- Sequences of any length (the EDGE forms of the kernels below).  Tiles past the end are filled with zeros and masked,
-// and probabilities and their gradients enter the products as two bf16 operands, value and remainder: these lengths used
-// to run on fp32 kernels, and the results are no further from the exact ones than those kernels' were.  2 x 1000 tokens, 16
-// heads of 128, causal, forward / dQ / dK dV: 422 / 395 / 516 us on fp32 matrix instructions, 53 / 51 / 113 here (bound by the
-// chain score -> exponential -> two-part product of one or two waves per SIMD; the longest key block sets the last).
+// ---- Sequences of any length (the EDGE forms of the kernels below).  Tiles past the end are filled with copies of the last
+// row and masked: no key makes a copy's score a NaN that does not make the real one's a NaN, as a zero row times an
+// infinite key would.  Probabilities and their gradients enter the products as two bf16 operands, value and remainder:
+// these lengths used to run on fp32 kernels, and the results are no further from the exact ones than those kernels' were.
+// 2 x 1000 tokens, 16 heads of 128, causal, forward / dQ / dK dV: 422 / 395 / 516 us on fp32 matrix instructions, 53 / 51 / 113
+// here (bound by the chain score -> exponential -> two-part product of one or two waves per SIMD; the longest key block
+// sets the last).
 // A zero times an infinity is a NaN in a matrix instruction, but a masked pair must not touch its row, and neither must the
 // remainder of a probability (zero or negative) take an infinity's sign: where a tile holds non-finite values, or a score
 // gradient is past what bf16 holds, the tile's rows are added element by element, allowed pairs only.
@@ -1011,7 +1013,7 @@ __global__ __launch_bounds__(NTHR_DKV, D == 64 && !EDGE ? 4 : 2) void attn_bwd_d
     if constexpr (EDGE) {
       qr.load_edge(base + (size_t)j * BLK * ld, ld, tid, S_seq - j * BLK);
       dor.load_edge(dob + (size_t)j * BLK * h, h, tid, S_seq - j * BLK);
-      // past the end: exp2(0 - inf) = 0, no probability
+      // past the end: exp2(score - inf) = 0, no probability
       if (tid < BLK) { lnext = i < S_seq ? lrow[i] * LOG2E : INFINITY; dnext = i < S_seq ? drow[i] : 0.f; }
     } else {
       qr.load(base + (size_t)j * BLK * ld, ld, tid);

