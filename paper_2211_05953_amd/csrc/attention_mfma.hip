@@ -31,6 +31,7 @@ typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4;
 typedef __attribute__((__vector_size__(4 * sizeof(short)))) short s16x4;
 typedef __attribute__((__vector_size__(8 * sizeof(short)))) short s16x8;
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
 
@@ -121,23 +122,27 @@ __device__ __forceinline__ bf16x8 pack8(const f32x16& a, int kk) {
   return o;
 }
 
-// what pack8 rounds away, as a second B operand: together they carry 16 bits of a probability
-__device__ __forceinline__ bf16x8 pack8_low(const f32x16& a, int kk) {
-  bf16x8 o;
+// the same as three B operands that add up to the 24 bits of the fp32 values (each difference is exact)
+__device__ __forceinline__ void pack8_parts(const f32x16& a, int kk, bf16x8& hi, bf16x8& mid, bf16x8& lo) {
 #pragma unroll
-  for (int e = 0; e < 8; ++e) o[e] = (__bf16)(a[8 * kk + e] - (float)(__bf16)a[8 * kk + e]);
-  return o;
+  for (int e = 0; e < 8; ++e) {
+    const float v = a[8 * kk + e], r = v - (float)(__bf16)v;
+    hi[e] = (__bf16)v;
+    mid[e] = (__bf16)r;
+    lo[e] = (__bf16)(r - (float)(__bf16)r);
+  }
 }
 
 // ---- Sequences of any length (the EDGE forms of the kernels below).  Tiles past the end are filled with copies of the last
 // row and masked: no key makes a copy's score a NaN that does not make the real one's a NaN, as a zero row times an
-// infinite key would.  Probabilities and their gradients enter the products as two bf16 operands, value and remainder:
-// these lengths used to run on fp32 kernels, and the results are no further from the exact ones than those kernels' were.
-// 2 x 1000 tokens, 16 heads of 128, causal, forward / dQ / dK dV: 422 / 395 / 516 us on fp32 matrix instructions, 53 / 51 / 113
-// here (bound by the chain score -> exponential -> two-part product of one or two waves per SIMD; the longest key block
-// sets the last).
+// infinite key would.  These lengths used to run on fp32 kernels, so probabilities and their gradients keep their 24 bits:
+// they enter the products as three bf16 operands.  (Two, 16 bits, are 4 % faster at S_head 128 and 10-20 % at 64, but nearly
+// uniform rows over values that cancel were 10 to 30 % further from the exact results than those kernels'.)
+// 2 x 1000 tokens, 16 heads of 128, causal, forward / backward: 422 / 911 us on fp32 matrix instructions, 44 / 158 here (bound
+// by the chain score -> exponential -> three-part product of one or two waves per SIMD; the longest key block sets the
+// end); 4 x 1000, 16 heads of 64, bidirectional: 52 / 218.
 // A zero times an infinity is a NaN in a matrix instruction, but a masked pair must not touch its row, and neither must the
-// remainder of a probability (zero or negative) take an infinity's sign: where a tile holds non-finite values, or a score
+// smaller parts of a probability (zero or negative) take an infinity's sign: where a tile holds non-finite values, or a score
 // gradient is past what bf16 holds, the tile's rows are added element by element, allowed pairs only.
 // acc (rows = head dims, column = this lane's row) += sum over the tile's rows of s (rows = tile rows) x tile.
 constexpr int DUMP = 16 * 32;  // fp32 words of LDS a wave needs for it
@@ -200,20 +205,30 @@ __device__ __forceinline__ void mfma_lds_pipeline() {
   __builtin_amdgcn_sched_barrier(0);
 }
 
-// acc += tile^T s over the 32 tile rows from row0 on, s (fp32 accumulator layout) as value and remainder
+// acc += tile^T s over the 32 tile rows from row0 on, s (fp32 accumulator layout) in three parts, the smallest first
 template <int D, typename FA>
 __device__ __forceinline__ void accumulate_split(f32x16 (&acc)[D / 32], const f32x16& s, const bf16_t* tile, int row0, const FA& fa) {
-  const bf16x8 lo[2] = {pack8_low(s, 0), pack8_low(s, 1)}, hi[2] = {pack8(s, 0), pack8(s, 1)};
-  __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-  for (int k2 = 0; k2 < 2; ++k2)
+  for (int k2 = 0; k2 < 2; ++k2) {
+    bf16x8 part[3], tf[D / 32];
+    pack8_parts(s, k2, part[2], part[1], part[0]);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int dt = 0; dt < D / 32; ++dt) tf[dt] = fa.frag_t(tile, row0 + 16 * k2, dt);
+    // a part over all head dimensions, then the next: the three products into one accumulator do not wait for each other
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+#pragma unroll
+      for (int dt = 0; dt < D / 32; ++dt) acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tf[dt], part[q], acc[dt], 0, 0, 0);
+    __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);  // two fragments (two reads each) ahead of the first products
 #pragma unroll
     for (int dt = 0; dt < D / 32; ++dt) {
-      const bf16x8 tf = fa.frag_t(tile, row0 + 16 * k2, dt);
-      acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tf, lo[k2], acc[dt], 0, 0, 0);
-      acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tf, hi[k2], acc[dt], 0, 0, 0);
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      if (dt + 2 < D / 32) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
     }
-  mfma_lds_pipeline<4 * (D / 32), 1, 4>();
+    __builtin_amdgcn_sched_group_barrier(0x008, 2 * (D / 32), 0);
+    __builtin_amdgcn_sched_barrier(0);
+  }
 }
 
 __device__ __forceinline__ int acc_row(int r, int lane) { return (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3); }
@@ -265,7 +280,6 @@ __device__ __forceinline__ void wave_colsum(const f32x16 (&acc)[D / 32], float m
 #pragma unroll
     for (int r = 0; r < 16; ++r) v[dt][r] = row16_sum(acc[dt][r] * mul);
   if ((lane & 15) == 0) {  // one lane per row stores the row's D / 2 sums, 16 bytes at a time
-    typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
     f32x4* dst = reinterpret_cast<f32x4*>(red + (lane >> 4) * (D / 2));
 #pragma unroll
     for (int dt = 0; dt < D / 32; ++dt)
@@ -520,7 +534,11 @@ __global__ __launch_bounds__(2 * ROWS * KG, ROWS == 128 && !(EDGE && D == 128 &&
   // The running maximum starts at the lowest finite value: while a row (or a key group's share of it) has met only scores of -inf, from
   // -inf or overflowing keys, their difference to it is -inf and adds exactly 0, where -inf - -inf would be a NaN.
   float m = -FLT_MAX, l = 0.f;
-  const float c2 = scale * LOG2E;
+  // EDGE: the exponent is the difference to the maximum times its factor, so that no rounding of the maximum enters every
+  // term and the log-sum-exp; where 1/sqrt(S_head) is no power of two the scores are scaled first, as the fp32 kernels do
+  // it, and no rounding of scale x log2(e) does either (log-sum-exp over 1000 keys: off by 4.8e-8 -> 4.3e-8, those kernels 4.4e-8)
+  constexpr bool SCALED = EDGE && D == 128;
+  const float c2 = SCALED ? LOG2E : scale * LOG2E;
 
   const int nblk = EDGE ? ((causal ? min(q0 + ROWS, S_seq) : S_seq) + BT - 1) / BT : causal ? (q0 + ROWS + (KG - 1) * BLK) / BT : S_seq / BT;
   TileRegs<BT, D, NT> kr, vr;
@@ -536,7 +554,7 @@ __global__ __launch_bounds__(2 * ROWS * KG, ROWS == 128 && !(EDGE && D == 128 &&
   typedef std::integral_constant<int, 0> I0;
   typedef std::integral_constant<int, 1> I1;
   fetch(0);
-  // tile j goes to an LDS stage: does it hold what must not meet a masked zero or a remainder
+  // tile j goes to an LDS stage: does it hold what must not meet a masked zero or a probability's smaller parts
   auto note = [&](int j, int stage, const TileRegs<BT, D, NT>& v) {
     if (EDGE && v.non_finite()) bad_tile[stage] = j + 1;
   };
@@ -585,6 +603,12 @@ __global__ __launch_bounds__(2 * ROWS * KG, ROWS == 128 && !(EDGE && D == 128 &&
         for (int r = 0; r < 16; ++r)
           if (kb + 32 * t + acc_row(r, lane) >= S_seq) s[t][r] = -INFINITY;
     }
+    if (SCALED) {
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) s[t][r] *= scale;
+    }
     float mx = m;
 #pragma unroll
     for (int t = 0; t < 2; ++t)
@@ -597,7 +621,6 @@ __global__ __launch_bounds__(2 * ROWS * KG, ROWS == 128 && !(EDGE && D == 128 &&
     for (int t = 0; t < 2; ++t)
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        // (EDGE: the difference first, so that no rounding of the maximum enters every term and the log-sum-exp)
         const float p = __builtin_amdgcn_exp2f(EDGE ? (s[t][r] - mx) * c2 : fmaf(s[t][r], c2, nmx));
         s[t][r] = p;
         sum += p;
@@ -671,7 +694,7 @@ __global__ __launch_bounds__(2 * ROWS * KG, ROWS == 128 && !(EDGE && D == 128 &&
   l += __shfl_xor(l, 32, 64);
   if (EDGE && q >= S_seq) return;
   store_rows<D>(o, ctx + ((size_t)b * S_seq + q) * h + head * D, lane, 1.0f / l);
-  if (lane < 32) lse[((size_t)b * N_heads + head) * S_seq + q] = m * scale + logf(l);
+  if (lane < 32) lse[((size_t)b * N_heads + head) * S_seq + q] = (SCALED ? m : m * scale) + logf(l);
 }
 
 // ------------------------------------------------------------------- backward, dQ pass
@@ -977,8 +1000,9 @@ __global__ __launch_bounds__(NTHR_DKV, D == 64 && !EDGE ? 4 : 2) void attn_bwd_d
                                                                 float scale, float* __restrict__ colpart) {
   __shared__ __attribute__((aligned(16))) bf16_t QOs[2][2][BLK * D];  // Q and dO tiles, double-buffered
   __shared__ __attribute__((aligned(16))) float stat_s[2][2][BLK];    // lse * log2(e) and delta of the tile's queries
-  __shared__ __attribute__((aligned(16))) bf16_t Ps[2][4][2][64 * 8]; // P of a sub-tile: [sub-tile][key group][register half][lane]
-  __shared__ __attribute__((aligned(16))) bf16_t Pl[EDGE ? 2 : 1][EDGE ? 4 : 1][EDGE ? 2 : 1][EDGE ? 64 * 8 : 8];  // what P's rounding left
+  // P of a sub-tile, in bf16 [sub-tile][key group][register half][lane]; EDGE: in fp32 [sub-tile][key group][register quarter][lane]
+  __shared__ __attribute__((aligned(16))) bf16_t Ps[EDGE ? 1 : 2][EDGE ? 1 : 4][EDGE ? 1 : 2][EDGE ? 8 : 64 * 8];
+  __shared__ __attribute__((aligned(16))) float Pf[EDGE ? 2 : 1][EDGE ? 4 : 1][EDGE ? 4 : 1][EDGE ? 64 * 4 : 4];
   __shared__ float dump[EDGE ? 8 * DUMP : 1];
   __shared__ int bad_tile[2];  // per LDS stage: 1 + the last tile staged there with a non-finite Q or dO
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -1079,13 +1103,15 @@ __global__ __launch_bounds__(NTHR_DKV, D == 64 && !EDGE ? 4 : 2) void attn_bwd_d
               for (int r = 0; r < 16; ++r)
                 if (key > qb + 32 * t + acc_row(r, lane)) s[u][r] = 0.f;
             }
-            pb[u][0] = pack8(s[u], 0);
-            pb[u][1] = pack8(s[u], 1);
-            *reinterpret_cast<bf16x8*>(&Ps[t][kg][0][lane * 8]) = pb[u][0];
-            *reinterpret_cast<bf16x8*>(&Ps[t][kg][1][lane * 8]) = pb[u][1];
             if constexpr (EDGE) {
-              *reinterpret_cast<bf16x8*>(&Pl[t][kg][0][lane * 8]) = pack8_low(s[u], 0);
-              *reinterpret_cast<bf16x8*>(&Pl[t][kg][1][lane * 8]) = pack8_low(s[u], 1);
+#pragma unroll
+              for (int q4 = 0; q4 < 4; ++q4)
+                *reinterpret_cast<f32x4*>(&Pf[t][kg][q4][lane * 4]) = f32x4{s[u][4 * q4], s[u][4 * q4 + 1], s[u][4 * q4 + 2], s[u][4 * q4 + 3]};
+            } else {
+              pb[u][0] = pack8(s[u], 0);
+              pb[u][1] = pack8(s[u], 1);
+              *reinterpret_cast<bf16x8*>(&Ps[t][kg][0][lane * 8]) = pb[u][0];
+              *reinterpret_cast<bf16x8*>(&Ps[t][kg][1][lane * 8]) = pb[u][1];
             }
           }
         } else {
@@ -1102,21 +1128,18 @@ __global__ __launch_bounds__(NTHR_DKV, D == 64 && !EDGE ? 4 : 2) void attn_bwd_d
       if constexpr (EDGE) {
         if (!skip) {
           if (dk_role) {
-            // dS = P (dP - delta), P from its two parts; masked pairs by selection (dP may be anything there)
+            // dS = P (dP - delta); masked pairs by selection (dP may be anything there)
 #pragma unroll
             for (int u = 0; u < NTT; ++u) {
               const int t = T0 + u;
-              bf16x8 hi[2], lo[2];
 #pragma unroll
-              for (int k2 = 0; k2 < 2; ++k2) {
-                hi[k2] = *reinterpret_cast<const bf16x8*>(&Ps[t][kg][k2][lane * 8]);
-                lo[k2] = *reinterpret_cast<const bf16x8*>(&Pl[t][kg][k2][lane * 8]);
-              }
+              for (int q4 = 0; q4 < 4; ++q4) {
+                const f32x4 p = *reinterpret_cast<const f32x4*>(&Pf[t][kg][q4][lane * 4]);
 #pragma unroll
-              for (int r = 0; r < 16; ++r) {
-                const float p = (float)hi[r >> 3][r & 7] + (float)lo[r >> 3][r & 7];
-                const int i = qb + 32 * t + acc_row(r, lane);
-                s[u][r] = (causal && key > i) || i >= S_seq ? 0.f : p * (s[u][r] - delta_s[32 * t + acc_row(r, lane)]);
+                for (int e = 0; e < 4; ++e) {
+                  const int r = 4 * q4 + e, i = qb + 32 * t + acc_row(r, lane);
+                  s[u][r] = (causal && key > i) || i >= S_seq ? 0.f : p[e] * (s[u][r] - delta_s[32 * t + acc_row(r, lane)]);
+                }
               }
             }
           }

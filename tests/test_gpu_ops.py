@@ -509,7 +509,7 @@ def test_split_contraction_of_few_tiles(M, N, K):
 @pytest.mark.parametrize("S_mb,S_seq,a,d", [(1, 2, 2, 64), (2, 63, 2, 64), (1, 65, 2, 128), (1, 129, 2, 128), (2, 300, 2, 64), (1, 255, 3, 128),
                                            (1, 451, 2, 128), (1, 257, 70, 64)])
 def test_attention_of_any_length_in_bf16(causal, S_mb, S_seq, a, d):
-    """Sequences that are not whole blocks of 128 on the bf16 matrix instructions, probabilities in two parts: no further
+    """Sequences that are not whole blocks of 128 on the bf16 matrix instructions, probabilities in three parts: no further
     from the oracle than the fp32 kernels that served them (2 % of the rounding of the outputs, which both share, for
     the chance of single roundings), nothing written outside, and finite wherever those are finite when infinities
     and NaN lie behind the mask."""
@@ -612,7 +612,7 @@ def test_attention_keys_without_a_finite_score(causal, keys, value, S_mb, S_seq,
 @pytest.mark.parametrize("S_mb,S_seq,a,d", [f for f in ATTENTION_FORMS if f[1] % 128])
 def test_attention_of_any_length_keeps_infinities(causal, where, S_mb, S_seq, a, d):
     """One infinite component per head: every output is an infinity of the same sign, a NaN or finite where the plain
-    kernels' is (value and remainder of a probability must not both meet it, nor a masked pair)."""
+    kernels' is (the parts of a probability must not all meet it, nor a masked pair)."""
     h = a * d
     qkv, dctx = (bf_inputs.normal(39, i, (S_mb, S_seq, n * h), bf16=True) for i, n in ((0, 3), (1, 1)))
     if where == "dctx":
@@ -624,3 +624,34 @@ def test_attention_of_any_length_keeps_infinities(causal, where, S_mb, S_seq, a,
     for name, x, y in zip(("ctx", "lse", "dqkv"), *got):
         kind = [np.where(np.isnan(t), 2, np.where(np.isinf(t), np.sign(t), 0)) for t in (x, y)]
         assert np.array_equal(*kind), (name, [[int((k == c).sum()) for c in (-1, 1, 2)] for k in kind])
+
+
+@pytest.mark.parametrize("causal", [0, 1])
+@pytest.mark.parametrize("S_mb,S_seq,a,d", [(1, 1000, 2, 64), (1, 1000, 2, 128), (1, 451, 70, 128), (1, 451, 200, 64)])
+def test_attention_of_any_length_keeps_the_bits_of_probabilities(causal, S_mb, S_seq, a, d):
+    """Nearly uniform rows over values that cancel: the outputs are the differences of the probabilities, 1e-3 of them, so
+    that 16 bits of a probability show above the outputs' rounding.  No further from the oracle than the plain fp32
+    kernels, 2 % for the chance of single roundings; neither is the log-sum-exp of ordinary rows, which is fp32."""
+    h = a * d
+    qkv, dctx = (bf_inputs.normal(41, i, (S_mb, S_seq, n * h), bf16=True) for i, n in ((0, 3), (1, 1)))
+    ordinary = _attention_by_both(S_mb, S_seq, a, d, causal, qkv, dctx)
+    q, k = (qkv[..., i * h:(i + 1) * h].astype(np.float64).reshape(S_mb, S_seq, a, d).transpose(0, 2, 1, 3) for i in (0, 1))
+    s = np.matmul(q[:, :8], k[:, :8].transpose(0, 1, 3, 2)) / math.sqrt(d)
+    if causal:
+        s = np.where(np.tril(np.ones((S_seq, S_seq), dtype=bool)), s, -np.inf)
+    lse = np.log(np.exp(s - s.max(-1, keepdims=True)).sum(-1)) + s.max(-1)
+    off = [np.linalg.norm(got[1][:, :8] - lse) for got in ordinary]
+    assert off[0] <= 1.02 * off[1], ("lse", off)
+    sign = np.where(np.arange(S_seq) % 2, -1, 1).astype(np.float32)[None, :, None]
+    qkv[..., :h] = bf_inputs.round_bf16(qkv[..., :h] * np.float32(2e-3))
+    qkv[..., 2 * h:] = sign
+    dctx[...] = sign
+    ctx, saved = L.attention_fwd(qkv.astype(np.float64), a, bool(causal))
+    dqkv = L.attention_bwd(dctx.astype(np.float64), saved, a)
+    got = _attention_by_both(S_mb, S_seq, a, d, causal, qkv, dctx)
+    even = slice(1, None, 2)   # rows of an even number of keys, where the values cancel
+    thirds = [("ctx", got[0][0][:, even], got[1][0][:, even], ctx[:, even])]
+    thirds += [(n, *(t[..., i * h:(i + 1) * h] for t in (got[0][2], got[1][2], dqkv))) for i, n in enumerate(("dq", "dk", "dv"))]
+    for name, x, y, ref in thirds:
+        off = [np.linalg.norm(t - ref) / np.linalg.norm(ref) for t in (x, y)]
+        assert off[0] <= 1.02 * off[1] + 1e-6, (name, off)
