@@ -1221,15 +1221,19 @@ __global__ __launch_bounds__(NTHR_DKV, D == 64 && !EDGE ? 4 : 2) void attn_bwd_d
 }
 
 template <int D>
-bf_status fwd_d(int S_mb, int S_seq, int N_heads, int causal, const void* qkv, void* ctx, float* lse, hipStream_t st) {
+bf_status fwd_d(int S_mb, int S_seq, int N_heads, int causal, const void* qkv, void* ctx, float* lse, hipStream_t st, bool shared_chip) {
   const long blocks = (long)(S_seq / WG_ROWS) * N_heads * S_mb;
   const float scale = 1.0f / sqrtf((float)D);
   // Two key groups per workgroup halve the chain of key tiles of a row, which is the time of a launch that leaves compute
   // units idle (all of them but those of the longest rows, if causal).  Measured, one group / two on 64 rows / two on 128
   // rows, us: S_head 128, S_seq 2048 causal, 8 heads 50 / 45 / 42, 16 heads 52 / 53 / 44, 32 heads 68 / 106 / 57, 64 heads
   // 88 / 206 / 111; bidirectional, 16 heads 53 / 87 / 49, 32 heads 76 / 199 / 93; S_seq 512, 16 heads 16.5 / 14.9 / 16.2;
-  // S_head 64, S_seq 2048 causal, 16 heads 36 / 30 / 27, 32 heads 46 / 43 / 35, 64 heads 62 / 85 / 76.
-  if (S_seq >= 1024 && blocks <= (causal ? 512 : 256)) {
+  // S_head 64, S_seq 2048 causal, 16 heads 36 / 30 / 27, 32 heads 46 / 43 / 35, 64 heads 62 / 85 / 76.  Shorter causal rows hide
+  // less: S_head 128, one group / two on 128 rows, S_seq 1280 at 480 blocks 38.0 / 40.4, 1152 at 432 34.5 / 36.1, 1024 at 384
+  // 30.9 / 31.7.  Beside another stream's kernels, which fill the units that the longest rows leave (a 2048-wide step on two
+  // chains, 256 blocks causal: 36.2 ms with two groups here, 35.5 with one): up to 128 blocks.
+  const long two_groups = shared_chip ? 128 : !causal ? 256 : D == 128 && S_seq < 1792 ? 320 : 512;
+  if (S_seq >= 1024 && blocks <= two_groups) {
     attn_fwd_general_kernel<D, 128, false, 2><<<(unsigned)blocks, 512, 0, st>>>((const bf16_t*)qkv, (bf16_t*)ctx, lse, S_seq, N_heads, S_mb, causal, scale);
   } else if (S_seq >= 256 && S_seq < 1024 && blocks <= 128) {
     attn_fwd_general_kernel<D, 64, false, 2><<<(unsigned)(2 * blocks), 256, 0, st>>>((const bf16_t*)qkv, (bf16_t*)ctx, lse, S_seq, N_heads, S_mb, causal, scale);
@@ -1270,7 +1274,8 @@ bf_status bwd_d(int S_mb, int S_seq, int N_heads, int causal, const void* qkv, c
   // into the rows per 256 (or 128) queries that the scratch has (4 us).
   // Beside another stream's kernels the longest rows' units are not the only busy ones, and from 257 workgroups on the
   // second group costs more than it hides (a 2048-wide step on two chains: attention backward 8.9 -> 9.9 ms, step 36.5 -> 37.6, with two).
-  if (S_seq >= 256 && 2 * (long)grid <= (causal && !shared_chip ? 512 : 256)) {
+  // Nor does it pay on rows of two tiles then (S_seq 256, 100 heads of 128, causal: 39.4 -> 43.3 us; 384, 80 heads: 47.2 / 47.5).
+  if (S_seq >= (grid > 128 ? 384 : 256) && 2 * (long)grid <= (causal && !shared_chip ? 512 : 256)) {
     attn_bwd_dq_general_kernel<D, 64, false, 2><<<grid * 2, 256, 0, st>>>((const bf16_t*)qkv, (const bf16_t*)ctx, (const bf16_t*)dctx, lse, delta, (bf16_t*)dqkv, S_seq, N_heads, S_mb, causal, scale, part_kv);
     if (part) {
       const int h = N_heads * D, rows = (int)attention_bwd_mfma_part_q_rows(S_mb, S_seq);
@@ -1289,13 +1294,16 @@ bf_status bwd_d(int S_mb, int S_seq, int N_heads, int causal, const void* qkv, c
 // The EDGE forms, the last block of rows partly empty; no partial column sums.  Two key groups for launches of few rows,
 // as in fwd_d and bwd_d (S_head 128 on 64 rows: on 128 they spill).  Forward, one group / two, us: S_head 128, causal, 1000
 // tokens, 16 heads 47 / 34, twice that 51 / 48 (bidirectional 51 / 70), 2 x 1900 tokens 90 / 126; S_head 64, 1900 tokens, 16
-// heads 51 / 36, 4 x 1000 tokens 33 / 31.
+// heads 51 / 36, 4 x 1000 tokens 33 / 31.  Short rows hide less: S_head 64, causal, 257 tokens at 300 blocks 12.0 / 15.9, 400 at
+// 400 18.0 / 21.0, 600 at 500 25.2 / 27.2, 700 at 480 25.4 / 26.4, 900 at 512 level; S_head 128, causal, 257 tokens at 240 blocks
+// 18.2 / 19.7, 300 at 240 19.6 / 19.8.
 template <int D>
 bf_status fwd_edge(int S_mb, int S_seq, int N_heads, int causal, const void* qkv, void* ctx, float* lse, hipStream_t st) {
   const long blocks = (long)((S_seq + 127) / 128) * N_heads * S_mb;
   const float scale = 1.0f / sqrtf((float)D);
   constexpr int EDGE_ROWS = D == 64 ? 128 : 64;
-  if (S_seq > 256 && blocks <= (causal ? 256 : 128) * (D == 64 ? 2 : 1))
+  const long two_groups = D == 64 ? (causal && S_seq >= 768 ? 512 : 256) : !causal ? 128 : S_seq >= 384 ? 256 : 192;
+  if (S_seq > 256 && blocks <= two_groups)
     attn_fwd_general_kernel<D, EDGE_ROWS, true, 2><<<(unsigned)((S_seq + EDGE_ROWS - 1) / EDGE_ROWS) * N_heads * S_mb, 4 * EDGE_ROWS, 0, st>>>((const bf16_t*)qkv, (bf16_t*)ctx, lse, S_seq, N_heads, S_mb, causal, scale);
   else
     attn_fwd_general_kernel<D, 128, true, 1><<<(unsigned)blocks, 256, 0, st>>>((const bf16_t*)qkv, (bf16_t*)ctx, lse, S_seq, N_heads, S_mb, causal, scale);
@@ -1349,10 +1357,10 @@ bf_status attention_bwd_mfma_edge(int S_mb, int S_seq, int N_heads, int S_head, 
 }
 
 bf_status attention_fwd_mfma(int S_mb, int S_seq, int N_heads, int S_head, int causal, const void* qkv, void* ctx,
-                             float* lse, hipStream_t st) {
+                             float* lse, hipStream_t st, bool shared_chip) {
   if (!args_ok(S_mb, S_seq, N_heads, S_head, qkv, ctx)) return BF_EINVAL;
-  if (S_head == 128) return fwd_d<128>(S_mb, S_seq, N_heads, causal, qkv, ctx, lse, st);
-  return fwd_d<64>(S_mb, S_seq, N_heads, causal, qkv, ctx, lse, st);
+  if (S_head == 128) return fwd_d<128>(S_mb, S_seq, N_heads, causal, qkv, ctx, lse, st, shared_chip);
+  return fwd_d<64>(S_mb, S_seq, N_heads, causal, qkv, ctx, lse, st, shared_chip);
 }
 
 // Rows of partial column sums the two backward kernels leave: one per (micro-batch sequence, query block) for dQ

@@ -262,10 +262,10 @@ bf_status attention_bwd_plain(int dtype, int S_mb, int S_seq, int N_heads, int S
 }
 
 bf_status attention_fwd(int dtype, int kernels, int S_mb, int S_seq, int N_heads, int S_head, int causal,
-                        const void* qkv, void* ctx, float* lse, hipStream_t st) {
+                        const void* qkv, void* ctx, float* lse, hipStream_t st, bool shared_chip) {
   if (dtype == BF_BF16 && kernels == BF_KERNELS_AUTO && attention_mfma_supported(S_seq, S_head)) {
     if (!qkv || !ctx || !lse) { set_error("attention_fwd: null pointer"); return BF_EINVAL; }
-    return attention_fwd_mfma(S_mb, S_seq, N_heads, S_head, causal, qkv, ctx, lse, st);
+    return attention_fwd_mfma(S_mb, S_seq, N_heads, S_head, causal, qkv, ctx, lse, st, shared_chip);
   }
   if (dtype == BF_BF16 && kernels == BF_KERNELS_AUTO && attention_mfma_edge_supported(S_mb, S_seq, N_heads, S_head) &&
       (((uintptr_t)qkv | (uintptr_t)ctx) & 15) == 0) {

@@ -123,8 +123,8 @@ bf_status attention_bwd_plain(int dtype, int S_mb, int S_seq, int N_heads, int S
                               void* dqkv, float* delta, hipStream_t st, bool matrix = false);
 bool attention_mfma_supported(int S_seq, int S_head);
 bf_status attention_fwd_mfma(int S_mb, int S_seq, int N_heads, int S_head, int causal,
-                             const void* qkv, void* ctx, float* lse, hipStream_t st);
-// The same for sequences of any length up to 4096 (16-byte aligned tensors), probabilities kept to 16 bits and more
+                             const void* qkv, void* ctx, float* lse, hipStream_t st, bool shared_chip = false);
+// The same for sequences of any length up to 4096 (16-byte aligned tensors), probabilities in fp32 throughout
 bool attention_mfma_edge_supported(int S_mb, int S_seq, int N_heads, int S_head);
 bf_status attention_fwd_mfma_edge(int S_mb, int S_seq, int N_heads, int S_head, int causal, const void* qkv, void* ctx, float* lse,
                                   hipStream_t st);
@@ -146,12 +146,13 @@ bf_status attention_fwd_f32(int dtype, int S_mb, int S_seq, int N_heads, int S_h
                             hipStream_t st);
 bf_status attention_bwd_f32(int dtype, int S_mb, int S_seq, int N_heads, int S_head, int causal, const void* qkv, const float* lse,
                             const float* delta, const void* dctx, void* dqkv, hipStream_t st);
+// shared_chip: another stream's kernels run beside these.
 bf_status attention_fwd(int dtype, int kernels, int S_mb, int S_seq, int N_heads, int S_head, int causal,
-                        const void* qkv, void* ctx, float* lse, hipStream_t st);
+                        const void* qkv, void* ctx, float* lse, hipStream_t st, bool shared_chip = false);
 // db_qkv (may be null): also db_qkv[3 S_hidden] = (accumulate ? db_qkv : 0) + column sums of dqkv, the bias
 // gradient of the QKV projection.  With `part` (attention_bwd_part_elems floats) the matrix-core kernels take the
 // sums on their way out and a small kernel adds their partial rows in fixed order; without it, or on the plain
-// path, dqkv is read a second time.  shared_chip: another stream's kernels run beside these.
+// path, dqkv is read a second time.
 bf_status attention_bwd(int dtype, int kernels, int S_mb, int S_seq, int N_heads, int S_head, int causal,
                         const void* qkv, const void* ctx, const float* lse, const void* dctx,
                         void* dqkv, float* delta, hipStream_t st, float* db_qkv = nullptr, float* part = nullptr,

@@ -464,7 +464,7 @@ bf_status p_attn_fwd(bf_stack* s, int S_mb, const void* qkv, void* ctx, float* l
   const bf_config& c = s->cfg;
   const double full = 4.0 * c.S_seq * (double)S_mb * c.S_seq * c.S_hidden;
   return timed(s, BF_K_ATTN_FWD, c.causal ? full / 2 : full, 0.0, st, [&] {
-    return attention_fwd(c.dtype, c.kernels, S_mb, c.S_seq, c.N_heads, c.S_head, c.causal, qkv, ctx, lse, st);
+    return attention_fwd(c.dtype, c.kernels, S_mb, c.S_seq, c.N_heads, c.S_head, c.causal, qkv, ctx, lse, st, s->chains_active == 2);
   });
 }
 // db_qkv: the QKV bias gradient (column sums of dqkv), taken on the way when `part` is there
