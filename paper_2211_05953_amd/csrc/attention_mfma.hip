@@ -993,8 +993,9 @@ constexpr int NTHR_DKV = 512;
 
 // S_head 64: two workgroups per compute unit want at most 128 registers, one fewer than the compiler takes by itself
 // (4 x 1024 tokens, 16 heads, bidirectional: 70 -> 53 us; the forward and dQ kernels would spill: 31 -> 39, 35 -> 49 us).
-template <int D, bool EDGE = false>
-__global__ __launch_bounds__(NTHR_DKV, D == 64 && !EDGE ? 4 : 2) void attn_bwd_dkv_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dctx,
+// SOLO: one per unit all the same, for launches in which the second would slow the longest blocks (bwd_d).
+template <int D, bool EDGE = false, bool SOLO = false>
+__global__ __launch_bounds__(NTHR_DKV, D == 64 && !EDGE && !SOLO ? 4 : 2) void attn_bwd_dkv_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dctx,
                                                                 const float* __restrict__ lse, const float* __restrict__ delta,
                                                                 bf16_t* __restrict__ dqkv, int S_seq, int N_heads, int S_mb, int causal,
                                                                 float scale, float* __restrict__ colpart) {
@@ -1285,7 +1286,15 @@ bf_status bwd_d(int S_mb, int S_seq, int N_heads, int causal, const void* qkv, c
     attn_bwd_dq_kernel<D, 256><<<grid / 2, 512, 0, st>>>((const bf16_t*)qkv, (const bf16_t*)ctx, (const bf16_t*)dctx, lse, delta, (bf16_t*)dqkv, S_seq, N_heads, S_mb, causal, scale, part);
   else
     attn_bwd_dq_kernel<D, 128><<<grid, NTHR, 0, st>>>((const bf16_t*)qkv, (const bf16_t*)ctx, (const bf16_t*)dctx, lse, delta, (bf16_t*)dqkv, S_seq, N_heads, S_mb, causal, scale, part);
-  attn_bwd_dkv_kernel<D><<<grid, NTHR_DKV, 0, st>>>((const bf16_t*)qkv, (const bf16_t*)dctx, lse, delta, (bf16_t*)dqkv, S_seq, N_heads, S_mb, causal, scale, part_kv);
+  // Causal, a little more than one block per unit: the blocks past the 256th are the shortest, and run faster after the first
+  // short ones end than beside the longest (S_head 64, S_seq 1536, 32 heads: backward 82.6 us with two to a unit, 79.6 with one;
+  // 768, 64 heads 49.7 / 48.2; level at the limits).
+  const unsigned solo_max = S_seq < 512 ? 288 : S_seq < 768 ? 340 : S_seq < 1152 ? 384 : S_seq < 1792 ? 416 : 448;
+  const bool solo = D == 64 && causal && S_seq >= 384 && grid > 256 && grid <= solo_max;
+  if (solo)
+    attn_bwd_dkv_kernel<D, false, D == 64><<<grid, NTHR_DKV, 0, st>>>((const bf16_t*)qkv, (const bf16_t*)dctx, lse, delta, (bf16_t*)dqkv, S_seq, N_heads, S_mb, causal, scale, part_kv);
+  else
+    attn_bwd_dkv_kernel<D><<<grid, NTHR_DKV, 0, st>>>((const bf16_t*)qkv, (const bf16_t*)dctx, lse, delta, (bf16_t*)dqkv, S_seq, N_heads, S_mb, causal, scale, part_kv);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) { set_error("attention_bwd_mfma launch failed: %s", hipGetErrorString(e)); return BF_EDEVICE; }
   return BF_OK;

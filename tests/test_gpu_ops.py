@@ -655,3 +655,28 @@ def test_attention_of_any_length_keeps_the_bits_of_probabilities(causal, S_mb, S
     for name, x, y, ref in thirds:
         off = [np.linalg.norm(t - ref) / np.linalg.norm(ref) for t in (x, y)]
         assert off[0] <= 1.02 * off[1] + 1e-6, (name, off)
+
+
+@pytest.mark.parametrize("S_mb,S_seq,a", [(1, 384, 90), (1, 640, 60), (2, 1024, 20)])
+def test_attention_backward_with_one_key_block_to_a_unit(S_mb, S_seq, a):
+    """Heads of 64, causal, 257 to 340 blocks: the dK / dV kernel in its form of one workgroup per compute unit.  A handful of
+    heads against the oracle, and the bias gradient's partial rows against the sums of what was stored."""
+    d, h = 64, a * 64
+    qkv, dctx = (bf_inputs.normal(43, i, (S_mb, S_seq, n * h), bf16=True) for i, n in ((0, 3), (1, 1)))
+    dQKV, dDC = to_dev(qkv, True), to_dev(dctx, True)
+    ctx, dqkv = (torch.full((S_mb, S_seq, n * h), float("nan"), dtype=torch.bfloat16, device="cuda") for n in (1, 3))
+    lse, delta = (torch.full((S_mb, a, S_seq), float("nan"), device="cuda") for _ in range(2))
+    part = torch.full((bf.bf_op_attention_bwd_part_elems(S_mb, S_seq, a, d) + 64,), float("nan"), device="cuda")
+    db = torch.full((3 * h,), float("nan"), device="cuda")
+    bf.bf_op_attention_fwd(bf.BF_BF16, 0, S_mb, S_seq, a, d, 1, dQKV, ctx, lse)
+    bf.bf_op_attention_bwd_bias(bf.BF_BF16, 0, S_mb, S_seq, a, d, 1, dQKV, ctx, lse, dDC, dqkv, delta, db, part, 0)
+    assert bool(torch.isnan(part[-64:]).all())
+    for head in (0, 1, a // 2, a - 1):
+        cols = slice(head * d, (head + 1) * d)
+        one = np.concatenate([qkv[..., i * h:][..., cols] for i in range(3)], axis=-1).astype(np.float64)
+        ref, saved = L.attention_fwd(one, 1, True)
+        ref_d = L.attention_bwd(dctx[..., cols].astype(np.float64), saved, 1)
+        assert rel_err(to_host(ctx)[..., cols], ref) <= TOL["bf16"]
+        for i in range(3):
+            assert rel_err(to_host(dqkv)[..., i * h:][..., cols], ref_d[..., i * d:(i + 1) * d]) <= TOL["bf16"], (head, i)
+    assert rel_err(to_host(db), to_host(dqkv).astype(np.float64).reshape(-1, 3 * h).sum(0)) <= 2.0 ** -8
