@@ -408,6 +408,25 @@ bool attention_fwd_f32_supported(int S_mb, int S_seq, int N_heads, int S_head) {
          fwd_scores_bytes(1, S_seq) + fwd_fixed_bytes(1, S_head <= 64 ? 64 : 128) <= LDS_MAX;
 }
 
+// Where they are faster than the plain kernels (same bits).  Forward: a tile of 64 keys costs two barriers and products over
+// heads padded to 64 or 128, so short rows on a mostly idle chip and small heads stay with the plain kernel.  One idle-chip
+// row against the plain kernel's: S_seq 128, one head of 64, fp32 0.96 of its time, 96 1.11; 400, 32 1.04; 64, 96 0.92; with the
+// chip full, 64 heads of 32 at S_seq 64 0.83, 16 heads at 128 0.93; bf16 loads are the plain kernel's cheaper ones: 128, one
+// head of 96 0.92, 96 1.04.  Heads up to 24: 64 heads of 8 at S_seq 256 0.63, at 400 1.19, at 1000 1.35 (the scores of long rows
+// leave room for fewer workgroups); fp32 heads of 24 keep ahead there, 16 heads at 1000 0.77.
+// Backward: 48 rows on (S_seq 16, 64 heads of 96 1.2; 48 1.02 at most), with wide or many heads 32 (64 heads of 64 0.7).
+bool attention_fwd_f32_better(int dtype, int S_mb, int S_seq, int N_heads, int S_head) {
+  const bool b16 = dtype == BF_BF16;
+  const long rows = (long)S_mb * S_seq * N_heads, d = S_head;
+  if (d <= 16 || (d <= 24 && b16)) return S_seq >= 192 && S_seq <= 256 && rows >= (b16 ? 8192 : 4096);
+  if (d <= 24) return S_seq >= 192 && rows >= 3072;
+  return S_seq >= 64 && (S_seq * d * d * d >= (b16 ? 100000000 : 1 << 25) || rows >= (b16 ? 4096 : 3072));
+}
+
+bool attention_bwd_f32_better(int S_mb, int S_seq, int N_heads, int S_head) {
+  return S_seq >= 48 || (S_seq >= 32 && (S_head > 64 || (S_head >= 32 && (long)S_mb * S_seq * N_heads >= 2048)));
+}
+
 template <typename T>
 static bf_status fwd_f32_t(int S_mb, int S_seq, int N_heads, int d, int causal, const void* qkv, void* ctx, float* lse, hipStream_t st) {
   return by_head<T>(d, qkv, qkv, [&](auto vc, auto dc) {

@@ -272,7 +272,8 @@ bf_status attention_fwd(int dtype, int kernels, int S_mb, int S_seq, int N_heads
     if (!qkv || !ctx || !lse) { set_error("attention_fwd: null pointer"); return BF_EINVAL; }
     return attention_fwd_mfma_edge(S_mb, S_seq, N_heads, S_head, causal, qkv, ctx, lse, st);
   }
-  if (kernels == BF_KERNELS_AUTO && attention_fwd_f32_supported(S_mb, S_seq, N_heads, S_head)) {
+  if (kernels == BF_KERNELS_AUTO && attention_fwd_f32_supported(S_mb, S_seq, N_heads, S_head) &&
+      attention_fwd_f32_better(dtype, S_mb, S_seq, N_heads, S_head)) {
     if (!qkv || !ctx || !lse) { set_error("attention_fwd: null pointer"); return BF_EINVAL; }
     return attention_fwd_f32(dtype, S_mb, S_seq, N_heads, S_head, causal, qkv, ctx, lse, st);
   }
@@ -306,7 +307,8 @@ bf_status attention_bwd(int dtype, int kernels, int S_mb, int S_seq, int N_heads
     if (r != BF_OK || !db_qkv) return r;
   } else {
     r = attention_bwd_plain(dtype, S_mb, S_seq, N_heads, S_head, causal, qkv, ctx, lse, dctx, dqkv, delta, st,
-                            kernels == BF_KERNELS_AUTO && attention_f32_supported(S_mb, S_seq, N_heads, S_head));
+                            kernels == BF_KERNELS_AUTO && attention_f32_supported(S_mb, S_seq, N_heads, S_head) &&
+                                attention_bwd_f32_better(S_mb, S_seq, N_heads, S_head));
     if (r != BF_OK || !db_qkv) return r;
   }
   return colsum(dtype, S_mb * S_seq, 3 * h, dqkv, db_qkv, accumulate, st);

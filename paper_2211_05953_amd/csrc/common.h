@@ -142,6 +142,8 @@ size_t attention_bwd_mfma_part_kv_rows(int S_mb, int S_seq);
 // forward pass keeps the scores of its rows in LDS, which bounds S_seq)
 bool attention_f32_supported(int S_mb, int S_seq, int N_heads, int S_head);
 bool attention_fwd_f32_supported(int S_mb, int S_seq, int N_heads, int S_head);
+bool attention_fwd_f32_better(int dtype, int S_mb, int S_seq, int N_heads, int S_head);  // and where they are faster than those
+bool attention_bwd_f32_better(int S_mb, int S_seq, int N_heads, int S_head);
 bf_status attention_fwd_f32(int dtype, int S_mb, int S_seq, int N_heads, int S_head, int causal, const void* qkv, void* ctx, float* lse,
                             hipStream_t st);
 bf_status attention_bwd_f32(int dtype, int S_mb, int S_seq, int N_heads, int S_head, int causal, const void* qkv, const float* lse,

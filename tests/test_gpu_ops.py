@@ -463,10 +463,12 @@ def test_gemm_on_partly_empty_tiles(mode, dtype, M, N, K):
 @pytest.mark.parametrize("mode,dtype", MODES)
 @pytest.mark.parametrize("causal", [1, 0])
 @pytest.mark.parametrize("poison", [False, True])
-@pytest.mark.parametrize("S_mb,S_seq,a,d", [(1, 1, 1, 8), (1, 128, 4, 60), (2, 65, 2, 33), (2, 100, 3, 40), (1, 200, 20, 128), (3, 129, 30, 64), (1, 1900, 1, 16)])
+@pytest.mark.parametrize("S_mb,S_seq,a,d", [(1, 1, 1, 8), (1, 128, 4, 60), (2, 65, 2, 33), (2, 100, 3, 40), (1, 200, 20, 128), (3, 129, 30, 64), (1, 1900, 1, 16),
+                                            (3, 65, 24, 33), (2, 100, 24, 40), (1, 200, 48, 16), (1, 500, 4, 60), (2, 48, 3, 20), (2, 32, 2, 100)])
 def test_attention_on_the_fp32_matrix_instructions(mode, dtype, causal, poison, S_mb, S_seq, a, d):
     """The same bits as the plain kernels (ascending chains, the same order of every sum): tiles of 64 with remainders,
-    16 and 32 rows per workgroup, odd head sizes, and infinities and NaN that the mask keeps from earlier rows."""
+    16 and 32 rows per workgroup, odd head sizes, and infinities and NaN that the mask keeps from earlier rows.  (Few
+    or short rows and small heads run forward on the plain kernels by themselves.)"""
     b16 = dtype == bf.BF_BF16
     if b16 and d in (64, 128):
         pytest.skip("bf16 heads of 64 and 128 run on the bf16 matrix instructions")
