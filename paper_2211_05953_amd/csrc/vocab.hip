@@ -25,6 +25,8 @@ __device__ __forceinline__ float wave_max(float v) {
   return v;
 }
 
+inline bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
+
 template <typename T, int VEC>
 struct alignas(sizeof(T) * VEC > 16 ? 16 : sizeof(T) * VEC) Vec {
   T v[VEC];
@@ -69,24 +71,27 @@ __global__ __launch_bounds__(ROW_THREADS) void embedding_fwd_kernel(const int32_
   }
 }
 
-// Token- and position-embedding gradients in one launch, without atomics.  Workgroups 0 .. n_rows-1: the one of the first
+// Token- and position-embedding gradients in one launch, without atomics.  Workgroups x < n_rows: the one of the first
 // position that uses a token sums the rows of every position using it, in ascending position, and adds the sum to that
 // token's gradient row; workgroups of later uses leave at once.  Distinct tokens, distinct rows.  The others: position
 // i sums its row over the samples of the micro-batch.
-// A frequent token's workgroup is the longest (300 of 2048 positions under a Zipf law): what bounds the launch is the
-// latency of its rows, so UN of them are in flight at a time (added in their order), grid.y splits the columns, and the
-// positions of a window of ids are found by all threads at once (eight ids each, ranked by a prefix sum).
-// 2048 tokens, 2048 columns, 50304 ids, bf16: 196 + 6 us (one row at a time, one wavefront searching) -> 28 us.
+// Two things bound the launch.  A frequent token's workgroup is the longest (300 of 2048 positions under a Zipf law), by the
+// latency and the bytes of its rows: UN of them are in flight at a time (added in their order), and its columns are split
+// over the workgroups of grid.y.  And every workgroup of a first position reads all the ids, which with few repeats is
+// n^2 reads: there only workgroup y = 0 does, and sums all the columns.  A token is frequent where FN pairs of
+// positions 256 apart in the FW from t on use it (one barrier); which side a token falls on changes no bit of its sum.
+// One row at a time and one wavefront searching / the columns of all tokens split / this, bf16, 50304 ids, us: 2048 tokens of 2048
+// columns, frequent ones among them 208 / 27 / 27, uniform 18 / 23 / 18; 16384 of 4096 4039 / 699 / 322 and 420 / 1071 / 298.
 template <typename T, int VEC>
 __global__ __launch_bounds__(ROW_THREADS) void embedding_bwd_kernel(const int32_t* __restrict__ tok, const T* __restrict__ d,
                                                                     float* __restrict__ g_tok, float* __restrict__ g_pos, int S_mb,
-                                                                    int S_seq, int S_voc, int h, int accumulate_pos) {
-  constexpr int PER = 8, WIN = ROW_THREADS * PER, UN = 16;
+                                                                    int S_seq, int S_voc, int h, int accumulate_pos, int tok16) {
+  constexpr int PER = 8, WIN = ROW_THREADS * PER, UN = 16, FW = 2 * ROW_THREADS, FN = 8, CHUNK = ROW_THREADS * VEC;
   typedef Vec<T, VEC> V;
+  typedef Vec<int32_t, 4> I4;  // used where tok16: the ids are 16-byte aligned
   const int n_rows = S_mb * S_seq, tid = threadIdx.x;
-  const int c = (blockIdx.y * ROW_THREADS + tid) * VEC;
   if ((int)blockIdx.x >= n_rows) {
-    const int i = blockIdx.x - n_rows;
+    const int i = blockIdx.x - n_rows, c = blockIdx.y * CHUNK + tid * VEC;
     if (c >= h) return;
     float* gr = g_pos + (size_t)i * h + c;
     float acc[VEC];
@@ -112,20 +117,65 @@ __global__ __launch_bounds__(ROW_THREADS) void embedding_bwd_kernel(const int32_
   const int t = blockIdx.x;
   const int v = tok[t];
   if (v < 0 || v >= S_voc) return;
+  int first_chunk = 0, chunks = gridDim.y;  // of the columns, this workgroup's
+  if (n_rows <= FW / 2) {  // reading the ids is nothing
+    first_chunk = blockIdx.y;
+    chunks = 1;
+  } else if (chunks > 1) {
+    const int i = t + tid;  // (pairs of positions are counted: one barrier)
+    const bool u0 = i < n_rows && tok[i] == v, u1 = i + ROW_THREADS < n_rows && tok[i + ROW_THREADS] == v;
+    if (__syncthreads_count(u0 || u1) >= FN) {
+      first_chunk = blockIdx.y;
+      chunks = 1;
+    } else if (blockIdx.y) {
+      return;
+    }
+  }
+  // an earlier use, among the first positions (a frequent token's is there), then among the others
   int earlier = 0;
-#pragma unroll 8
-  for (int i = tid; i < t; i += ROW_THREADS) earlier |= tok[i] == v;
+  const int near = min(t, 4 * ROW_THREADS);
+#pragma unroll 4
+  for (int i = tid; i < near; i += ROW_THREADS) earlier |= tok[i] == v;
   if (__syncthreads_or(earlier)) return;
+  if (t > near) {
+    if (tok16) {
+#pragma unroll 4
+      for (int i = near + tid * 4; i + 4 <= t; i += ROW_THREADS * 4) {
+        const I4 u = *reinterpret_cast<const I4*>(tok + i);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) earlier |= u.v[e] == v;
+      }
+      if (tid < (t & 3)) earlier |= tok[(t & ~3) + tid] == v;
+    } else {
+#pragma unroll 8
+      for (int i = near + tid; i < t; i += ROW_THREADS) earlier |= tok[i] == v;
+    }
+    if (__syncthreads_or(earlier)) return;
+  }
   const int lane = tid & 63, w = tid >> 6;
-  float acc[VEC];
-#pragma unroll
-  for (int j = 0; j < VEC; ++j) acc[j] = 0.f;
-  for (int w0 = t; w0 < n_rows; w0 += WIN) {
+  // The positions that use the token, a window at a time (one without it costs a barrier).  Windows share the list while it
+  // has room; a chunk of columns is summed from it in one go, or, where the uses did not fit, list after list.
+  int w0 = 0, n = 0;  // the next window, entries of the list
+  bool whole = true;  // the list has held all uses since the first window
+  auto fill = [&] {   // false: no more windows, or no room for this one's uses
+    if (w0 >= n_rows) return false;
+    const int i0 = w0 + tid * PER;
     unsigned hits = 0;
+    if (tok16 && i0 + PER <= n_rows) {
 #pragma unroll
-    for (int e = 0; e < PER; ++e) {
-      const int i = w0 + tid * PER + e;
-      if (i < n_rows && tok[i] == v) hits |= 1u << e;
+      for (int q = 0; q < PER / 4; ++q) {
+        const I4 u = *reinterpret_cast<const I4*>(tok + i0 + 4 * q);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) hits |= (u.v[e] == v ? 1u : 0u) << (4 * q + e);
+      }
+    } else {
+#pragma unroll
+      for (int e = 0; e < PER; ++e)
+        if (i0 + e < n_rows && tok[i0 + e] == v) hits |= 1u << e;
+    }
+    if (!__syncthreads_or(hits)) {  // (also: wave_n has been read)
+      w0 += WIN;
+      return true;
     }
     int before = __popc(hits);  // hits of the wave's lanes up to this one
 #pragma unroll
@@ -136,43 +186,65 @@ __global__ __launch_bounds__(ROW_THREADS) void embedding_bwd_kernel(const int32_
     if (lane == 63) wave_n[w] = before;
     before -= __popc(hits);
     __syncthreads();
-    int n = 0;
+    int more = 0;
 #pragma unroll
     for (int q = 0; q < ROW_THREADS / 64; ++q) {
       if (q < w) before += wave_n[q];
-      n += wave_n[q];
+      more += wave_n[q];
     }
+    if (n + more > WIN) return false;
+    before += n;
 #pragma unroll
     for (int e = 0; e < PER; ++e)
-      if (hits >> e & 1) list[before++] = w0 + tid * PER + e;
-    __syncthreads();
-    if (c < h) {
-      int k = 0;
-      for (; k + UN <= n; k += UN) {
-        V r[UN];
+      if (hits >> e & 1) list[before++] = i0 + e;
+    n += more;
+    w0 += WIN;
+    return true;
+  };
+  for (int ch = first_chunk; ch < first_chunk + chunks; ++ch) {
+    const int c = ch * CHUNK + tid * VEC;
+    float acc[VEC];
 #pragma unroll
-        for (int u = 0; u < UN; ++u) r[u] = *reinterpret_cast<const V*>(d + (size_t)list[k + u] * h + c);
-#pragma unroll
-        for (int u = 0; u < UN; ++u)
-#pragma unroll
-          for (int j = 0; j < VEC; ++j) acc[j] += (float)r[u].v[j];
+    for (int j = 0; j < VEC; ++j) acc[j] = 0.f;
+    bool last = whole && ch > first_chunk;  // the list is there from the chunk before
+    if (!last) w0 = t & ~(PER - 1);         // (positions before t do not use the token)
+    for (bool first = true;; first = false) {
+      if (!last) {
+        if (!first || ch > first_chunk) __syncthreads();  // the list has been read
+        n = 0;
+        while (fill()) {}
+        last = w0 >= n_rows;
+        if (!(first && last)) whole = false;
+        __syncthreads();
       }
-      for (; k < n; ++k) {
-        float r[VEC];
-        load_vec<T, VEC>(d + (size_t)list[k] * h + c, r);
+      if (c < h) {
+        int k = 0;
+        for (; k + UN <= n; k += UN) {
+          V r[UN];
 #pragma unroll
-        for (int j = 0; j < VEC; ++j) acc[j] += r[j];
+          for (int u = 0; u < UN; ++u) r[u] = *reinterpret_cast<const V*>(d + (size_t)list[k + u] * h + c);
+#pragma unroll
+          for (int u = 0; u < UN; ++u)
+#pragma unroll
+            for (int j = 0; j < VEC; ++j) acc[j] += (float)r[u].v[j];
+        }
+        for (; k < n; ++k) {
+          float r[VEC];
+          load_vec<T, VEC>(d + (size_t)list[k] * h + c, r);
+#pragma unroll
+          for (int j = 0; j < VEC; ++j) acc[j] += r[j];
+        }
       }
+      if (last) break;
     }
-    __syncthreads();  // the window's list has been read
-  }
-  if (c < h) {
-    float* gr = g_tok + (size_t)v * h + c;
-    float g[VEC];
-    load_vec<float, VEC>(gr, g);
+    if (c < h) {
+      float* gr = g_tok + (size_t)v * h + c;
+      float g[VEC];
+      load_vec<float, VEC>(gr, g);
 #pragma unroll
-    for (int j = 0; j < VEC; ++j) g[j] += acc[j];
-    store_vec<float, VEC>(gr, g);
+      for (int j = 0; j < VEC; ++j) g[j] += acc[j];
+      store_vec<float, VEC>(gr, g);
+    }
   }
 }
 
@@ -312,7 +384,6 @@ __global__ __launch_bounds__(ROW_THREADS) void sum_rows_kernel(const float* __re
   if (threadIdx.x == 0) out[0] = red[0];
 }
 
-inline bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 
 #define BF_LAUNCH_CHECK()                                                                  \
   do {                                                                                     \
@@ -341,9 +412,10 @@ bf_status embedding_bwd(int dtype, int S_mb, int S_seq, int S_voc, int h, const 
                         float* g_pos, int accumulate_pos, hipStream_t st) {
   if (S_mb < 1 || S_seq < 1 || S_voc < 1 || h < 1 || !tok || !d || !g_tok || !g_pos) { set_error("embedding_bwd: bad argument"); return BF_EINVAL; }
   const bool vec = h % 4 == 0 && aligned16(d) && aligned16(g_tok) && aligned16(g_pos);
-  const int per = ROW_THREADS * (vec ? 4 : 1);
+  const int per = ROW_THREADS * (vec ? 4 : 1), tok16 = aligned16(tok) ? 1 : 0;
   const dim3 grid((unsigned)(S_mb * S_seq + S_seq), (unsigned)((h + per - 1) / per));
-#define BF_EMB_BWD(T, VEC) embedding_bwd_kernel<T, VEC><<<grid, ROW_THREADS, 0, st>>>(tok, (const T*)d, g_tok, g_pos, S_mb, S_seq, S_voc, h, accumulate_pos)
+#define BF_EMB_BWD(T, VEC) \
+  embedding_bwd_kernel<T, VEC><<<grid, ROW_THREADS, 0, st>>>(tok, (const T*)d, g_tok, g_pos, S_mb, S_seq, S_voc, h, accumulate_pos, tok16)
   if (dtype == BF_BF16) {
     if (vec) BF_EMB_BWD(bf16_t, 4);
     else BF_EMB_BWD(bf16_t, 1);

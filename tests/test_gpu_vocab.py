@@ -247,3 +247,30 @@ def test_embedding_bwd_of_frequent_tokens(S_mb, S_seq, V, h):
     n = S_mb * S_seq
     assert (np.abs(g_tok.cpu().numpy() - want) <= (n + 1) * 2.0 ** -24 * size).all()
     assert np.abs(g_pos.cpu().numpy() - (2.0 + d.astype(np.float64).sum(0))).max() <= 1e-5
+
+
+@pytest.mark.parametrize("kind,S_mb,S_seq,h", [("rare", 3, 1000, 2056), ("late", 2, 2300, 1100), ("late", 1, 3300, 33), ("rare", 1, 256, 2056),
+                                               ("rare", 1, 257, 2056), ("few", 2, 700, 1100)])
+@pytest.mark.parametrize("offset", [0, 1])
+def test_embedding_bwd_windows_and_column_chunks(kind, S_mb, S_seq, h, offset):
+    """Columns of several workgroups or of one, ids that are 16-byte aligned or not, tokens that are all rare, all frequent, or
+    become frequent late: not in the window that decides on the columns, then with more uses than the list of positions
+    holds.  fp32 sums in ascending position: against 64 bits within n 2^-24 of the sum of magnitudes."""
+    rng = np.random.default_rng(h + S_seq)
+    n, V = S_mb * S_seq, 30000 if kind == "rare" else 9
+    tok = rng.integers(0, V, n)
+    if kind == "late":
+        tok[:1000] = rng.integers(1000, 3000, 1000)
+        tok[[5, 900]] = 4
+        tok[1000:] = np.where(rng.random(n - 1000) < 0.8, 4, tok[1000:])
+        V = 3000
+    d = rng.standard_normal((n, h)).astype(np.float32)
+    buf = torch.full((n + 8,), -1, dtype=torch.int32, device="cuda")
+    buf[offset:offset + n] = torch.from_numpy(tok.astype(np.int32)).cuda()
+    g_tok, g_pos = torch.ones((V, h), device="cuda"), torch.full((S_seq, h), 2.0, device="cuda")
+    bf.bf_op_embedding_bwd(bf.BF_FP32, S_mb, S_seq, V, h, buf[offset:offset + n], torch.from_numpy(d).cuda(), g_tok, g_pos, 1)
+    want, size = np.ones((V, h)), np.ones((V, h))
+    np.add.at(want, tok, d.astype(np.float64))
+    np.add.at(size, tok, np.abs(d))
+    assert (np.abs(g_tok.cpu().numpy() - want) <= (n + 1) * 2.0 ** -24 * size).all()
+    assert np.abs(g_pos.cpu().numpy() - (2.0 + d.reshape(S_mb, S_seq, h).astype(np.float64).sum(0))).max() <= 1e-5
