@@ -203,9 +203,9 @@ def test_lm_step_argument_errors():
 
 
 @pytest.mark.parametrize("dtype,bar", [(bf.BF_FP32, 1e-5), (bf.BF_BF16, 2e-2)])
-@pytest.mark.parametrize("V", [8, 1000, 2048, 2056, 8192, 8200, 32768, 50304, 57344, 57352])
+@pytest.mark.parametrize("V", [8, 1000, 2048, 2056, 8192, 8200, 16384, 16392, 32768, 50304, 57344, 57352])
 def test_ce_loss_row_kept_in_registers(dtype, bar, V):
-    """Vocabularies around the sizes at which a thread's share of the row grows (256 or 1024 threads, 1 to 13 vectors each)
+    """Vocabularies around the sizes at which a thread's share of the row grows (256, 512 or 1024 threads, 1 to 13 vectors each)
     and past the largest, with a row half masked (by -inf where the row stays in registers) and labels out of range;
     bars as for every kernel."""
     n = 5
