@@ -91,6 +91,7 @@ bool gemm_mfma_few_tiles(int layout, int M, int N);
 bf_status gemm_mfma_edge(int layout, int epi, const GemmArgs& a, hipStream_t st);
 // fp32 matrix-core product: any shape, both storage types (operands widened), all layouts and epilogues
 bool gemm_f32_supported(int layout, int epi, const GemmArgs& a);
+bool gemm_f32_better(int epi, const GemmArgs& a);  // than the plain kernel
 bf_status gemm_f32(int dtype, int layout, int epi, const GemmArgs& a, hipStream_t st);
 // tile (rows x columns of C per workgroup) the MFMA kernel runs an unsplit product of this shape on; 0 x 0 if none fits
 void gemm_mfma_tile(int layout, int epi, int M, int N, int* bm, int* bn);

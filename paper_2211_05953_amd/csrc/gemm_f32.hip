@@ -359,6 +359,15 @@ bool gemm_f32_supported(int layout, int epi, const GemmArgs& a) {
          a.N <= ldmax && a.K <= ldmax && tiles < (1l << 31) && (a.n_seg <= 1 || layout == L_TN);
 }
 
+// Where it is faster than the vector kernel (same bits): not a short contraction into a large output, which is bound by the
+// epilogue, whose stores the vector kernel has four to a lane.  1416 x 16000, fp32, vector kernel / this: forward with
+// residual K = 41 77 / 98 us, 72 94 / 104, 100 level; GeLU backward 69 / 104, 87 / 103, level; weight gradient 17 54 / 58, 65 92 / 88;
+// bf16, plain epilogue 9 25 / 32, 17 34 / 31; up to 1000 x 1000 this one wins or is level throughout.
+bool gemm_f32_better(int epi, const GemmArgs& a) {
+  const int k_min = epi == E_NONE || epi == E_BIAS ? 17 : epi == E_ACCUM ? 48 : epi == E_BIAS_GELU ? 64 : epi == E_BIAS_RES ? 80 : 88;
+  return a.K >= k_min || a.n_seg > 1 || (long)a.M * a.N < 2000000;
+}
+
 bf_status gemm_f32(int dtype, int layout, int epi, const GemmArgs& a, hipStream_t st) {
   if (!gemm_f32_supported(layout, epi, a)) { set_error("gemm_f32: shape not supported"); return BF_EINVAL; }
   if (dtype == BF_BF16) return by_layout<bf16_t, 1>(layout, epi, a, st);

@@ -1,6 +1,7 @@
 // Plain GEMM: LDS-tiled fp32 FMA, any shape, any of the three operand layouts, both
-// storage types.  It is what BF_KERNELS_PLAIN asks for (the matrix-core kernels are checked against it) and the
-// fallback for sizes past their 32-bit offsets; it is not meant to be fast.
+// storage types.  It is what BF_KERNELS_PLAIN asks for (the matrix-core kernels are checked against it), the
+// fallback for sizes past their 32-bit offsets, and the faster one for short contractions into large outputs
+// (gemm_f32_better).
 #include "common.h"
 #include "epilogue.h"
 
@@ -174,7 +175,8 @@ bf_status gemm(int dtype, int kernels, int layout, int epi, const GemmArgs& a, h
       return gemm_splitk_finish(epi, a.M, a.N, slices, a.splitk_ws, a.bias, a.R, a.C, st);
     }
     s = whole ? gemm_mfma(layout, epi, b, st) : gemm_mfma_edge(layout, epi, b, st);
-  } else if (kernels == BF_KERNELS_AUTO && (dtype == BF_FP32 || dtype == BF_BF16) && gemm_f32_supported(layout, epi, a)) {
+  } else if (kernels == BF_KERNELS_AUTO && (dtype == BF_FP32 || dtype == BF_BF16) && gemm_f32_supported(layout, epi, a) &&
+             gemm_f32_better(epi, a)) {
     s = gemm_check(layout, epi, a);
     if (s != BF_OK) return s;
     s = gemm_f32(dtype, layout, epi, a, st);
