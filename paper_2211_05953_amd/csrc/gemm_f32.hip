@@ -356,7 +356,7 @@ bool gemm_f32_supported(int layout, int epi, const GemmArgs& a) {
   const long ldmax = 1l << 21;
   const long tiles = (long)((a.M + 31) / 32) * ((a.N + 31) / 32);
   return layout >= L_NN && layout <= L_TN && (layout == L_TN) == (epi == E_ACCUM) && a.M >= 1 && a.N >= 1 && a.K >= 1 && a.M <= ldmax &&
-         a.N <= ldmax && a.K <= ldmax && tiles < (1l << 31) && (a.n_seg <= 1 || layout == L_TN);
+         a.N <= ldmax && (layout == L_TN || a.K <= ldmax) && tiles < (1l << 31) && (a.n_seg <= 1 || layout == L_TN);
 }
 
 // Where it is faster than the vector kernel (same bits): not a short contraction into a large output, which is bound by the

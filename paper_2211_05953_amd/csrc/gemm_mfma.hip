@@ -698,8 +698,8 @@ inline int choose_edge_tile(int layout, int M, int N) {
 bool gemm_mfma_edge_supported(int layout, int epi, int M, int N, int K) {
   if (layout < L_NN || layout > L_TN || (layout == L_TN) != (epi == E_ACCUM) || epi < E_NONE || epi > E_ACCUM) return false;
   if (M < 1 || N < 1 || K < 1 || N % 8) return false;
-  const long ldmax = 1l << 21;  // 32-bit lane offsets over 256 rows
-  if (M > ldmax || N > ldmax || K > ldmax) return false;
+  const long ldmax = 1l << 21;  // 32-bit lane offsets over 256 rows (K is a row's length, but for the weight gradient)
+  if (M > ldmax || N > ldmax || (layout != L_TN && K > ldmax)) return false;
   return layout == L_TN ? M % 8 == 0 : K % 8 == 0;
 }
 

@@ -146,8 +146,9 @@ bf_status gemm(int dtype, int kernels, int layout, int epi, const GemmArgs& a, h
   // 64 x 64 tiles the chip is full enough that the second pass only pays for a longer one (below).
   const bool split = slices > 1 && a.splitk_ws_elems >= (size_t)slices * a.M * a.N && ((uintptr_t)a.splitk_ws & 15) == 0 &&
                      (a.K >= SPLITK_FEW_TILES_K || !gemm_mfma_few_tiles(layout, a.M, a.N));
-  const bool whole = fits && (split || !gemm_mfma_edge_better(layout, a.M, a.N));
-  if (whole || (mfma && gemm_mfma_edge_supported(layout, epi, a.M, a.N, a.K))) {
+  const bool edge = mfma && gemm_mfma_edge_supported(layout, epi, a.M, a.N, a.K);
+  const bool whole = fits && (split || !edge || !gemm_mfma_edge_better(layout, a.M, a.N));
+  if (whole || edge) {
     s = gemm_check(layout, epi, a);
     if (s != BF_OK) return s;
     // (not on 64 x 64 tiles: colsum_part has a row per 128, and a second pass over so small an output takes no longer

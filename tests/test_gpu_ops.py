@@ -682,3 +682,30 @@ def test_attention_backward_with_one_key_block_to_a_unit(S_mb, S_seq, a):
         for i in range(3):
             assert rel_err(to_host(dqkv)[..., i * h:][..., cols], ref_d[..., i * d:(i + 1) * d]) <= TOL["bf16"], (head, i)
     assert rel_err(to_host(db), to_host(dqkv).astype(np.float64).reshape(-1, 3 * h).sum(0)) <= 2.0 ** -8
+
+
+@pytest.mark.parametrize("dtype,layout,M,N", [(bf.BF_BF16, bf.BF_TN, 128, 128), (bf.BF_BF16, bf.BF_TN, 72, 40), (bf.BF_BF16, bf.BF_NN, 128, 128),
+                                              (bf.BF_BF16, bf.BF_NT, 128, 256), (bf.BF_FP32, bf.BF_TN, 40, 36)])
+def test_gemm_of_few_tiles_over_more_than_two_million(dtype, layout, M, N):
+    """Contractions longer than the 32-bit offsets of the small-tile kernel's rows reach, in layouts where K is a row's length
+    and in the weight gradient's, where it is not: still on the matrix cores.  Ones in A and small whole numbers in B: every
+    partial sum is exact, in any order.  That the vector kernel did not run shows in random bf16 values, whose sums round
+    differently there (in fp32 the bits are the same, so only the sums are looked at)."""
+    K = 2 ** 21 + 128
+    td = torch.bfloat16 if dtype == bf.BF_BF16 else torch.float32
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(3)
+    B = torch.randint(-2, 3, (K, N), generator=gen, device="cuda").to(td)
+    A = torch.ones((K, M), device="cuda", dtype=td)
+    def run(kernels, A, B):
+        out = torch.full((M, N), float("nan"), dtype=torch.float32 if layout == bf.BF_TN else td, device="cuda")
+        a, b = (A if layout == bf.BF_TN else A.t().contiguous()), (B.t().contiguous() if layout == bf.BF_NT else B)
+        bf.bf_op_gemm(dtype, kernels, layout, bf.BF_EPI_ACCUM if layout == bf.BF_TN else bf.BF_EPI_NONE, M, N, K, a, b, out, accumulate=0)
+        return out
+    want = B.float().sum(0).to(torch.float32 if layout == bf.BF_TN else td).expand(M, N)
+    assert torch.equal(run(bf.BF_KERNELS_AUTO, A, B), want)
+    if dtype == bf.BF_BF16 and layout == bf.BF_TN:
+        B = torch.randn((K, N), generator=gen, device="cuda").to(td)
+        A = torch.randn((K, M), generator=gen, device="cuda").to(td)
+        auto, plain = run(bf.BF_KERNELS_AUTO, A, B), run(bf.BF_KERNELS_PLAIN, A, B)
+        assert rel_err(to_host(auto), to_host(plain).astype(np.float64)) <= 1e-4 and not torch.equal(auto, plain)
