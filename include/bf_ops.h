@@ -59,8 +59,7 @@ bf_status bf_op_gemm_gelu_bwd_colsum(int dtype, int kernels, int M, int N, int K
 bf_status bf_op_gemm_splitk(int dtype, int kernels, int layout, int epilogue, int M, int N, int K, const void* A,
                             const void* B, void* C, const float* bias, const void* R, float* planes,
                             size_t planes_elems, void* stream);
-/* Slices that call would use for this shape (1: the contraction is not split), and what its scratch is sized by.  A
- * product of at most 512 tiles of 64 x 64 and K < 4608 fills the chip with those and runs unsplit all the same. */
+/* Slices that call uses for this shape, given the scratch for them (1: the contraction is not split). */
 int bf_op_gemm_splitk_slices(int layout, int epilogue, int M, int N, int K);
 /* 1 if the problem is whole tiles of the bf16 MFMA kernel, 0 if not.  Other bf16 problems run on the same kernel with
  * partly empty tiles where their rows are whole 16-byte chunks (N % 8 == 0, and K % 8 == 0 or, weight gradient, M % 8

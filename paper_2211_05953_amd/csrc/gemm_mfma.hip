@@ -779,11 +779,18 @@ bf_status gemm_mfma(int layout, int epi, const GemmArgs& a, hipStream_t st) {
 // ascending order and applies the epilogue, so the result does not depend on which slice finishes first.  Measured on
 // the step of a 2048-wide, 6-layer model (8 micro-batches of 2048 rows): 48.8 -> 44.6 ms with K >= 4096 split, 44.3 with
 // K >= 2048; four slices on 256 x 256 tiles instead: 45.6.
+// Products of few tiles (64 x 64 ones) fill the chip better unsplit, and the second pass only pays for a longer contraction:
+// a k-tile takes 0.31 us on up to 256 of those and 0.47 on twice as many, so two slices save a quarter of the loop
+// and cost a pass over the planes (6 us).  1024 x 1024 x 8192: 55 us unsplit, 38 split (55 in slices of 256 x 128 tiles);
+// 1024 x 2048 x 4608: 40 either way; 1024 x 1024 x 2048: 13 against 14 and more.
+constexpr int SPLITK_FEW_TILES_K = 4608;
+
 int gemm_splitk_slices(int layout, int epi, int M, int N, int K) {
   if (layout != L_NN && layout != L_NT) return 1;
   if (epi != E_NONE && epi != E_BIAS && epi != E_BIAS_RES) return 1;
   if (K < 2048 || K % (2 * BK) || !gemm_mfma_supported(layout, epi, M, N, K)) return 1;
   if (M % 256 || N % 128) return 1;
+  if (K < SPLITK_FEW_TILES_K && few_tiles(layout, M, N)) return 1;
   if (choose_tile(M, N) != SPLITK_TILE) return 1;
   const long tiles = (long)(M / 256) * (N / 128);
   return tiles <= 128 ? 2 : 1;

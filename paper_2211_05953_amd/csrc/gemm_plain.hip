@@ -126,11 +126,6 @@ bf_status gemm_plain(int dtype, int layout, int epi, const GemmArgs& a, hipStrea
   return BF_EINVAL;
 }
 
-// A k-tile takes 0.31 us on up to 256 tiles of 64 x 64 and 0.47 on twice as many, so two slices save a quarter of the loop
-// and cost a pass over the planes (6 us).  1024 x 1024 x 8192: 55 us unsplit, 38 split (55 in slices of 256 x 128 tiles);
-// 1024 x 2048 x 4608: 40 either way; 1024 x 1024 x 2048: 13 against 14 and more.
-constexpr int SPLITK_FEW_TILES_K = 4608;
-
 bf_status gemm(int dtype, int kernels, int layout, int epi, const GemmArgs& a, hipStream_t st) {
   if (a.colsum && layout != L_TN && epi != E_GELU_BWD) {
     set_error("gemm: column sums go with the weight-gradient layout or the GeLU-backward epilogue");
@@ -142,10 +137,8 @@ bf_status gemm(int dtype, int kernels, int layout, int epi, const GemmArgs& a, h
   const bool mfma = dtype == BF_BF16 && kernels == BF_KERNELS_AUTO && (al & 15) == 0 && seg_ok;
   const bool fits = mfma && gemm_mfma_supported(layout, epi, a.M, a.N, a.K);
   const int slices = fits && a.splitk_ws ? gemm_splitk_slices(layout, epi, a.M, a.N, a.K) : 1;
-  // few tiles, long contraction: slices of K on more workgroups into fp32 planes, then the planes added in order.  On
-  // 64 x 64 tiles the chip is full enough that the second pass only pays for a longer one (below).
-  const bool split = slices > 1 && a.splitk_ws_elems >= (size_t)slices * a.M * a.N && ((uintptr_t)a.splitk_ws & 15) == 0 &&
-                     (a.K >= SPLITK_FEW_TILES_K || !gemm_mfma_few_tiles(layout, a.M, a.N));
+  // few tiles, long contraction: slices of K on more workgroups into fp32 planes, then the planes added in order
+  const bool split = slices > 1 && a.splitk_ws_elems >= (size_t)slices * a.M * a.N && ((uintptr_t)a.splitk_ws & 15) == 0;
   const bool edge = mfma && gemm_mfma_edge_supported(layout, epi, a.M, a.N, a.K);
   const bool whole = fits && (split || !edge || !gemm_mfma_edge_better(layout, a.M, a.N));
   if (whole || edge) {

@@ -233,7 +233,7 @@ def test_attention_fwd_bwd(mode, dtype, kernels, causal, S_mb, S_seq, a, d):
         assert rel_err(to_host(db), 2.0 * first.astype(np.float64)) <= 1e-6
 
 
-@pytest.mark.parametrize("M,N,K", [(2048, 2048, 8192), (2048, 2048, 6144), (1024, 1024, 4096), (256, 128, 2048)])
+@pytest.mark.parametrize("M,N,K", [(2048, 2048, 8192), (2048, 2048, 2048), (1024, 1024, 4608), (256, 128, 4608)])
 def test_gemm_with_a_split_contraction(M, N, K):
     """bf_op_gemm_splitk: few tiles and a long contraction run K in two slices into fp32 planes that a second kernel adds
     in order, with each of the epilogues it serves, in both layouts; the result agrees with the unsplit product to the
@@ -253,6 +253,8 @@ def test_gemm_with_a_split_contraction(M, N, K):
             ref = torch.empty_like(out)
             bf.bf_op_gemm_splitk(bf.BF_BF16, 0, layout, epi, M, N, K, dA, Bd, out, bias=dbias, R=dR, planes=planes)
             bf.bf_op_gemm(bf.BF_BF16, 0, layout, epi, M, N, K, dA, Bd, ref, bias=dbias, R=dR)
+            assert bool(torch.isfinite(planes).all())   # both slices were run
+            planes.fill_(float("nan"))
             assert rel_err(to_host(out), want) <= TOL["bf16"], (layout, epi)
             assert rel_err(to_host(out), to_host(ref).astype(np.float64)) <= 2.0 ** -7, (layout, epi)
             # deterministic: a second call gives the same bits
@@ -272,6 +274,8 @@ def test_split_contraction_is_chosen_only_where_it_pays():
     s = bf.bf_op_gemm_splitk_slices
     assert s(bf.BF_NN, bf.BF_EPI_BIAS_RES, 2048, 2048, 2048) == 2
     assert s(bf.BF_NN, bf.BF_EPI_BIAS_RES, 2048, 2048, 1024) == 1      # contraction too short
+    assert s(bf.BF_NN, bf.BF_EPI_BIAS, 1024, 1024, 4608) == 2          # few tiles: only a longer one pays
+    assert s(bf.BF_NN, bf.BF_EPI_BIAS, 1024, 1024, 4096) == 1 and s(bf.BF_NT, bf.BF_EPI_NONE, 256, 512, 2048) == 1
     assert s(bf.BF_NN, bf.BF_EPI_BIAS, 2048, 8192, 8192) == 1          # a full round of tiles already
     assert s(bf.BF_NT, bf.BF_EPI_NONE, 2048, 6144, 18432) == 1
     assert s(bf.BF_NN, bf.BF_EPI_BIAS_GELU, 2048, 2048, 8192) == 1     # epilogues with a second output are not split

@@ -221,6 +221,7 @@ def _a_product_splits_its_contraction(dtype, T, h, f):
     ("fp32", bf.BF_FP32, 4, 2, 256, 4, 1024, 128, 1, 2),       # one micro-batch per chain
     ("bf16", bf.BF_BF16, 4, 2, 256, 2, 1024, 256, 1, 4),       # MFMA kernels
     ("bf16", bf.BF_BF16, 4, 4, 512, 4, 2048, 128, 2, 5),
+    ("bf16", bf.BF_BF16, 2, 2, 256, 2, 4608, 128, 2, 3),       # the one-chain step splits its FC2 products
     ("bf16", bf.BF_BF16, 4, 1, 256, 2, 1024, 256, 1, 3),       # one stage
 ])
 @pytest.mark.parametrize("ckpt", [bf.BF_CKPT_NONE, bf.BF_CKPT_LAYER])
@@ -244,7 +245,7 @@ def test_two_chains_of_micro_batches_side_by_side(mode, dtype, Lyr, N_loop, h, a
     assert two["report"].mb_chains == 2 and one["report"].mb_chains == 1
     _compare(two, ref, TOL[mode], Lyr)
     split = _a_product_splits_its_contraction(dtype, S_mb * S_seq, h, f)
-    assert split == (h == 512)   # the cases cover both
+    assert split == (f == 4608)   # the cases cover both
     if split:
         assert rel_err(two["y"], one["y"]) <= TOL[mode] and rel_err(two["dx"], one["dx"]) <= TOL[mode]
     else:
