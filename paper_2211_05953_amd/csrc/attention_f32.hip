@@ -402,7 +402,7 @@ bool attention_f32_supported(int S_mb, int S_seq, int N_heads, int S_head) {
   return S_mb >= 1 && N_heads >= 1 && S_mb <= 65535 && N_heads <= 65535 && S_seq >= 1 && S_seq <= 4096 && S_head >= 1 && S_head <= 128;
 }
 
-// The scores of 16 rows have to fit beside the tiles (S_seq up to 1856 at head sizes up to 128, 2112 up to 64).
+// The scores of 16 rows have to fit beside the tiles (S_seq up to 1856 at head sizes up to 128, 2176 up to 64).
 bool attention_fwd_f32_supported(int S_mb, int S_seq, int N_heads, int S_head) {
   return attention_f32_supported(S_mb, S_seq, N_heads, S_head) &&
          fwd_scores_bytes(1, S_seq) + fwd_fixed_bytes(1, S_head <= 64 ? 64 : 128) <= LDS_MAX;

@@ -66,8 +66,8 @@ def test_gemm_all_layouts_and_epilogues(mode, dtype, kernels, M, N, K):
 def test_gelu_backward_product_with_the_bias_gradient_on_the_way(mode, dtype, kernels, M, N, K):
     """dU = (dY W^T) gelu'(U) and db = column sums of dU: in the MFMA kernel's epilogue (per-tile partial sums in a
     scratch buffer, then a fixed-order reduction), or as a second pass when there is no scratch or the plain kernel
-    runs; overwriting and accumulating.  Shapes cover the 128-, 256 x 128- and 256 x 256-tile forms, several tile
-    rows, and a ragged one."""
+    runs; overwriting and accumulating.  In bf16 all of these are products of few tiles, which take the second pass with
+    the scratch or without (test_gemm_on_whole_tiles has those whose epilogue leaves partial sums)."""
     b16 = dtype == bf.BF_BF16
     A = bf_inputs.normal(4, 0, (M, K), bf16=b16)
     Bt = bf_inputs.normal(4, 1, (N, K), 0.05, bf16=b16)
@@ -287,7 +287,7 @@ def test_split_contraction_is_chosen_only_where_it_pays():
 
 @pytest.mark.parametrize("M,N,K", [(2048, 4096, 512), (4096, 2048, 192), (512, 16384, 128)])
 def test_gemm_mfma_large_tile(M, N, K):
-    """Shapes that take the 256 x 256 workgroup tile of the MFMA kernel, all layouts."""
+    """Products of many tiles of the MFMA kernel (256 x 128 ones), all layouts."""
     assert bf.bf_op_gemm_uses_mfma(bf.BF_NN, bf.BF_EPI_NONE, M, N, K)
     A = bf_inputs.normal(5, 0, (M, K), bf16=True)
     B = bf_inputs.normal(5, 1, (K, N), 0.05, bf16=True)
@@ -348,7 +348,8 @@ def test_gemm_mfma_tile_of_192_columns(M, N, K):
                                              (768, 128, 64, 1, 0), (200, 136, 72, 3, 16), (256, 256, 64, 2, 4)])
 def test_wgrad_over_the_micro_batches_of_a_stage(mode, dtype, kernels, M, N, K, n_seg, gap):
     """G = sum_i X_i^T dY_i and db = sum_i colsum(dY_i) in one call (Sec. 4.2: the gradient of a stage
-    is needed only after all its micro-batches); segments lie `gap` elements apart beyond their size."""
+    is needed only after all its micro-batches); segments lie `gap` elements apart beyond their size.  (bf16 products of few
+    tiles, and ragged ones; test_gemm_on_whole_tiles has segments on the larger tiles.)"""
     b16 = dtype == bf.BF_BF16
     sx, sy = K * M + gap, K * N + gap
     X = bf_inputs.normal(9, 0, (n_seg * sx,), bf16=b16)
@@ -713,3 +714,114 @@ def test_gemm_of_few_tiles_over_more_than_two_million(dtype, layout, M, N):
         A = torch.randn((K, M), generator=gen, device="cuda").to(td)
         auto, plain = run(bf.BF_KERNELS_AUTO, A, B), run(bf.BF_KERNELS_PLAIN, A, B)
         assert rel_err(to_host(auto), to_host(plain).astype(np.float64)) <= 1e-4 and not torch.equal(auto, plain)
+
+
+@pytest.mark.parametrize("K", [64, 128, 192])
+@pytest.mark.parametrize("M,N,tile", [(384, 8192, (128, 128)), (512, 4224, (256, 128)), (2048, 8192, (256, 256))])
+def test_gemm_on_whole_tiles(M, N, tile, K):
+    """Each whole tile of the MFMA kernel on products of more tiles than the small-tile form takes: every layout and
+    epilogue, the column sums from the epilogue's partial rows (one per row of tiles, which shows that it ran) and
+    without them, and the weight gradient over three segments with a gap, 1 to 3 k-tiles each (a power of two or not)."""
+    for layout, epi in ((bf.BF_NN, bf.BF_EPI_NONE), (bf.BF_NN, bf.BF_EPI_BIAS_GELU), (bf.BF_NT, bf.BF_EPI_GELU_BWD), (bf.BF_TN, bf.BF_EPI_ACCUM)):
+        assert bf.bf_op_gemm_tile(layout, epi, M, N, K) == tile and (M // 64) * (N // 64) > 512
+    A, B = bf_inputs.normal(51, 0, (M, K), bf16=True), bf_inputs.normal(51, 1, (K, N), 0.05, bf16=True)
+    bias, R = bf_inputs.normal(51, 2, (N,), 0.5), bf_inputs.normal(51, 3, (M, N), bf16=True)
+    acc, R64 = A.astype(np.float64) @ B.astype(np.float64), R.astype(np.float64)
+    dA, dB, dBt, dR, dbias = to_dev(A, True), to_dev(B, True), to_dev(np.ascontiguousarray(B.T), True), to_dev(R, True), to_dev(bias, False)
+    grad = acc * L.gelu_grad(R64)
+    for layout, op in ((bf.BF_NN, dB), (bf.BF_NT, dBt)):
+        for epi, ref in ((bf.BF_EPI_NONE, acc), (bf.BF_EPI_BIAS, acc + bias), (bf.BF_EPI_BIAS_RES, acc + bias + R64),
+                         (bf.BF_EPI_BIAS_GELU, acc + bias), (bf.BF_EPI_GELU_BWD, grad)):
+            out, out2 = (torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+            bf.bf_op_gemm(bf.BF_BF16, 0, layout, epi, M, N, K, dA, op, out, bias=dbias, R=dR, C2=out2)
+            assert rel_err(to_host(out), ref) <= TOL["bf16"], (layout, epi)
+            if epi == bf.BF_EPI_BIAS_GELU:
+                assert rel_err(to_host(out2), L.gelu(acc + bias)) <= TOL["bf16"]
+    for with_part in (True, False):
+        out, db = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda"), torch.full((N,), float("nan"), device="cuda")
+        part = torch.full(((M + 127) // 128, N), float("nan"), device="cuda") if with_part else None
+        bf.bf_op_gemm_gelu_bwd_colsum(bf.BF_BF16, 0, M, N, K, dA, dBt, out, dR, db, part)
+        assert rel_err(to_host(out), grad) <= TOL["bf16"]
+        assert rel_err(to_host(db), to_host(out).astype(np.float64).sum(0)) <= 1e-5
+        if with_part:
+            written = torch.isfinite(part).all(1).cpu().numpy()
+            assert np.array_equal(written, np.arange(len(written)) < M // tile[0])
+    n_seg, gap = 3, 64
+    sx, sy = K * M + gap, K * N + gap
+    X, dY = bf_inputs.normal(53, 0, (n_seg * sx,), bf16=True), bf_inputs.normal(53, 1, (n_seg * sy,), 0.3, bf16=True)
+    G_ref, db_ref = np.zeros((M, N)), np.zeros(N)
+    for i in range(n_seg):
+        dYi = dY[i * sy:i * sy + K * N].reshape(K, N).astype(np.float64)
+        G_ref += X[i * sx:i * sx + K * M].reshape(K, M).astype(np.float64).T @ dYi
+        db_ref += dYi.sum(0)
+    G, db = torch.full((M, N), float("nan"), device="cuda"), torch.full((N,), float("nan"), device="cuda")
+    for accumulate in (0, 1):
+        bf.bf_op_wgrad(bf.BF_BF16, 0, M, N, K, n_seg, to_dev(X, True), sx, to_dev(dY, True), sy, G, db, accumulate=accumulate)
+        assert rel_err(to_host(G), (1 + accumulate) * G_ref) <= 1e-5 and rel_err(to_host(db), (1 + accumulate) * db_ref) <= 1e-5
+
+
+def _check_heads(S_mb, S_seq, a, d, causal, poison=False):
+    """Forward and backward of a launch of many heads, four of them against the oracle (or, with infinities and NaN behind the
+    mask, against where the plain kernels are finite)."""
+    h = a * d
+    qkv, dctx = (bf_inputs.normal(57, i, (S_mb, S_seq, n * h), bf16=True) for i, n in ((0, 3), (1, 1)))
+    if poison:
+        qkv[:, S_seq - 1, 2 * h + 3::d], qkv[:, 2 * S_seq // 3, h + 1:2 * h:d] = np.inf, np.nan
+        qkv[:, S_seq // 3, 5:h:d], dctx[:, S_seq // 2, 2::d] = -np.inf, np.nan
+    dQKV, dDC = to_dev(qkv, True), to_dev(dctx, True)
+    got = []
+    for kernels in ((bf.BF_KERNELS_AUTO, bf.BF_KERNELS_PLAIN) if poison else (bf.BF_KERNELS_AUTO,)):
+        ctx, dqkv = (torch.full((S_mb, S_seq, n * h), 7.0, dtype=torch.bfloat16, device="cuda") for n in (1, 3))
+        lse, delta = (torch.full((S_mb, a, S_seq), 7.0, device="cuda") for _ in range(2))
+        bf.bf_op_attention_fwd(bf.BF_BF16, kernels, S_mb, S_seq, a, d, causal, dQKV, ctx, lse)
+        bf.bf_op_attention_bwd(bf.BF_BF16, kernels, S_mb, S_seq, a, d, causal, dQKV, ctx, lse, dDC, dqkv, delta)
+        got.append([to_host(t) for t in (ctx, dqkv, lse)])
+    if poison:
+        for x, y in zip(*got):
+            assert np.array_equal(np.isfinite(x), np.isfinite(y))
+        return
+    for head in (0, 1, a // 2, a - 1):
+        cols = slice(head * d, (head + 1) * d)
+        one = np.concatenate([qkv[..., i * h:][..., cols] for i in range(3)], axis=-1).astype(np.float64)
+        ref, saved = L.attention_fwd(one, 1, bool(causal))
+        ref_d = L.attention_bwd(dctx[..., cols].astype(np.float64), saved, 1)
+        assert rel_err(got[0][0][..., cols], ref) <= TOL["bf16"], head
+        for i in range(3):
+            assert rel_err(got[0][1][..., i * h:][..., cols], ref_d[..., i * d:(i + 1) * d]) <= TOL["bf16"], (head, i)
+
+
+@pytest.mark.parametrize("causal", [1, 0])
+@pytest.mark.parametrize("S_mb,S_seq,a,d", [(2, 451, 33, 128), (2, 451, 70, 64), (1, 1000, 80, 64), (2, 1000, 16, 128), (1, 770, 70, 64), (1, 300, 64, 128),
+                                            (1, 300, 65, 128)])
+@pytest.mark.parametrize("poison", [False, True])
+def test_attention_of_any_length_in_large_launches(causal, poison, S_mb, S_seq, a, d):
+    """Both sides of the numbers of blocks up to which a row's keys go to two groups: 264 and 560 blocks of 128 rows
+    (one group in both passes), 640, 256, 490, and 192 / 195 of short rows."""
+    _check_heads(S_mb, S_seq, a, d, causal, poison)
+
+
+@pytest.mark.parametrize("causal", [1, 0])
+@pytest.mark.parametrize("S_mb,S_seq,a,d", [(4, 1024, 16, 64), (1, 1024, 70, 64), (1, 384, 90, 128), (1, 384, 180, 64), (1, 1024, 40, 128), (1, 1024, 41, 128),
+                                            (1, 256, 65, 128), (1, 384, 44, 128)])
+def test_attention_of_whole_blocks_in_large_launches(causal, S_mb, S_seq, a, d):
+    """The 256-row kernels with heads of 64 (512 and 560 blocks), the 128-row ones over several blocks of both head sizes, and
+    both sides of the numbers of blocks that two key groups serve (320 / 328 forward, 130 at S_seq 256 and 132 at 384 for dQ)."""
+    _check_heads(S_mb, S_seq, a, d, causal)
+
+
+@pytest.mark.parametrize("causal", [1, 0])
+@pytest.mark.parametrize("S_seq,a,d", [(2176, 1, 64), (2177, 1, 64), (1856, 2, 128), (1857, 2, 128), (4096, 1, 64), (4096, 1, 128)])
+def test_fp32_attention_at_the_limits_of_the_scores_in_lds(causal, S_seq, a, d):
+    """The longest rows whose scores fit the forward kernel's LDS, one past them (the plain kernel), and the longest rows
+    there are: the same bits as the plain kernels, forward and backward."""
+    h = a * d
+    qkv, dctx = (to_dev(bf_inputs.normal(59, i, (1, S_seq, n * h)), False) for i, n in ((0, 3), (1, 1)))
+    got = []
+    for kernels in (bf.BF_KERNELS_AUTO, bf.BF_KERNELS_PLAIN):
+        ctx, dqkv = (torch.full((1, S_seq, n * h), 7.0, device="cuda") for n in (1, 3))
+        lse, delta = (torch.full((1, a, S_seq), 7.0, device="cuda") for _ in range(2))
+        bf.bf_op_attention_fwd(bf.BF_FP32, kernels, 1, S_seq, a, d, causal, qkv, ctx, lse)
+        bf.bf_op_attention_bwd(bf.BF_FP32, kernels, 1, S_seq, a, d, causal, qkv, ctx, lse, dctx, dqkv, delta)
+        got.append((ctx, lse, dqkv))
+    for x, y in zip(*got):
+        assert torch.equal(x, y)
