@@ -47,7 +47,8 @@ bf_status bf_op_gemm(int dtype, int kernels, int layout, int epilogue, int M, in
  *   db[N]  = (accumulate ? db : 0) + sum_m C[m,:]                of the stored (rounded) C
  * part: device fp32 scratch of ceil(M / 128) * N elements, owned by the caller: with it the MFMA kernel takes the
  * sums in its epilogue (one row of partial sums per row of tiles, added up in a fixed order by a small kernel);
- * NULL, or a problem that goes to the plain kernel: a second pass over C takes them.  db: device fp32 [N]. */
+ * NULL, a product of few tiles (see bf_op_gemm_tile) or one that goes to another kernel: a second pass over C takes
+ * them and the scratch is left alone.  db: device fp32 [N]. */
 bf_status bf_op_gemm_gelu_bwd_colsum(int dtype, int kernels, int M, int N, int K, const void* A, const void* Bt, void* C,
                                      const void* R, float* db, float* part, int accumulate, void* stream);
 /* bf_op_gemm for the forward / dgrad layouts (BF_NN, BF_NT; epilogues none, bias, bias + residual) with scratch for a
@@ -61,17 +62,19 @@ bf_status bf_op_gemm_splitk(int dtype, int kernels, int layout, int epilogue, in
                             size_t planes_elems, void* stream);
 /* Slices that call uses for this shape, given the scratch for them (1: the contraction is not split). */
 int bf_op_gemm_splitk_slices(int layout, int epilogue, int M, int N, int K);
-/* 1 if the problem is whole tiles of the bf16 MFMA kernel, 0 if not.  Other bf16 problems run on the same kernel with
- * partly empty tiles where their rows are whole 16-byte chunks (N % 8 == 0, and K % 8 == 0 or, weight gradient, M % 8
- * == 0), on the fp32 matrix instructions where they are not. */
+/* 1 if the problem is whole tiles of the bf16 MFMA kernel (M and N multiples of 128, K of 64), 0 if not: not whether
+ * matrix cores serve it.  Other bf16 problems run on the same kernel with partly empty tiles where their rows are whole
+ * 16-byte chunks (N % 8 == 0, and K % 8 == 0 or, weight gradient, M % 8 == 0), and where they are not on the fp32
+ * matrix instructions or, a short contraction into a large output, on the plain kernel, whichever is faster. */
 int bf_op_gemm_uses_mfma(int layout, int epilogue, int M, int N, int K);
 /* The tile of C (rows x columns per workgroup) that the MFMA kernel runs an unsplit product of this shape on by itself:
  * 256 x 256, 256 x 128, 128 x 128, or 256 x 192 (forward and dgrad layouts with the epilogues none, bias, bias + residual
  * and N a multiple of 192, where that fills the rounds of the grid better: 2048 x 6144 outputs are 256 such tiles).  A
- * step that runs two chains of micro-batches does not take the last shape.  Products of few tiles (at most 512 of 64 x 64,
- * weight gradients 256) run on 64 x 64 tiles instead, and weight gradients with an odd multiple of 128 on partly empty
- * 256 x 256 ones where that is faster; the shape given is the whole tile they would otherwise take.  Host arithmetic only.  Returns 1 and the tile in tile_m / tile_n (host ints), or 0
- * (and 0 x 0) where bf_op_gemm_uses_mfma is 0. */
+ * step that runs two chains of micro-batches does not take the last shape.  Not what every call runs on: products of few
+ * tiles (at most 512 of 64 x 64, weight gradients 256) run on 64 x 64 ones instead, and weight gradients with an odd
+ * multiple of 128 on partly empty 256 x 256 ones where that is faster; the shape given is the whole tile they would
+ * otherwise take.  Host arithmetic only.  Returns 1 and the tile in tile_m / tile_n (host ints), or 0 (and 0 x 0) where
+ * bf_op_gemm_uses_mfma is 0. */
 int bf_op_gemm_tile(int layout, int epilogue, int M, int N, int K, int* tile_m, int* tile_n);
 
 /* Weight and bias gradient of one linear layer over all the micro-batches of a stage in one
@@ -79,9 +82,9 @@ int bf_op_gemm_tile(int layout, int epilogue, int M, int N, int K, int* tile_m, 
  * before the gradient is needed, Sec. 4.2; fp32 main-grads, App. D):
  *   G[M,N]  = (accumulate ? G  : 0) + sum_{i < n_seg} X_i[K,M]^T dY_i[K,N]
  *   db[N]   = (accumulate ? db : 0) + sum_{i < n_seg} sum_k dY_i[k,:]          (db may be NULL)
- * X_i = X + i * stride_x and dY_i = dY + i * stride_dy (strides in elements; the MFMA kernel takes
- * bf16 segments that are 16-byte aligned, others go to the plain kernel), both in the activation dtype, device memory; G and db fp32, device
- * memory, owned by the caller.  BF_EINVAL for bad sizes, null X / dY / G or n_seg < 1. */
+ * X_i = X + i * stride_x and dY_i = dY + i * stride_dy (strides in elements; the bf16 MFMA kernel takes
+ * segments that are 16-byte aligned, others run on the fp32 matrix instructions), both in the activation dtype, device
+ * memory; G and db fp32, device memory, owned by the caller.  BF_EINVAL for bad sizes, null X / dY / G or n_seg < 1. */
 bf_status bf_op_wgrad(int dtype, int kernels, int M, int N, int K, int n_seg, const void* X, size_t stride_x,
                       const void* dY, size_t stride_dy, float* G, float* db, int accumulate, void* stream);
 
@@ -117,9 +120,9 @@ bf_status bf_op_attention_bwd(int dtype, int kernels, int S_mb, int S_seq, int N
 /* The same with the bias gradient of the QKV projection (App. A.1: qkv = a W_qkv + b_qkv, so the gradient of b_qkv
  * is the column sum of dqkv over the S_mb * S_seq rows): db_qkv[3 S_hidden] (device fp32) = (accumulate ? db_qkv : 0)
  * + those sums.  part: device fp32 scratch of bf_op_attention_bwd_part_elems(...) elements owned by the caller (0
- * elements: shape not served by the matrix-core kernels); with it the two backward kernels leave per query / key
+ * elements: not whole blocks of 128 rows of heads of 64 or 128); with it the two backward kernels leave per query / key
  * block partial sums of what they store (before rounding to bf16) and one small kernel adds them in a fixed order;
- * NULL, fp32, or a shape outside the matrix-core kernels: dqkv is read a second time (bf_op_colsum). */
+ * NULL, fp32, or another shape: dqkv is read a second time (bf_op_colsum). */
 bf_status bf_op_attention_bwd_bias(int dtype, int kernels, int S_mb, int S_seq, int N_heads, int S_head, int causal,
                                    const void* qkv, const void* ctx, const float* lse, const void* dctx,
                                    void* dqkv, float* delta, float* db_qkv, float* part, int accumulate, void* stream);
