@@ -41,7 +41,8 @@ typedef enum { BF_FP32 = 0, BF_BF16 = 1 } bf_dtype;
  * micro-batch and recomputes the layer's forward before its backward (App. A.2.2,
  * Eq. mem_ckpt).  BF_CKPT_NONE keeps every activation the backward needs. */
 typedef enum { BF_CKPT_NONE = 0, BF_CKPT_LAYER = 1 } bf_ckpt;
-/* Kernel family.  BF_KERNELS_AUTO picks the MFMA kernels wherever they serve the shape and type;
+/* Kernel family.  BF_KERNELS_AUTO picks the MFMA kernels wherever they serve the shape and type
+ * (in fp32 and for odd bf16 shapes: and are faster there; the results are the same bits either way);
  * BF_KERNELS_PLAIN forces the simple fp32-FMA kernels (any shape, slow). */
 typedef enum { BF_KERNELS_AUTO = 0, BF_KERNELS_PLAIN = 1 } bf_kernels;
 

@@ -1,7 +1,8 @@
 // Plain attention, forward and backward: one wavefront per query (or key) row, fp32
 // arithmetic, scores staged in LDS.  Any head size, S_seq up to 4096, both storage
-// types.  It is what BF_KERNELS_PLAIN asks for (the matrix-core kernels are checked against it) and
-// the fallback for shapes those do not take.  All reductions run in a fixed order.
+// types.  It is what BF_KERNELS_PLAIN asks for (the matrix-core kernels are checked against it), and
+// serves the shapes those do not take and, short rows and small heads, where it is the faster one
+// (attention_fwd_f32_better, attention_bwd_f32_better).  All reductions run in a fixed order.
 //
 // Layout: qkv [S_mb, S_seq, 3 S_hidden] packed [Q | K | V], head a at columns
 // a*S_head..; ctx [S_mb, S_seq, S_hidden]; lse [S_mb, N_heads, S_seq] = log sum exp of the
