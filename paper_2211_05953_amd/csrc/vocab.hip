@@ -71,6 +71,17 @@ __global__ __launch_bounds__(ROW_THREADS) void embedding_fwd_kernel(const int32_
   }
 }
 
+// How many of the workgroup's threads say yes, in one barrier; `slot` must not be written again before all have read it.
+__device__ __forceinline__ int count_threads(bool yes, int (&slot)[ROW_THREADS / 64]) {
+  const int n = __popcll(__ballot(yes));
+  if ((threadIdx.x & 63) == 0) slot[threadIdx.x >> 6] = n;
+  __syncthreads();
+  int sum = 0;
+#pragma unroll
+  for (int q = 0; q < ROW_THREADS / 64; ++q) sum += slot[q];
+  return sum;
+}
+
 // Token- and position-embedding gradients in one launch, without atomics.  Workgroups x < n_rows: the one of the first
 // position that uses a token sums the rows of every position using it, in ascending position, and adds the sum to that
 // token's gradient row; workgroups of later uses leave at once.  Distinct tokens, distinct rows.  The others: position
@@ -113,7 +124,7 @@ __global__ __launch_bounds__(ROW_THREADS) void embedding_bwd_kernel(const int32_
     return;
   }
   __shared__ int list[WIN];
-  __shared__ int wave_n[ROW_THREADS / 64];
+  __shared__ int wave_n[ROW_THREADS / 64], votes[3][ROW_THREADS / 64], hit_votes[2][ROW_THREADS / 64];
   const int t = blockIdx.x;
   const int v = tok[t];
   if (v < 0 || v >= S_voc) return;
@@ -124,7 +135,7 @@ __global__ __launch_bounds__(ROW_THREADS) void embedding_bwd_kernel(const int32_
   } else if (chunks > 1) {
     const int i = t + tid;  // (pairs of positions are counted: one barrier)
     const bool u0 = i < n_rows && tok[i] == v, u1 = i + ROW_THREADS < n_rows && tok[i + ROW_THREADS] == v;
-    if (__syncthreads_count(u0 || u1) >= FN) {
+    if (count_threads(u0 || u1, votes[0]) >= FN) {
       first_chunk = blockIdx.y;
       chunks = 1;
     } else if (blockIdx.y) {
@@ -136,7 +147,7 @@ __global__ __launch_bounds__(ROW_THREADS) void embedding_bwd_kernel(const int32_
   const int near = min(t, 4 * ROW_THREADS);
 #pragma unroll 4
   for (int i = tid; i < near; i += ROW_THREADS) earlier |= tok[i] == v;
-  if (__syncthreads_or(earlier)) return;
+  if (count_threads(earlier, votes[1])) return;
   if (t > near) {
     if (tok16) {
 #pragma unroll 4
@@ -150,12 +161,12 @@ __global__ __launch_bounds__(ROW_THREADS) void embedding_bwd_kernel(const int32_
 #pragma unroll 8
       for (int i = near + tid; i < t; i += ROW_THREADS) earlier |= tok[i] == v;
     }
-    if (__syncthreads_or(earlier)) return;
+    if (count_threads(earlier, votes[2])) return;
   }
   const int lane = tid & 63, w = tid >> 6;
   // The positions that use the token, a window at a time (one without it costs a barrier).  Windows share the list while it
   // has room; a chunk of columns is summed from it in one go, or, where the uses did not fit, list after list.
-  int w0 = 0, n = 0;  // the next window, entries of the list
+  int w0 = 0, n = 0, turn = 0;  // the next window, entries of the list, which votes
   bool whole = true;  // the list has held all uses since the first window
   auto fill = [&] {   // false: no more windows, or no room for this one's uses
     if (w0 >= n_rows) return false;
@@ -173,7 +184,8 @@ __global__ __launch_bounds__(ROW_THREADS) void embedding_bwd_kernel(const int32_
       for (int e = 0; e < PER; ++e)
         if (i0 + e < n_rows && tok[i0 + e] == v) hits |= 1u << e;
     }
-    if (!__syncthreads_or(hits)) {  // (also: wave_n has been read)
+    turn ^= 1;
+    if (!count_threads(hits != 0, hit_votes[turn])) {  // (also: wave_n and the votes before have been read)
       w0 += WIN;
       return true;
     }
