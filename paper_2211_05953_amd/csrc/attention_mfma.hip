@@ -138,7 +138,7 @@ __device__ __forceinline__ void pack8_parts(const f32x16& a, int kk, bf16x8& hi,
 // infinite key would.  These lengths used to run on fp32 kernels, so probabilities and their gradients keep their 24 bits:
 // they enter the products as three bf16 operands.  (Two, 16 bits, are 4 % faster at S_head 128 and 10-20 % at 64, but nearly
 // uniform rows over values that cancel were 10 to 30 % further from the exact results than those kernels'.)
-// 2 x 1000 tokens, 16 heads of 128, causal, forward / backward: 422 / 911 us on fp32 matrix instructions, 44 / 158 here (bound
+// 2 x 1000 tokens, 16 heads of 128, causal, forward / backward: 422 / 911 us on fp32 matrix instructions, 44 / 149 here (bound
 // by the chain score -> exponential -> three-part product of one or two waves per SIMD; the longest key block sets the
 // end); 4 x 1000, 16 heads of 64, bidirectional: 52 / 218.
 // A zero times an infinity is a NaN in a matrix instruction, but a masked pair must not touch its row, and neither must the
@@ -1326,7 +1326,10 @@ bf_status bwd_edge(int S_mb, int S_seq, int N_heads, int causal, const void* qkv
                    const void* dctx, void* dqkv, float* delta, hipStream_t st) {
   const float scale = 1.0f / sqrtf((float)D);
   const unsigned grid = (unsigned)((S_seq + 127) / 128) * N_heads * S_mb;
-  if (S_seq > 128 && 2 * (long)grid <= (causal && D == 64 ? 512 : 256))
+  // Two key groups up to 256 causal blocks of 128 rows; up to 128 bidirectional ones, and causal ones of short rows at S_head
+  // 128.  One group / two, backward, us: S_head 128, causal, 256 blocks, 1000 tokens 156.8 / 147.7, 900 145.2 / 138.0, 400
+  // 3 % more with two, 200 11 %; 300 to 512 blocks 4 to 10 %; bidirectional, 129 to 256 blocks 7 to 20 %.
+  if (S_seq > 128 && 2 * (long)grid <= (causal && (D == 64 || S_seq >= 900) ? 512 : 256))
     attn_bwd_dq_general_kernel<D, 64, true, 2><<<(unsigned)((S_seq + 63) / 64) * N_heads * S_mb, 256, 0, st>>>((const bf16_t*)qkv, (const bf16_t*)ctx, (const bf16_t*)dctx, lse, delta, (bf16_t*)dqkv, S_seq, N_heads, S_mb, causal, scale, nullptr);
   else
     attn_bwd_dq_general_kernel<D, 128, true, 1><<<grid, NTHR, 0, st>>>((const bf16_t*)qkv, (const bf16_t*)ctx, (const bf16_t*)dctx, lse, delta, (bf16_t*)dqkv, S_seq, N_heads, S_mb, causal, scale, nullptr);
