@@ -73,12 +73,19 @@ typedef struct {
   int32_t causal;                                  /* 1: mask j > i (GPT); 0: bidirectional */
   int32_t kernels;                                 /* bf_kernels */
   int32_t queue_depth;  /* > 0: the host never runs more than this many stage-level ops ahead of
-                           the device (App. D.2, bounded kernel queue); 0: unbounded */
+                           the device (App. D.2, bounded kernel queue; ops that share launches count as one);
+                           0: unbounded */
   int32_t fuse_wgrad;   /* 1: in breadth-first order the weight-matrix gradients of a stage are taken once per
                            stage, as one product over all its micro-batches, after the stage's last backward
                            (breadth-first groups the work by stage, Sec. 4.2): the fp32 main-grad is written once
                            instead of read-modified-written N_mb times.  The sum over micro-batches is then
                            one long fp32 contraction, so BF and DF gradients agree to rounding, not bitwise.
+                           With stored activations (BF_CKPT_NONE) the micro-batches of a stage also share launches, as
+                           many of them as it takes for the layer's narrowest product to fill the chip (2^24 outputs:
+                           8192 rows at S_hidden 2048, one 2048-row micro-batch at 8192); their rows are then those of
+                           one larger micro-batch, so that bias and LayerNorm gradients are the same sums in another
+                           order, and outputs agree with DF's to the rounding of the outputs where the larger product
+                           or attention launch is not split as the smaller one is (else bitwise).
                            The per-micro-batch operands of one stage are kept until then (with
                            BF_CKPT_LAYER: the recomputed ones).  0: accumulate per micro-batch. */
   int32_t N_loop_min;   /* smallest N_loop bf_run_step will be called with (0 or 1: any).  Sizes the per-stage
@@ -112,7 +119,9 @@ typedef struct {
                            gradient arena of the layers' size (with BF_CKPT_LAYER also by a second recomputation
                            record).  Needs fuse_wgrad = 1, dp_fs = 0, queue_depth = 0, S_voc = 0, and y and
                            dx given to bf_run_step / bf_run_rank_step; depth-first steps and steps of
-                           one micro-batch run as with 1.  A two-chain step splits no contraction and, with whole blocks
+                           one micro-batch run as with 1.  A two-chain step runs every micro-batch in launches of its
+                           own (a one-chain step shares them, see fuse_wgrad, and is the faster of the two where
+                           activations are stored: 2048-wide, 32 ms).  It splits no contraction and, with whole blocks
                            of 128 rows and more than 128 of them, no row's keys (the one-chain step does where a product or an
                            attention launch leaves the chip idle; results then differ by the rounding of the outputs,
                            otherwise outputs and weight-matrix gradients are the same bits).  Bias and LayerNorm
@@ -151,7 +160,8 @@ typedef struct {
   int32_t n_events;
   int32_t timed;            /* 1 if gpu_ms / adam_ms are valid (bf_run_step ... timing != 0) */
   /* timing == 2 (every class) or 3 (the weight-gradient products): per kernel class, summed over
-   * the step's launches: device time between events recorded around each launch on its stream, launch count, algorithmic flops
+   * the step's launches: device time between events recorded around each launch on its stream, launch count (a launch that
+   * serves several micro-batches counts as that many), algorithmic flops
    * (2 M N K per product; attention with the causal half; backward attention 2.5 x forward) and
    * algorithmic HBM bytes (every operand read once, every result written once).  With two chains of
    * micro-batches (mb_chains = 2) launches of the two streams overlap, so the classes' times add up to

@@ -119,8 +119,10 @@ struct WsLayout {
   size_t off_lm, logits_bytes;  // S_voc > 0: buffers of the input / output layers
   size_t rec_bytes;        // one full record (without y)
   size_t y_bytes;          // one [T, h] tensor
-  size_t off_records;      // NONE: L * N_mb_max full records (each with y); LAYER: 1 scratch record
+  size_t off_records;      // NONE: L blocks of N_mb_max full records (each with y); LAYER: 1 scratch record
+  size_t layer_rec_bytes;  // NONE: one layer's block: every tensor of the record for all micro-batches in a row
   size_t n_full_records;
+  int group;               // micro-batches of a stage a launch of a breadth-first step serves at most
   size_t off_ckpt;         // LAYER: L * N_mb_max [T, h] tensors (outputs of each layer)
   size_t off_tmp;          // backward temporaries
   size_t off_tmp2;         // mb_chains = 2: the second chain's backward temporaries
@@ -131,19 +133,41 @@ struct WsLayout {
   size_t wrec_bytes;
   size_t off_step;         // optimizer step count (one int)
   size_t off_bhand;        // 2 x N_mb_max [T, h] (two sets, alternating by stage)
-  size_t off_scratch_out;  // [T, h] x 2: discarded outputs / ping-pong
+  size_t off_scratch_out;  // [T, h] x 2 for a group of micro-batches: discarded outputs / ping-pong
   size_t total;
 };
 
+// How many micro-batches of a stage one launch of a breadth-first step serves.  They are all there when the stage starts
+// and do not depend on each other (Sec. 4.1), their rows follow each other in memory, and every kernel of a layer treats its
+// rows (or its sequences) alike, so g of them are simply g times the rows.  As many as it takes for the layer's narrowest
+// product, T x h, to be one whole round of 256 x 256 tiles over the 256 compute units, 2^24 output elements: below that
+// the launches leave compute units idle or do not outlast their own latency, above it nothing is gained (an 8192-wide
+// stack on 2048-row micro-batches keeps one at a time) and the activations between two kernels leave the memory-side cache.
+// Needs the stage-wide weight gradients (which keep every micro-batch's gradients, and with which breadth-first and
+// depth-first results agree to rounding only), stored activations and rows without padding between the micro-batches.
+constexpr long GROUP_OUTPUTS = 1l << 24;
+constexpr long GROUP_ROWS = 1l << 15;        // and no more rows than this, whatever the width,
+constexpr long GROUP_BYTES = 1l << 30;       // nor a larger activation tensor
+
+int mb_group(const bf_config& c) {
+  const long es = c.dtype == BF_BF16 ? 2 : 4, T = (long)c.S_mb_max * c.S_seq, h = c.S_hidden, f = c.S_mlp;
+  if (c.fuse_wgrad != 1 || c.ckpt_mode != BF_CKPT_NONE || c.kernels != BF_KERNELS_AUTO || c.mb_chains == 2) return 1;
+  if ((T * h * es) % (long)ALIGN || (T * f * es) % (long)ALIGN) return 1;
+  const long rows = std::min((GROUP_OUTPUTS + h - 1) / h, std::min(GROUP_ROWS, GROUP_BYTES / (es * std::max(3 * h, f))));
+  return (int)std::max(1l, std::min((rows + T - 1) / T, std::min((long)c.N_mb_max, GROUP_ROWS / T)));
+}
+
 struct RecSizes { size_t a, qkv, ctx, x1, c, u, g, ln1, ln2, lse, total; };
 
+// bytes from one micro-batch's tensor to the next one's
 RecSizes rec_sizes(const bf_config& c) {
   const size_t es = c.dtype == BF_BF16 ? 2 : 4;
   const size_t T = (size_t)c.S_mb_max * c.S_seq, h = c.S_hidden, f = c.S_mlp;
+  const size_t al = mb_group(c) > 1 ? 4 : ALIGN;  // grouped micro-batches' statistics follow each other without a gap
   RecSizes r;
   r.a = up(T * h * es); r.qkv = up(T * 3 * h * es); r.ctx = up(T * h * es); r.x1 = up(T * h * es);
   r.c = up(T * h * es); r.u = up(T * f * es); r.g = up(T * f * es);
-  r.ln1 = up(T * 2 * 4); r.ln2 = up(T * 2 * 4); r.lse = up((size_t)c.S_mb_max * c.N_heads * c.S_seq * 4);
+  r.ln1 = up(T * 2 * 4, al); r.ln2 = up(T * 2 * 4, al); r.lse = up((size_t)c.S_mb_max * c.N_heads * c.S_seq * 4, al);
   r.total = r.a + r.qkv + r.ctx + r.x1 + r.c + r.u + r.g + r.ln1 + r.ln2 + r.lse;
   return r;
 }
@@ -168,24 +192,28 @@ TmpSizes tmp_sizes(const bf_config& c) {
 TmpSizes tmp_sizes_of(const bf_config& c) {
   const size_t es = c.dtype == BF_BF16 ? 2 : 4;
   const size_t T = (size_t)c.S_mb_max * c.S_seq, h = c.S_hidden, f = c.S_mlp;
+  const size_t ng = mb_group(c), Tg = ng * T;  // rows of a group of micro-batches
   TmpSizes t;
-  t.du = up(T * f * es); t.dc = up(T * h * es); t.dx1 = up(T * h * es); t.dctx = up(T * h * es);
-  t.dqkv = up(T * 3 * h * es); t.delta = up((size_t)c.S_mb_max * c.N_heads * c.S_seq * 4); t.ping = up(T * h * es);
+  t.du = up(T * f * es); t.dc = up(Tg * h * es); t.dx1 = up(T * h * es); t.dctx = up(Tg * h * es);
+  t.dqkv = up(T * 3 * h * es); t.delta = up(ng * c.S_mb_max * c.N_heads * c.S_seq * 4); t.ping = up(T * h * es);
   // partial column sums that a product's epilogue leaves per row of (at least 128-row) tiles: [T / 128][f] fp32
-  t.colpart = up(((T + 127) / 128) * f * 4);
-  // partial column sums of the one-pass LayerNorm backward: one row of [3][h] per workgroup
-  t.lnpart = up(layernorm_bwd_part_elems((int)T, (int)h) * 4);
+  t.colpart = up(((Tg + 127) / 128) * f * 4);
+  // Partial column sums of the one-pass LayerNorm backward: one row of [3][h] per workgroup, at most 256, but fewer rows
+  // of input can take more of them (300 rows 150, 200 rows 200), and a step may have smaller micro-batches than these
+  t.lnpart = up(layernorm_bwd_part_elems((int)std::min(Tg, (size_t)256), (int)h) * 4);
   // partial column sums of dqkv that the attention backward kernels leave per query / key block
-  t.attnpart = up(attention_bwd_part_elems(c.S_mb_max, c.S_seq, c.N_heads, c.S_head) * 4);
+  t.attnpart = up(attention_bwd_part_elems((int)ng * c.S_mb_max, c.S_seq, c.N_heads, c.S_head) * 4);
   // fp32 planes of the products whose contraction is split (few tiles, long K): the largest such product of a layer
   size_t planes = 0;
   if (c.dtype == BF_BF16 && c.kernels == BF_KERNELS_AUTO) {
-    const int Ti = (int)T, hi = (int)h, fi = (int)f;
-    const int cand[6][5] = {{L_NN, E_BIAS, Ti, 3 * hi, hi},     {L_NN, E_BIAS_RES, Ti, hi, hi}, {L_NN, E_BIAS_RES, Ti, hi, fi},
-                            {L_NT, E_NONE, Ti, hi, 3 * hi},     {L_NT, E_NONE, Ti, hi, hi},     {L_NT, E_NONE, Ti, hi, fi}};
-    for (const auto& k : cand) {
-      const int sl = gemm_splitk_slices(k[0], k[1], k[2], k[3], k[4]);
-      if (sl > 1) planes = std::max(planes, (size_t)sl * k[2] * k[3]);
+    for (size_t k = 1; k <= ng; ++k) {
+      const int Ti = (int)(k * T), hi = (int)h, fi = (int)f;
+      const int cand[6][5] = {{L_NN, E_BIAS, Ti, 3 * hi, hi},     {L_NN, E_BIAS_RES, Ti, hi, hi}, {L_NN, E_BIAS_RES, Ti, hi, fi},
+                              {L_NT, E_NONE, Ti, hi, 3 * hi},     {L_NT, E_NONE, Ti, hi, hi},     {L_NT, E_NONE, Ti, hi, fi}};
+      for (const auto& p : cand) {
+        const int sl = gemm_splitk_slices(p[0], p[1], p[2], p[3], p[4]);
+        if (sl > 1) planes = std::max(planes, (size_t)sl * p[2] * p[3]);
+      }
     }
   }
   t.splitk = up(planes * 4);
@@ -226,10 +254,15 @@ void fill_layout(const bf_config& c, const Dims& D, WsLayout* Lo) {
   Lo->rec_bytes = rec_sizes(c).total;
   Lo->y_bytes = up(T * c.S_hidden * es);
   Lo->off_records = off;
+  Lo->group = mb_group(c);
+  Lo->layer_rec_bytes = 0;
   const size_t slots = (size_t)c.N_layers * c.N_mb_max;
   if (c.ckpt_mode == BF_CKPT_NONE) {
     Lo->n_full_records = slots;
-    off += slots * (Lo->rec_bytes + Lo->y_bytes);
+    const RecSizes r = rec_sizes(c);
+    const size_t n = c.N_mb_max;
+    Lo->layer_rec_bytes = n * (r.a + r.qkv + r.ctx + r.x1 + r.c + r.u + r.g + Lo->y_bytes) + up(n * r.ln1) + up(n * r.ln2) + up(n * r.lse);
+    off += c.N_layers * Lo->layer_rec_bytes;
     Lo->off_ckpt = off;
   } else {
     Lo->n_full_records = c.mb_chains == 2 ? 2 : 1;  // one scratch record per chain of micro-batches
@@ -255,12 +288,12 @@ void fill_layout(const bf_config& c, const Dims& D, WsLayout* Lo) {
     if (fuse_wgrad_possible(c) && c.ckpt_mode == BF_CKPT_LAYER) off += stage_slots * Lo->wrec_bytes;
   }
   Lo->off_bhand = off; off += 2 * (size_t)c.N_mb_max * Lo->y_bytes;
-  Lo->off_scratch_out = off; off += 2 * Lo->y_bytes;
-  // input / output layers: embedded inputs and loss gradients per micro-batch, the last layer's output,
-  // its normalised form and the gradient of that, LayerNorm statistics, logits of one micro-batch, row losses
+  Lo->off_scratch_out = off; off += 2 * Lo->group * Lo->y_bytes;
+  // input / output layers: embedded inputs and loss gradients per micro-batch, the last layer's output (of a group of
+  // micro-batches), its normalised form and the gradient of that, LayerNorm statistics, logits of one micro-batch, row losses
   Lo->off_lm = off;
   Lo->logits_bytes = up(T * (size_t)(c.S_voc > 0 ? c.S_voc : 0) * es);
-  if (c.S_voc > 0) off += (2 * (size_t)c.N_mb_max + 3) * Lo->y_bytes + up(T * 8) + Lo->logits_bytes + up(T * 4);
+  if (c.S_voc > 0) off += (2 * (size_t)c.N_mb_max + Lo->group + 2) * Lo->y_bytes + up(T * 8) + Lo->logits_bytes + up(T * 4);
   Lo->off_step = off; off += ALIGN;
   Lo->total = off;
 }
@@ -294,7 +327,7 @@ struct bf_stack {
   bool prof_on;
   unsigned prof_mask;
   std::vector<hipEvent_t> prof_ev;
-  struct ProfRec { int cls; double flops, bytes; };
+  struct ProfRec { int cls; double flops, bytes; int n; };
   std::vector<ProfRec> prof_rec;
   int step;               // optimizer step counter (host mirror; the kernels read d_step)
   int* d_step;            // the same count on the device, bumped by a one-thread kernel at the start of an
@@ -306,6 +339,7 @@ struct bf_stack {
   // directions of the meeting at a stage's end and the join at the step's end
   int chain;
   int chains_active;  // chains of the step being issued (1 outside a two-chain step)
+  int group_now;      // micro-batches the launches being issued serve (1 but for the layers of a grouped step)
   float* g32b;
   hipStream_t chain_st;
   hipEvent_t ev_chain[4];
@@ -353,10 +387,15 @@ Record record_at(bf_stack* s, char* base) {
 // being issued) with.
 Record record_for(bf_stack* s, int layer, int mb) {
   if (s->cfg.ckpt_mode == BF_CKPT_NONE) {
-    const size_t slot = (size_t)layer * s->cfg.N_mb_max + mb;
-    char* base = s->ws + s->Lo.off_records + slot * (s->Lo.rec_bytes + s->Lo.y_bytes);
-    Record R = record_at(s, base);
-    R.y = base + s->Lo.rec_bytes;
+    // tensor by tensor, each for all micro-batches in a row
+    const RecSizes r = rec_sizes(s->cfg);
+    const size_t n = s->cfg.N_mb_max;
+    char* p = s->ws + s->Lo.off_records + (size_t)layer * s->Lo.layer_rec_bytes;
+    auto take = [&](size_t bytes) { char* q = p + mb * bytes; p += up(n * bytes); return q; };
+    Record R;
+    R.a = take(r.a); R.qkv = take(r.qkv); R.ctx = take(r.ctx); R.x1 = take(r.x1); R.c = take(r.c); R.u = take(r.u); R.g = take(r.g);
+    R.y = take(s->Lo.y_bytes);
+    R.ln1 = (float*)take(r.ln1); R.ln2 = (float*)take(r.ln2); R.lse = (float*)take(r.lse);
     return R;
   }
   Record R = record_at(s, s->ws + s->Lo.off_records + (s->chain ? s->Lo.rec_bytes : 0));
@@ -366,15 +405,18 @@ Record record_for(bf_stack* s, int layer, int mb) {
 
 struct Tmp { char *du, *dc, *dx1, *dctx, *dqkv, *ping[2]; float *delta, *colpart, *lnpart, *attnpart, *splitk; size_t splitk_elems; };
 
-// Per (layer, micro-batch) gradients kept for the fused weight gradient of a stage.
+// Per (layer, micro-batch) gradients kept for the fused weight gradient of a stage: tensor by tensor, each for all
+// micro-batches in a row.
 struct GradRec { char *dy, *du, *dx1, *dqkv; };
 
 // ls: index of the layer inside its stage
 GradRec grad_rec(bf_stack* s, int ls, int mb) {
   TmpSizes t = tmp_sizes(s->cfg);
-  char* p = s->ws + s->Lo.off_grec + ((size_t)ls * s->cfg.N_mb_max + mb) * s->Lo.grec_bytes;
+  const size_t n = s->cfg.N_mb_max;
+  char* p = s->ws + s->Lo.off_grec + (size_t)ls * n * s->Lo.grec_bytes;
+  auto take = [&](size_t bytes) { char* q = p + mb * bytes; p += n * bytes; return q; };
   GradRec g;
-  g.dy = p; p += t.ping; g.du = p; p += t.du; g.dx1 = p; p += t.dx1; g.dqkv = p;
+  g.dy = take(t.ping); g.du = take(t.du); g.dx1 = take(t.dx1); g.dqkv = take(t.dqkv);
   return g;
 }
 
@@ -413,7 +455,7 @@ bf_status timed(bf_stack* s, int cls, double flops, double bytes, hipStream_t st
   bf_status r = call();
   if (r != BF_OK) return r;
   BF_HIP_CHECK(hipEventRecord(s->prof_ev[2 * i + 1], st));
-  s->prof_rec.push_back({cls, flops, bytes});
+  s->prof_rec.push_back({cls, flops, bytes, s->group_now});
   return BF_OK;
 }
 
@@ -575,25 +617,26 @@ bf_status layer_wgrad_fused(bf_stack* s, int layer, int ls, int S_mb, int N_mb, 
   const int T = S_mb * c.S_seq, h = c.S_hidden, f = c.S_mlp;
   const size_t esz = c.dtype == BF_BF16 ? 2 : 4;
   Record R0 = record_for(s, layer, 0);
-  size_t rec_stride = (s->Lo.rec_bytes + s->Lo.y_bytes) / esz;
+  RecSizes r = rec_sizes(c);
   if (c.ckpt_mode == BF_CKPT_LAYER) {
     redirect_wgrad_operands(s, ls, 0, &R0);
-    rec_stride = s->Lo.wrec_bytes / esz;
+    r.a = r.ctx = r.c = r.g = s->Lo.wrec_bytes;
   }
   const GradRec K0 = grad_rec(s, ls, 0);
-  const size_t grec_stride = s->Lo.grec_bytes / esz;
+  const TmpSizes t = tmp_sizes(c);
   auto G = [&](int tid) { return param_ptr(s, s->g32, layer, tid); };
-  auto run = [&](int M, int N, const void* A, const void* B, size_t sb, float* out) {
+  // sa, sb: bytes from one micro-batch's operand to the next one's
+  auto run = [&](int M, int N, const void* A, size_t sa, const void* B, size_t sb, float* out) {
     GemmArgs g{M, N, T, A, B, out, nullptr, nullptr, nullptr, 0};
     g.n_seg = N_mb;
-    g.seg_stride_a = rec_stride;
-    g.seg_stride_b = sb;
+    g.seg_stride_a = sa / esz;
+    g.seg_stride_b = sb / esz;
     return p_gemm(s, L_TN, E_ACCUM, g, st);
   };
-  BF_TRY(run(f, h, R0.g, dy0, dy_stride, G(BF_W_FC2)));
-  BF_TRY(run(h, f, R0.c, K0.du, grec_stride, G(BF_W_FC1)));
-  BF_TRY(run(h, h, R0.ctx, K0.dx1, grec_stride, G(BF_W_O)));
-  BF_TRY(run(h, 3 * h, R0.a, K0.dqkv, grec_stride, G(BF_W_QKV)));
+  BF_TRY(run(f, h, R0.g, r.g, dy0, dy_stride * esz, G(BF_W_FC2)));
+  BF_TRY(run(h, f, R0.c, r.c, K0.du, t.du, G(BF_W_FC1)));
+  BF_TRY(run(h, h, R0.ctx, r.ctx, K0.dx1, t.dx1, G(BF_W_O)));
+  BF_TRY(run(h, 3 * h, R0.a, r.a, K0.dqkv, t.dqkv, G(BF_W_QKV)));
   return BF_OK;
 }
 
@@ -662,6 +705,7 @@ bf_status bf_create_stack(const bf_config* cfg, void* workspace, size_t bytes, v
   s->ev_grad_ready = s->ev_side_done = s->ev_t0 = s->ev_t1 = nullptr;
   s->chain = 0;
   s->chains_active = 1;
+  s->group_now = 1;
   s->g32b = cfg->mb_chains == 2 ? (float*)(s->ws + s->Lo.off_g32b) : nullptr;
   s->chain_st = nullptr;
   for (auto& e : s->ev_chain) e = nullptr;
@@ -873,13 +917,13 @@ static bf_status run_rank_step(bf_stack* s, int schedule, int N_PP, int rank, bo
   // gradients a stage received stay intact until its fused weight-gradient products have run
   auto bhand = [&](int stage, int m) { return s->ws + s->Lo.off_bhand + ((size_t)(stage & 1) * c.N_mb_max + m) * s->Lo.y_bytes; };
   char* scratch_out = s->ws + s->Lo.off_scratch_out;
-  // input / output layers: embedded input and loss gradient of every micro-batch, then one micro-batch's
-  // last-layer output, its normalised form, the gradient of that, LayerNorm statistics, logits, row losses
+  // input / output layers: embedded input and loss gradient of every micro-batch, then the last-layer output of a group
+  // of micro-batches, one micro-batch's normalised form of it, the gradient of that, LayerNorm statistics, logits, row losses
   char* lm_base = s->ws + s->Lo.off_lm;
   auto emb_x = [&](int m) { return lm_base + (size_t)m * s->Lo.y_bytes; };
   auto dy_lm = [&](int m) { return lm_base + ((size_t)c.N_mb_max + m) * s->Lo.y_bytes; };
   char* y_top = lm_base + 2 * (size_t)c.N_mb_max * s->Lo.y_bytes;
-  char* hn = y_top + s->Lo.y_bytes;
+  char* hn = y_top + s->Lo.group * s->Lo.y_bytes;
   char* dhn = hn + s->Lo.y_bytes;
   float* lnf_stats = (float*)(dhn + s->Lo.y_bytes);
   char* logits = (char*)lnf_stats + up((size_t)c.S_mb_max * c.S_seq * 8);
@@ -901,6 +945,10 @@ static bf_status run_rank_step(bf_stack* s, int schedule, int N_PP, int rank, bo
   const int chains = c.mb_chains == 2 && fuse && !lm && N_mb >= 2 && y && dx ? 2 : 1;
   auto stream_of = [&](int m) { return chains == 2 && (m & 1) ? s->chain_st : st; };
   s->chains_active = chains;
+  // micro-batches of a stage that one launch serves (mb_group); the rows follow each other in the workspace when the
+  // micro-batches are as large as it was laid out for
+  const int group = fuse && chains == 1 && S_mb == c.S_mb_max ? std::min(s->Lo.group, N_mb) : 1;
+  const int even = (N_mb + (N_mb + group - 1) / group - 1) / ((N_mb + group - 1) / group);  // groups of about equal size
   if (c.dp_fs && per_stage > lps_max(c)) {
     set_error("bf_run_step: dp_fs holds stages of up to %d layers (N_loop_min = %d), N_loop = %d gives %d", lps_max(c),
               c.N_loop_min, N_loop, per_stage);
@@ -984,9 +1032,14 @@ static bf_status run_rank_step(bf_stack* s, int schedule, int N_PP, int rank, bo
     return record_for(s, layer - 1, m).y;
   };
 
-  for (size_t oi = 0; oi < ops.size(); ++oi) {
+  for (size_t oi = 0; oi < ops.size();) {
     const SchedOp& op = ops[oi];
     const int ls = local(op), l0 = ls * per_stage, l1 = l0 + per_stage, m = op.mb;
+    // this op and those behind it that do the same for the next micro-batches, up to a group of them
+    int ng = 1;
+    while (ng < even && oi + ng < ops.size() && ops[oi + ng].op == op.op && ops[oi + ng].stage == op.stage && ops[oi + ng].mb == m + ng) ++ng;
+    const int m_end = m + ng;
+    s->group_now = 1;
     // the stream this op is issued on, and with it the set of temporaries and the arena of the small gradients
     hipStream_t os = stream_of(m);
     s->chain = chains == 2 ? m & 1 : 0;
@@ -1001,41 +1054,44 @@ static bf_status run_rank_step(bf_stack* s, int schedule, int N_PP, int rank, bo
       if (j + 1 < (int)ivs.size() && ivs[j + 1].load) BF_TRY(reconstruct(j + 1));
     }
     if (op.op == 0) {
-      if (lm && l0 == 0) {
-        if (m == 0)  // the token rows' gradients are added to, use by use: start from zero
+      for (int k = m; lm && l0 == 0 && k < m_end; ++k) {
+        if (k == 0)  // the token rows' gradients are added to, use by use: start from zero
           BF_TRY(fill_f32(s->D.voc_elems[0], param_ptr(s, s->g32, 0, BF_E_TOK), 0.f, os));
         BF_TRY(timed(s, BF_K_VOCAB, 0.0, (double)T_mb * c.S_hidden * (8.0 + es), os, [&] {
-          return embedding_fwd(c.dtype, T_mb, c.S_seq, c.S_voc, c.S_hidden, lm->tokens + (size_t)m * T_mb,
-                               param_ptr(s, s->w32, 0, BF_E_TOK), param_ptr(s, s->w32, 0, BF_E_POS), emb_x(m), os);
+          return embedding_fwd(c.dtype, T_mb, c.S_seq, c.S_voc, c.S_hidden, lm->tokens + (size_t)k * T_mb,
+                               param_ptr(s, s->w32, 0, BF_E_TOK), param_ptr(s, s->w32, 0, BF_E_POS), emb_x(k), os);
         }));
       }
+      s->group_now = ng;
       for (int l = l0; l < l1; ++l) {
         Record R = record_for(s, l, m);
         void* out = R.y;
         if (is_top(l)) out = lm ? y_top : y ? (char*)y + io_off(ls, m) : scratch_out;
-        BF_TRY(layer_forward(s, l, S_mb, input_of(l, m), R, out, false, os));
-        ++live;
+        BF_TRY(layer_forward(s, l, ng * S_mb, input_of(l, m), R, out, false, os));
       }
-      if (lm && l1 == c.N_layers) {
+      s->group_now = 1;
+      for (int k = m; lm && l1 == c.N_layers && k < m_end; ++k) {
         // output layer, loss and their backward at once: nothing downstream has to be waited for
         const int h = c.S_hidden, V = c.S_voc;
+        char* y_mb = y_top + (size_t)(k - m) * s->Lo.y_bytes;
         float* gw = param_ptr(s, s->g32, 0, BF_W_OUT);
-        BF_TRY(p_ln_fwd(s, T_mb, h, y_top, param_ptr(s, s->w32, 0, BF_LNF_G), param_ptr(s, s->w32, 0, BF_LNF_B), c.ln_eps, hn,
+        BF_TRY(p_ln_fwd(s, T_mb, h, y_mb, param_ptr(s, s->w32, 0, BF_LNF_G), param_ptr(s, s->w32, 0, BF_LNF_B), c.ln_eps, hn,
                         lnf_stats, os));
         GemmArgs g{T_mb, V, h, hn, weight_ptr(s, 0, BF_W_OUT), logits, nullptr, nullptr, nullptr, 0};
         BF_TRY(p_gemm(s, L_NT, E_NONE, g, os));
         const float scale = 1.0f / ((float)N_mb * (float)T_mb);
         BF_TRY(timed(s, BF_K_VOCAB, 0.0, 3.0 * es * T_mb * V, os, [&] {
-          return ce_loss(c.dtype, T_mb, V, logits, lm->labels + (size_t)m * T_mb, scale, row_loss, lm->loss + m, os);
+          return ce_loss(c.dtype, T_mb, V, logits, lm->labels + (size_t)k * T_mb, scale, row_loss, lm->loss + k, os);
         }));
         g = GemmArgs{T_mb, h, V, logits, weight_ptr(s, 0, BF_W_OUT), dhn, nullptr, nullptr, nullptr, 0};
         BF_TRY(p_gemm(s, L_NN, E_NONE, g, os));
-        g = GemmArgs{V, h, T_mb, logits, hn, gw, nullptr, nullptr, nullptr, m > 0};
+        g = GemmArgs{V, h, T_mb, logits, hn, gw, nullptr, nullptr, nullptr, k > 0};
         BF_TRY(p_gemm(s, L_TN, E_ACCUM, g, os));
-        BF_TRY(p_ln_bwd(s, T_mb, h, dhn, y_top, param_ptr(s, s->w32, 0, BF_LNF_G), lnf_stats, nullptr, dy_lm(m),
-                        param_ptr(s, s->g32, 0, BF_LNF_G), param_ptr(s, s->g32, 0, BF_LNF_B), nullptr, m > 0, os));
+        BF_TRY(p_ln_bwd(s, T_mb, h, dhn, y_mb, param_ptr(s, s->w32, 0, BF_LNF_G), lnf_stats, nullptr, dy_lm(k),
+                        param_ptr(s, s->g32, 0, BF_LNF_G), param_ptr(s, s->g32, 0, BF_LNF_B), nullptr, k > 0, os));
       }
     } else {
+      s->group_now = ng;
       for (int l = l1 - 1; l >= l0; --l) {
         Record R = record_for(s, l, m);
         const void* xin = input_of(l, m);
@@ -1050,7 +1106,7 @@ static bf_status run_rank_step(bf_stack* s, int schedule, int N_PP, int rank, bo
         else if (l == l1 - 1) din = bhand(ls, m);
         else din = fuse ? grad_rec(s, l - l0, m).dy : tmp.ping[(l + 1) & 1];
         void* dout;
-        if (is_bottom(l)) dout = dx ? (char*)dx + io_off(ls, m) : scratch_out + s->Lo.y_bytes;
+        if (is_bottom(l)) dout = dx ? (char*)dx + io_off(ls, m) : scratch_out + s->Lo.group * s->Lo.y_bytes;
         else if (l == l0) dout = bhand(ls - 1, m);
         else dout = fuse ? grad_rec(s, l - 1 - l0, m).dy : tmp.ping[l & 1];
         GradRec keep{};
@@ -1059,17 +1115,17 @@ static bf_status run_rank_step(bf_stack* s, int schedule, int N_PP, int rank, bo
         // the chain, or of a stage when the stages do not feed each other) has had its FC2 bias gradient taken there.
         const bool fed_from_above = !is_top(l);
         float* below = is_bottom(l) ? nullptr : param_ptr(s, s->chain ? s->g32b : s->g32, l - 1, BF_B_FC2);
-        BF_TRY(layer_backward(s, l, S_mb, xin, R, din, dout, first, fuse ? &keep : nullptr, fed_from_above, below, os));
-        --live;
+        BF_TRY(layer_backward(s, l, ng * S_mb, xin, R, din, dout, first, fuse ? &keep : nullptr, fed_from_above, below, os));
       }
-      if (lm && l0 == 0) {
-        char* dxe = scratch_out + s->Lo.y_bytes;  // where layer 0 left the gradient of its input
+      s->group_now = 1;
+      for (int k = m; lm && l0 == 0 && k < m_end; ++k) {
+        char* dxe = scratch_out + ((size_t)s->Lo.group + (k - m)) * s->Lo.y_bytes;  // where layer 0 left the gradient of its input
         BF_TRY(timed(s, BF_K_VOCAB, 0.0, (double)T_mb * c.S_hidden * (es + 16.0), os, [&] {
-          return embedding_bwd(c.dtype, S_mb, c.S_seq, c.S_voc, c.S_hidden, lm->tokens + (size_t)m * T_mb, dxe,
-                               param_ptr(s, s->g32, 0, BF_E_TOK), param_ptr(s, s->g32, 0, BF_E_POS), m > 0, os);
+          return embedding_bwd(c.dtype, S_mb, c.S_seq, c.S_voc, c.S_hidden, lm->tokens + (size_t)k * T_mb, dxe,
+                               param_ptr(s, s->g32, 0, BF_E_TOK), param_ptr(s, s->g32, 0, BF_E_POS), k > 0, os);
         }));
       }
-      if (fuse && m == N_mb - 1) {
+      if (fuse && m_end == N_mb) {
         if (chains == 2) {
           // the stage's last micro-batch: wait for the other chain's, which the products below read
           BF_HIP_CHECK(hipEventRecord(s->ev_chain[1], stream_of(m + 1)));
@@ -1081,7 +1137,7 @@ static bf_status run_rank_step(bf_stack* s, int schedule, int N_PP, int rank, bo
           size_t stride;
           if (is_top(l)) { dy0 = (const char*)dy + io_off(ls, 0); stride = io_stride / es; }
           else if (l == l1 - 1) { dy0 = bhand(ls, 0); stride = s->Lo.y_bytes / es; }
-          else { dy0 = grad_rec(s, l - l0, 0).dy; stride = s->Lo.grec_bytes / es; }
+          else { dy0 = grad_rec(s, l - l0, 0).dy; stride = tmp_sizes(c).ping / es; }
           BF_TRY(layer_wgrad_fused(s, l, l - l0, S_mb, N_mb, dy0, stride, os));
         }
         if (chains == 2) {
@@ -1097,10 +1153,13 @@ static bf_status run_rank_step(bf_stack* s, int schedule, int N_PP, int rank, bo
         }
       }
     }
-    peak_live = live > peak_live ? live : peak_live;
-    s->trace.push_back(bf_event{op.op, op.stage, m, live});
+    for (int k = m; k < m_end; ++k) {
+      live += op.op == 0 ? per_stage : -per_stage;
+      peak_live = live > peak_live ? live : peak_live;
+      s->trace.push_back(bf_event{op.op, op.stage, k, live});
+    }
 
-    if (op.op == 1 && m == N_mb - 1) {
+    if (op.op == 1 && m_end == N_mb) {
       // this stage's gradient is final (Sec. 4.2: breadth-first groups the work by stage)
       if (apply_optimizer) {
         const size_t off = (size_t)l0 * s->D.layer_elems, n = (size_t)per_stage * s->D.layer_elems;
@@ -1137,12 +1196,14 @@ static bf_status run_rank_step(bf_stack* s, int schedule, int N_PP, int rank, bo
       s->trace.push_back(bf_event{2, op.stage, -1, live});
     }
     if (!s->queue_ev.empty()) {
-      // bounded launch queue (App. D.2): wait for the op issued queue_depth ops ago
+      // bounded launch queue (App. D.2): wait for the op issued queue_depth ops ago (a group of micro-batches is as many
+      // launches as one, and counts as one)
       hipEvent_t e = s->queue_ev[qi % s->queue_ev.size()];
       if (qi >= s->queue_ev.size()) BF_HIP_CHECK(hipEventSynchronize(e));
       BF_HIP_CHECK(hipEventRecord(e, os));
       ++qi;
     }
+    oi += ng;
   }
   s->chain = 0;
   s->chains_active = 1;
@@ -1216,7 +1277,7 @@ static bf_status run_rank_step(bf_stack* s, int schedule, int N_PP, int rank, bo
         BF_HIP_CHECK(hipEventElapsedTime(&ms, s->prof_ev[2 * i], s->prof_ev[2 * i + 1]));
         const int k = s->prof_rec[i].cls;
         report->kernel_ms[k] += ms;
-        report->kernel_launches[k] += 1;
+        report->kernel_launches[k] += s->prof_rec[i].n;
         report->kernel_flops[k] += s->prof_rec[i].flops;
         report->kernel_bytes[k] += s->prof_rec[i].bytes;
       }
