@@ -137,6 +137,11 @@ bf_status attention_bwd_mfma_edge(int S_mb, int S_seq, int N_heads, int S_head, 
 bf_status attention_bwd_mfma(int S_mb, int S_seq, int N_heads, int S_head, int causal,
                              const void* qkv, const void* ctx, const float* lse, const void* dctx,
                              void* dqkv, float* delta, hipStream_t st, float* part = nullptr, bool shared_chip = false);
+// dK / dV on wider workgroups, and where those are faster (part_kv as above)
+bool attention_bwd_dkv_wide_supported(int S_mb, int S_seq, int N_heads, int S_head);
+bool attention_bwd_dkv_wide_better(int S_mb, int S_seq, int N_heads, int S_head, int causal);
+bf_status attention_bwd_dkv_wide(int S_mb, int S_seq, int N_heads, int S_head, int causal, const void* qkv, const float* lse, const void* dctx,
+                                 void* dqkv, const float* delta, float* part_kv, hipStream_t st);
 size_t attention_bwd_mfma_part_q_rows(int S_mb, int S_seq);
 size_t attention_bwd_mfma_part_kv_rows(int S_mb, int S_seq);
 // The plain kernels' results, bit for bit, on the fp32 matrix instructions (both storage types, head sizes up to 128; the

@@ -689,6 +689,31 @@ def test_attention_backward_with_one_key_block_to_a_unit(S_mb, S_seq, a):
     assert rel_err(to_host(db), to_host(dqkv).astype(np.float64).reshape(-1, 3 * h).sum(0)) <= 2.0 ** -8
 
 
+@pytest.mark.parametrize("causal,S_mb,S_seq,a", [(0, 66, 256, 2), (0, 1, 512, 70), (0, 3, 768, 20), (1, 2, 1024, 48), (1, 3, 1280, 24), (1, 1, 2048, 44)])
+def test_attention_backward_on_256_key_workgroups(causal, S_mb, S_seq, a):
+    """Heads of 128 in launches that fill the chip, of one key block per head to eight: a handful of heads against the oracle,
+    and the bias gradient's partial rows (two per workgroup) against the sums of what was stored."""
+    d, h = 128, a * 128
+    qkv, dctx = (bf_inputs.normal(47, i, (S_mb, S_seq, n * h), bf16=True) for i, n in ((0, 3), (1, 1)))
+    dQKV, dDC = to_dev(qkv, True), to_dev(dctx, True)
+    ctx, dqkv = (torch.full((S_mb, S_seq, n * h), float("nan"), dtype=torch.bfloat16, device="cuda") for n in (1, 3))
+    lse, delta = (torch.full((S_mb, a, S_seq), float("nan"), device="cuda") for _ in range(2))
+    part = torch.full((bf.bf_op_attention_bwd_part_elems(S_mb, S_seq, a, d) + 64,), float("nan"), device="cuda")
+    db = torch.full((3 * h,), float("nan"), device="cuda")
+    bf.bf_op_attention_fwd(bf.BF_BF16, 0, S_mb, S_seq, a, d, causal, dQKV, ctx, lse)
+    bf.bf_op_attention_bwd_bias(bf.BF_BF16, 0, S_mb, S_seq, a, d, causal, dQKV, ctx, lse, dDC, dqkv, delta, db, part, 0)
+    assert bool(torch.isnan(part[-64:]).all())
+    got = to_host(dqkv)
+    for m, head in ((0, 0), (S_mb - 1, 1), (S_mb // 2, a // 2), (S_mb - 1, a - 1)):
+        cols = slice(head * d, (head + 1) * d)
+        one = np.concatenate([qkv[m:m + 1, :, i * h:][..., cols] for i in range(3)], axis=-1).astype(np.float64)
+        ref, saved = L.attention_fwd(one, 1, bool(causal))
+        ref_d = L.attention_bwd(dctx[m:m + 1, :, cols].astype(np.float64), saved, 1)
+        for i in range(3):
+            assert rel_err(got[m:m + 1, :, i * h:][..., cols], ref_d[..., i * d:(i + 1) * d]) <= TOL["bf16"], (m, head, i)
+    assert rel_err(to_host(db), got.astype(np.float64).reshape(-1, 3 * h).sum(0)) <= 2.0 ** -8
+
+
 @pytest.mark.parametrize("dtype,layout,M,N", [(bf.BF_BF16, bf.BF_TN, 128, 128), (bf.BF_BF16, bf.BF_TN, 72, 40), (bf.BF_BF16, bf.BF_NN, 128, 128),
                                               (bf.BF_BF16, bf.BF_NT, 128, 256), (bf.BF_FP32, bf.BF_TN, 40, 36)])
 def test_gemm_of_few_tiles_over_more_than_two_million(dtype, layout, M, N):
