@@ -24,6 +24,13 @@ __device__ __forceinline__ void static_for_(F&& f, std::integer_sequence<int, I.
 template <int N, typename F>
 __device__ __forceinline__ void static_for(F&& f) { static_for_(f, std::make_integer_sequence<int, N>{}); }
 
+// f(row) for the share of rows R0 .. R1 - 1 that step C of N takes
+template <int R0, int R1, int C, int N, typename F>
+__device__ __forceinline__ void share(F&& f) {
+  constexpr int r0 = R0 + (R1 - R0) * C / N, r1 = R0 + (R1 - R0) * (C + 1) / N;
+  static_for<r1 - r0>([&](auto rc) { f(std::integral_constant<int, r0 + decltype(rc)::value>{}); });
+}
+
 typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
 __device__ __forceinline__ uint32_t pack2(float a, float b) {
   uint32_t two = __builtin_bit_cast(uint32_t, bf16x2{(__bf16)a, (__bf16)b});
@@ -34,19 +41,21 @@ __device__ __forceinline__ uint32_t pack2(float a, float b) {
 // The products, in assembly where 64 rows fill the registers: left to itself the compiler wants every accumulator of the kernel
 // in one half of the register file, and they are more than a half.  mfma_v keeps scores where the vector unit reads them,
 // mfma_a the sums over tiles in the other half (ASM false: the builtin).  What the compiler then does not see: a product
-// must not follow within two cycles of vector instructions that write its operands (`first` inserts them; only the first
-// product on new operands can be that close), and a score must not be read within 12 issue slots of its last product (two
-// further products lie between, 16 slots).  Their sources are waited for as usual: they are operands of the block.
+// must not follow within two cycles of vector instructions that write its operands (`nop` keeps them apart: for the first
+// products on new operands, and everywhere outside the loops over tiles, where the compiler may move registers about;
+// tests/test_host_logic.py looks for others in the listing), and a score must not be read within 12 issue slots of its
+// last product (two further products lie between, 16 slots).  Loads into the operands are waited for as usual.
 template <bool ASM>
-__device__ __forceinline__ void mfma_v(f32x16& c, const bf16x8& a, const bf16x8& b, bool first, const f32x16& init) {
+__device__ __forceinline__ void mfma_v(f32x16& c, const bf16x8& a, const bf16x8& b, bool first, const f32x16& init, bool nop) {
   if constexpr (!ASM) c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, first ? init : c, 0, 0, 0);
   else if (first) asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %3" : "=&v"(c) : "v"(a), "v"(b), "v"(init));
+  else if (nop) asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b));
   else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b));
 }
 template <bool ASM>
-__device__ __forceinline__ void mfma_a(f32x16& c, const bf16x8& a, const bf16x8& b, bool first) {
+__device__ __forceinline__ void mfma_a(f32x16& c, const bf16x8& a, const bf16x8& b, bool nop) {
   if constexpr (!ASM) c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
-  else if (first) asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
+  else if (nop) asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
   else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
 }
 template <bool ASM>
@@ -149,9 +158,12 @@ __device__ __forceinline__ f32x16 rows16(const float* p) {
 // form hands P from one wave to another).  S and dP start from the rows' -lse sqrt(d) and -delta in place of zero, which saves
 // two operations per element.  Phases of a sub-tile of 32 queries and what runs beside them: S; dP, exponentials of the
 // first 10 rows of a lane; dV, the others and dS; dK, the rest of dS.
-// S_head 128, G = 2, S_seq 2048: causal, 64 heads 178 -> 144 us (0.95 PFLOP/s), bidirectional 285 -> 213 (1.29, what the
-// large products reach at the power limit).  S_head 64, G = 1 (two workgroups per compute unit, 1 KB per product as
-// before, but no hand-over): 16 x 1024 tokens, 16 heads, bidirectional 200 -> 180.
+// Backward of S_head 128, G = 2, S_seq 2048, 64 heads: causal 302 -> 266 us, bidirectional 521 -> 441.  Bound by the products: with
+// neither LDS reads, vector work nor the next tile's loads in the loop (bidirectional) 80 % of the kernel's time remains, a
+// tenth of it the loads of K and V and the stores at either end, which one workgroup per compute unit cannot hide; without
+// the LDS reads 87 %, the vector work 90 %, the loads 95 %.  Vector work of both products after both, in place of half after each,
+// costs 3 %.  S_head 64, G = 1 (two workgroups per compute unit, 1 KB per product as before, but no hand-over): 16 x 1024 tokens, 16
+// heads, bidirectional 319 -> 298; three to a unit want 168 registers and take 381.
 template <int D, int G>
 __global__ __launch_bounds__(256, G == 1 ? 2 : 1) void attn_bwd_dkv_wide_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dctx,
                                                                    const float* __restrict__ lse, const float* __restrict__ delta,
@@ -227,63 +239,51 @@ __global__ __launch_bounds__(256, G == 1 ? 2 : 1) void attn_bwd_dkv_wide_kernel(
       f32x16 s[G], dp[G];
       u32x4 pb[G][2], db[G][2];  // P and dS in bf16, rows 8 k .. 8 k + 7: the B operands of dV and dK
       // P = exp(S / sqrt(d) - lse) of row r
-      auto exp_row = [&](auto rc) {
+      auto exp_row = [&](int g, auto rc) {
         constexpr int r = decltype(rc)::value;
-#pragma unroll
-        for (int g = 0; g < G; ++g) {
-          float v = __builtin_amdgcn_exp2f(s[g][r] * c2);
-          if (DIAG && kw + 32 * g + (lane & 31) > qb + 32 * t + acc_row(r, lane)) v = 0.f;
-          s[g][r] = v;
-          if constexpr (r % 2 == 1) pb[g][r / 8][r % 8 / 2] = pack2(s[g][r - 1], v);
-        }
+        float v = __builtin_amdgcn_exp2f(s[g][r] * c2);
+        if (DIAG && kw + 32 * g + (lane & 31) > qb + 32 * t + acc_row(r, lane)) v = 0.f;
+        s[g][r] = v;
+        if constexpr (r % 2 == 1) pb[g][r / 8][r % 8 / 2] = pack2(s[g][r - 1], v);
       };
       // dS = P (dP - delta) (the factor 1/sqrt(d) is applied once, to dK; masked entries of P are zero)
-      auto ds_row = [&](auto rc) {
+      auto ds_row = [&](int g, auto rc) {
         constexpr int r = decltype(rc)::value;
-#pragma unroll
-        for (int g = 0; g < G; ++g) {
-          const uint32_t two = pb[g][r / 8][r % 8 / 2];
-          dp[g][r] *= __builtin_bit_cast(float, r % 2 ? two & 0xffff0000u : two << 16);
-          if constexpr (r % 2 == 1) db[g][r / 8][r % 8 / 2] = pack2(dp[g][r - 1], dp[g][r]);
-        }
+        const uint32_t two = pb[g][r / 8][r % 8 / 2];
+        dp[g][r] *= __builtin_bit_cast(float, r % 2 ? two & 0xffff0000u : two << 16);
+        if constexpr (r % 2 == 1) db[g][r / 8][r % 8 / 2] = pack2(dp[g][r - 1], dp[g][r]);
       };
-      // rows R0 + (R1 - R0) c / H .. of the c-th of H steps that share rows R0 .. R1 - 1
-#define BF_SHARE(fn, R0, R1, c, H)                                                        \
-  do {                                                                                    \
-    constexpr int r0_ = (R0) + ((R1) - (R0)) * (c) / (H), r1_ = (R0) + ((R1) - (R0)) * ((c) + 1) / (H); \
-    static_for<r1_ - r0_>([&](auto rc) { fn(std::integral_constant<int, r0_ + decltype(rc)::value>{}); }); \
-  } while (0)
       constexpr int RB = 10, H = NC / 2;  // dV and dK need rows 0-7 first
       static_for<PER>([&](auto pc) {
         constexpr int p = decltype(pc)::value, i = t * PER + p;
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (i + AHEAD < 2 * PER) ring[(i + AHEAD) % (AHEAD + 1)] = frag(std::integral_constant<int, i + AHEAD>{});
         const bf16x8 f = ring[i % (AHEAD + 1)];
-        if constexpr (p < NK) {
-#pragma unroll
-          for (int g = 0; g < G; ++g) mfma_v<ASM>(s[g], f, kf[g][p], p == 0, init);
-          if constexpr (p == NK - 2) init = rows16(st0 + BLK + 32 * t);
-        } else if constexpr (p < 2 * NK) {
-          constexpr int k = p - NK;
-#pragma unroll
-          for (int g = 0; g < G; ++g) mfma_v<ASM>(dp[g], f, vf[g][k], k == 0, init);
+        static_for<G>([&](auto gc) {  // a product, then vector work in its shadow
+          constexpr int g = decltype(gc)::value;
+          if constexpr (p < NK) {
+            mfma_v<ASM>(s[g], f, kf[g][p], p == 0, init, DIAG);
+          } else if constexpr (p < 2 * NK) {
+            constexpr int k = p - NK;
+            mfma_v<ASM>(dp[g], f, vf[g][k], k == 0, init, DIAG);
+            __builtin_amdgcn_sched_barrier(0);
+            share<0, RB, k, NK>([&](auto rc) { exp_row(g, rc); });
+          } else if constexpr (p < 2 * NK + NC) {
+            constexpr int c = p - 2 * NK;
+            mfma_a<ASM>(dv[g][c % (D / 32)], f, __builtin_bit_cast(bf16x8, pb[g][c / (D / 32)]), DIAG || c % (D / 32) == 0);
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (c < H) share<RB, 16, c, H>([&](auto rc) { exp_row(g, rc); });
+            else share<0, 8, c - H, H>([&](auto rc) { ds_row(g, rc); });
+          } else {
+            constexpr int c = p - 2 * NK - NC;
+            mfma_a<ASM>(dk[g][c % (D / 32)], f, __builtin_bit_cast(bf16x8, db[g][c / (D / 32)]), DIAG || c % (D / 32) == 0);
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (c < H) share<8, 16, c, H>([&](auto rc) { ds_row(g, rc); });
+          }
           __builtin_amdgcn_sched_barrier(0);
-          BF_SHARE(exp_row, 0, RB, k, NK);
-        } else if constexpr (p < 2 * NK + NC) {
-          constexpr int c = p - 2 * NK;
-#pragma unroll
-          for (int g = 0; g < G; ++g) mfma_a<ASM>(dv[g][c % (D / 32)], f, __builtin_bit_cast(bf16x8, pb[g][c / (D / 32)]), c % (D / 32) == 0);
-          __builtin_amdgcn_sched_barrier(0);
-          if constexpr (c < H) BF_SHARE(exp_row, RB, 16, c, H);
-          else BF_SHARE(ds_row, 0, 8, c - H, H);
-        } else {
-          constexpr int c = p - 2 * NK - NC;
-#pragma unroll
-          for (int g = 0; g < G; ++g) mfma_a<ASM>(dk[g][c % (D / 32)], f, __builtin_bit_cast(bf16x8, db[g][c / (D / 32)]), c % (D / 32) == 0);
-          __builtin_amdgcn_sched_barrier(0);
-          if constexpr (c < H) BF_SHARE(ds_row, 8, 16, c, H);
-          if constexpr (t == 0 && c == NC - 2) init = rows16(st0 + 32);
-        }
+        });
+        if constexpr (p == NK - 2) init = rows16(st0 + BLK + 32 * t);
+        if constexpr (t == 0 && p == PER - 2) init = rows16(st0 + 32);
         mv.template step<i, 2 * PER>(jn, next);
       });
     });
@@ -348,9 +348,9 @@ __global__ __launch_bounds__(256, G == 1 ? 2 : 1) void attn_bwd_dkv_wide_kernel(
 // Which launches of S_head 128 go to 256-key workgroups.  A tile of those takes about 1.5 times as long as one of the 128-key
 // form and covers twice the keys; a launch lasts as long as its longest block or its share per compute unit, whichever is more
 // (rounds of equal blocks where nothing is masked), and the 128-key form's causal share comes out 1.12 times its tiles.
-// Backward, 128- / 256-key form, us: causal, S_seq 2048, 32 heads 174 / 198, 40 210 / 207, 48 236 / 217, 64 302 / 275; 1024, 64
+// Backward, 128- / 256-key form, us: causal, S_seq 2048, 32 heads 174 / 198, 40 210 / 207, 48 236 / 217, 64 302 / 266; 1024, 64
 // heads 110 / 120, 80 132 / 128, 96 151 / 150; shorter rows never: 512, 160 heads 103 / 106, 256, 400 heads 111 / 114; 4096, 16
-// heads 307 / 358, 24 415 / 393; bidirectional, 2048, 16 heads 160 / 200, 24 239 / 199, 64 521 / 448; 1024, 96 heads 243 / 248;
+// heads 307 / 358, 24 415 / 393; bidirectional, 2048, 16 heads 160 / 200, 24 239 / 199, 64 521 / 441; 1024, 96 heads 243 / 248;
 // 512, 300 heads 256 / 246; 256, 256 heads 71 / 64, 300 heads 108 / 110.  S_head 64 is faster here throughout (4 x 1024 tokens, 16
 // heads, bidirectional 91 / 83; 8 x 1024 causal 108 / 99; 2048, 8 heads, causal 84 / 71; 128, 256 heads level).
 bool attention_bwd_dkv_wide_better(int S_mb, int S_seq, int N_heads, int S_head, int causal) {
@@ -386,5 +386,6 @@ bf_status attention_bwd_dkv_wide(int S_mb, int S_seq, int N_heads, int S_head, i
   if (e != hipSuccess) { set_error("attention_bwd_dkv_wide launch failed: %s", hipGetErrorString(e)); return BF_EDEVICE; }
   return BF_OK;
 }
+
 
 }  // namespace bf

@@ -155,3 +155,51 @@ def test_tile_choice_invariants_without_a_device():
     assert bf.bf_op_gemm_tile(bf.BF_NN, bf.BF_EPI_NONE, 100, 128, 64) is None      # rows not a multiple of 128
     assert bf.bf_op_gemm_tile(bf.BF_NN, bf.BF_EPI_NONE, 128, 128, 96) is None      # K not a multiple of 64
     assert bf.bf_op_gemm_tile(bf.BF_TN, bf.BF_EPI_NONE, 128, 128, 64) is None      # the weight-gradient layout stores fp32
+
+
+def test_assembly_products_keep_their_distance(tmp_path):
+    """attention_wide.hip issues matrix products from assembly blocks, inside which the compiler does not see them.  In the
+    listing of its kernels, taking every instruction at the earliest it can issue (a slot each, a product every eight): no
+    vector instruction writes an operand of a product less than two slots before it, and nothing but the next product of the
+    same sum touches a result less than 12 slots after its product."""
+    import subprocess
+    from paper_2211_05953_amd import build
+    out = tmp_path / "wide.s"
+    src = os.path.join(build.CSRC, "attention_wide.hip")
+    subprocess.run([build._hipcc()] + build.FLAGS + ["-x", "hip", "-S", "--cuda-device-only", src, "-o", str(out)], check=True, capture_output=True)
+
+    def regs(op):
+        m = re.match(r"-?\|?([av])(?:\[(\d+):(\d+)\]|(\d+)\b)", op)
+        if not m:
+            return set()
+        lo, hi = (m.group(2), m.group(3)) if m.group(2) else (m.group(4), m.group(4))
+        return {(m.group(1), r) for r in range(int(lo), int(hi) + 1)}
+
+    products, bad, inside = 0, [], False
+    for line in out.read_text().split("\n"):
+        m = re.match(r"(_Z\w+):", line)
+        if m:
+            inside, t, free, written, ready = "wide_kernel" in m.group(1), 0, 0, {}, {}
+        text = line.split(";")[0].strip()
+        if not inside or not text or text.startswith(".") or text.endswith(":"):
+            continue
+        op, _, rest = text.partition(" ")
+        args = [regs(a) for a in re.split(r",\s*", rest.strip())]
+        if op == "s_nop":
+            t += int(rest) + 1
+        elif op.startswith("v_mfma"):
+            products += 1
+            t = max(t, free)
+            operands = args[1] | args[2] | args[3]
+            bad += [(text, r) for r in operands if t - written.get(r, -9) < 3]
+            if args[3] != args[0]:
+                bad += [(text, r) for r in operands if ready.get(r, 0) > t]
+            free = t + 8
+            ready.update({r: t + 12 for r in args[0]})
+            t += 1
+        else:
+            bad += [(text, r) for r in set().union(*args) if ready.get(r, 0) > t]
+            if op.startswith("v_") and not op.startswith("v_cmp"):
+                written.update({r: t for r in args[0]})
+            t += 1
+    assert products > 200 and not bad, bad[:5]
