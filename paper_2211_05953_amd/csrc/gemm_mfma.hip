@@ -37,9 +37,10 @@ constexpr int BK = 64;
 constexpr double TILE_RATE_MID = 0.84, TILE_RATE_SMALL = 0.68, TILE_RATE_WIDE = 0.95;
 constexpr int TPAD = 32;  // padding (elements) of a transposed LDS row: stride = 64 bytes mod 128
 
-template <int BM_, int BN_, int WM_, int WN_>
+template <int BM_, int BN_, int WM_, int WN_, int KG_ = 1>
 struct Tile {
   static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_;
+  static constexpr int KG = KG_;  // groups of WM x WN waves that share the contraction of the tile
   static constexpr int NT = WM * WN * 64;
   static constexpr int TM = BM / WM, TN = BN / WN;
   static constexpr int MI = TM / 16, NI = TN / 16;
@@ -100,9 +101,12 @@ struct Stager {
   // past K of the other kind; chunks past K of a K-contiguous row are sent past the end; columns past R_ext of a
   // K-slow operand pick up values of the next row, which only reach outputs that are not stored.  The whole offset
   // goes through the lane register: a scalar offset would take part in the range check by subtraction.
+  // PAST: k0 may lie behind K.
+  template <bool PAST = false>
   __device__ __forceinline__ void load_edge(const bf16_t* __restrict__ g, size_t ld, int r0, int k0, int R_ext, int K) {
     const bf16_t* base = KCONTIG ? g + (size_t)r0 * ld + k0 : g + (size_t)k0 * ld + r0;
-    const size_t left = KCONTIG ? (size_t)(R_ext - r0) * ld - k0 : (size_t)(K - k0) * ld - r0;  // elements to the end
+    // elements to the end
+    const size_t left = KCONTIG ? (size_t)(R_ext - r0) * ld - k0 : PAST && k0 >= K ? 0 : (size_t)(K - k0) * ld - r0;
     const size_t cap = (size_t)0x7fffff00 / sizeof(bf16_t);
     __amdgpu_buffer_rsrc_t rsrc =
         __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, (int)((left < cap ? left : cap) * sizeof(bf16_t)), 0x00020000);
@@ -212,19 +216,21 @@ __device__ __forceinline__ bf16x8 load_frag(const bf16_t* lds, int r16, int kk, 
 // EDGE: the tiles may reach past M, N and K (K-contiguous rows a multiple of 8 long, outputs N % 8 == 0): guarded loads
 // (Stager::load_edge) and stores, everything else the same.
 template <typename TL, bool AK, bool BKC, int EPI, typename TO, bool SEG_POW2, bool EDGE>
-__global__ __launch_bounds__(TL::NT) void gemm_mfma_kernel(int M, int N, int K, const bf16_t* __restrict__ A,
+__global__ __launch_bounds__(TL::NT * TL::KG) void gemm_mfma_kernel(int M, int N, int K, const bf16_t* __restrict__ A,
                                                            const bf16_t* __restrict__ B, TO* __restrict__ C,
                                                            const float* __restrict__ bias, const TO* __restrict__ R,
                                                            TO* __restrict__ C2, int accumulate, int tiles_m, int remap,
                                                            int n_seg, size_t seg_a, size_t seg_b, float* __restrict__ colpart,
                                                            int ldk) {
-  constexpr int BM = TL::BM, BN = TL::BN, NT = TL::NT, MI = TL::MI, NI = TL::NI;
+  constexpr int BM = TL::BM, BN = TL::BN, NT = TL::NT, MI = TL::MI, NI = TL::NI, KG = TL::KG;
   constexpr int A_ST = stage_elems<AK, BM>(), B_ST = stage_elems<BKC, BN>();
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-  bf16_t* smem = reinterpret_cast<bf16_t*>(smem_raw);
   constexpr int STAGE = A_ST + B_ST;  // stage s: A tile at smem + s * STAGE, B tile right after it
+  // KG groups of waves, each with its own LDS stages, take every KG-th k-tile of the same output tile
+  const int grp = KG == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / NT);
+  bf16_t* smem = reinterpret_cast<bf16_t*>(smem_raw) + grp * 2 * STAGE;
 
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int tid = KG == 1 ? threadIdx.x : threadIdx.x % NT, lane = tid & 63, w = tid >> 6;
   const int wm = w % TL::WM, wn = w / TL::WM;
   // Workgroups go to the 8 XCDs round-robin and each XCD has its own L2: give XCD x a contiguous
   // range of the tile order, and walk that order in groups of 8 row-tiles so that the ~32
@@ -271,7 +277,7 @@ __global__ __launch_bounds__(TL::NT) void gemm_mfma_kernel(int M, int N, int K, 
     // Accumulating into the main-grad: the accumulators START from the stored values, so the reads
     // of C overlap the first k-tiles and the epilogue is a plain store (read-modify-write at the end
     // would stall every workgroup of the round on HBM latency at once).
-    if (accumulate) {
+    if (accumulate && (KG == 1 || grp == 0)) {
 #pragma unroll
       for (int i = 0; i < MI; ++i)
 #pragma unroll
@@ -305,7 +311,7 @@ __global__ __launch_bounds__(TL::NT) void gemm_mfma_kernel(int M, int N, int K, 
 #pragma unroll
         for (int q = 0; q < NQ; ++q) {
           const int c = tid + q * NT, lr = c / (BN / 8), lc = (c % (BN / 8)) * 8;
-          if (EDGE && (m0 + p * PR + lr >= M || n0 + lc >= N)) {
+          if (EDGE && (grp != 0 || m0 + p * PR + lr >= M || n0 + lc >= N)) {
 #pragma unroll
             for (int e = 0; e < 8; ++e) rpre[p][q][e] = (__bf16)0.f;
             continue;
@@ -314,21 +320,23 @@ __global__ __launch_bounds__(TL::NT) void gemm_mfma_kernel(int M, int N, int K, 
         }
     }
   };
-  const int nk_seg = EDGE ? (K + BK - 1) / BK : K / BK, nk = nk_seg * n_seg;
+  const int nk_seg = EDGE ? (K + BK - 1) / BK : K / BK, nk = (nk_seg * n_seg + KG - 1) / KG;
   // k-tile kt lives in segment kt / nk_seg (one segment unless this is a multi-micro-batch weight gradient)
   // (only the weight-gradient product is launched with segments: the others skip the division)
-  constexpr bool SEGS = EPI == E_ACCUM;
+  constexpr bool SEGS = EPI == E_ACCUM && KG == 1;
   const int seg_shift = __builtin_ctz(nk_seg);
   auto seg_of = [&](int kt) { return SEG_POW2 ? kt >> seg_shift : kt / nk_seg; };
   auto seg_a_of = [&](int kt) { return SEGS ? A + (size_t)seg_of(kt) * seg_a : A; };
   auto seg_b_of = [&](int kt) { return SEGS ? B + (size_t)seg_of(kt) * seg_b : B; };
   auto k0_of = [&](int kt) { return !SEGS ? kt * BK : SEG_POW2 ? (kt & (nk_seg - 1)) * BK : (kt % nk_seg) * BK; };
   auto load_a = [&](int kt) {
-    if constexpr (EDGE) sa.load_edge(seg_a_of(kt), lda, m0, k0_of(kt), M, K);
+    if constexpr (KG > 1) sa.template load_edge<true>(A, lda, m0, (kt * KG + grp) * BK, M, K);
+    else if constexpr (EDGE) sa.load_edge(seg_a_of(kt), lda, m0, k0_of(kt), M, K);
     else sa.load(seg_a_of(kt), lda, m0, k0_of(kt));
   };
   auto load_b = [&](int kt) {
-    if constexpr (EDGE) sb.load_edge(seg_b_of(kt), ldb, n0, k0_of(kt), N, K);
+    if constexpr (KG > 1) sb.template load_edge<true>(B, ldb, n0, (kt * KG + grp) * BK, N, K);
+    else if constexpr (EDGE) sb.load_edge(seg_b_of(kt), ldb, n0, k0_of(kt), N, K);
     else sb.load(seg_b_of(kt), ldb, n0, k0_of(kt));
   };
   {
@@ -463,6 +471,32 @@ __global__ __launch_bounds__(TL::NT) void gemm_mfma_kernel(int M, int N, int K, 
     __syncthreads();
   }
 
+  if constexpr (KG > 1) {
+    // the other groups hand their sums to the first, lane to lane, added in order; the loop ended on a barrier
+    float* hand = reinterpret_cast<float*>(smem_raw);
+    static_assert(EDGE && (size_t)(KG - 1) * BM * BN * 4 <= (size_t)KG * 2 * STAGE * sizeof(bf16_t), "the hand-over does not fit");
+    if (grp > 0) {
+#pragma unroll
+      for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NI; ++j)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) hand[(((grp - 1) * MI + i) * NI + j) * 4 * NT + r * NT + tid] = acc[i][j][r];
+    }
+    __syncthreads();
+    if (grp == 0) {
+#pragma unroll
+      for (int g = 0; g < KG - 1; ++g)
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+          for (int j = 0; j < NI; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[i][j][r] += hand[((g * MI + i) * NI + j) * 4 * NT + r * NT + tid];
+    }
+    __syncthreads();
+  }
+  // (the other groups pass the epilogue's barriers and store nothing)
   if constexpr (EPI == E_ACCUM) {
     // fp32 main-grad: 16 lanes cover 64 contiguous bytes of a row, stored directly
 #pragma unroll
@@ -473,14 +507,14 @@ __global__ __launch_bounds__(TL::NT) void gemm_mfma_kernel(int M, int N, int K, 
         for (int r = 0; r < 4; ++r) {
           const size_t row = m0 + wm * TL::TM + i * 16 + (lane >> 4) * 4 + r;
           const size_t col = n0 + wn * TL::TN + j * 16 + (lane & 15);
-          if (!EDGE || (row < (size_t)M && col < (size_t)N)) C[row * (size_t)N + col] = acc[i][j][r];
+          if (!EDGE || (grp == 0 && row < (size_t)M && col < (size_t)N)) C[row * (size_t)N + col] = acc[i][j][r];
         }
   } else {
     // bf16 outputs: the fp32 accumulators pass through LDS, 64 tile rows at a time, so that every
     // thread finishes 8 adjacent columns (bias, residual, GeLU in fp32, one rounding) and the
     // global accesses of C, C2 and R are 16 bytes per lane over whole 512-byte row segments.
     constexpr int LDC = BN + 4;
-    float* cs = reinterpret_cast<float*>(smem_raw);
+    float* cs = reinterpret_cast<float*>(smem);
     static_assert((size_t)PR * LDC * 4 <= 2 * (size_t)STAGE * sizeof(bf16_t), "epilogue staging does not fit");
     // E_GELU_BWD with colpart: the column sums of this tile's (rounded) outputs, i.e. the tile's share of the bias
     // gradient of the linear layer whose pre-activation gradient is being written; a thread keeps the sums of
@@ -503,7 +537,7 @@ __global__ __launch_bounds__(TL::NT) void gemm_mfma_kernel(int M, int N, int K, 
       for (int q = 0; q < NQ; ++q) {
         const int c = tid + q * NT, lr = c / (BN / 8), lc = (c % (BN / 8)) * 8;
         const size_t row = m0 + p * PR + lr, col = n0 + lc, idx = row * (size_t)N + col;
-        if (EDGE && (row >= (size_t)M || col >= (size_t)N)) continue;
+        if (EDGE && (grp != 0 || row >= (size_t)M || col >= (size_t)N)) continue;
         float v[8];
         *reinterpret_cast<f32x4*>(v) = *reinterpret_cast<const f32x4*>(cs + lr * LDC + lc);
         *reinterpret_cast<f32x4*>(v + 4) = *reinterpret_cast<const f32x4*>(cs + lr * LDC + lc + 4);
@@ -549,7 +583,7 @@ __global__ __launch_bounds__(TL::NT) void gemm_mfma_kernel(int M, int N, int K, 
         for (int e = 0; e < 8; ++e) cs[rg * BN + g * 8 + e] = csum[e];
         __syncthreads();
         for (int c = tid; c < BN; c += NT) {
-          if (EDGE && n0 + c >= N) break;
+          if (EDGE && (grp != 0 || n0 + c >= N)) break;
           float t = 0.f;
 #pragma unroll 8
           for (int r = 0; r < RG; ++r) t += cs[r * BN + c];
@@ -571,9 +605,13 @@ typedef Tile<256, 192, 4, 2> TileWide;
 
 // 4 waves, 32 x 32 per wave, for products of few tiles (edge form only)
 typedef Tile<64, 64, 2, 2> TileTiny;
+// with the contraction shared by two or four groups of waves (key_groups)
+typedef Tile<64, 64, 2, 2, 2> TileTiny2;
+typedef Tile<64, 64, 2, 2, 4> TileTiny4;
+typedef Tile<128, 64, 2, 2, 2> TileTall2;
 
 template <typename TL, bool AK, bool BKC>
-constexpr size_t lds_bytes() { return 2 * (size_t)(stage_elems<AK, TL::BM>() + stage_elems<BKC, TL::BN>()) * sizeof(bf16_t); }
+constexpr size_t lds_bytes() { return TL::KG * 2 * (size_t)(stage_elems<AK, TL::BM>() + stage_elems<BKC, TL::BN>()) * sizeof(bf16_t); }
 
 template <typename TL, bool AK, bool BKC, int EPI, typename TO, bool EDGE = false, bool SEG_POW2 = false>
 bf_status launch(const GemmArgs& a, hipStream_t st) {
@@ -600,7 +638,7 @@ bf_status launch(const GemmArgs& a, hipStream_t st) {
   // gets the slice length and the row length of the K-contiguous operands separately
   const int slices = (EPI == E_ACCUM && AK && a.k_slices > 1) ? a.k_slices : 1;
   const dim3 grid((unsigned)(tiles_m * tiles_n), (unsigned)slices);
-  kern<<<grid, TL::NT, lds, st>>>(a.M, a.N, a.K / slices, (const bf16_t*)a.A, (const bf16_t*)a.B, (TO*)a.C, a.bias,
+  kern<<<grid, TL::NT * TL::KG, lds, st>>>(a.M, a.N, a.K / slices, (const bf16_t*)a.A, (const bf16_t*)a.B, (TO*)a.C, a.bias,
                                   (const TO*)a.R, (TO*)a.C2, a.accumulate, tiles_m, remap, a.n_seg > 1 ? a.n_seg : 1,
                                   a.seg_stride_a, a.seg_stride_b, EPI == E_GELU_BWD ? a.colsum_part : nullptr, a.K);
   if (EPI == E_GELU_BWD && a.colsum_rows) *a.colsum_rows = tiles_m;
@@ -679,6 +717,24 @@ inline bool few_tiles(int layout, int M, int N) {
   return (long)((M + 63) / 64) * ((N + 63) / 64) <= (layout == L_TN ? 256 : 512);
 }
 
+// Few tiles and a contraction of some length: a tile's k-tiles are a chain of loads, barriers and fragment reads that one
+// or two workgroups per compute unit do not overlap, so two (or four) groups of waves share it, each on every second
+// (fourth) k-tile with LDS stages of its own, and add their sums in LDS at the end.  More than 256 tiles of 64 x 64 (two
+// workgroups to a unit already) also take 128 x 64 ones, which load a quarter less per product.  One group / two / four on 64 x 64 / two on
+// 128 x 64, us: forward 1000 x 2048 x 8192 75.0 / 67.2 / - / 53.0, dgrad 59.4 / 53.3 / - / 46.2, forward 1000 x 2048 x 2048 18.8 / 17.3 / - / 16.5,
+// dgrad 1100 x 1000 x 1024 9.2 / 9.1 / 11.9 / 8.7; forward 1000 x 1024 x 8192 55.3 / 37.8 / 33.1 / 46.1, 500 x 1024 x 4096 31.7 / 20.6 / 17.3 /
+// 25.7, 300 x 512 x 2048 12.9 / 10.7 / 10.3 / 14.4, 64 x 512 x 50304 350 / 207 / 153 / 252, dgrad 128 x 256 x 1024 6.7 / 6.0 / 6.4 / 8.1, 1000 x 1000 x 768 7.5 /
+// 7.2 / 7.9 / 8.9.  Weight gradients, one / two on 64 x 64: 512 x 512 over 4096 28.4 / 20.6, 1024 x 1024 over 1000 9.6 / 8.0, 512 x 512 over 512 5.9 / 5.4,
+// 1000 x 1024 over 300 5.4 / 5.5.  (Four groups there want more LDS than there is.)
+enum Groups { G_ONE, G_TWO, G_FOUR, G_TWO_TALL };
+inline Groups key_groups(int layout, int M, int N, int K, int n_seg) {
+  if (!few_tiles(layout, M, N) || n_seg > 1) return G_ONE;
+  if (layout == L_TN) return K >= 512 ? G_TWO : G_ONE;
+  if (K < 1024) return G_ONE;
+  if ((long)((M + 63) / 64) * ((N + 63) / 64) > 256) return G_TWO_TALL;
+  return K >= 4096 ? G_FOUR : G_TWO;
+}
+
 // Tile of the edge form: 0: 256 x 256, 1: 128 x 128 (by the estimate of choose_tile, the last tiles partly empty), 2: 64 x 64.
 inline int choose_edge_tile(int layout, int M, int N) {
   if (few_tiles(layout, M, N)) return 2;
@@ -724,7 +780,19 @@ bf_status gemm_mfma_edge(int layout, int epi, const GemmArgs& a, hipStream_t st)
   switch (choose_edge_tile(layout, a.M, a.N)) {
     case 0: return by_layout<TileBig, true>(layout, epi, a, st);
     case 1: return by_layout<TileSmall, true>(layout, epi, a, st);
-    default: return by_layout<TileTiny, true>(layout, epi, a, st);
+    default: break;
+  }
+  GemmArgs b = a;
+  if (a.n_seg > 1 && a.seg_stride_a == (size_t)a.K * a.M && a.seg_stride_b == (size_t)a.K * a.N && (long)a.K * a.n_seg < (1l << 31)) {
+    // segments that follow each other without a gap are one contraction
+    b.K = a.K * a.n_seg;
+    b.n_seg = 1;
+  }
+  switch (key_groups(layout, b.M, b.N, b.K, b.n_seg)) {
+    case G_TWO: return by_layout<TileTiny2, true>(layout, epi, b, st);
+    case G_FOUR: return layout == L_NN ? by_epilogue<TileTiny4, true, false, true>(epi, b, st) : by_epilogue<TileTiny4, true, true, true>(epi, b, st);
+    case G_TWO_TALL: return layout == L_NN ? by_epilogue<TileTall2, true, false, true>(epi, b, st) : by_epilogue<TileTall2, true, true, true>(epi, b, st);
+    default: return by_layout<TileTiny, true>(layout, epi, b, st);
   }
 }
 

@@ -714,6 +714,40 @@ def test_attention_backward_on_256_key_workgroups(causal, S_mb, S_seq, a):
     assert rel_err(to_host(db), got.astype(np.float64).reshape(-1, 3 * h).sum(0)) <= 2.0 ** -8
 
 
+@pytest.mark.parametrize("M,N,K", [(1, 8, 1024), (100, 72, 1032), (65, 64, 4104), (128, 256, 4224), (1000, 1000, 4096), (1100, 1000, 1032), (1030, 1024, 2048)])
+def test_gemm_of_few_tiles_by_groups_of_waves(M, N, K):
+    """Two and four groups of waves on the k-tiles of one output tile: contractions that leave a group with fewer of them than
+    the others, output tiles that are mostly empty, both tiles, every epilogue of the forward and dgrad layouts."""
+    A, B = bf_inputs.normal(61, 0, (M, K), bf16=True), bf_inputs.normal(61, 1, (K, N), 0.05, bf16=True)
+    bias, R = bf_inputs.normal(61, 2, (N,), 0.5), bf_inputs.normal(61, 3, (M, N), bf16=True)
+    dA, dB, dBt, dR, dbias = to_dev(A, True), to_dev(B, True), to_dev(np.ascontiguousarray(B.T), True), to_dev(R, True), to_dev(bias, False)
+    acc = A.astype(np.float64) @ B.astype(np.float64)
+    r64 = R.astype(np.float64)
+    u = to_host(to_dev(acc + bias, True)).astype(np.float64)
+    for layout, op, epi, want in ((bf.BF_NN, dB, bf.BF_EPI_NONE, acc), (bf.BF_NN, dB, bf.BF_EPI_BIAS_RES, acc + bias + r64),
+                                  (bf.BF_NN, dB, bf.BF_EPI_BIAS_GELU, acc + bias), (bf.BF_NT, dBt, bf.BF_EPI_NONE, acc),
+                                  (bf.BF_NT, dBt, bf.BF_EPI_GELU_BWD, acc * L.gelu_grad(r64))):
+        out, out2 = (torch.full((M + 1, N), float("nan"), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+        bf.bf_op_gemm(bf.BF_BF16, 0, layout, epi, M, N, K, dA, op, out, bias=dbias, R=dR, C2=out2)
+        assert rel_err(to_host(out[:M]), want) <= TOL["bf16"], (layout, epi)
+        if epi == bf.BF_EPI_BIAS_GELU:
+            assert rel_err(to_host(out2[:M]), L.gelu(u)) <= TOL["bf16"]
+        assert bool(torch.isnan(out[M:]).all()) and bool(torch.isnan(out2[M:]).all())
+
+
+@pytest.mark.parametrize("M,N,K,n_seg,gap", [(8, 8, 512, 1, 0), (72, 40, 584, 1, 0), (64, 128, 200, 3, 0), (64, 128, 200, 3, 64), (1000, 1024, 520, 1, 0)])
+@pytest.mark.parametrize("accumulate", [0, 1])
+def test_weight_gradient_of_few_tiles_by_groups_of_waves(M, N, K, n_seg, gap, accumulate):
+    """The same in the weight-gradient layout, added to or not, over segments that follow each other without a gap (one
+    contraction, and long enough only as one) or with one."""
+    X, dY = bf_inputs.normal(62, 0, (n_seg, K * M + gap), bf16=True), bf_inputs.normal(62, 1, (n_seg, K * N + gap), bf16=True)
+    G = torch.full((M + 1, N), 2.0, device="cuda")
+    bf.bf_op_wgrad(bf.BF_BF16, 0, M, N, K, n_seg, to_dev(X, True), K * M + gap, to_dev(dY, True), K * N + gap, G, accumulate=accumulate)
+    x, d = (t[:, :K * w].astype(np.float64).reshape(n_seg * K, w) for t, w in ((X, M), (dY, N)))
+    assert rel_err(to_host(G)[:M], x.T @ d + 2.0 * accumulate) <= 1e-5
+    assert bool((G[M:] == 2.0).all())
+
+
 @pytest.mark.parametrize("dtype,layout,M,N", [(bf.BF_BF16, bf.BF_TN, 128, 128), (bf.BF_BF16, bf.BF_TN, 72, 40), (bf.BF_BF16, bf.BF_NN, 128, 128),
                                               (bf.BF_BF16, bf.BF_NT, 128, 256), (bf.BF_FP32, bf.BF_TN, 40, 36)])
 def test_gemm_of_few_tiles_over_more_than_two_million(dtype, layout, M, N):
