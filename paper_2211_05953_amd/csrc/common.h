@@ -58,6 +58,8 @@ struct GemmArgs {
   // whose tiles would leave half of the chip idle (see gemm_splitk_slices) and finishes it with a second kernel.
   float* splitk_ws = nullptr;
   size_t splitk_ws_elems = 0;
+  // Matrix-core kernel: only the first m_part rows / n_part columns of C (0: all of them; whole tiles)
+  int m_part = 0, n_part = 0;
   // The product shares the chip with another stream's kernels (two chains of micro-batches): compute units that
   // its grid leaves idle are taken by those, so nothing is gained by trading a tile's efficiency for a fuller
   // round: no 256 x 192 tile (measured on a 6144-wide stack with two chains: 3066 ms per step without, 3154 with).
@@ -96,7 +98,10 @@ bf_status gemm_f32(int dtype, int layout, int epi, const GemmArgs& a, hipStream_
 // tile (rows x columns of C per workgroup) the MFMA kernel runs an unsplit product of this shape on; 0 x 0 if none fits
 void gemm_mfma_tile(int layout, int epi, int M, int N, int* bm, int* bn);
 // Slices the matrix-core path would cut the contraction of this forward / dgrad product into (1: no split).
-int gemm_splitk_slices(int layout, int epi, int M, int N, int K);
+// fits: the planes there is room for.
+int gemm_splitk_slices(int layout, int epi, int M, int N, int K, int fits = 64);
+// true where an unsplit product of whole tiles runs as whole rounds of 256 x 256 tiles and a rest
+bool gemm_mfma_in_rounds(int layout, int epi, const GemmArgs& a);
 // C[M,N] (bf16) = epilogue(sum over the planes of part[slices][M][N], added in ascending order); epilogues
 // E_NONE, E_BIAS, E_BIAS_RES.
 bf_status gemm_splitk_finish(int epi, int M, int N, int slices, const float* part, const float* bias, const void* R,

@@ -632,7 +632,8 @@ bf_status launch(const GemmArgs& a, hipStream_t st) {
     if (e != hipSuccess) { set_error("gemm_mfma: cannot reserve %zu bytes of LDS: %s", lds, hipGetErrorString(e)); return BF_EDEVICE; }
     if (dev < 64) attr_set.fetch_or(bit, std::memory_order_release);
   }
-  const int tiles_m = (a.M + TL::BM - 1) / TL::BM, tiles_n = (a.N + TL::BN - 1) / TL::BN;  // exact without EDGE
+  const int rows = a.m_part ? a.m_part : a.M, cols = a.n_part ? a.n_part : a.N;
+  const int tiles_m = (rows + TL::BM - 1) / TL::BM, tiles_n = (cols + TL::BN - 1) / TL::BN;  // exact without EDGE
   const int remap = (tiles_m * tiles_n) % 8 == 0 ? 1 : 0;
   // split-K (fp32 planes of partial results, forward / dgrad layouts only): a.K is the whole contraction, the kernel
   // gets the slice length and the row length of the K-contiguous operands separately
@@ -691,7 +692,8 @@ constexpr int SPLITK_TILE = 1;  // split contractions run on the 256 x 128 tile
 // beat 768 of 256 x 128, 128 large tiles lose to 256 of them).
 // 0: 256 x 256 (one per compute unit), 1: 256 x 128 (one), 2: 128 x 128 (two), 3: 256 x 192 (one; only where the
 // caller says the product can take it).
-inline int choose_tile(int M, int N, bool wide = false) {
+// est: where the estimate goes (in outputs of a 256 x 256 tile per compute unit).
+inline int choose_tile(int M, int N, bool wide = false, double* est = nullptr) {
   const int bm[4] = {256, 256, 128, 256}, bn[4] = {256, 128, 128, 192};
   const long slots[4] = {256, 256, 512, 256};
   const double rate[4] = {1.0, TILE_RATE_MID, TILE_RATE_SMALL / 2, TILE_RATE_WIDE};
@@ -704,8 +706,12 @@ inline int choose_tile(int M, int N, bool wide = false) {
     const double t = rounds * bm[i] * bn[i] / rate[i];
     if (best < 0 || t < best_t) { best = i; best_t = t; }
   }
+  if (est) *est = best_t;
   return best;
 }
+
+// Time of a k-tile (64 of K) on 256 x 256 tiles with every compute unit at work, and of starting another kernel, us.
+constexpr double K_TILE_US = 1.65, LAUNCH_US = 3.0;
 
 // Products of few tiles run on 64 x 64 ones, whole or not: a workgroup that has a compute unit to itself takes 1.2, 0.72,
 // 0.6-0.7 and 0.3 us per k-tile on 256 x 256, 256 x 128, 128 x 128 and 64 x 64 (two of the last: 0.5), so up to two of
@@ -811,6 +817,84 @@ void gemm_mfma_tile(int layout, int epi, int M, int N, int* bm, int* bn) {
   *bn = t < 0 ? 0 : cols[t];
 }
 
+// Whole rounds and a rest.  A grid of 256 x 256 tiles that fills the chip several times over and then a few tiles' width
+// more (50304 columns by 2048 rows: 6.14 rounds, and 50304 is no multiple of 256) runs the whole rounds by themselves and the
+// rest, whole tiles of 128, as a second launch on the tile that suits it, where the estimates of the two and a launch come to less
+// than that of one grid.  Rows of the weight gradient (M), columns of the others.  One grid / two, us: dgrad layout 2048 x
+// 50304 x 2048 393 / 365 (256 x 192 tiles), x 512 138 / 130, 1024 x 50304 x 1024 115 / 108, 2048 x 8320 x 2048 89 / 79; forward 431 / 409; weight gradient
+// 50304 x 2048 x 2048 436 / 393, 50304 x 1024 x 2048 236 / 212, 9216 x 2048 x 4096 187 / 147; not taken: 50304 x 512 x 2048 116 / 126, dgrad 2048 x
+// 9216 x 8192 270 / 278 (1.5 rounds of 256 x 192), 2048 x 32000 x 1024 123 / 126.
+// 0, or the rows / columns of the whole rounds.
+static int whole_rounds(int layout, int epi, int M, int N, int K, bool shared_chip) {
+  const int fixed = layout == L_TN ? N : M, var = layout == L_TN ? M : N, across = fixed / 256;
+  if (fixed % 256 || across > 256 || 256 % across) return 0;
+  const int unit = 256 / across * 256, main = var / unit * unit, rest = var - main;
+  if (!main || !rest || rest % 128) return 0;
+  double one, two;
+  if (layout == L_TN && choose_edge_tile(layout, M, N) == 0) {
+    const long tiles = (long)((M + 255) / 256) * (N / 256), last = tiles % 256;
+    one = ((double)(tiles / 256) + (last ? 0.5 + 0.5 * (double)last / 256 : 0.0)) * 65536;
+  } else {
+    choose_tile(M, N, !shared_chip && wide_fits(layout, epi, M, N), &one);
+  }
+  choose_tile(layout == L_TN ? rest : M, layout == L_TN ? N : rest, false, &two);
+  two += (double)main / unit * 65536;
+  const double us = (double)K / BK * K_TILE_US / 65536;
+  return two * us + LAUNCH_US < one * us ? main : 0;
+}
+
+bool gemm_mfma_in_rounds(int layout, int epi, const GemmArgs& a) {
+  // (partial column sums have a row per row of tiles of the one grid)
+  return a.n_seg <= 1 && !(epi == E_GELU_BWD && a.colsum_part) && !few_tiles(layout, a.M, a.N) && whole_rounds(layout, epi, a.M, a.N, a.K, a.shared_chip) > 0;
+}
+
+static bf_status in_rounds(int layout, int epi, const GemmArgs& a, int main, hipStream_t st) {
+  GemmArgs b = a;
+  (layout == L_TN ? b.m_part : b.n_part) = main;
+  bf_status r = by_layout<TileBig>(layout, epi, b, st);
+  if (r != BF_OK) return r;
+  // the rest: the same matrices from row / column `main` on
+  b = a;
+  const size_t m = (size_t)main;
+  if (layout == L_TN) {
+    b.A = (const bf16_t*)a.A + m;
+    b.C = (float*)a.C + m * a.N;
+    b.m_part = a.M - main;
+  } else {
+    b.B = (const bf16_t*)a.B + (layout == L_NT ? m * a.K : m);
+    b.C = (bf16_t*)a.C + m;
+    if (a.bias) b.bias = a.bias + m;
+    if (a.R) b.R = (const bf16_t*)a.R + m;
+    if (a.C2) b.C2 = (bf16_t*)a.C2 + m;
+    b.n_part = a.N - main;
+  }
+  switch (layout == L_TN ? choose_tile(a.M - main, a.N) : choose_tile(a.M, a.N - main)) {
+    case 0: return by_layout<TileBig>(layout, epi, b, st);
+    case 1: return by_layout<TileMid>(layout, epi, b, st);
+    default: return by_layout<TileSmall>(layout, epi, b, st);
+  }
+}
+
+// Slices of a very long contraction (a 50304-word vocabulary's) on 256 x 256 tiles, as many as make the estimate of rounds and
+// of the pass over the planes the least; 0: not for these.  256 x 128 tiles in two slices / here, us: 2048 x 2048 x 50304 416 / 400 (3), 2048 x
+// 1024 x 50304 360 / 217 (6), 1024 x 1536 x 50304 314 / 189 (6), 2048 x 1024 x 32000 201 / 163 (4); at K = 8192 level (2048 x 2048 75.7 / 76.6 in 4, 1024 x
+// 2048 58.0 / 55.9), where two planes are less scratch.
+static int big_slices(int M, int N, int K) {
+  if (K < 16384 || M % 256 || N % 256 || K % BK) return 0;
+  const long tiles = (long)(M / 256) * (N / 256);
+  if (tiles > 128) return 0;
+  int best = 0;
+  double best_t = 0;
+  for (int s = 2; s <= 8; ++s) {
+    if (K % (s * BK)) continue;
+    const long wgs = tiles * s, last = wgs % 256;
+    const double rounds = (double)(wgs / 256) + (last ? 0.5 + 0.5 * (double)last / 256 : 0.0);
+    const double t = rounds * (K / s / BK) * K_TILE_US + s * (double)M * N * 8 / 4.5e6;  // planes written and read at 4.5 TB/s
+    if (!best || t < best_t) { best = s; best_t = t; }
+  }
+  return best;
+}
+
 bf_status gemm_mfma(int layout, int epi, const GemmArgs& a, hipStream_t st) {
   const bool planes = epi == E_ACCUM && layout != L_TN;  // split contraction of a forward / dgrad product
   if (planes) {
@@ -826,9 +910,12 @@ bf_status gemm_mfma(int layout, int epi, const GemmArgs& a, hipStream_t st) {
   }
   const uintptr_t al = (uintptr_t)a.A | (uintptr_t)a.B | (uintptr_t)a.C | (uintptr_t)a.R | (uintptr_t)a.C2 | (uintptr_t)a.bias;
   if (al & 15) { set_error("gemm_mfma: operands must be 16-byte aligned"); return BF_EINVAL; }
+  if (planes && a.k_slices == big_slices(a.M, a.N, a.K))
+    return layout == L_NN ? launch<TileBig, true, false, E_ACCUM, float>(a, st) : launch<TileBig, true, true, E_ACCUM, float>(a, st);
   // slices of a product of few tiles: on 64 x 64 as well, as long as both slices' workgroups find room
   if (planes && (long)(a.M / 64) * (a.N / 64) <= 256)
     return layout == L_NN ? launch<TileTiny, true, false, E_ACCUM, float>(a, st) : launch<TileTiny, true, true, E_ACCUM, float>(a, st);
+  if (!planes && gemm_mfma_in_rounds(layout, epi, a)) return in_rounds(layout, epi, a, whole_rounds(layout, epi, a.M, a.N, a.K, a.shared_chip), st);
   switch (planes ? SPLITK_TILE : choose_tile(a.M, a.N, !a.shared_chip && wide_fits(layout, epi, a.M, a.N))) {
     case 0: return by_layout<TileBig>(layout, epi, a, st);
     case 1: return by_layout<TileMid>(layout, epi, a, st);
@@ -853,11 +940,15 @@ bf_status gemm_mfma(int layout, int epi, const GemmArgs& a, hipStream_t st) {
 // 1024 x 2048 x 4608: 40 either way; 1024 x 1024 x 2048: 13 against 14 and more.
 constexpr int SPLITK_FEW_TILES_K = 4608;
 
-int gemm_splitk_slices(int layout, int epi, int M, int N, int K) {
+// fits: planes that the caller has room for
+int gemm_splitk_slices(int layout, int epi, int M, int N, int K, int fits) {
   if (layout != L_NN && layout != L_NT) return 1;
   if (epi != E_NONE && epi != E_BIAS && epi != E_BIAS_RES) return 1;
   if (K < 2048 || K % (2 * BK) || !gemm_mfma_supported(layout, epi, M, N, K)) return 1;
   if (M % 256 || N % 128) return 1;
+  const int big = big_slices(M, N, K);
+  if (big && big <= fits) return big;
+  if (fits < 2) return 1;
   if (K < SPLITK_FEW_TILES_K && few_tiles(layout, M, N)) return 1;
   if (choose_tile(M, N) != SPLITK_TILE) return 1;
   const long tiles = (long)(M / 256) * (N / 128);

@@ -136,11 +136,13 @@ bf_status gemm(int dtype, int kernels, int layout, int epi, const GemmArgs& a, h
   const bool seg_ok = a.n_seg <= 1 || ((a.seg_stride_a | a.seg_stride_b) & 7) == 0;  // 16-byte aligned segments
   const bool mfma = dtype == BF_BF16 && kernels == BF_KERNELS_AUTO && (al & 15) == 0 && seg_ok;
   const bool fits = mfma && gemm_mfma_supported(layout, epi, a.M, a.N, a.K);
-  const int slices = fits && a.splitk_ws ? gemm_splitk_slices(layout, epi, a.M, a.N, a.K) : 1;
+  const size_t planes = a.M > 0 && a.N > 0 ? a.splitk_ws_elems / ((size_t)a.M * a.N) : 0;
   // few tiles, long contraction: slices of K on more workgroups into fp32 planes, then the planes added in order
-  const bool split = slices > 1 && a.splitk_ws_elems >= (size_t)slices * a.M * a.N && ((uintptr_t)a.splitk_ws & 15) == 0;
+  const int slices = fits && a.splitk_ws && ((uintptr_t)a.splitk_ws & 15) == 0
+                         ? gemm_splitk_slices(layout, epi, a.M, a.N, a.K, planes < 64 ? (int)planes : 64) : 1;
+  const bool split = slices > 1;
   const bool edge = mfma && gemm_mfma_edge_supported(layout, epi, a.M, a.N, a.K);
-  const bool whole = fits && (split || !edge || !gemm_mfma_edge_better(layout, a.M, a.N));
+  const bool whole = fits && (split || !edge || !gemm_mfma_edge_better(layout, a.M, a.N) || gemm_mfma_in_rounds(layout, epi, a));
   if (whole || edge) {
     s = gemm_check(layout, epi, a);
     if (s != BF_OK) return s;

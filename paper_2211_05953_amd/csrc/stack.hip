@@ -215,6 +215,10 @@ TmpSizes tmp_sizes_of(const bf_config& c) {
         if (sl > 1) planes = std::max(planes, (size_t)sl * p[2] * p[3]);
       }
     }
+    if (c.S_voc > 0) {  // the output layer's input gradient
+      const int sl = gemm_splitk_slices(L_NN, E_NONE, (int)T, (int)h, c.S_voc);
+      if (sl > 1) planes = std::max(planes, (size_t)sl * T * h);
+    }
   }
   t.splitk = up(planes * 4);
   t.total = t.du + t.dc + t.dx1 + t.dctx + t.dqkv + t.delta + 2 * t.ping + t.colpart + t.lnpart + t.attnpart + t.splitk;

@@ -748,6 +748,56 @@ def test_weight_gradient_of_few_tiles_by_groups_of_waves(M, N, K, n_seg, gap, ac
     assert bool((G[M:] == 2.0).all())
 
 
+@pytest.mark.parametrize("layout,epi,M,N,K", [(bf.BF_NT, bf.BF_EPI_NONE, 2048, 8320, 1536), (bf.BF_NN, bf.BF_EPI_BIAS_RES, 2048, 8320, 1536),
+                                              (bf.BF_NN, bf.BF_EPI_BIAS_GELU, 1024, 16640, 1536), (bf.BF_NT, bf.BF_EPI_GELU_BWD, 2048, 8320, 1536),
+                                              (bf.BF_TN, bf.BF_EPI_ACCUM, 8576, 2048, 1536), (bf.BF_TN, bf.BF_EPI_ACCUM, 16768, 1024, 2048)])
+def test_gemm_in_whole_rounds_and_a_rest(layout, epi, M, N, K):
+    """A round of 256 x 256 tiles over the chip and one, two or three blocks of 128 rows or columns more, which run as a launch of
+    their own: against fp32 products of the same operands on either side of the seam, and the first and last of both."""
+    g = torch.Generator(device="cuda").manual_seed(63)
+    mk = lambda *s, sc=1.0: (torch.randn(s, generator=g, device="cuda") * sc).bfloat16()
+    A, B = mk(*((K, M) if layout == bf.BF_TN else (M, K))), mk(*((N, K) if layout == bf.BF_NT else (K, N)), sc=0.05)
+    bias, R = torch.randn(N, generator=g, device="cuda"), mk(M, N)
+    out = torch.full((M, N), 1.0 if epi == bf.BF_EPI_ACCUM else float("nan"), dtype=torch.float32 if epi == bf.BF_EPI_ACCUM else torch.bfloat16, device="cuda")
+    out2 = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+    bf.bf_op_gemm(bf.BF_BF16, 0, layout, epi, M, N, K, A, B, out, bias=bias, R=R, C2=out2, accumulate=1)
+    a32, b32 = (A.t() if layout == bf.BF_TN else A).float(), (B.t() if layout == bf.BF_NT else B).float()
+    assert bool(torch.isfinite(out).all())
+    for rows, cols in ((slice(0, 300), slice(0, 300)), (slice(M - 700, M), slice(N - 700, N)), (slice(M - 700, M), slice(0, 200)), (slice(0, 200), slice(N - 700, N))):
+        want = a32[rows] @ b32[:, cols]
+        if epi == bf.BF_EPI_ACCUM:
+            want = want + 1.0
+        if epi in (bf.BF_EPI_BIAS_RES, bf.BF_EPI_BIAS_GELU):
+            want = want + bias[cols]
+        if epi == bf.BF_EPI_BIAS_RES:
+            want = want + R[rows, cols].float()
+        if epi == bf.BF_EPI_GELU_BWD:
+            want = want * torch.from_numpy(L.gelu_grad(to_host(R[rows, cols]).astype(np.float64))).float().cuda()
+        tol = 1e-5 if epi == bf.BF_EPI_ACCUM else TOL["bf16"]
+        assert rel_err(to_host(out[rows, cols]), to_host(want)) <= tol, (rows, cols)
+        if epi == bf.BF_EPI_BIAS_GELU:
+            assert rel_err(to_host(out2[rows, cols]), L.gelu(to_host(out[rows, cols]).astype(np.float64))) <= TOL["bf16"]
+
+
+@pytest.mark.parametrize("M,N,K", [(256, 256, 16384), (512, 256, 16512), (256, 512, 50304)])
+def test_very_long_contraction_in_slices_on_large_tiles(M, N, K):
+    """Contractions of a vocabulary's length in more than two slices, all of whose planes are used; with room for two planes only,
+    and for one, in two and unsplit."""
+    s = bf.bf_op_gemm_splitk_slices(bf.BF_NN, bf.BF_EPI_BIAS_RES, M, N, K)
+    assert s > 2 and K % (64 * s) == 0
+    g = torch.Generator(device="cuda").manual_seed(64)
+    A, B = torch.randn((M, K), generator=g, device="cuda").bfloat16(), (torch.randn((K, N), generator=g, device="cuda") * 0.02).bfloat16()
+    Bt, bias, R = B.t().contiguous(), torch.randn(N, generator=g, device="cuda"), torch.randn((M, N), generator=g, device="cuda").bfloat16()
+    acc = to_host(A).astype(np.float64) @ to_host(B).astype(np.float64)
+    for layout, op, epi, want in ((bf.BF_NN, B, bf.BF_EPI_BIAS_RES, acc + to_host(bias) + to_host(R)), (bf.BF_NT, Bt, bf.BF_EPI_NONE, acc)):
+        for n in (s, 2, 1):
+            planes = torch.full((n, M, N), float("nan"), device="cuda")
+            out = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+            bf.bf_op_gemm_splitk(bf.BF_BF16, 0, layout, epi, M, N, K, A, op, out, bias=bias, R=R, planes=planes.reshape(-1))
+            assert bool(torch.isfinite(planes).all()) if n > 1 else bool(torch.isnan(planes).all())
+            assert rel_err(to_host(out), want) <= TOL["bf16"], (layout, n)
+
+
 @pytest.mark.parametrize("dtype,layout,M,N", [(bf.BF_BF16, bf.BF_TN, 128, 128), (bf.BF_BF16, bf.BF_TN, 72, 40), (bf.BF_BF16, bf.BF_NN, 128, 128),
                                               (bf.BF_BF16, bf.BF_NT, 128, 256), (bf.BF_FP32, bf.BF_TN, 40, 36)])
 def test_gemm_of_few_tiles_over_more_than_two_million(dtype, layout, M, N):
