@@ -29,6 +29,15 @@ __device__ __forceinline__ float gelu_grad_f(float u) {
   return fmaf(s, fmaf(-s, w, w), s);     // s (1 + w (1 - s))
 }
 
+// The stored value of the epilogues that write one tensor without reading it.
+template <int EPI>
+__device__ __forceinline__ float epilogue_value(float acc, float bias, float r) {
+  if (EPI == E_BIAS) return acc + bias;
+  if (EPI == E_BIAS_RES) return acc + bias + r;
+  if (EPI == E_GELU_BWD) return acc * gelu_grad_f(r);
+  return acc;
+}
+
 // Applies epilogue EPI to one accumulator value at (m, n) and stores it.
 // TO is the activation type for E_NONE..E_GELU_BWD and float for E_ACCUM.
 template <int EPI, typename TO>
@@ -38,9 +47,9 @@ __device__ __forceinline__ void epilogue_store(float acc, size_t m, size_t n, si
   if (EPI == E_NONE) {
     C[idx] = (TO)acc;
   } else if (EPI == E_BIAS) {
-    C[idx] = (TO)(acc + bias[n]);
+    C[idx] = (TO)epilogue_value<EPI>(acc, bias[n], 0.f);
   } else if (EPI == E_BIAS_RES) {
-    C[idx] = (TO)(acc + bias[n] + (float)R[idx]);
+    C[idx] = (TO)epilogue_value<EPI>(acc, bias[n], (float)R[idx]);
   } else if (EPI == E_BIAS_GELU) {
     // the pre-activation is stored in TO first and the GeLU is taken of the stored
     // value, which is what the backward will read
@@ -48,7 +57,7 @@ __device__ __forceinline__ void epilogue_store(float acc, size_t m, size_t n, si
     C[idx] = u;
     C2[idx] = (TO)gelu_f((float)u);
   } else if (EPI == E_GELU_BWD) {
-    C[idx] = (TO)(acc * gelu_grad_f((float)R[idx]));
+    C[idx] = (TO)epilogue_value<EPI>(acc, 0.f, (float)R[idx]);
   } else {  // E_ACCUM
     C[idx] = (TO)(accumulate ? (float)C[idx] + acc : acc);
   }

@@ -10,8 +10,12 @@
 // matrix pipeline and what the waves issue beside it count: one barrier per k-tile, global -> registers -> LDS with two
 // tiles in flight in registers, a few scalar instructions per tile (the waves of a compute unit share one scalar unit:
 // recomputing addresses for every tile held the 128 x 128 tile at 117 TFLOP/s, advancing them gives 136 at 8192^3; the
-// installed library 154).  Products of an fp32 layer of width 1024 on 512 tokens, vector kernel against this one:
-// 1024 -> 4096 220 -> 57 us, 4096 -> 1024 842 -> 58 us, weight gradient 139 -> 54 us; 256-wide on 128 tokens 34-133 -> 3-8 us.
+// installed library 154), and everything else of a k-tile issued behind an MFMA (see the loop).  Products of an fp32 layer of
+// width 1024 on 512 tokens, vector kernel / this one with the rest of a k-tile in one piece and an epilogue that waits for each
+// of its reads / now: 1024 -> 4096 220 / 56 / 49 us, 4096 -> 1024 842 / 58 / 55, weight gradient 139 / 54 / 46, the whole
+// MLP 306 -> 271; a plain 1024 x 4096 output 116 -> 124 TFLOP/s at K = 1024 and 124 -> 135 at 4096, transposed operands 98 -> 117.  What is
+// left at 512 x 1024 x 4096: two waves per SIMD of one 16 x 16 accumulator each (a 64 x 32 tile of two chains per wave: the same
+// 49 us), rows 16 KB apart in one tile.
 #include <type_traits>
 
 #include "common.h"
@@ -66,7 +70,7 @@ struct Stage {
     }
     __device__ __forceinline__ void next() { p += per_tile; left -= per_tile; }
   };
-  float v[CHUNKS][VEC];
+  typename std::conditional<VEC == 4, f32x4, float>::type v[CHUNKS];
   uint32_t goff, step;
   int loff, kcol;
   __device__ __forceinline__ void init(size_t ld, int tid) {
@@ -78,37 +82,33 @@ struct Stage {
   }
   // k_left: k from the tile's start to the end (not positive past the last tile: the loop's loads have no branch around
   // them, which would make the compiler wait for all of them at once; they return zeros without touching memory)
-  __device__ __forceinline__ void load(const Walk& wk, int k_left) {
+  __amdgpu_buffer_rsrc_t rsrc;
+  uint32_t off;
+  __device__ __forceinline__ void aim(const Walk& wk, int k_left) {
     const long cap = (long)(0x7fffff00 / sizeof(TI));
     const long n = wk.left < cap ? (wk.left > 0 ? wk.left : 0) : cap;
-    __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)wk.p, 0, (int)(n * (long)sizeof(TI)), 0x00020000);
-    const uint32_t off = KCONTIG && kcol >= k_left ? 0x7fffff00u : goff;
-#pragma unroll
-    for (int i = 0; i < CHUNKS; ++i) {
-      if constexpr (VEC == 4) {
-        static_assert(std::is_same<TI, float>::value, "wide chunks are fp32");
-        const f32x4 u = __builtin_bit_cast(f32x4, (u32x4)__builtin_amdgcn_raw_buffer_load_b128(rsrc, off + i * step, 0, 0));
-#pragma unroll
-        for (int j = 0; j < 4; ++j) v[i][j] = u[j];
-      } else if constexpr (std::is_same<TI, float>::value) {
-        v[i][0] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rsrc, off + i * step, 0, 0));
-      } else {
-        v[i][0] = __builtin_bit_cast(float, (uint32_t)(uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rsrc, off + i * step, 0, 0) << 16);
-      }
+    rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)wk.p, 0, (int)(n * (long)sizeof(TI)), 0x00020000);
+    off = KCONTIG && kcol >= k_left ? 0x7fffff00u : goff;
+  }
+  __device__ __forceinline__ void load(int i) {
+    if constexpr (VEC == 4) {
+      static_assert(std::is_same<TI, float>::value, "wide chunks are fp32");
+      v[i] = __builtin_bit_cast(f32x4, (u32x4)__builtin_amdgcn_raw_buffer_load_b128(rsrc, off + i * step, 0, 0));
+    } else if constexpr (std::is_same<TI, float>::value) {
+      v[i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rsrc, off + i * step, 0, 0));
+    } else {
+      v[i] = __builtin_bit_cast(float, (uint32_t)(uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rsrc, off + i * step, 0, 0) << 16);
     }
   }
-  __device__ __forceinline__ void store(float* lds) const {
-#pragma unroll
-    for (int i = 0; i < CHUNKS; ++i) {
-      float* d = lds + loff + i * STEP * LD;
-      if constexpr (VEC == 4 && KCONTIG && MT == 32) {
-        *reinterpret_cast<f32x2*>(d) = f32x2{v[i][0], v[i][2]};
-        *reinterpret_cast<f32x2*>(d + 4) = f32x2{v[i][1], v[i][3]};
-      } else if constexpr (VEC == 4) {
-        *reinterpret_cast<f32x4*>(d) = f32x4{v[i][0], v[i][1], v[i][2], v[i][3]};
-      } else {
-        *d = v[i][0];
-      }
+  __device__ __forceinline__ void store(float* lds, int i) const {
+    float* d = lds + loff + i * STEP * LD;
+    if constexpr (VEC == 4 && KCONTIG && MT == 32) {
+      *reinterpret_cast<f32x2*>(d) = f32x2{v[i][0], v[i][2]};
+      *reinterpret_cast<f32x2*>(d + 4) = f32x2{v[i][1], v[i][3]};
+    } else if constexpr (VEC == 4) {
+      *reinterpret_cast<f32x4*>(d) = v[i];
+    } else {
+      *d = v[i];
     }
   }
   // values of the four MFMA steps of k group kg for row / column r0 + lane % MT
@@ -144,6 +144,34 @@ struct Acc<16> {
   static __device__ __forceinline__ int row(int r, int lane) { return (lane >> 4) * 4 + r; }
 };
 
+// A wave's elements of a row-major M x N matrix, in the order of its accumulators.  The descriptor ends where the matrix does and
+// columns past N are sent past its end: nothing is read or written there, and there is no branch around an access.
+template <typename C, typename TO>
+struct Outer {
+  __amdgpu_buffer_rsrc_t rsrc;
+  int col0, N;
+  uint32_t base, pitch;
+  __device__ __forceinline__ Outer(TO* p, int m0, int n0, int M, int N_, int wm, int wn, int lane) {
+    const long left = (long)(M - m0) * N_ * (long)sizeof(TO);
+    rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)(p + (size_t)m0 * N_), 0, (int)(left < 0x7fffff00 ? left : 0x7fffff00), 0x00020000);
+    N = N_;
+    col0 = n0 + wn * C::NI * C::MT + (lane & (C::MT - 1));
+    pitch = (uint32_t)N_ * sizeof(TO);
+    base = (uint32_t)(wm * C::MI * C::MT + Acc<C::MT>::row(0, lane)) * pitch + (uint32_t)col0 * sizeof(TO);
+  }
+  __device__ __forceinline__ uint32_t off(int i, int j, int r) const {
+    return col0 + j * C::MT < N ? base + (uint32_t)(i * C::MT + Acc<C::MT>::row(r, 0)) * pitch + j * C::MT * (uint32_t)sizeof(TO) : 0x7fffff00u;
+  }
+  __device__ __forceinline__ float load(int i, int j, int r) const {
+    if constexpr (std::is_same<TO, float>::value) return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rsrc, off(i, j, r), 0, 0));
+    else return __builtin_bit_cast(float, (uint32_t)(uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rsrc, off(i, j, r), 0, 0) << 16);
+  }
+  __device__ __forceinline__ void store(TO v, int i, int j, int r) const {
+    if constexpr (std::is_same<TO, float>::value) __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), rsrc, off(i, j, r), 0, 0);
+    else __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(uint16_t, v), rsrc, off(i, j, r), 0, 0);
+  }
+};
+
 template <typename C, typename TI, int VEC, bool AK, bool BKC, int EPI, typename TO>
 __global__ __launch_bounds__(NT) void gemm_f32_kernel(int M, int N, int K, const TI* __restrict__ A, const TI* __restrict__ B,
                                                       TO* __restrict__ Cm, const float* __restrict__ bias, const TO* __restrict__ R,
@@ -171,15 +199,31 @@ __global__ __launch_bounds__(NT) void gemm_f32_kernel(int M, int N, int K, const
 #pragma unroll
       for (int j = 0; j < C::NI; ++j)
 #pragma unroll
-        for (int r = 0; r < C::NR; ++r)
-          f(i, j, r, m0 + (wm * C::MI + i) * C::MT + AC::row(r, lane), n0 + (wn * C::NI + j) * C::MT + (lane & (C::MT - 1)));
+        for (int r = 0; r < C::NR; ++r) f(i, j, r);
   };
-  each([&](int i, int j, int r, int row, int col) {
-    acc[i][j][r] = 0.f;
-    tot[i][j][r] = 0.f;
+  // What the epilogue reads.  Element by element between the stores every read waits for the memory by itself, 10 us of a
+  // product's 57 at 512 x 1024 x 4096; so all are requested together, in front of the k loop where their registers cost
+  // no second workgroup on the compute unit.
+  constexpr bool READS_R = EPI == E_BIAS_RES || EPI == E_GELU_BWD, EARLY_R = C::MI * C::NI <= 2;
+  typedef Outer<C, TO> OT;
+  const OT out(Cm, m0, n0, M, N, wm, wn, lane), out2(EPI == E_BIAS_GELU ? C2 : Cm, m0, n0, M, N, wm, wn, lane);
+  typename AC::T rv[C::MI][C::NI];
+  float bv[C::NI];
+  auto read_r = [&] {
+    const OT from((TO*)R, m0, n0, M, N, wm, wn, lane);
+    each([&](int i, int j, int r) { rv[i][j][r] = from.load(i, j, r); });
+  };
+  auto read_ahead = [&] {
+    each([&](int i, int j, int r) {
+      acc[i][j][r] = 0.f;
+      tot[i][j][r] = 0.f;
+    });
     if constexpr (EPI == E_ACCUM)
-      if (accumulate && row < M && col < N) tot[i][j][r] = (float)Cm[(size_t)row * N + col];
-  });
+      if (accumulate) each([&](int i, int j, int r) { tot[i][j][r] = out.load(i, j, r); });
+#pragma unroll
+    for (int j = 0; j < C::NI; ++j) bv[j] = EPI == E_BIAS || EPI == E_BIAS_RES || EPI == E_BIAS_GELU ? bias[min(out.col0 + j * C::MT, N - 1)] : 0.f;
+    if constexpr (READS_R && EARLY_R) read_r();
+  };
   SA sa[2];  // set t & 1 carries tile t
   SB sb[2];
 #pragma unroll
@@ -193,10 +237,13 @@ __global__ __launch_bounds__(NT) void gemm_f32_kernel(int M, int N, int K, const
   wa.init(A, lda, m0, M, K);
   wb.init(B, ldb, n0, N, K);
   int k_left = K, seg = 0;
-  auto load = [&](auto setc) {
+  typedef std::integral_constant<int, 0> I0;
+  typedef std::integral_constant<int, 1> I1;
+  constexpr int NCA = SA::CHUNKS, NC = SA::CHUNKS + SB::CHUNKS;
+  auto aim = [&](auto setc) {
     constexpr int SET = decltype(setc)::value;
-    sa[SET].load(wa, k_left);
-    sb[SET].load(wb, k_left);
+    sa[SET].aim(wa, k_left);
+    sb[SET].aim(wb, k_left);
     wa.next();
     wb.next();
     k_left -= C::BK;
@@ -209,53 +256,62 @@ __global__ __launch_bounds__(NT) void gemm_f32_kernel(int M, int N, int K, const
       wb.left = seg < n_seg ? wb.left0 : 0;
     }
   };
-  // fragments of the k group being contracted and of the next one
-  f32x4 a[2][C::MI], b[2][C::NI];
-  auto fetch = [&](int buf, int stage, int g) {
-    const float* as = smem + stage * STAGE;
-#pragma unroll
-    for (int i = 0; i < C::MI; ++i) a[buf][i] = SA::frag(as, (wm * C::MI + i) * C::MT, g, lane);
-#pragma unroll
-    for (int j = 0; j < C::NI; ++j) b[buf][j] = SB::frag(as + SA::ELEMS, (wn * C::NI + j) * C::MT, g, lane);
-  };
-  typedef std::integral_constant<int, 0> I0;
-  typedef std::integral_constant<int, 1> I1;
-  auto store = [&](auto setc, int stage) {
+  auto load = [&](auto setc, int c) {
     constexpr int SET = decltype(setc)::value;
-    sa[SET].store(smem + stage * STAGE);
-    sb[SET].store(smem + stage * STAGE + SA::ELEMS);
+    if (c < NCA) sa[SET].load(c);
+    else sb[SET].load(c - NCA);
   };
-  load(I0{});
-  load(I1{});
-  store(I0{}, 0);
-  load(I0{});
-  __syncthreads();
-  fetch(0, 0, 0);
+  auto store = [&](auto setc, int stage, int c) {
+    constexpr int SET = decltype(setc)::value;
+    if (c < NCA) sa[SET].store(smem + stage * STAGE, c);
+    else sb[SET].store(smem + stage * STAGE + SA::ELEMS, c - NCA);
+  };
+  // fragments of the k group being contracted and of the next one
+  constexpr int NF = C::MI + C::NI;
+  f32x4 a[2][C::MI], b[2][C::NI];
+  auto fetch = [&](int buf, int stage, int g, int f) {
+    const float* as = smem + stage * STAGE;
+    if (f < C::MI) a[buf][f] = SA::frag(as, (wm * C::MI + f) * C::MT, g, lane);
+    else b[buf][f - C::MI] = SB::frag(as + SA::ELEMS, (wn * C::NI + f - C::MI) * C::MT, g, lane);
+  };
   // Tiles are requested three iterations before they are contracted (two register sets and an LDS stage).  One barrier per
-  // k-tile, in front of its last group: by then every wave holds that group's fragments in registers and has written
-  // tile kt + 1 into the other stage, so the first fragments of the next tile arrive under the group's MFMAs.
-  auto iter = [&](auto stagec, auto parity) {
-    constexpr int CUR = decltype(stagec)::value, P = decltype(parity)::value;  // LDS stage; fragment buffer of the first group
+  // k-tile, in its last group: by then every wave holds that group's fragments in registers and has written
+  // tile kt + 1 into the other stage, so the first fragments of the next tile arrive under the rest of the group's MFMAs.
+  // A wave is alone on its SIMD or shares it with one more and issues in order, so whatever stands between two groups
+  // leaves the matrix pipeline idle: the next group's fragments, the stores of the next tile and the loads of the
+  // one after go one or two at a time behind an MFMA each (64 cycles, of which its issue takes four).
+  constexpr int NG = 4 * C::MI * C::NI, PRE = NG / 4;                    // MFMAs of a group; those in front of the barrier
+  constexpr int PER = (2 * NC + (C::KW - 1) * (NG - NF) - 1) / ((C::KW - 1) * (NG - NF));  // stores and loads behind one MFMA
+  auto iter = [&](auto stagec) {
+    constexpr int CUR = decltype(stagec)::value;  // LDS stage
     typedef std::integral_constant<int, CUR ^ 1> Next;
-    store(Next{}, CUR ^ 1);
-    load(Next{});
 #pragma unroll
     for (int g = 0; g < C::KW; ++g) {
-      const int buf = (P + g) & 1;
-      if (g + 1 < C::KW) {
-        fetch(buf ^ 1, CUR, g + 1);
-      } else {
-        __builtin_amdgcn_sched_barrier(0);  // the previous group's MFMAs stay in front of the barrier
-        __syncthreads();
-        fetch(buf ^ 1, CUR ^ 1, 0);
+      const int buf = g & 1;
+#pragma unroll
+      for (int m = 0; m < NG; ++m) {
+        const int s = m / (C::MI * C::NI), i = m / C::NI % C::MI, j = m % C::NI;
+        acc[i][j] = AC::mma(a[buf][i][s], b[buf][j][s], acc[i][j]);
+        if (g + 1 < C::KW) {
+          if (m < NF) {
+            fetch(buf ^ 1, CUR, g + 1, m);
+          } else {
+#pragma unroll
+            for (int q = 0; q < PER; ++q) {
+              const int item = (g * (NG - NF) + m - NF) * PER + q;
+              if (item < NC) store(Next{}, CUR ^ 1, item);
+              if (item == NC) aim(Next{});
+              if (item >= NC && item < 2 * NC) load(Next{}, item - NC);
+            }
+          }
+        } else if (m == PRE - 1) {
+          __builtin_amdgcn_sched_barrier(0);
+          __syncthreads();
+#pragma unroll
+          for (int f = 0; f < NF; ++f) fetch(buf ^ 1, CUR ^ 1, 0, f);
+        }
+        __builtin_amdgcn_sched_barrier(0);
       }
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int s = 0; s < 4; ++s)
-#pragma unroll
-        for (int i = 0; i < C::MI; ++i)
-#pragma unroll
-          for (int j = 0; j < C::NI; ++j) acc[i][j] = AC::mma(a[buf][i][s], b[buf][j][s], acc[i][j]);
     }
   };
   int left = nk_seg;  // k-tiles to the end of the segment
@@ -263,24 +319,56 @@ __global__ __launch_bounds__(NT) void gemm_f32_kernel(int M, int N, int K, const
     if constexpr (EPI == E_ACCUM) {
       if (--left == 0) {
         left = nk_seg;
-        each([&](int i, int j, int r, int, int) {
+        each([&](int i, int j, int r) {
           tot[i][j][r] += acc[i][j][r];
           acc[i][j][r] = 0.f;
         });
       }
     }
   };
-  for (int kt = 0; kt < nk; kt += 2) {
-    iter(I0{}, I0{});
+  // requests the first three tiles and lays down the first
+  auto begin = [&](auto stagec) {
+    constexpr int CUR = decltype(stagec)::value;
+    typedef std::integral_constant<int, CUR ^ 1> Next;
+    aim(stagec);
+#pragma unroll
+    for (int c = 0; c < NC; ++c) load(stagec, c);
+    aim(Next{});
+#pragma unroll
+    for (int c = 0; c < NC; ++c) load(Next{}, c);
+    read_ahead();
+#pragma unroll
+    for (int c = 0; c < NC; ++c) store(stagec, CUR, c);
+    aim(stagec);
+#pragma unroll
+    for (int c = 0; c < NC; ++c) load(stagec, c);
+    __syncthreads();
+#pragma unroll
+    for (int f = 0; f < NF; ++f) fetch(0, CUR, 0, f);
+  };
+  static_assert(C::KW % 2 == 0, "an iteration ends with the fragment buffer it began with");
+  begin(I0{});
+  // Left in the middle after an odd number of tiles, and never joined there again: where paths with the loads of one set and
+  // of both in flight meet, the compiler waits for both.
+  for (int kt = nk;;) {
+    iter(I0{});
     segment();
-    if (kt + 1 < nk) {
-      iter(I1{}, std::integral_constant<int, C::KW & 1>{});
-      segment();
-    }
+    if (--kt == 0) break;
+    iter(I1{});
+    segment();
+    if (--kt == 0) break;
   }
-  each([&](int i, int j, int r, int row, int col) {
-    if (row < M && col < N)
-      epilogue_store<EPI, TO>(EPI == E_ACCUM ? tot[i][j][r] : acc[i][j][r], row, col, N, Cm, bias, R, C2, 0);
+  if constexpr (READS_R && !EARLY_R) read_r();
+  each([&](int i, int j, int r) {
+    if constexpr (EPI == E_ACCUM) {
+      out.store(tot[i][j][r], i, j, r);
+    } else if constexpr (EPI == E_BIAS_GELU) {
+      const TO u = (TO)(acc[i][j][r] + bv[j]);
+      out.store(u, i, j, r);
+      out2.store((TO)gelu_f((float)u), i, j, r);
+    } else {
+      out.store((TO)epilogue_value<EPI>(acc[i][j][r], bv[j], READS_R ? rv[i][j][r] : 0.f), i, j, r);
+    }
   });
 }
 

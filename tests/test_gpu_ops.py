@@ -465,6 +465,32 @@ def test_gemm_on_partly_empty_tiles(mode, dtype, M, N, K):
             assert rel_err(to_host(db), ref) <= TOL[mode]
 
 
+@pytest.mark.parametrize("K", [31, 64, 97, 200])
+@pytest.mark.parametrize("M,N", [(1021, 4092), (509, 4092), (500, 1990), (61, 260)])
+def test_fp32_products_of_odd_and_even_numbers_of_k_tiles(M, N, K):
+    """Each of the four fp32 tiles, one to seven k-tiles with remainders, ragged rows and columns: the chain of the plain
+    kernel, so the same bits, with the epilogues that read (all of their reads are requested in front of the first
+    product or behind the last) and with what an accumulated weight gradient starts from, over two segments as well."""
+    A, B = bf_inputs.normal(23, 0, (M, K)), bf_inputs.normal(23, 1, (K, N), 0.05)
+    bias, R = to_dev(bf_inputs.normal(23, 2, (N,), 0.5), False), _guarded(bf_inputs.normal(23, 3, (M, N)), False)
+    gA, gB, gBt, gAt = (_guarded(np.ascontiguousarray(x), False) for x in (A, B, B.T, A.T))
+
+    def both(call):
+        outs = []
+        for kernels in (bf.BF_KERNELS_AUTO, bf.BF_KERNELS_PLAIN):
+            out = torch.full((2, M * N + 128), 7.0, device="cuda")
+            call(kernels, out[0][64:], out[1][64:])
+            outs.append(out)
+        assert bool((outs[0][:, :64] == 7.0).all()) and bool((outs[0][:, 64 + M * N:] == 7.0).all())
+        assert torch.equal(outs[0], outs[1])
+    for layout, op in ((bf.BF_NN, gB), (bf.BF_NT, gBt)):
+        for epi in (bf.BF_EPI_BIAS_RES, bf.BF_EPI_BIAS_GELU, bf.BF_EPI_GELU_BWD):
+            both(lambda kern, o, o2: bf.bf_op_gemm(bf.BF_FP32, kern, layout, epi, M, N, K, gA, op, o, bias=bias, R=R, C2=o2))
+    both(lambda kern, o, o2: bf.bf_op_gemm(bf.BF_FP32, kern, bf.BF_TN, bf.BF_EPI_ACCUM, M, N, K, gAt, gB, o, accumulate=1))
+    if K % 2 == 0:
+        both(lambda kern, o, o2: bf.bf_op_wgrad(bf.BF_FP32, kern, M, N, K // 2, 2, gAt, K // 2 * M, gB, K // 2 * N, o))
+
+
 @pytest.mark.parametrize("mode,dtype", MODES)
 @pytest.mark.parametrize("causal", [1, 0])
 @pytest.mark.parametrize("poison", [False, True])
