@@ -670,23 +670,30 @@ __global__ __launch_bounds__(2 * ROWS * KG, ROWS == 128 && !EDGE ? 2 : 1) void a
 // products per sub-tile and holds one 32 x S_head accumulator set plus its own K or V rows in
 // registers, which leaves room for precomputed fragment addresses: two waves share a SIMD and one
 // role's exponentials overlap the other's MFMAs.
+// EDGE: the three parts of a probability take those registers (S_head 128: 12 scratch reads per sub-tile with them, 3 with
+// addresses from two registers).  QG = 2: 64 keys a workgroup, waves 2, 3, 6 and 7 take the second half of every query tile and
+// their sums are added at the end; bound by the same chain, but the longest key block is half as long.  2 x 1000 tokens, 16 heads of
+// 128, causal, this pass: 112 us, 99 without branches around the score gradients and with the addresses from two registers, 66 with QG = 2.
 constexpr int NTHR_DKV = 512;
 
-template <int D, bool EDGE = false>
+template <int D, bool EDGE = false, int QG = 1>
 __global__ __launch_bounds__(NTHR_DKV, 2) void attn_bwd_dkv_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dctx,
                                                                 const float* __restrict__ lse, const float* __restrict__ delta,
                                                                 bf16_t* __restrict__ dqkv, int S_seq, int N_heads, int S_mb, int causal,
                                                                 float scale, float* __restrict__ colpart) {
+  static_assert(QG == 1 || (QG == 2 && EDGE), "whole lengths have one query group");
+  constexpr int KEYS = WG_ROWS / QG, KGS = KEYS / 32;  // keys of the workgroup, and groups of 32 of them
   __shared__ __attribute__((aligned(16))) bf16_t QOs[2][2][BLK * D];  // Q and dO tiles, double-buffered
   __shared__ __attribute__((aligned(16))) float stat_s[2][2][BLK];    // lse * log2(e) and delta of the tile's queries
   // P of a sub-tile, in bf16 [sub-tile][key group][register half][lane]; EDGE: in fp32 [sub-tile][key group][register quarter][lane]
   __shared__ __attribute__((aligned(16))) bf16_t Ps[EDGE ? 1 : 2][EDGE ? 1 : 4][EDGE ? 1 : 2][EDGE ? 8 : 64 * 8];
-  __shared__ __attribute__((aligned(16))) float Pf[EDGE ? 2 : 1][EDGE ? 4 : 1][EDGE ? 4 : 1][EDGE ? 64 * 4 : 4];
+  __shared__ __attribute__((aligned(16))) float Pf[EDGE ? 2 : 1][EDGE ? KGS : 1][EDGE ? 4 : 1][EDGE ? 64 * 4 : 4];
   __shared__ float dump[EDGE ? 8 * DUMP : 1];
   __shared__ int bad_tile[2];  // per LDS stage: 1 + the last tile staged there with a non-finite Q or dO
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   if (EDGE && tid < 2) bad_tile[tid] = 0;
-  const int kg = w & 3;
+  const int kg = w & (KGS - 1);
+  const int qg = QG == 1 ? 0 : (w >> 1) & 1;  // the half of every query tile that the wave takes
   const bool dk_role = w >= 4;  // wave-uniform
   const int nhb = N_heads * S_mb;
   const int kblk = blockIdx.x / nhb;  // earliest keys see the most queries: those blocks of every head go first
@@ -697,9 +704,9 @@ __global__ __launch_bounds__(NTHR_DKV, 2) void attn_bwd_dkv_kernel(const bf16_t*
   const bf16_t* dob = dctx + (size_t)b * S_seq * h + head * D;
   const float* lrow = lse + ((size_t)b * N_heads + head) * S_seq;
   const float* drow = delta + ((size_t)b * N_heads + head) * S_seq;
-  const int k0 = kblk * WG_ROWS, kw = k0 + 32 * kg, key = kw + (lane & 31);
+  const int k0 = kblk * KEYS, kw = k0 + 32 * kg, key = kw + (lane & 31);
 
-  FragAddr<D> fa;
+  typename std::conditional<EDGE, FragAddrXor<D>, FragAddr<D>>::type fa;
   fa.init(lane);
   bf16x8 kvf[D / 16];  // this wave's K rows (dV role) or V rows (dK role): the B operand of its score-sized product
   load_rowfrags<D>(base + (size_t)(EDGE ? min(key, S_seq - 1) : key) * ld + (dk_role ? 2 * h : h), lane, kvf);
@@ -739,6 +746,7 @@ __global__ __launch_bounds__(NTHR_DKV, 2) void attn_bwd_dkv_kernel(const bf16_t*
   // (the other LDS stage is complete, this one may be overwritten).
   for (int j = jbeg; j < nblk; ++j) {
     const int cur = (j - jbeg) & 1;
+    if constexpr (EDGE) fa.loop();
     const bf16_t* Qs = QOs[cur][0];
     const bf16_t* dOs = QOs[cur][1];
     const float* lse_s = stat_s[cur][0];
@@ -752,12 +760,13 @@ __global__ __launch_bounds__(NTHR_DKV, 2) void attn_bwd_dkv_kernel(const bf16_t*
     if (j + 2 < nblk) fetch(j + 2);
     const int qb = j * BLK;
     // every query of the tile is before this pair's keys: nothing to add (the partner skips as well)
-    const bool skip = (causal && qb + BLK - 1 < kw) || (EDGE && kw >= S_seq);
-    const bool diag = causal && qb < kw + 31;
+    const bool skip = (causal && qb + (QG == 1 ? BLK : 32 * qg + 32) - 1 < kw) || (EDGE && kw >= S_seq);
+    const bool diag = causal && qb + 32 * qg < kw + 31;
     // Sub-tiles T0 .. T1-1 (32 queries each) go through the two stages together; every wave passes the
     // hand-over barrier between the stages, whether it has work or not.
     auto stages = [&](auto t0, auto t1) {
-      constexpr int T0 = decltype(t0)::value, NTT = decltype(t1)::value - T0;
+      constexpr int TC = decltype(t0)::value, NTT = decltype(t1)::value - TC;
+      const int T0 = QG == 1 ? TC : qg;
       bf16x8 pb[NTT][2];
       f32x16 s[NTT];  // S, then P (dV role); dP, then dS (dK role)
 #pragma unroll
@@ -807,17 +816,24 @@ __global__ __launch_bounds__(NTHR_DKV, 2) void attn_bwd_dkv_kernel(const bf16_t*
       if constexpr (EDGE) {
         if (!skip) {
           if (dk_role) {
-            // dS = P (dP - delta); masked pairs by selection (dP may be anything there)
+            // dS = P (dP - delta); masked pairs by selection (dP may be anything there), in a pass of its own: a condition at
+            // every pair became a branch around its LDS reads, 16 waits in a row
+            const bool mask = diag || qb + BLK > S_seq;
 #pragma unroll
             for (int u = 0; u < NTT; ++u) {
               const int t = T0 + u;
 #pragma unroll
               for (int q4 = 0; q4 < 4; ++q4) {
                 const f32x4 p = *reinterpret_cast<const f32x4*>(&Pf[t][kg][q4][lane * 4]);
+                const f32x4 dl = *reinterpret_cast<const f32x4*>(&delta_s[32 * t + acc_row(4 * q4, lane)]);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                  const int r = 4 * q4 + e, i = qb + 32 * t + acc_row(r, lane);
-                  s[u][r] = (causal && key > i) || i >= S_seq ? 0.f : p[e] * (s[u][r] - delta_s[32 * t + acc_row(r, lane)]);
+                for (int e = 0; e < 4; ++e) s[u][4 * q4 + e] = p[e] * (s[u][4 * q4 + e] - dl[e]);
+              }
+              if (mask) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                  const int i = qb + 32 * t + acc_row(r, lane), last = causal ? key : 0;
+                  if (i < last || i >= S_seq) s[u][r] = 0.f;
                 }
               }
             }
@@ -872,7 +888,9 @@ __global__ __launch_bounds__(NTHR_DKV, 2) void attn_bwd_dkv_kernel(const bf16_t*
     typedef std::integral_constant<int, 0> T_0;
     typedef std::integral_constant<int, 1> T_1;
     typedef std::integral_constant<int, 2> T_2;
-    if constexpr (D == 128 && !EDGE) {
+    if constexpr (QG == 2) {
+      stages(T_0{}, T_1{});
+    } else if constexpr (D == 128 && !EDGE) {
       // both sub-tiles together: two independent accumulators in the score-sized products, one
       // hand-over barrier per tile (measured: 2 % faster than one sub-tile at a time at S_head 128,
       // 7 % slower at S_head 64)
@@ -883,11 +901,29 @@ __global__ __launch_bounds__(NTHR_DKV, 2) void attn_bwd_dkv_kernel(const bf16_t*
     }
     __syncthreads();
   }
+  if constexpr (QG == 2) {
+    // the second query group's sums, lane to lane (the tiles are free: the loop ended on a barrier)
+    constexpr int NV = D / 2;
+    static_assert(4 * NV * 64 * 4 <= sizeof(QOs), "the hand-over does not fit");
+    float* hb = reinterpret_cast<float*>(&QOs[0][0][0]) + ((dk_role ? 2 : 0) + kg) * NV * 64 + lane;
+    if (qg == 1) {
+#pragma unroll
+      for (int dt = 0; dt < D / 32; ++dt)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) hb[(dt * 16 + r) * 64] = acc[dt][r];
+    }
+    __syncthreads();
+    if (qg == 1) return;
+#pragma unroll
+    for (int dt = 0; dt < D / 32; ++dt)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[dt][r] += hb[(dt * 16 + r) * 64];
+  }
   if (EDGE && key >= S_seq) return;
   bf16_t* out = dqkv + ((size_t)b * S_seq + key) * ld + head * D;
   if (dk_role) store_rows<D>(acc, out + h, lane, scale);
   else store_rows<D>(acc, out + 2 * h, lane, 1.0f);
-  if (colpart) {
+  if (!EDGE && colpart) {
     // row (b, key block) of the partial column sums of [dK | dV], [S_mb * S_seq / 128][2 N_heads * D]
     float* red = reinterpret_cast<float*>(&QOs[0][0][0]);
     wave_colsum<D>(acc, dk_role ? scale : 1.0f, red + (size_t)w * 4 * (D / 2), lane);
@@ -1011,7 +1047,19 @@ bf_status bwd_edge(int S_mb, int S_seq, int N_heads, int causal, const void* qkv
     attn_bwd_dq_general_kernel<D, 64, true, 2><<<(unsigned)((S_seq + 63) / 64) * N_heads * S_mb, 256, 0, st>>>((const bf16_t*)qkv, (const bf16_t*)ctx, (const bf16_t*)dctx, lse, delta, (bf16_t*)dqkv, S_seq, N_heads, S_mb, causal, scale, nullptr);
   else
     attn_bwd_dq_general_kernel<D, 128, true, 1><<<grid, NTHR, 0, st>>>((const bf16_t*)qkv, (const bf16_t*)ctx, (const bf16_t*)dctx, lse, delta, (bf16_t*)dqkv, S_seq, N_heads, S_mb, causal, scale, nullptr);
-  attn_bwd_dkv_kernel<D, true><<<grid, NTHR_DKV, 0, st>>>((const bf16_t*)qkv, (const bf16_t*)dctx, lse, delta, (bf16_t*)dqkv, S_seq, N_heads, S_mb, causal, scale, nullptr);
+  // Two query groups (64 keys a workgroup, half of every query tile each) where the chip does not fill: a workgroup has a compute
+  // unit to itself and takes 0.52 (S_head 128) or 0.6 (64) of the time of 128 keys with one group, so for bidirectional
+  // launches the rounds of 256 decide, and causal ones, whose longest key block is twice the mean, gain more.  Backward, one
+  // group / two, us, S_head 128: causal, 1000 tokens, 128 blocks of 128 keys 121 / 81, 256 136 / 104, 384 148 / 146, from 512
+  // level; bidirectional, 1000 tokens, 128 blocks 123 / 85, 256 (two rounds) 152 / 154, 384 (three for two) 291 / 254, 500 tokens,
+  // 192 blocks 84 / 86.  S_head 64: causal, 700 tokens, 192 blocks 58 / 46, 288 67 / 64, 384 69 / 74; bidirectional, 128
+  // blocks 74 / 58, 192 65 / 75, 384 in three rounds for two 115 / 112, 576 in five for three 170 / 179.
+  const long grid2 = (long)((S_seq + 63) / 64) * N_heads * S_mb, rounds1 = ((long)grid + 255) / 256, rounds2 = (grid2 + 255) / 256;
+  const bool two_query_groups = causal ? D == 128 || grid <= 288 : D == 128 ? rounds2 < 2 * rounds1 : 5 * rounds2 <= 8 * rounds1;
+  if (two_query_groups && grid2 < (1l << 31))
+    attn_bwd_dkv_kernel<D, true, 2><<<(unsigned)grid2, NTHR_DKV, 0, st>>>((const bf16_t*)qkv, (const bf16_t*)dctx, lse, delta, (bf16_t*)dqkv, S_seq, N_heads, S_mb, causal, scale, nullptr);
+  else
+    attn_bwd_dkv_kernel<D, true><<<grid, NTHR_DKV, 0, st>>>((const bf16_t*)qkv, (const bf16_t*)dctx, lse, delta, (bf16_t*)dqkv, S_seq, N_heads, S_mb, causal, scale, nullptr);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) { set_error("attention_bwd_mfma launch failed: %s", hipGetErrorString(e)); return BF_EDEVICE; }
   return BF_OK;

@@ -320,6 +320,29 @@ struct FragAddr {
   }
 };
 
+// The same interface from two registers: chunk and key occupy different bits, so every offset is the first one of its kind XOR a
+// constant (eight rows on flips bit 1 of the key), one instruction with the addition of the tile's address.  `loop` at the
+// head of a loop keeps the compiler from computing them all in front of it, into the registers that this form is to save.
+template <int D>
+struct FragAddrXor {
+  int k0, t0;
+  __device__ __forceinline__ void init(int lane) {
+    const int tt = lane & 15, blk = lane >> 4;
+    k0 = swz<D>(lane & 31, 8 * (lane >> 5));
+    t0 = swz<D>(4 * (blk >> 1) + (tt >> 2), 16 * (blk & 1) + 4 * (tt & 3));
+  }
+  __device__ __forceinline__ void loop() { asm volatile("" : "+v"(k0), "+v"(t0)); }
+  __device__ __forceinline__ bf16x8 frag_k(const bf16_t* tile, int row0, int kk) const {
+    return *reinterpret_cast<const bf16x8*>(tile + row0 * D + (k0 ^ (16 * kk)));
+  }
+  __device__ __forceinline__ bf16x8 frag_t(const bf16_t* tile, int rowbase, int dt) const {
+    typedef s16x4 __attribute__((address_space(3))) * lds_v4;
+    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4)(tile + rowbase * D + (t0 ^ (32 * dt))));
+    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4)(tile + (rowbase + 8) * D + (t0 ^ (32 * dt) ^ 16)));
+    return __builtin_bit_cast(bf16x8, (s16x8)__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+  }
+};
+
 // The same interface computing every address on the fly: for kernels that have no 16 registers to spare.
 template <int D>
 struct FragAddrLive {

@@ -690,6 +690,21 @@ def test_attention_of_any_length_keeps_the_bits_of_probabilities(causal, S_mb, S
         assert off[0] <= 1.02 * off[1] + 1e-6, (name, off)
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("causal,S_mb,S_seq,a", [(1, 2, 31, 3), (1, 1, 97, 2), (0, 1, 161, 2), (1, 1, 607, 2), (0, 2, 200, 32), (0, 1, 200, 65), (0, 1, 300, 96),
+                                                 (1, 1, 140, 144), (1, 1, 140, 150), (0, 1, 140, 256)])
+def test_attention_backward_with_one_and_two_query_groups(d, causal, S_mb, S_seq, a):
+    """The dK / dV kernel for any length with 64 and with 128 keys a workgroup, on both sides of what decides (rounds of 256
+    workgroups, 288 causal blocks at S_head 64), last blocks of 31, 33 and 64 keys and last query tiles with an empty second half.
+    Against the plain kernels: fp32 sums in another order and one bf16 rounding on either side, 2^-7."""
+    h = a * d
+    qkv, dctx = (bf_inputs.normal(47, i, (S_mb, S_seq, n * h), bf16=True) for i, n in ((0, 3), (1, 1)))
+    got = _attention_by_both(S_mb, S_seq, a, d, causal, qkv, dctx)
+    for i in range(3):
+        x, y = (t[2][..., i * h:(i + 1) * h].astype(np.float64) for t in got)
+        assert np.isfinite(x).all() and rel_err(x, y) <= 2.0 ** -7, i
+
+
 @pytest.mark.parametrize("S_mb,S_seq,a", [(1, 384, 90), (1, 640, 60), (2, 1024, 20)])
 def test_attention_backward_with_one_key_block_to_a_unit(S_mb, S_seq, a):
     """Heads of 64, causal, 257 to 340 blocks: the dK / dV kernel in its form of one workgroup per compute unit.  A handful of
