@@ -79,6 +79,7 @@ void set_error(const char* fmt, ...);
 
 // ---- kernel launchers (each returns BF_OK / BF_EINVAL / BF_EDEVICE) -------------------
 // dtype: BF_FP32 or BF_BF16 (activation storage type).
+bf_status gemm_check(int layout, int epi, const GemmArgs& a);
 bf_status gemm_plain(int dtype, int layout, int epi, const GemmArgs& a, hipStream_t st);
 // true if the MFMA kernel covers this problem (bf16, sizes multiples of its tiles)
 bool gemm_mfma_supported(int layout, int epi, int M, int N, int K);
@@ -95,6 +96,10 @@ bf_status gemm_mfma_edge(int layout, int epi, const GemmArgs& a, hipStream_t st)
 bool gemm_f32_supported(int layout, int epi, const GemmArgs& a);
 bool gemm_f32_better(int epi, const GemmArgs& a);  // than the plain kernel
 bf_status gemm_f32(int dtype, int layout, int epi, const GemmArgs& a, hipStream_t st);
+// fp32 weight-gradient products that do not depend on each other in one launch
+constexpr int GEMM_F32_BATCH = 16;  // at most
+bool gemm_f32_batch_supported(const GemmArgs* a, int n);
+bf_status gemm_f32_batch(const GemmArgs* a, int n, hipStream_t st);
 // tile (rows x columns of C per workgroup) the MFMA kernel runs an unsplit product of this shape on; 0 x 0 if none fits
 void gemm_mfma_tile(int layout, int epi, int M, int N, int* bm, int* bn);
 // Slices the matrix-core path would cut the contraction of this forward / dgrad product into (1: no split).

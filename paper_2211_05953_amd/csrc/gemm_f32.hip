@@ -172,11 +172,11 @@ struct Outer {
   }
 };
 
+// one tile of a product
 template <typename C, typename TI, int VEC, bool AK, bool BKC, int EPI, typename TO>
-__global__ __launch_bounds__(NT) void gemm_f32_kernel(int M, int N, int K, const TI* __restrict__ A, const TI* __restrict__ B,
-                                                      TO* __restrict__ Cm, const float* __restrict__ bias, const TO* __restrict__ R,
-                                                      TO* __restrict__ C2, int accumulate, int tiles_m, int n_seg, size_t seg_a,
-                                                      size_t seg_b) {
+__device__ __forceinline__ void tile_product(int lin, int M, int N, int K, const TI* __restrict__ A, const TI* __restrict__ B, TO* __restrict__ Cm,
+                                             const float* __restrict__ bias, const TO* __restrict__ R, TO* __restrict__ C2, int accumulate,
+                                             int tiles_m, int n_seg, size_t seg_a, size_t seg_b) {
   typedef Stage<TI, VEC, AK, C::BM, C::BK, C::MT> SA;
   typedef Stage<TI, VEC, BKC, C::BN, C::BK, C::MT> SB;
   typedef Acc<C::MT> AC;
@@ -184,10 +184,6 @@ __global__ __launch_bounds__(NT) void gemm_f32_kernel(int M, int N, int K, const
   __shared__ __attribute__((aligned(16))) float smem[2 * STAGE];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int wm = w % C::WM, wn = w / C::WM;
-  // XCD x (workgroups go to the eight round-robin) gets a contiguous range of the tile order, so that the tiles that
-  // share its L2 share operand panels
-  int lin = blockIdx.x;
-  if ((gridDim.x & 7) == 0) lin = (lin & 7) * (int)(gridDim.x >> 3) + (lin >> 3);
   const int m0 = lin % tiles_m * C::BM, n0 = lin / tiles_m * C::BN;
   const size_t lda = AK ? K : M, ldb = BKC ? K : N;
   // Sums of one segment; of all segments so far (weight gradients: one chain per micro-batch, added in order to what the
@@ -372,6 +368,42 @@ __global__ __launch_bounds__(NT) void gemm_f32_kernel(int M, int N, int K, const
   });
 }
 
+// XCD x (workgroups go to the eight round-robin) gets a contiguous range of the tile order, so that the tiles that
+// share its L2 share operand panels
+__device__ __forceinline__ int tile_of_block() {
+  const int lin = blockIdx.x;
+  return (gridDim.x & 7) == 0 ? (lin & 7) * (int)(gridDim.x >> 3) + (lin >> 3) : lin;
+}
+
+template <typename C, typename TI, int VEC, bool AK, bool BKC, int EPI, typename TO>
+__global__ __launch_bounds__(NT) void gemm_f32_kernel(int M, int N, int K, const TI* __restrict__ A, const TI* __restrict__ B,
+                                                      TO* __restrict__ Cm, const float* __restrict__ bias, const TO* __restrict__ R,
+                                                      TO* __restrict__ C2, int accumulate, int tiles_m, int n_seg, size_t seg_a,
+                                                      size_t seg_b) {
+  tile_product<C, TI, VEC, AK, BKC, EPI, TO>(tile_of_block(), M, N, K, A, B, Cm, bias, R, C2, accumulate, tiles_m, n_seg, seg_a, seg_b);
+}
+
+// The weight gradients of a stage in one launch.  In a small stack each has 64 to 256 tiles of a few microseconds, of which a
+// launch, the first loads and the last stores are the most: one after the other they leave most of the chip idle.
+struct Batch {
+  struct Item {
+    const float *A, *B;
+    float* C;
+    size_t seg_a, seg_b;
+    int M, N, K, n_seg, accumulate, tiles_m, end;  // end: tiles of the items up to and with this one
+  } it[GEMM_F32_BATCH];
+};
+
+template <typename C>
+__global__ __launch_bounds__(NT) void gemm_f32_batch_kernel(Batch b) {
+  const int lin = tile_of_block();
+  int p = 0, first = 0;
+  while (lin >= b.it[p].end) first = b.it[p++].end;
+  const Batch::Item& t = b.it[p];
+  tile_product<C, float, 4, false, false, E_ACCUM, float>(lin - first, t.M, t.N, t.K, t.A, t.B, t.C, nullptr, nullptr, nullptr, t.accumulate, t.tiles_m, t.n_seg,
+                                                          t.seg_a, t.seg_b);
+}
+
 typedef Cfg<2, 2, 2, 2, 32, 32> CLarge;  // 128 x 128
 typedef Cfg<2, 2, 2, 1, 32, 32> CTall;   // 128 x 64
 typedef Cfg<2, 2, 1, 1, 32, 32> CMid;    // 64 x 64
@@ -387,13 +419,15 @@ void launch(const GemmArgs& a, hipStream_t st) {
 
 // The matrix pipeline bounds every tile, so a product takes as long as the compute unit with the most tiles: tiles per
 // unit (of 256) times the tile's area, plus what the smaller tiles lose between their k-tiles.
-inline int choose(int M, int N) {
+// n products of one launch share the rounds.
+inline int choose(const GemmArgs* a, int n) {
   const int bm[4] = {128, 128, 64, 32}, bn[4] = {128, 64, 64, 32};
   const double rate[4] = {1.0, 0.95, 0.93, 0.78};
   int best = 0;
   double best_t = 0;
   for (int i = 0; i < 4; ++i) {
-    const long t = (long)((M + bm[i] - 1) / bm[i]) * ((N + bn[i] - 1) / bn[i]);
+    long t = 0;
+    for (int p = 0; p < n; ++p) t += (long)((a[p].M + bm[i] - 1) / bm[i]) * ((a[p].N + bn[i] - 1) / bn[i]);
     const double cost = (double)((t + 255) / 256) * bm[i] * bn[i] / rate[i];
     if (i == 0 || cost < best_t) { best = i; best_t = cost; }
   }
@@ -402,7 +436,7 @@ inline int choose(int M, int N) {
 
 template <typename TI, int VEC, bool AK, bool BKC, int EPI, typename TO>
 void by_tile(const GemmArgs& a, hipStream_t st) {
-  switch (choose(a.M, a.N)) {
+  switch (choose(&a, 1)) {
     case 0: launch<CLarge, TI, VEC, AK, BKC, EPI, TO>(a, st); break;
     case 1: launch<CTall, TI, VEC, AK, BKC, EPI, TO>(a, st); break;
     case 2: launch<CMid, TI, VEC, AK, BKC, EPI, TO>(a, st); break;
@@ -456,14 +490,64 @@ bool gemm_f32_better(int epi, const GemmArgs& a) {
   return a.K >= k_min || a.n_seg > 1 || (long)a.M * a.N < 2000000;
 }
 
+namespace {
+
+template <typename C>
+void launch_batch(const GemmArgs* a, int n, hipStream_t st) {
+  Batch b{};
+  int end = 0;
+  for (int p = 0; p < n; ++p) {
+    const int tm = (a[p].M + C::BM - 1) / C::BM, tn = (a[p].N + C::BN - 1) / C::BN;
+    end += tm * tn;
+    b.it[p] = {(const float*)a[p].A, (const float*)a[p].B, (float*)a[p].C, a[p].seg_stride_a, a[p].seg_stride_b,
+               a[p].M, a[p].N, a[p].K, a[p].n_seg > 1 ? a[p].n_seg : 1, a[p].accumulate, tm, end};
+  }
+  gemm_f32_batch_kernel<C><<<(unsigned)end, NT, 0, st>>>(b);
+}
+
+// whole 16-byte chunks along the fast dimension of both operands
+bool wide_chunks(int layout, const GemmArgs& a) {
+  const int ra = layout == L_TN ? a.M : a.K, rb = layout == L_NT ? a.K : a.N;
+  const size_t seg = a.n_seg > 1 ? a.seg_stride_a | a.seg_stride_b : 0;
+  return ((ra | rb) & 3) == 0 && (seg & 3) == 0 && (((uintptr_t)a.A | (uintptr_t)a.B) & 15) == 0;
+}
+
+}  // namespace
+
+// Every product of the batch would run here by itself, from wide chunks, and the tiles of all can be counted.
+bool gemm_f32_batch_supported(const GemmArgs* a, int n) {
+  long tiles = 0;
+  for (int p = 0; p < n; ++p) {
+    if (!gemm_f32_supported(L_TN, E_ACCUM, a[p]) || !gemm_f32_better(E_ACCUM, a[p]) || !wide_chunks(L_TN, a[p]) || a[p].colsum) return false;
+    tiles += (long)((a[p].M + 31) / 32) * ((a[p].N + 31) / 32);
+  }
+  return n >= 1 && n <= GEMM_F32_BATCH && tiles < (1l << 31);
+}
+
+// The same bits as one launch each.  Stage of two fp32 layers of width 256 over 4 x 128 tokens: eight
+// launches 54 us, one 24.
+bf_status gemm_f32_batch(const GemmArgs* a, int n, hipStream_t st) {
+  if (!gemm_f32_batch_supported(a, n)) { set_error("gemm_f32_batch: shapes not supported"); return BF_EINVAL; }
+  for (int p = 0; p < n; ++p) {
+    const bf_status s = gemm_check(L_TN, E_ACCUM, a[p]);
+    if (s != BF_OK) return s;
+  }
+  switch (choose(a, n)) {
+    case 0: launch_batch<CLarge>(a, n, st); break;
+    case 1: launch_batch<CTall>(a, n, st); break;
+    case 2: launch_batch<CMid>(a, n, st); break;
+    default: launch_batch<CSmall>(a, n, st); break;
+  }
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) { set_error("gemm_f32_batch launch failed: %s", hipGetErrorString(e)); return BF_EDEVICE; }
+  return BF_OK;
+}
+
 bf_status gemm_f32(int dtype, int layout, int epi, const GemmArgs& a, hipStream_t st) {
   if (!gemm_f32_supported(layout, epi, a)) { set_error("gemm_f32: shape not supported"); return BF_EINVAL; }
   if (dtype == BF_BF16) return by_layout<bf16_t, 1>(layout, epi, a, st);
-  // whole 16-byte chunks along the fast dimension of both operands, or element by element
-  const int ra = layout == L_TN ? a.M : a.K, rb = layout == L_NT ? a.K : a.N;
-  const size_t seg = a.n_seg > 1 ? a.seg_stride_a | a.seg_stride_b : 0;
-  const bool vec = ((ra | rb) & 3) == 0 && (seg & 3) == 0 && (((uintptr_t)a.A | (uintptr_t)a.B) & 15) == 0;
-  return vec ? by_layout<float, 4>(layout, epi, a, st) : by_layout<float, 1>(layout, epi, a, st);
+  // element by element where there are no wide chunks
+  return wide_chunks(layout, a) ? by_layout<float, 4>(layout, epi, a, st) : by_layout<float, 1>(layout, epi, a, st);
 }
 
 }  // namespace bf

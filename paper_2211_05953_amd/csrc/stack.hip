@@ -610,12 +610,36 @@ bf_status layer_backward(bf_stack* s, int layer, int S_mb, const void* x, const 
   return BF_OK;
 }
 
+// Weight-gradient products that are ready together (those of a stage): in one launch each, or, in fp32, up to 16 in one.
+struct WgradList {
+  GemmArgs a[GEMM_F32_BATCH];
+  int n = 0;
+};
+bf_status run_wgrads(bf_stack* s, WgradList& w, hipStream_t st) {
+  const int n = w.n;
+  w.n = 0;
+  if (n > 1 && s->cfg.dtype == BF_FP32 && s->cfg.kernels == BF_KERNELS_AUTO && gemm_f32_batch_supported(w.a, n)) {
+    double flops = 0, bytes = 0;
+    for (int i = 0; i < n; ++i) {
+      const double seg = w.a[i].n_seg > 1 ? w.a[i].n_seg : 1, m = w.a[i].M, nn = w.a[i].N, k = w.a[i].K * seg;
+      flops += 2.0 * m * nn * k;
+      bytes += 4.0 * (m * k + k * nn + m * nn);
+    }
+    s->group_now = n;  // counted as the launches it stands for
+    const bf_status r = timed(s, BF_K_GEMM_WGRAD, flops, bytes, st, [&] { return gemm_f32_batch(w.a, n, st); });
+    s->group_now = 1;
+    return r;
+  }
+  for (int i = 0; i < n; ++i) BF_TRY(p_gemm(s, L_TN, E_ACCUM, w.a[i], st));
+  return BF_OK;
+}
+
 // The four weight-matrix gradients of one layer as products over all N_mb micro-batches at once
 // (breadth-first only: every micro-batch of the stage has been through its backward, Sec. 4.2).
 // G = sum_m X_m^T dY_m is one long contraction, written once: no read-modify-write of the fp32
 // main-grad per micro-batch.  dy0 / dy_stride: the layer's incoming gradients, micro-batch 0 and
 // the distance (elements) between micro-batches.
-bf_status layer_wgrad_fused(bf_stack* s, int layer, int ls, int S_mb, int N_mb, const void* dy0, size_t dy_stride,
+bf_status layer_wgrad_fused(bf_stack* s, int layer, int ls, int S_mb, int N_mb, const void* dy0, size_t dy_stride, WgradList& w,
                             hipStream_t st) {
   const bf_config& c = s->cfg;
   const int T = S_mb * c.S_seq, h = c.S_hidden, f = c.S_mlp;
@@ -635,7 +659,8 @@ bf_status layer_wgrad_fused(bf_stack* s, int layer, int ls, int S_mb, int N_mb, 
     g.n_seg = N_mb;
     g.seg_stride_a = sa / esz;
     g.seg_stride_b = sb / esz;
-    return p_gemm(s, L_TN, E_ACCUM, g, st);
+    w.a[w.n++] = g;
+    return w.n == GEMM_F32_BATCH ? run_wgrads(s, w, st) : BF_OK;
   };
   BF_TRY(run(f, h, R0.g, r.g, dy0, dy_stride * esz, G(BF_W_FC2)));
   BF_TRY(run(h, f, R0.c, r.c, K0.du, t.du, G(BF_W_FC1)));
@@ -1136,14 +1161,16 @@ static bf_status run_rank_step(bf_stack* s, int schedule, int N_PP, int rank, bo
           BF_HIP_CHECK(hipStreamWaitEvent(os, s->ev_chain[1], 0));
         }
         // every micro-batch of the stage is through: one weight-gradient product per matrix
+        WgradList wgrads;
         for (int l = l1 - 1; l >= l0; --l) {
           const void* dy0;
           size_t stride;
           if (is_top(l)) { dy0 = (const char*)dy + io_off(ls, 0); stride = io_stride / es; }
           else if (l == l1 - 1) { dy0 = bhand(ls, 0); stride = s->Lo.y_bytes / es; }
           else { dy0 = grad_rec(s, l - l0, 0).dy; stride = tmp_sizes(c).ping / es; }
-          BF_TRY(layer_wgrad_fused(s, l, l - l0, S_mb, N_mb, dy0, stride, os));
+          BF_TRY(layer_wgrad_fused(s, l, l - l0, S_mb, N_mb, dy0, stride, wgrads, os));
         }
+        BF_TRY(run_wgrads(s, wgrads, os));
         if (chains == 2) {
           // the two chains' bias / LayerNorm gradient sums become one, always in this order
           const int small[8] = {BF_LN1_G, BF_LN1_B, BF_B_QKV, BF_B_O, BF_LN2_G, BF_LN2_B, BF_B_FC1, BF_B_FC2};

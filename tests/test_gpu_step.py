@@ -243,6 +243,25 @@ def test_micro_batches_of_a_stage_share_launches(mode, dtype, Lyr, N_loop, h, a,
     st.close()
 
 
+@pytest.mark.parametrize("Lyr,h,a,f,S_seq,N_mb", [(5, 96, 2, 200, 40, 3), (10, 256, 4, 1024, 33, 2), (5, 512, 8, 2048, 64, 2)])
+def test_weight_gradients_of_a_stage_share_a_launch(Lyr, h, a, f, S_seq, N_mb):
+    """fp32: the weight gradients of a stage in one launch of up to 16, here of 20 or 40 (one stage), against those of one layer at
+    a time (4 a launch, on other tiles) and against single products, one per micro-batch, each added to the one before: the same
+    chains, so the same bits, for sizes of whole and partly empty tiles."""
+    params = bf_inputs.make_params(47, Lyr, h, f, bf16=False)
+    x, dy = bf_inputs.make_batch(47, N_mb, 1, S_seq, h, bf16=False)
+    runs = [_run_gpu(bf.make_config(h, a, f, S_seq, Lyr, N_mb, 1, dtype=bf.BF_FP32, fuse_wgrad=1, N_loop_min=1), params, x, dy,
+                     bf.BF_SCHED_BF, loop, N_mb, 1) for loop in (1, Lyr)]
+    for l in range(Lyr):
+        for name in ("w_qkv", "w_o", "w_fc1", "w_fc2"):
+            assert np.array_equal(runs[0]["grads"][l][name], runs[1]["grads"][l][name]), (l, name)
+    # each product by itself: with fuse_wgrad = 0 every micro-batch adds its chain to the main-grad, in order
+    one = _run_gpu(bf.make_config(h, a, f, S_seq, Lyr, N_mb, 1, dtype=bf.BF_FP32, fuse_wgrad=0), params, x, dy, bf.BF_SCHED_BF, 1, N_mb, 1)
+    for l in range(Lyr):
+        for name in ("w_qkv", "w_o", "w_fc1", "w_fc2"):
+            assert np.array_equal(runs[0]["grads"][l][name], one["grads"][l][name]), (l, name)
+
+
 MATRICES = ("w_qkv", "w_o", "w_fc1", "w_fc2")
 
 
