@@ -673,7 +673,7 @@ __global__ __launch_bounds__(2 * ROWS * KG, ROWS == 128 && !EDGE ? 2 : 1) void a
 // EDGE: the three parts of a probability take those registers (S_head 128: 12 scratch reads per sub-tile with them, 3 with
 // addresses from two registers).  QG = 2: 64 keys a workgroup, waves 2, 3, 6 and 7 take the second half of every query tile and
 // their sums are added at the end; bound by the same chain, but the longest key block is half as long.  2 x 1000 tokens, 16 heads of
-// 128, causal, this pass: 112 us, about 100 without branches around the score gradients and with the addresses from two registers, 66 with QG = 2.
+// 128, causal, this pass: 112 us, about 100 without branches around the score gradients and with the addresses from two registers, 68 with QG = 2.
 constexpr int NTHR_DKV = 512;
 
 template <int D, bool EDGE = false, int QG = 1>
