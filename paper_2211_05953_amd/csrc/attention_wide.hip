@@ -41,10 +41,12 @@ __device__ __forceinline__ uint32_t pack2(float a, float b) {
 // The products, in assembly where 64 rows fill the registers: left to itself the compiler wants every accumulator of the kernel
 // in one half of the register file, and they are more than a half.  mfma_v keeps scores where the vector unit reads them,
 // mfma_a the sums over tiles in the other half (ASM false: the builtin).  What the compiler then does not see: a product
-// must not follow within two cycles of vector instructions that write its operands (`nop` keeps them apart: for the first
-// products on new operands, and everywhere outside the loops over tiles, where the compiler may move registers about;
-// tests/test_host_logic.py looks for others in the listing), and a score must not be read within 12 issue slots of its
-// last product (two further products lie between, 16 slots).  Loads into the operands are waited for as usual.
+// must have two issue slots between it and vector instructions that write its operands (`nop` keeps them apart: for the first
+// products on new operands, and everywhere outside the loops over tiles, where the compiler may move registers about),
+// there must be 12 between a score's last product and its use (two further products, 16 slots, lie between), and 7 between
+// a product whose third operand is not its result and anything that writes that operand's registers: it is read over the
+// product's first 8 (`still_read` behind the next product keeps them from being given away at once).  tests/test_host_logic.py
+// looks for all three in the listing.  Loads into the operands are waited for as usual.
 template <bool ASM>
 __device__ __forceinline__ void mfma_v(f32x16& c, const bf16x8& a, const bf16x8& b, bool first, const f32x16& init, bool nop) {
   if constexpr (!ASM) c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, first ? init : c, 0, 0, 0);
@@ -58,6 +60,7 @@ __device__ __forceinline__ void mfma_a(f32x16& c, const bf16x8& a, const bf16x8&
   else if (nop) asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
   else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
 }
+__device__ __forceinline__ void still_read(const f32x16& c) { asm volatile("" :: "v"(c)); }
 template <bool ASM>
 __device__ __forceinline__ void zero_acc(f32x16& c) {
   c = zero16();
@@ -263,9 +266,11 @@ __global__ __launch_bounds__(256, G == 1 ? 2 : 1) void attn_bwd_dkv_wide_kernel(
           constexpr int g = decltype(gc)::value;
           if constexpr (p < NK) {
             mfma_v<ASM>(s[g], f, kf[g][p], p == 0, init, DIAG);
+            if constexpr (ASM && p == 1 && g == 0) still_read(init);
           } else if constexpr (p < 2 * NK) {
             constexpr int k = p - NK;
             mfma_v<ASM>(dp[g], f, vf[g][k], k == 0, init, DIAG);
+            if constexpr (ASM && k == 1 && g == 0) still_read(init);
             __builtin_amdgcn_sched_barrier(0);
             share<0, RB, k, NK>([&](auto rc) { exp_row(g, rc); });
           } else if constexpr (p < 2 * NK + NC) {

@@ -157,49 +157,122 @@ def test_tile_choice_invariants_without_a_device():
     assert bf.bf_op_gemm_tile(bf.BF_TN, bf.BF_EPI_NONE, 128, 128, 64) is None      # the weight-gradient layout stores fp32
 
 
+def _listing_distances(text, kernel):
+    """Products and violations in a listing's kernels whose name contains `kernel`.  Every instruction is taken at the earliest it
+    can issue (a slot each, a product every eight), along every path through the branches: a vector instruction writes an
+    operand of a product less than two slots in front of it; anything but the next product of the same sum touches a result with
+    less than 12 slots between; an instruction other than a product writes a register of a third operand with less than 7 between,
+    while the product may still be reading it.  (The numbers are what the compiler's own hazard pass keeps for this product.)"""
+    WRITTEN, READY, READ, EIGHT = 2, 12, 7, 8
+
+    def regs(op):
+        m = re.match(r"-?\|?([av])(?:\[(\d+):(\d+)\]|(\d+)\b)", op)
+        if not m:
+            return frozenset()
+        lo, hi = (m.group(2), m.group(3)) if m.group(2) else (m.group(4), m.group(4))
+        return frozenset((m.group(1), r) for r in range(int(lo), int(hi) + 1))
+
+    kernels, code = [], None
+    for line in text.split("\n"):
+        m = re.match(r"(_Z\w+):", line)
+        if m:
+            code = []
+            if kernel in m.group(1):
+                kernels.append(code)
+        t = line.split(";")[0].strip()
+        if code is not None and t and (not t.startswith(".") or re.match(r"\.LBB\w+:$", t)):
+            op, _, rest = t.partition(" ")
+            code.append((t, op, rest.strip(), [regs(a) for a in re.split(r",\s*", rest.strip())]))
+
+    def step(state, ins):
+        """State after one instruction, and what it violates.  Per register the slots still to pass before a product may use
+        it, before anything may touch it and before anything else may write it; the slots until the next product can issue."""
+        written, ready, read, free = state
+        t, op, rest, args = ins
+        bad, took, w, r, c, f = [], 1, {}, {}, {}, 0
+        if op == "s_nop":
+            took = int(rest) + 1
+        elif op.startswith("v_mfma"):
+            operands = args[1] | args[2] | args[3]
+            late = [x for x in operands if written.get(x, 0) > free]
+            if args[3] != args[0]:
+                late += [x for x in operands if ready.get(x, 0) > free]
+                c = dict.fromkeys(args[3], READ)
+            bad = [(t, x) for x in late]
+            took, r, f = free + 1, dict.fromkeys(args[0], READY), EIGHT - 1
+        else:
+            bad = [(t, x) for x in frozenset().union(*args) if ready.get(x, 0) > 0]
+            if (op.startswith("v_") and not op.startswith("v_cmp")) or re.match(r"(ds_read|buffer_load|global_load|scratch_load)", op):
+                bad += [(t, x, "third operand") for x in args[0] if read.get(x, 0) > 0]
+                if op.startswith("v_"):
+                    w = dict.fromkeys(args[0], WRITTEN)
+        age = lambda d, n: {x: v - took for x, v in d.items() if v > took and x not in n}
+        return ({**age(written, w), **w}, {**age(ready, r), **r}, {**age(read, c), **c}, max(f, free - took, 0)), bad
+
+    def merge(a, b):
+        most = lambda x, y: {k: max(x.get(k, 0), y.get(k, 0)) for k in x.keys() | y.keys()}
+        return b if a is None else (most(a[0], b[0]), most(a[1], b[1]), most(a[2], b[2]), min(a[3], b[3]))
+
+    products, bad = 0, set()
+    for code in kernels:
+        label = {c[0][:-1]: i for i, c in enumerate(code) if c[0].endswith(":")}
+        products += sum(c[1].startswith("v_mfma") for c in code)
+        entry, todo = {0: ({}, {}, {}, 0)}, [0]
+        while todo:
+            i = todo.pop()
+            state = entry[i]
+            while i < len(code):
+                t, op, rest, _ = code[i]
+                after = [i + 1]
+                if t.endswith(":"):
+                    merged = merge(entry.get(i), state)
+                    if i in entry and merged == entry[i] and state != entry[i]:
+                        break
+                    entry[i] = state = merged
+                else:
+                    state, b = step(state, code[i])
+                    bad.update(b)
+                    if op in ("s_branch", "s_endpgm"):
+                        after = []
+                    if "branch" in op:
+                        j = label[rest]
+                        merged = merge(entry.get(j), state)
+                        if entry.get(j) != merged:
+                            entry[j] = merged
+                            todo.append(j)
+                if not after:
+                    break
+                i += 1
+    return products, sorted(bad, key=str)
+
+
 def test_assembly_products_keep_their_distance(tmp_path):
-    """attention_wide.hip issues matrix products from assembly blocks, inside which the compiler does not see them.  In the
-    listing of its kernels, taking every instruction at the earliest it can issue (a slot each, a product every eight): no
-    vector instruction writes an operand of a product less than two slots before it, and nothing but the next product of the
-    same sum touches a result less than 12 slots after its product."""
+    """attention_wide.hip issues matrix products from assembly blocks, inside which the compiler does not see them, so the waits
+    that it would put around them have to come from the code: looked for in the listing of its kernels, loops included."""
     import subprocess
     from paper_2211_05953_amd import build
     out = tmp_path / "wide.s"
     src = os.path.join(build.CSRC, "attention_wide.hip")
     subprocess.run([build._hipcc()] + build.FLAGS + ["-x", "hip", "-S", "--cuda-device-only", src, "-o", str(out)], check=True, capture_output=True)
-
-    def regs(op):
-        m = re.match(r"-?\|?([av])(?:\[(\d+):(\d+)\]|(\d+)\b)", op)
-        if not m:
-            return set()
-        lo, hi = (m.group(2), m.group(3)) if m.group(2) else (m.group(4), m.group(4))
-        return {(m.group(1), r) for r in range(int(lo), int(hi) + 1)}
-
-    products, bad, inside = 0, [], False
-    for line in out.read_text().split("\n"):
-        m = re.match(r"(_Z\w+):", line)
-        if m:
-            inside, t, free, written, ready = "wide_kernel" in m.group(1), 0, 0, {}, {}
-        text = line.split(";")[0].strip()
-        if not inside or not text or text.startswith(".") or text.endswith(":"):
-            continue
-        op, _, rest = text.partition(" ")
-        args = [regs(a) for a in re.split(r",\s*", rest.strip())]
-        if op == "s_nop":
-            t += int(rest) + 1
-        elif op.startswith("v_mfma"):
-            products += 1
-            t = max(t, free)
-            operands = args[1] | args[2] | args[3]
-            bad += [(text, r) for r in operands if t - written.get(r, -9) < 3]
-            if args[3] != args[0]:
-                bad += [(text, r) for r in operands if ready.get(r, 0) > t]
-            free = t + 8
-            ready.update({r: t + 12 for r in args[0]})
-            t += 1
-        else:
-            bad += [(text, r) for r in set().union(*args) if ready.get(r, 0) > t]
-            if op.startswith("v_") and not op.startswith("v_cmp"):
-                written.update({r: t for r in args[0]})
-            t += 1
+    products, bad = _listing_distances(out.read_text(), "wide_kernel")
     assert products > 200 and not bad, bad[:5]
+
+
+MFMA = "v_mfma_f32_32x32x16_bf16 "
+
+
+@pytest.mark.parametrize("code,n", [
+    ("v_mov_b32_e32 v0, v90\ns_nop 0\n" + MFMA + "v[16:31], v[0:3], v[4:7], v[16:31]", 1),       # an operand written one slot in front
+    ("v_mov_b32_e32 v0, v90\ns_nop 1\n" + MFMA + "v[16:31], v[0:3], v[4:7], v[16:31]", 0),
+    (MFMA + "v[16:31], v[0:3], v[4:7], v[16:31]\ns_nop 10\nv_mov_b32_e32 v90, v31", 1),            # a result read
+    (MFMA + "v[16:31], v[0:3], v[4:7], v[16:31]\ns_nop 11\nv_mov_b32_e32 v90, v31", 0),
+    (MFMA + "v[16:31], v[0:3], v[4:7], v[32:47]\ns_nop 5\nv_mov_b32_e32 v47, v90", 1),             # a third operand written
+    (MFMA + "v[16:31], v[0:3], v[4:7], v[32:47]\ns_nop 5\nds_read_b128 v[44:47], v90", 4),
+    (MFMA + "v[16:31], v[0:3], v[4:7], v[32:47]\ns_nop 6\nv_mov_b32_e32 v47, v90", 0),
+    (MFMA + "v[16:31], v[0:3], v[4:7], v[32:47]\nv_mov_b32_e32 v0, v90", 0),                       # (the other two are read at once)
+    (MFMA + "v[16:31], v[0:3], v[4:7], v[32:47]\n" + MFMA + "v[48:63], v[0:3], v[4:7], v[48:63]\nv_mov_b32_e32 v47, v90", 0),
+    (".LBB0_1:\nv_mov_b32_e32 v47, v90\ns_nop 15\n" + MFMA + "v[16:31], v[0:3], v[4:7], v[32:47]\ns_cbranch_scc1 .LBB0_1", 1),  # over a loop's end
+    (MFMA + "v[16:31], v[0:3], v[4:7], v[32:47]\ns_cbranch_scc1 .LBB0_1\ns_nop 15\n.LBB0_1:\nv_mov_b32_e32 v47, v90", 1),       # past a branch
+])
+def test_listing_distances_finds_what_is_too_close(code, n):
+    assert len(_listing_distances("_Zkernel:\n" + code + "\ns_endpgm\n", "kernel")[1]) == n
