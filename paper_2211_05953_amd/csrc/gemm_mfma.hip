@@ -514,7 +514,8 @@ __global__ __launch_bounds__(TL::NT * TL::KG) void gemm_mfma_kernel(int M, int N
     // thread finishes 8 adjacent columns (bias, residual, GeLU in fp32, one rounding) and the
     // global accesses of C, C2 and R are 16 bytes per lane over whole 512-byte row segments.
     constexpr int LDC = BN + 4;
-    float* cs = reinterpret_cast<float*>(smem);
+    // (with one group the array itself: behind the other pointer the stores lose their constant addresses)
+    float* cs = KG == 1 ? reinterpret_cast<float*>(smem_raw) : reinterpret_cast<float*>(smem);
     static_assert((size_t)PR * LDC * 4 <= 2 * (size_t)STAGE * sizeof(bf16_t), "epilogue staging does not fit");
     // E_GELU_BWD with colpart: the column sums of this tile's (rounded) outputs, i.e. the tile's share of the bias
     // gradient of the linear layer whose pre-activation gradient is being written; a thread keeps the sums of
