@@ -879,7 +879,9 @@ static bf_status in_rounds(int layout, int epi, const GemmArgs& a, int main, hip
 // Slices of a very long contraction (a 50304-word vocabulary's) on 256 x 256 tiles, as many as make the estimate of rounds and
 // of the pass over the planes the least; 0: not for these.  256 x 128 tiles in two slices / here, us: 2048 x 2048 x 50304 416 / 400 (3), 2048 x
 // 1024 x 50304 360 / 217 (6), 1024 x 1536 x 50304 314 / 189 (6), 2048 x 1024 x 32000 201 / 163 (4); at K = 8192 level (2048 x 2048 75.7 / 76.6 in 4, 1024 x
-// 2048 58.0 / 55.9), where two planes are less scratch.
+// 2048 58.0 / 55.9), where two planes are less scratch.  Up to 256 tiles of 64 x 64 two slices run on those, at 0.4 us per 128 of K
+// against 1.2 us per 64 of K and slice here: from six slices on.  Two on 64 x 64 / here: 256 x 1024 x 16384 55.5 / 48.5 (8), 512 x 512 x
+// 50304 161 / 160 (6; dgrad layout, 256 rows 157 / 159), 512 x 2048 x 50304 219 / 170, but 256 x 1024 x 32000 101 / 124 (5), 1024 x 1024 x 32000 116 / 128.
 static int big_slices(int M, int N, int K) {
   if (K < 16384 || M % 256 || N % 256 || K % BK) return 0;
   const long tiles = (long)(M / 256) * (N / 256);
@@ -893,7 +895,7 @@ static int big_slices(int M, int N, int K) {
     const double t = rounds * (K / s / BK) * K_TILE_US + s * (double)M * N * 8 / 4.5e6;  // planes written and read at 4.5 TB/s
     if (!best || t < best_t) { best = s; best_t = t; }
   }
-  return best;
+  return best < 6 && (M / 64) * (N / 64) <= 256 ? 0 : best;
 }
 
 bf_status gemm_mfma(int layout, int epi, const GemmArgs& a, hipStream_t st) {

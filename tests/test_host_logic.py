@@ -157,6 +157,16 @@ def test_tile_choice_invariants_without_a_device():
     assert bf.bf_op_gemm_tile(bf.BF_TN, bf.BF_EPI_NONE, 128, 128, 64) is None      # the weight-gradient layout stores fp32
 
 
+def test_slices_of_a_very_long_contraction_without_a_device():
+    """Contractions from 16384 on run in up to eight slices on large tiles, but not where up to 256 tiles of 64 x 64 take
+    two slices in less time, which is where K divides into fewer than six."""
+    for layout, epi in ((bf.BF_NN, bf.BF_EPI_BIAS_RES), (bf.BF_NT, bf.BF_EPI_NONE)):
+        s = lambda *shape: bf.bf_op_gemm_splitk_slices(layout, epi, *shape)
+        for M, N in ((256, 256), (256, 1024), (512, 512), (768, 512), (1024, 1024), (512, 2048)):
+            assert (s(M, N, 16384), s(M, N, 32000), s(M, N, 50304)) == (8, 2, 6), (M, N)
+        assert s(1024, 2048, 32000) == 5 and s(2048, 2048, 50304) == 3
+
+
 def _listing_distances(text, kernel):
     """Products and violations in a listing's kernels whose name contains `kernel`.  Every instruction is taken at the earliest it
     can issue (a slot each, a product every eight), along every path through the branches: a vector instruction writes an
