@@ -275,12 +275,24 @@ __device__ __forceinline__ void tile_product(int lin, int M, int N, int K, const
   // tile kt + 1 into the other stage, so the first fragments of the next tile arrive under the rest of the group's MFMAs.
   // A wave is alone on its SIMD or shares it with one more and issues in order, so whatever stands between two groups
   // leaves the matrix pipeline idle: the next group's fragments, the stores of the next tile and the loads of the
-  // one after go one or two at a time behind an MFMA each (64 cycles, of which its issue takes four).
+  // one after go one or two at a time behind an MFMA each (64 cycles, of which its issue takes four).  Not so the stores and
+  // loads of the smallest tile with K-contiguous rows: its k-tile is 16 short MFMAs, and loads a third of it later are not back
+  // in time for long contractions.  In front of the first MFMA / behind them, us: 768 x 256 x 2048 dgrad layout 16.6 / 17.7, forward
+  // 16.6 / 17.3, x 4096 30.4 / 32.3, 30.2 / 31.7, x 1024 level; weight gradient, whose rows are short, x 2048 21.6 / 17.1.
+  constexpr bool FRONT = C::MT == 16 && AK;
   constexpr int NG = 4 * C::MI * C::NI, PRE = NG / 4;                    // MFMAs of a group; those in front of the barrier
   constexpr int PER = (2 * NC + (C::KW - 1) * (NG - NF) - 1) / ((C::KW - 1) * (NG - NF));  // stores and loads behind one MFMA
   auto iter = [&](auto stagec) {
     constexpr int CUR = decltype(stagec)::value;  // LDS stage
     typedef std::integral_constant<int, CUR ^ 1> Next;
+    if constexpr (FRONT) {
+#pragma unroll
+      for (int c = 0; c < NC; ++c) store(Next{}, CUR ^ 1, c);
+      aim(Next{});
+#pragma unroll
+      for (int c = 0; c < NC; ++c) load(Next{}, c);
+      __builtin_amdgcn_sched_barrier(0);
+    }
 #pragma unroll
     for (int g = 0; g < C::KW; ++g) {
       const int buf = g & 1;
@@ -291,7 +303,7 @@ __device__ __forceinline__ void tile_product(int lin, int M, int N, int K, const
         if (g + 1 < C::KW) {
           if (m < NF) {
             fetch(buf ^ 1, CUR, g + 1, m);
-          } else {
+          } else if constexpr (!FRONT) {
 #pragma unroll
             for (int q = 0; q < PER; ++q) {
               const int item = (g * (NG - NF) + m - NF) * PER + q;
