@@ -19,6 +19,7 @@
 // bank conflicts.
 #include <float.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "attention_tiles.h"
@@ -1049,13 +1050,20 @@ bf_status bwd_edge(int S_mb, int S_seq, int N_heads, int causal, const void* qkv
     attn_bwd_dq_general_kernel<D, 128, true, 1><<<grid, NTHR, 0, st>>>((const bf16_t*)qkv, (const bf16_t*)ctx, (const bf16_t*)dctx, lse, delta, (bf16_t*)dqkv, S_seq, N_heads, S_mb, causal, scale, nullptr);
   // Two query groups (64 keys a workgroup, half of every query tile each) where the chip does not fill: a workgroup has a compute
   // unit to itself and takes 0.52 (S_head 128) or 0.6 (64) of the time of 128 keys with one group, so for bidirectional
-  // launches the rounds of 256 decide, and causal ones, whose longest key block is twice the mean, gain more.  Backward, one
-  // group / two, us, S_head 128: causal, 1000 tokens, 128 blocks of 128 keys 121 / 81, 256 136 / 104, 384 148 / 146, from 512
-  // level; bidirectional, 1000 tokens, 128 blocks 123 / 85, 256 (two rounds) 152 / 154, 384 (three for two) 291 / 254, 500 tokens,
-  // 192 blocks 84 / 86.  S_head 64: causal, 700 tokens, 192 blocks 58 / 46, 288 67 / 64, 384 69 / 74; bidirectional, 128
+  // launches the rounds of 256 decide.  Causal ones last as long as their longest key block, twice the mean, until the other
+  // blocks' tiles come to more than that per compute unit (`fill`, in longest blocks), and past that the second group only costs;
+  // long rows, with many blocks to even out, gain a little longer.  Backward, one group / two, us, S_head 128: causal,
+  // 1000 tokens, 128 blocks of 128 keys 121 / 81 (fill 0.28), 256 136 / 104 (0.56), 384 148 / 146 (0.84), 896 355 / 350 (2.0), 1024 388 / 399;
+  // 300 tokens, 192 blocks 62 / 48 (0.45), 384 79.7 / 83.5 (0.9), 200 tokens, 256 blocks 58 / 54 (0.75), 512 97.6 / 102.6 (1.5), 65 tokens, 128
+  // 34 / 31 (0.5), 256 38.4 / 40.2 (1.0); bidirectional, 1000 tokens, 128 blocks 123 / 85, 256 (two rounds) 152 / 154, 384 (three for two)
+  // 291 / 254, 500 tokens, 192 blocks 84 / 86.  S_head 64: causal, 700 tokens, 192 blocks 58 / 46 (0.41), 288 67 / 64 (0.61), 384 69 / 74
+  // (0.82), 2000 tokens, 256 blocks 18 % less (0.53), 320 2 % less (0.66), 384 6 % more (0.8); bidirectional, 128
   // blocks 74 / 58, 192 65 / 75, 384 in three rounds for two 115 / 112, 576 in five for three 170 / 179.
-  const long grid2 = (long)((S_seq + 63) / 64) * N_heads * S_mb, rounds1 = ((long)grid + 255) / 256, rounds2 = (grid2 + 255) / 256;
-  const bool two_query_groups = causal ? D == 128 || grid <= 288 : D == 128 ? rounds2 < 2 * rounds1 : 5 * rounds2 <= 8 * rounds1;
+  const long heads = (long)N_heads * S_mb, n = (S_seq + 63) / 64, blocks = (S_seq + 127) / 128;
+  const long grid2 = n * heads, rounds1 = ((long)grid + 255) / 256, rounds2 = (grid2 + 255) / 256;
+  const double fill = (double)heads * (double)(blocks * n - blocks * (blocks - 1)) / (256.0 * (double)n);
+  const double fill_max = D == 64 ? 0.68 : std::max(0.85, std::min(2.0, (double)n / 8));
+  const bool two_query_groups = causal ? fill <= fill_max : D == 128 ? rounds2 < 2 * rounds1 : 5 * rounds2 <= 8 * rounds1;
   if (two_query_groups && grid2 < (1l << 31))
     attn_bwd_dkv_kernel<D, true, 2><<<(unsigned)grid2, NTHR_DKV, 0, st>>>((const bf16_t*)qkv, (const bf16_t*)dctx, lse, delta, (bf16_t*)dqkv, S_seq, N_heads, S_mb, causal, scale, nullptr);
   else
