@@ -356,10 +356,12 @@ __global__ __launch_bounds__(256, G == 1 ? 2 : 1) void attn_bwd_dkv_wide_kernel(
 // Backward, 128- / 256-key form, us: causal, S_seq 2048, 32 heads 174 / 198, 40 210 / 207, 48 236 / 217, 64 302 / 266; 1024, 64
 // heads 110 / 120, 80 132 / 128, 96 151 / 150; shorter rows never: 512, 160 heads 103 / 106, 256, 400 heads 111 / 114; 4096, 16
 // heads 307 / 358, 24 415 / 393; bidirectional, 2048, 16 heads 160 / 200, 24 239 / 199, 64 521 / 441; 1024, 96 heads 243 / 248;
-// 512, 300 heads 256 / 246; 256, 256 heads 71 / 64, 300 heads 108 / 110.  S_head 64 is faster here throughout (4 x 1024 tokens, 16
-// heads, bidirectional 91 / 83; 8 x 1024 causal 108 / 99; 2048, 8 heads, causal 84 / 71; 128, 256 heads level).
+// 512, 300 heads 256 / 246; 256, 256 heads 71 / 64, 300 heads 108 / 110.  S_head 64 is faster here (4 x 1024 tokens, 16
+// heads, bidirectional 91 / 83; 8 x 1024 causal 108 / 99; 2048, 8 heads, causal 84 / 71; 256, 64 to 512 heads 1 to 4 % less), but not in launches
+// of more than 256 blocks that have two query tiles each, most of whose time are the loads and stores at either end, better hidden
+// by 16 waves to a unit than by 8 (128, 256 heads level, causal 400 heads 29.9 / 30.9, 512 30.7 / 31.4, bidirectional 512 30.8 / 31.7, 1024 56.1 / 57.6).
 bool attention_bwd_dkv_wide_better(int S_mb, int S_seq, int N_heads, int S_head, int causal) {
-  if (S_head == 64) return true;
+  if (S_head == 64) return S_seq > 128 || (long)N_heads * S_mb <= 256;
   if (S_seq % 256 || (causal && S_seq < 1024)) return false;
   const double n = S_seq / 128, hb = (double)N_heads * S_mb;  // tiles of a whole block: 2 n
   double narrow, wide;

@@ -706,10 +706,12 @@ def test_attention_backward_with_one_and_two_query_groups(d, causal, S_mb, S_seq
         assert np.isfinite(x).all() and rel_err(x, y) <= 2.0 ** -7, i
 
 
-@pytest.mark.parametrize("S_mb,S_seq,a", [(1, 384, 90), (1, 640, 60), (2, 1024, 20)])
-def test_attention_backward_with_one_key_block_to_a_unit(S_mb, S_seq, a):
-    """Heads of 64, causal, 257 to 340 blocks: the dK / dV kernel in its form of one workgroup per compute unit.  A handful of
-    heads against the oracle, and the bias gradient's partial rows against the sums of what was stored."""
+@pytest.mark.parametrize("causal,S_mb,S_seq,a", [(1, 1, 384, 90), (1, 1, 640, 60), (1, 2, 1024, 20), (0, 2, 384, 50), (0, 3, 1024, 12), (1, 4, 128, 64),
+                                                 (1, 5, 128, 52), (0, 5, 128, 52), (0, 4, 128, 64)])
+def test_attention_backward_of_heads_of_64_in_large_launches(causal, S_mb, S_seq, a):
+    """256 to 340 blocks of 128 keys: the dK / dV kernel of 32 keys a wave, and, above 256 blocks of a single one per head, the one
+    of eight waves in pairs.  A handful of heads against the oracle, and the bias gradient's partial rows against the sums of what
+    was stored."""
     d, h = 64, a * 64
     qkv, dctx = (bf_inputs.normal(43, i, (S_mb, S_seq, n * h), bf16=True) for i, n in ((0, 3), (1, 1)))
     dQKV, dDC = to_dev(qkv, True), to_dev(dctx, True)
@@ -717,13 +719,13 @@ def test_attention_backward_with_one_key_block_to_a_unit(S_mb, S_seq, a):
     lse, delta = (torch.full((S_mb, a, S_seq), float("nan"), device="cuda") for _ in range(2))
     part = torch.full((bf.bf_op_attention_bwd_part_elems(S_mb, S_seq, a, d) + 64,), float("nan"), device="cuda")
     db = torch.full((3 * h,), float("nan"), device="cuda")
-    bf.bf_op_attention_fwd(bf.BF_BF16, 0, S_mb, S_seq, a, d, 1, dQKV, ctx, lse)
-    bf.bf_op_attention_bwd_bias(bf.BF_BF16, 0, S_mb, S_seq, a, d, 1, dQKV, ctx, lse, dDC, dqkv, delta, db, part, 0)
+    bf.bf_op_attention_fwd(bf.BF_BF16, 0, S_mb, S_seq, a, d, causal, dQKV, ctx, lse)
+    bf.bf_op_attention_bwd_bias(bf.BF_BF16, 0, S_mb, S_seq, a, d, causal, dQKV, ctx, lse, dDC, dqkv, delta, db, part, 0)
     assert bool(torch.isnan(part[-64:]).all())
     for head in (0, 1, a // 2, a - 1):
         cols = slice(head * d, (head + 1) * d)
         one = np.concatenate([qkv[..., i * h:][..., cols] for i in range(3)], axis=-1).astype(np.float64)
-        ref, saved = L.attention_fwd(one, 1, True)
+        ref, saved = L.attention_fwd(one, 1, bool(causal))
         ref_d = L.attention_bwd(dctx[..., cols].astype(np.float64), saved, 1)
         assert rel_err(to_host(ctx)[..., cols], ref) <= TOL["bf16"]
         for i in range(3):
