@@ -65,7 +65,10 @@ def time_steps(st, bf, schedule, N_loop, N_mb, S_mb, x, dy, y, dx, steps, warmup
     for _ in range(steps):
         reports.append(run(timing))
     torch.cuda.synchronize()
-    return (time.perf_counter() - t0) / steps, reports
+    sec = (time.perf_counter() - t0) / steps
+    for rp in reports:
+        rp.launches_made = st.bf_get_launch_counts()  # the same for every step
+    return sec, reports
 
 
 def cpu_baseline(w, causal=True):
@@ -323,7 +326,7 @@ def main():
         out = {}
         for i, name in enumerate(bf.binding.KERNEL_CLASSES):
             ms = sum(rp.kernel_ms[i] for rp in reps) / len(reps)
-            n = sum(rp.kernel_launches[i] for rp in reps) / len(reps)
+            n = sum(rp.launches_made[i] for rp in reps) / len(reps)
             fl = sum(rp.kernel_flops[i] for rp in reps) / len(reps)
             by = sum(rp.kernel_bytes[i] for rp in reps) / len(reps)
             if n:
@@ -344,7 +347,7 @@ def main():
     # the opening copy's readings) gave for this command.  The algorithmic bytes (every operand read once,
     # the result written once) stand beside it.
     roofline["traffic_algorithmic"] = sum(rp.kernel_bytes[bf.binding.KERNEL_CLASSES.index(dom)] for rp in rep_bf) / \
-        max(1, sum(rp.kernel_launches[bf.binding.KERNEL_CLASSES.index(dom)] for rp in rep_bf))
+        max(1, sum(rp.launches_made[bf.binding.KERNEL_CLASSES.index(dom)] for rp in rep_bf))
     roofline["traffic_source"] = None
     traffic_file = os.path.join(ROOT, "profiles", "traffic.json")
     if os.path.exists(traffic_file):

@@ -161,7 +161,8 @@ typedef struct {
   int32_t timed;            /* 1 if gpu_ms / adam_ms are valid (bf_run_step ... timing != 0) */
   /* timing == 2 (every class) or 3 (the weight-gradient products): per kernel class, summed over
    * the step's launches: device time between events recorded around each launch on its stream, launch count (a launch that
-   * serves several micro-batches counts as that many), algorithmic flops
+   * serves several micro-batches, or takes several fp32 weight gradients of a stage together, counts as that many: the count
+   * does not depend on what shares a launch; bf_get_launch_counts has the launches as made), algorithmic flops
    * (2 M N K per product; attention with the causal half; backward attention 2.5 x forward) and
    * algorithmic HBM bytes (every operand read once, every result written once).  With two chains of
    * micro-batches (mb_chains = 2) launches of the two streams overlap, so the classes' times add up to
@@ -285,6 +286,11 @@ bf_status bf_run_lm_step(bf_stack* s, int schedule, int N_loop, int N_mb, int S_
 
 /* Integer event trace of the last bf_run_step / bf_run_rank_step: copies min(cap, n) events, *n = total. */
 bf_status bf_get_trace(const bf_stack* s, bf_event* dst, size_t cap, size_t* n);
+
+/* Timed launches of the last step as they were made, per kernel class (dst: BF_N_KERNEL_CLASSES counts, all 0 unless the step
+ * had timing == 2 or 3): kernel_ms of its report over these is the mean time of a launch, over kernel_launches that
+ * of a micro-batch's share of it. */
+bf_status bf_get_launch_counts(const bf_stack* s, int64_t* dst);
 
 /* Pure host arithmetic, no device needed: the order in which rank `rank` of an N_PP-deep
  * looped pipeline runs its ops (stage index in the trace is the GLOBAL stage

@@ -80,6 +80,7 @@ _SIGNATURES = {
                                  C.POINTER(bf_step_report)]),
     "bf_run_rank_step": (C.c_int, [_P, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, _P, _P, _P, _P, C.c_int, C.c_int, _P,
                               C.POINTER(bf_step_report)]),
+    "bf_get_launch_counts": (C.c_int, [_P, C.POINTER(C.c_int64)]),
     "bf_get_trace": (C.c_int, [_P, C.POINTER(bf_event), C.c_size_t, C.POINTER(C.c_size_t)]),
     "bf_schedule_trace": (C.c_int, [C.c_int] * 7 + [C.POINTER(bf_event), C.c_size_t, C.POINTER(C.c_size_t),
                                                     C.POINTER(bf_sched_stats)]),
@@ -261,6 +262,12 @@ class Stack:
         buf = (bf_event * max(1, n.value))()
         check(load().bf_get_trace(self.handle, buf, n.value, C.byref(n)))
         return [(e.op, e.stage, e.mb, e.live_ckpt) for e in buf[:n.value]]
+
+    def bf_get_launch_counts(self):
+        """Timed launches of the last step as made, in the order of KERNEL_CLASSES."""
+        buf = (C.c_int64 * len(KERNEL_CLASSES))()
+        check(load().bf_get_launch_counts(self.handle, buf))
+        return list(buf)
 
 
 def bf_schedule_trace(schedule, N_PP, N_loop, N_mb, rank, t_fwd=1, t_bwd=2):

@@ -343,7 +343,7 @@ struct bf_stack {
   // directions of the meeting at a stage's end and the join at the step's end
   int chain;
   int chains_active;  // chains of the step being issued (1 outside a two-chain step)
-  int group_now;      // micro-batches the launches being issued serve (1 but for the layers of a grouped step)
+  int group_now;      // micro-batches (or products of a stage) the launches being issued serve: what kernel_launches counts
   float* g32b;
   hipStream_t chain_st;
   hipEvent_t ev_chain[4];
@@ -625,7 +625,7 @@ bf_status run_wgrads(bf_stack* s, WgradList& w, hipStream_t st) {
       flops += 2.0 * m * nn * k;
       bytes += 4.0 * (m * k + k * nn + m * nn);
     }
-    s->group_now = n;  // counted as the launches it stands for
+    s->group_now = n;  // counted as the products it takes
     const bf_status r = timed(s, BF_K_GEMM_WGRAD, flops, bytes, st, [&] { return gemm_f32_batch(w.a, n, st); });
     s->group_now = 1;
     return r;
@@ -888,6 +888,13 @@ bf_status bf_get_trace(const bf_stack* s, bf_event* dst, size_t cap, size_t* n) 
     const size_t k = cap < s->trace.size() ? cap : s->trace.size();
     if (k) memcpy(dst, s->trace.data(), k * sizeof(bf_event));
   }
+  return BF_OK;
+}
+
+bf_status bf_get_launch_counts(const bf_stack* s, int64_t* dst) {
+  if (!s || !dst) { set_error("bf_get_launch_counts: null argument"); return BF_EINVAL; }
+  for (int k = 0; k < BF_N_KERNEL_CLASSES; ++k) dst[k] = 0;
+  for (const auto& r : s->prof_rec) dst[r.cls] += 1;
   return BF_OK;
 }
 

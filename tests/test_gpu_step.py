@@ -803,6 +803,30 @@ def test_timing_modes_fill_the_report_and_leave_the_numbers_alone(chains):
     st.close()
 
 
+@pytest.mark.parametrize("dtype,fuse,groups,wgrad", [(bf.BF_BF16, 1, 1, 4), (bf.BF_BF16, 0, 3, 12), (bf.BF_FP32, 1, 1, 1)])
+def test_launch_counts_of_grouped_micro_batches(dtype, fuse, groups, wgrad):
+    """kernel_launches counts micro-batches (and products) whatever shares a launch; bf_get_launch_counts the launches that were
+    made and timed: one for the three micro-batches of a stage here, and one for a stage's fp32 weight gradients."""
+    Lyr, N_loop, h, a, f, S_seq, S_mb, N_mb = 4, 4, 256, 2, 1024, 128, 1, 3
+    x, dy = bf_inputs.make_batch(37, N_mb, S_mb, S_seq, h, bf16=dtype == bf.BF_BF16)
+    st = bf.Stack(bf.make_config(h, a, f, S_seq, Lyr, N_mb, S_mb, dtype=dtype, fuse_wgrad=fuse, N_loop_min=N_loop))
+    K_ = {n: i for i, n in enumerate(bf.binding.KERNEL_CLASSES)}
+    dX, dDY = to_dev(x, dtype == bf.BF_BF16), to_dev(dy, dtype == bf.BF_BF16)
+    for timing in (2, 3, 1):
+        rep = st.bf_run_step(bf.BF_SCHED_BF, N_loop, N_mb, S_mb, dX, dDY, torch.empty_like(dX), torch.empty_like(dX), timing=timing)
+        torch.cuda.synchronize()
+        made = dict(zip(bf.binding.KERNEL_CLASSES, st.bf_get_launch_counts()))
+        if timing == 1:
+            assert not any(made.values())
+            continue
+        assert made["gemm_wgrad"] == wgrad * Lyr
+        assert rep.kernel_launches[K_["gemm_wgrad"]] == 4 * Lyr * (1 if fuse else N_mb)
+        for name, n in (("gemm_fwd", 4), ("gemm_dgrad", 4), ("attn_fwd", 1), ("attn_bwd", 1), ("ln_fwd", 2), ("ln_bwd", 2)):
+            assert made[name] == (n * Lyr * groups if timing == 2 else 0), name
+            assert rep.kernel_launches[K_[name]] == (n * Lyr * N_mb if timing == 2 else 0), name
+    st.close()
+
+
 @pytest.mark.parametrize("depth", [1, 3, 64])
 def test_bounded_launch_queue_changes_nothing_but_the_host_pace(depth):
     """queue_depth > 0: the host waits for the op issued `depth` ops earlier before issuing the next one
