@@ -73,8 +73,9 @@ typedef struct {
   int32_t causal;                                  /* 1: mask j > i (GPT); 0: bidirectional */
   int32_t kernels;                                 /* bf_kernels */
   int32_t queue_depth;  /* > 0: the host never runs more than this many stage-level ops ahead of
-                           the device (App. D.2, bounded kernel queue; ops that share launches count as one);
-                           0: unbounded */
+                           the device (App. D.2, bounded kernel queue; micro-batches that share launches, see
+                           fuse_wgrad, count one by one, and are issued as soon as nothing is ahead of the device
+                           where they are more than this); 0: unbounded */
   int32_t fuse_wgrad;   /* 1: in breadth-first order the weight-matrix gradients of a stage are taken once per
                            stage, as one product over all its micro-batches, after the stage's last backward
                            (breadth-first groups the work by stage, Sec. 4.2): the fp32 main-grad is written once

@@ -1050,7 +1050,7 @@ static bf_status run_rank_step(bf_stack* s, int schedule, int N_PP, int rank, bo
   }
   int live = 0;
   int64_t peak_live = 0;
-  size_t n_adam = 0, qi = 0;
+  size_t n_adam = 0;
   if (timing) BF_HIP_CHECK(hipEventRecord(s->ev_t0, st));
   if (chains == 2) {
     // the second chain starts after everything the caller's stream holds so far
@@ -1068,6 +1068,19 @@ static bf_status run_rank_step(bf_stack* s, int schedule, int N_PP, int rank, bo
     return record_for(s, layer - 1, m).y;
   };
 
+  // Bounded launch queue (App. D.2): behind an op the host waits for the one queue_depth in front of it.  Launches that serve a
+  // group of micro-batches count as that many ops: the waits that would stand between those come in front of the group (one, for
+  // the last of them).  An op inside a group is over when the group is, so a group as large as the bound or larger waits for
+  // everything in front of it.  One event for each of the last queue_depth groups, all on one stream: a group whose event has been
+  // recorded again has been waited for.
+  std::vector<long> issued;  // ops up to the end of each group
+  auto wait_for_op = [&](long o) -> bf_status {
+    if (o < 0 || issued.empty()) return BF_OK;
+    const size_t g = std::min((size_t)(std::upper_bound(issued.begin(), issued.end(), o) - issued.begin()), issued.size() - 1);
+    if (g + s->queue_ev.size() >= issued.size()) BF_HIP_CHECK(hipEventSynchronize(s->queue_ev[g % s->queue_ev.size()]));
+    return BF_OK;
+  };
+
   for (size_t oi = 0; oi < ops.size();) {
     const SchedOp& op = ops[oi];
     const int ls = local(op), l0 = ls * per_stage, l1 = l0 + per_stage, m = op.mb;
@@ -1076,6 +1089,7 @@ static bf_status run_rank_step(bf_stack* s, int schedule, int N_PP, int rank, bo
     while (ng < even && oi + ng < ops.size() && ops[oi + ng].op == op.op && ops[oi + ng].stage == op.stage && ops[oi + ng].mb == m + ng) ++ng;
     const int m_end = m + ng;
     s->group_now = 1;
+    if (!s->queue_ev.empty()) BF_TRY(wait_for_op((long)oi + ng - 2 - c.queue_depth));
     // the stream this op is issued on, and with it the set of temporaries and the arena of the small gradients
     hipStream_t os = stream_of(m);
     s->chain = chains == 2 ? m & 1 : 0;
@@ -1234,12 +1248,9 @@ static bf_status run_rank_step(bf_stack* s, int schedule, int N_PP, int rank, bo
       s->trace.push_back(bf_event{2, op.stage, -1, live});
     }
     if (!s->queue_ev.empty()) {
-      // bounded launch queue (App. D.2): wait for the op issued queue_depth ops ago (a group of micro-batches is as many
-      // launches as one, and counts as one)
-      hipEvent_t e = s->queue_ev[qi % s->queue_ev.size()];
-      if (qi >= s->queue_ev.size()) BF_HIP_CHECK(hipEventSynchronize(e));
-      BF_HIP_CHECK(hipEventRecord(e, os));
-      ++qi;
+      BF_TRY(wait_for_op((long)oi + ng - 1 - c.queue_depth));
+      BF_HIP_CHECK(hipEventRecord(s->queue_ev[issued.size() % s->queue_ev.size()], os));
+      issued.push_back((long)oi + ng);
     }
     oi += ng;
   }

@@ -850,6 +850,31 @@ def test_bounded_launch_queue_changes_nothing_but_the_host_pace(depth):
                 assert np.array_equal(a0["params"][l][name], a1["params"][l][name]), (l, name)
 
 
+@pytest.mark.parametrize("fuse,depth,waits", [(1, 1, True), (1, 5, True), (1, 9, True), (0, 5, True), (1, 12, False), (0, 12, False)])
+def test_bounded_launch_queue_counts_micro_batches_that_share_launches(fuse, depth, waits):
+    """A step of 12 ops behind work that keeps the device busy for longer than it takes to issue the step: with fewer than 12 in the
+    queue the call returns only after an op, and with it all of that work, is over, whether the three micro-batches of a
+    stage run one by one or (four groups) in the same launches."""
+    Lyr, N_loop, h, a, f, S_seq, S_mb, N_mb = 2, 2, 256, 2, 512, 128, 1, 3
+    x, dy = bf_inputs.make_batch(53, N_mb, S_mb, S_seq, h, bf16=True)
+    st = bf.Stack(bf.make_config(h, a, f, S_seq, Lyr, N_mb, S_mb, dtype=bf.BF_BF16, fuse_wgrad=fuse, N_loop_min=N_loop, queue_depth=depth))
+    dX, dDY = to_dev(x, True), to_dev(dy, True)
+    y, dx = torch.empty_like(dX), torch.empty_like(dX)
+    big = torch.ones((16384, 16384), device="cuda", dtype=torch.bfloat16)
+    out, busy = torch.empty_like(big), torch.cuda.Event()
+    step = lambda: st.bf_run_step(bf.BF_SCHED_BF, N_loop, N_mb, S_mb, dX, dDY, y, dx)
+    step()
+    torch.mm(big, big, out=out)
+    torch.cuda.synchronize()
+    for _ in range(40):  # 6 ms each
+        torch.mm(big, big, out=out)
+    busy.record()
+    step()
+    assert busy.query() == waits
+    torch.cuda.synchronize()
+    st.close()
+
+
 @pytest.mark.parametrize("ckpt", [bf.BF_CKPT_NONE, bf.BF_CKPT_LAYER])
 def test_activation_bytes_count_what_the_fused_weight_gradient_keeps(ckpt):
     """peak_act_bytes from the sizes of the stored tensors (bf16, S_mlp = 4 S_hidden: 32 S_hidden T bytes per layer
