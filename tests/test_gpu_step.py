@@ -243,6 +243,19 @@ def test_micro_batches_of_a_stage_share_launches(mode, dtype, Lyr, N_loop, h, a,
     st.close()
 
 
+def test_grouped_micro_batches_on_other_kernels_than_single_ones():
+    """Four micro-batches of six causal sequences of 1024, 4 heads of 128: dK / dV of one runs on 128 keys a workgroup, of the
+    group of four, 96 blocks' worth of heads, on 256, which rounds a probability to another bf16 neighbour now and then.
+    Both against the oracle at the bf16 bars."""
+    Lyr, N_loop, h, a, f, S_seq, S_mb, N_mb = 1, 1, 512, 4, 512, 1024, 6, 4
+    params = bf_inputs.make_params(61, Lyr, h, f, bf16=True)
+    x, dy = bf_inputs.make_batch(61, N_mb, S_mb, S_seq, h, bf16=True)
+    ref = _oracle(params, x, dy, K.SCHED_BF, N_loop, a)
+    for fuse in (1, 0):
+        cfg = bf.make_config(h, a, f, S_seq, Lyr, N_mb, S_mb, dtype=bf.BF_BF16, fuse_wgrad=fuse, N_loop_min=N_loop)
+        _compare(_run_gpu(cfg, params, x, dy, bf.BF_SCHED_BF, N_loop, N_mb, S_mb), ref, TOL["bf16"], Lyr)
+
+
 @pytest.mark.parametrize("Lyr,h,a,f,S_seq,N_mb", [(5, 96, 2, 200, 40, 3), (10, 256, 4, 1024, 33, 2), (5, 512, 8, 2048, 64, 2)])
 def test_weight_gradients_of_a_stage_share_a_launch(Lyr, h, a, f, S_seq, N_mb):
     """fp32: the weight gradients of a stage in one launch of up to 16, here of 20 or 40 (one stage), against those of one layer at

@@ -166,6 +166,30 @@ def test_lm_step_matches_oracle_in_both_orders(mode, dtype, ckpt, fuse, fs, Lyr,
     assert got["BF"]["report"].flops_model - base == 6.0 * S_voc * h * N_mb * S_mb * S_seq
 
 
+@pytest.mark.parametrize("mode,dtype,h,a,S_mb,N_mb,S_voc", [
+    ("fp32", bf.BF_FP32, 256, 4, 96, 3, 97),      # 12288 rows each: groups of 2 and 1
+    ("bf16", bf.BF_BF16, 256, 2, 60, 5, 640),     # 7680: 3 and 2
+])
+def test_lm_step_of_micro_batches_that_share_launches(mode, dtype, h, a, S_mb, N_mb, S_voc):
+    """Two groups of unequal size in a stage: the input and output layers still run micro-batch by micro-batch, on a group's rows.
+    Against a step that runs everything one by one: the losses and the five vocabulary tensors' gradients bit for bit (no product
+    here splits its contraction or an attention row's keys), the layers' to the rounding of fp32 sums over 38400 rows (a chain of n
+    additions of random terms ends about 2^-24 sqrt(n / 24) of its value off, 2.4e-6, and two are compared at their worst entry)."""
+    Lyr, N_loop, f, S_seq = 2, 2, 512, 128
+    b16 = dtype == bf.BF_BF16
+    params = bf_inputs.make_params(59, Lyr, h, f, bf16=b16)
+    vp = bf_inputs.make_vocab_params(59, S_voc, S_seq, h, init_std=0.1, bf16=b16)
+    tokens, labels = bf_inputs.make_tokens(59, N_mb, S_mb, S_seq, S_voc)
+    got, one = (_run_lm(bf.make_config(h, a, f, S_seq, Lyr, N_mb, S_mb, dtype=dtype, fuse_wgrad=fuse, N_loop_min=N_loop, S_voc=S_voc),
+                        params, vp, tokens, labels, bf.BF_SCHED_BF, N_loop, N_mb, S_mb) for fuse in (1, 0))
+    assert np.array_equal(got["loss_mb"], one["loss_mb"]) and got["trace"] == one["trace"]
+    for k in bf.VOCAB_TENSOR_IDS:
+        assert np.array_equal(got["vgrads"][k], one["vgrads"][k]), k
+    for l in range(Lyr):
+        for k in bf.TENSOR_IDS:
+            assert rel_err(got["grads"][l][k], one["grads"][l][k]) <= 1e-5, (l, k)
+
+
 def test_lm_optimizer_moves_input_and_output_layers_once():
     Lyr, N_loop, h, a, f, S_seq, S_mb, N_mb, S_voc = 2, 2, 64, 2, 256, 32, 1, 3, 50
     params = bf_inputs.make_params(31, Lyr, h, f)
