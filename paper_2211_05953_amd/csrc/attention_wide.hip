@@ -43,14 +43,14 @@ __device__ __forceinline__ uint32_t pack2(float a, float b) {
 // mfma_a the sums over tiles in the other half (ASM false: the builtin).  What the compiler then does not see: a product
 // must have two issue slots between it and vector instructions that write its operands (`nop` keeps them apart: for the first
 // products on new operands, and everywhere outside the loops over tiles, where the compiler may move registers about),
-// there must be 12 between a score's last product and its use (two further products, 16 slots, lie between), and 7 between
-// a product whose third operand is not its result and anything that writes that operand's registers: it is read over the
-// product's first 8 (`still_read` behind the next product keeps them from being given away at once).  tests/test_host_logic.py
+// and there must be 12 between a score's last product and its use (two further products, 16 slots, lie between).  A third operand
+// in registers of its own would be read over a product's first 8 slots, and nothing might write those registers for 7 of them;
+// there is none here: a sum is its own, and a first product starts from the constant.  tests/test_host_logic.py
 // looks for all three in the listing.  Loads into the operands are waited for as usual.
 template <bool ASM>
-__device__ __forceinline__ void mfma_v(f32x16& c, const bf16x8& a, const bf16x8& b, bool first, const f32x16& init, bool nop) {
-  if constexpr (!ASM) c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, first ? init : c, 0, 0, 0);
-  else if (first) asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %3" : "=&v"(c) : "v"(a), "v"(b), "v"(init));
+__device__ __forceinline__ void mfma_v(f32x16& c, const bf16x8& a, const bf16x8& b, bool first, bool nop) {
+  if constexpr (!ASM) c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, first ? zero16() : c, 0, 0, 0);
+  else if (first) asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(c) : "v"(a), "v"(b));
   else if (nop) asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b));
   else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b));
 }
@@ -60,7 +60,6 @@ __device__ __forceinline__ void mfma_a(f32x16& c, const bf16x8& a, const bf16x8&
   else if (nop) asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
   else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
 }
-__device__ __forceinline__ void still_read(const f32x16& c) { asm volatile("" :: "v"(c)); }
 template <bool ASM>
 __device__ __forceinline__ void zero_acc(f32x16& c) {
   c = zero16();
@@ -144,29 +143,19 @@ struct TileMover {
   }
 };
 
-// 16 rows' values of a statistic, in the accumulator's row order (p: the tile's, from this lane half's first row on)
-__device__ __forceinline__ f32x16 rows16(const float* p) {
-  f32x16 o;
-#pragma unroll
-  for (int q4 = 0; q4 < 4; ++q4) {
-    const f32x4 v = *reinterpret_cast<const f32x4*>(p + 8 * q4);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) o[4 * q4 + e] = v[e];
-  }
-  return o;
-}
-
 // ----------------------------------------------------------------- backward, dK/dV pass
 // 4 waves of 32 G keys, each with both gradients of its keys: S and dP, then P and dS from them, all in the wave (the 8-wave
-// form hands P from one wave to another).  S and dP start from the rows' -lse sqrt(d) and -delta in place of zero, which saves
-// two operations per element.  Phases of a sub-tile of 32 queries and what runs beside them: S; dP, exponentials of the
+// form hands P from one wave to another).  Every value is rounded where the 128-key form rounds it and every sum has its order, column
+// sums included, so the results are the same bits whichever form a launch takes, that is, however many sequences share it.
+// (S and dP started from the rows' -lse sqrt(d) and -delta save an operation per element, 1 % of the backward at S_head 128 and 3 %
+// at 64, and are other bits.)  Phases of a sub-tile of 32 queries and what runs beside them: S; dP, exponentials of the
 // first 10 rows of a lane; dV, the others and dS; dK, the rest of dS.
-// Backward of S_head 128, G = 2, S_seq 2048, 64 heads: causal 302 -> 266 us, bidirectional 521 -> 441.  Bound by the products: with
+// Backward of S_head 128, G = 2, S_seq 2048, 64 heads: causal 302 -> 272 us, bidirectional 512 -> 444.  Bound by the products: with
 // neither LDS reads, vector work nor the next tile's loads in the loop (bidirectional) 80 % of the kernel's time remains, a
 // tenth of it the loads of K and V and the stores at either end, which one workgroup per compute unit cannot hide; without
 // the LDS reads 87 %, the vector work 90 %, the loads 95 %.  Vector work of both products after both, in place of half after each,
-// costs 3 %.  S_head 64, G = 1 (two workgroups per compute unit, 1 KB per product as before, but no hand-over): 16 x 1024 tokens, 16
-// heads, bidirectional 319 -> 298; three to a unit want 168 registers and take 381.
+// costs 3 %.  S_head 64, G = 1 (two workgroups per compute unit, 1 KB per product as before, but no hand-over): 4 x 1024 tokens, 16
+// heads, bidirectional 89 -> 84; three to a unit want 168 registers and were slower.
 template <int D, int G>
 __global__ __launch_bounds__(256, G == 1 ? 2 : 1) void attn_bwd_dkv_wide_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dctx,
                                                                    const float* __restrict__ lse, const float* __restrict__ delta,
@@ -175,7 +164,7 @@ __global__ __launch_bounds__(256, G == 1 ? 2 : 1) void attn_bwd_dkv_wide_kernel(
   constexpr bool ASM = G == 2;
   constexpr int ROWS = 128 * G, NK = D / 16, NC = D / 16, PER = 2 * NK + 2 * NC, AHEAD = 3;  // steps of a score-sized product, of a gradient product, of a sub-tile
   __shared__ __attribute__((aligned(16))) bf16_t QOs[2][2][BLK * D];  // Q and dO tiles, double-buffered
-  __shared__ __attribute__((aligned(16))) float stat_s[2][2][BLK];    // -lse sqrt(d) and -delta of the tile's queries
+  __shared__ __attribute__((aligned(16))) float stat_s[2][2][BLK];    // -lse log2(e) and -delta of the tile's queries
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);  // (uniform, and with it the loop over tiles)
   const int nhb = N_heads * S_mb;
   const int kblk = blockIdx.x / nhb;  // earliest keys see the most queries: those blocks of every head go first
@@ -200,14 +189,14 @@ __global__ __launch_bounds__(256, G == 1 ? 2 : 1) void attn_bwd_dkv_wide_kernel(
 #pragma unroll
     for (int dt = 0; dt < D / 32; ++dt) { zero_acc<ASM>(dk[g][dt]); zero_acc<ASM>(dv[g][dt]); }
   }
-  const float c2 = scale * LOG2E, inv_scale = -1.0f / scale;
+  const float c2 = scale * LOG2E;
   const int jbeg = causal ? k0 / BLK : 0, nblk = S_seq / BLK;
   TileMover<D, D == 128 && G == 2 ? 2 : BLK * D / 8 / 256> mv;
   mv.init(base, 3 * h, dob, h, tid);
   const bool has_stat = tid < BLK;
   float lnext = 0.f, dnext = 0.f;
   auto next_stats = [&](int j) {
-    if (has_stat) { lnext = lrow[j * BLK + tid] * inv_scale; dnext = -drow[j * BLK + tid]; }
+    if (has_stat) { lnext = -(lrow[j * BLK + tid] * LOG2E); dnext = -drow[j * BLK + tid]; }
   };
   auto store_stats = [&](int stage) {
     if (has_stat) { stat_s[stage][0][tid] = lnext; stat_s[stage][1][tid] = dnext; }
@@ -236,15 +225,15 @@ __global__ __launch_bounds__(256, G == 1 ? 2 : 1) void attn_bwd_dkv_wide_kernel(
     };
     bf16x8 ring[AHEAD + 1];
     static_for<AHEAD>([&](auto ic) { ring[decltype(ic)::value] = frag(ic); });
-    f32x16 init = rows16(st0);  // what a score-sized product starts from
     static_for<2>([&](auto tc) {
       constexpr int t = decltype(tc)::value;
       f32x16 s[G], dp[G];
+      f32x4 nl[4], nd[4];        // -lse log2(e) and -delta of rows 4 q .. 4 q + 3, read two steps before their first use
       u32x4 pb[G][2], db[G][2];  // P and dS in bf16, rows 8 k .. 8 k + 7: the B operands of dV and dK
       // P = exp(S / sqrt(d) - lse) of row r
       auto exp_row = [&](int g, auto rc) {
         constexpr int r = decltype(rc)::value;
-        float v = __builtin_amdgcn_exp2f(s[g][r] * c2);
+        float v = __builtin_amdgcn_exp2f(fmaf(s[g][r], c2, nl[r / 4][r % 4]));
         if (DIAG && kw + 32 * g + (lane & 31) > qb + 32 * t + acc_row(r, lane)) v = 0.f;
         s[g][r] = v;
         if constexpr (r % 2 == 1) pb[g][r / 8][r % 8 / 2] = pack2(s[g][r - 1], v);
@@ -253,10 +242,13 @@ __global__ __launch_bounds__(256, G == 1 ? 2 : 1) void attn_bwd_dkv_wide_kernel(
       auto ds_row = [&](int g, auto rc) {
         constexpr int r = decltype(rc)::value;
         const uint32_t two = pb[g][r / 8][r % 8 / 2];
-        dp[g][r] *= __builtin_bit_cast(float, r % 2 ? two & 0xffff0000u : two << 16);
+        dp[g][r] = __builtin_bit_cast(float, r % 2 ? two & 0xffff0000u : two << 16) * (dp[g][r] + nd[r / 4][r % 4]);
         if constexpr (r % 2 == 1) db[g][r / 8][r % 8 / 2] = pack2(dp[g][r - 1], dp[g][r]);
       };
       constexpr int RB = 10, H = NC / 2;  // dV and dK need rows 0-7 first
+      // the step that takes row r first
+      constexpr auto exp_step = [](int r) { return r < RB ? NK + ((r + 1) * NK - 1) / RB : 2 * NK + ((r + 1 - RB) * H - 1) / (16 - RB); };
+      constexpr auto ds_step = [](int r) { return (r < 8 ? 2 * NK + H : 2 * NK + NC) + ((r % 8 + 1) * H - 1) / 8; };
       static_for<PER>([&](auto pc) {
         constexpr int p = decltype(pc)::value, i = t * PER + p;
         __builtin_amdgcn_sched_barrier(0);
@@ -265,12 +257,10 @@ __global__ __launch_bounds__(256, G == 1 ? 2 : 1) void attn_bwd_dkv_wide_kernel(
         static_for<G>([&](auto gc) {  // a product, then vector work in its shadow
           constexpr int g = decltype(gc)::value;
           if constexpr (p < NK) {
-            mfma_v<ASM>(s[g], f, kf[g][p], p == 0, init, DIAG);
-            if constexpr (ASM && p == 1 && g == 0) still_read(init);
+            mfma_v<ASM>(s[g], f, kf[g][p], p == 0, DIAG);
           } else if constexpr (p < 2 * NK) {
             constexpr int k = p - NK;
-            mfma_v<ASM>(dp[g], f, vf[g][k], k == 0, init, DIAG);
-            if constexpr (ASM && k == 1 && g == 0) still_read(init);
+            mfma_v<ASM>(dp[g], f, vf[g][k], k == 0, DIAG);
             __builtin_amdgcn_sched_barrier(0);
             share<0, RB, k, NK>([&](auto rc) { exp_row(g, rc); });
           } else if constexpr (p < 2 * NK + NC) {
@@ -287,8 +277,11 @@ __global__ __launch_bounds__(256, G == 1 ? 2 : 1) void attn_bwd_dkv_wide_kernel(
           }
           __builtin_amdgcn_sched_barrier(0);
         });
-        if constexpr (p == NK - 2) init = rows16(st0 + BLK + 32 * t);
-        if constexpr (t == 0 && p == PER - 2) init = rows16(st0 + 32);
+        static_for<4>([&](auto qc) {
+          constexpr int q = decltype(qc)::value;
+          if constexpr (p == exp_step(4 * q) - 2) nl[q] = *reinterpret_cast<const f32x4*>(st0 + 32 * t + 8 * q);
+          if constexpr (p == ds_step(4 * q) - 2) nd[q] = *reinterpret_cast<const f32x4*>(st0 + BLK + 32 * t + 8 * q);
+        });
         mv.template step<i, 2 * PER>(jn, next);
       });
     });
@@ -325,25 +318,25 @@ __global__ __launch_bounds__(256, G == 1 ? 2 : 1) void attn_bwd_dkv_wide_kernel(
     end_tile();
   }
   if constexpr (ASM) drain();
+  const int ln = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));  // (the lane again: no register holds it over the loop)
+  // (the loop ended on a barrier; a sum is read out for the store and for its column sums at once)
+  float* red = reinterpret_cast<float*>(&QOs[0][0][0]);
+  float colscale = scale;
+  asm("" : "+v"(colscale));  // (not the products that were stored: multiplied and added in one operation, as in the 128-key form)
 #pragma unroll
   for (int g = 0; g < G; ++g) {
-    bf16_t* out = dqkv + ((size_t)b * S_seq + kw + 32 * g + (lane & 31)) * ld + head * D;
-    store_rows<D>(dk[g], out + h, lane, scale);
-    store_rows<D>(dv[g], out + 2 * h, lane, 1.0f);
+    bf16_t* out = dqkv + ((size_t)b * S_seq + kw + 32 * g + (ln & 31)) * ld + head * D;
+    store_rows<D>(dk[g], out + h, ln, scale);
+    if (colpart) wave_colsum<D>(dk[g], colscale, red + (size_t)(4 * G + w * G + g) * 4 * (D / 2), ln);
+    store_rows<D>(dv[g], out + 2 * h, ln, 1.0f);
+    if (colpart) wave_colsum<D>(dv[g], 1.0f, red + (size_t)(w * G + g) * 4 * (D / 2), ln);
   }
   if (colpart) {
-    // rows (b, 128 keys) of the partial column sums of [dK | dV], [S_mb * S_seq / 128][2 N_heads * D]; the loop ended on a barrier
-    float* red = reinterpret_cast<float*>(&QOs[0][0][0]);
-#pragma unroll
-    for (int g = 1; g < G; ++g)
-#pragma unroll
-      for (int dt = 0; dt < D / 32; ++dt) { dk[0][dt] += dk[g][dt]; dv[0][dt] += dv[g][dt]; }
-    wave_colsum<D>(dv[0], 1.0f, red + (size_t)w * 4 * (D / 2), lane);
-    wave_colsum<D>(dk[0], scale, red + (size_t)(4 + w) * 4 * (D / 2), lane);
+    // rows (b, 128 keys) of the partial column sums of [dK | dV], [S_mb * S_seq / 128][2 N_heads * D], 32 keys at a time in order
     __syncthreads();
-    for (int c = tid; c < 2 * D * G; c += 256) {
-      const int blk = c / (2 * D), dvs = c / D % 2, d = c % D;  // 4 / G waves to 128 keys
-      colpart[((size_t)b * (S_seq / WG_ROWS) + kblk * G + blk) * 2 * h + dvs * h + head * D + d] = colsum_of<D>(red, (dvs ? 0 : 4) + blk * (4 / G), 4 / G, d);
+    for (int c = 64 * w + ln; c < 2 * D * G; c += 256) {
+      const int blk = c / (2 * D), dvs = c / D % 2, d = c % D;
+      colpart[((size_t)b * (S_seq / WG_ROWS) + kblk * G + blk) * 2 * h + dvs * h + head * D + d] = colsum_of<D>(red, (dvs ? 0 : 4 * G) + blk * 4, 4, d);
     }
   }
 }
@@ -356,12 +349,12 @@ __global__ __launch_bounds__(256, G == 1 ? 2 : 1) void attn_bwd_dkv_wide_kernel(
 // Backward, 128- / 256-key form, us: causal, S_seq 2048, 32 heads 174 / 198, 40 210 / 207, 48 236 / 217, 64 302 / 266; 1024, 64
 // heads 110 / 120, 80 132 / 128, 96 151 / 150; shorter rows never: 512, 160 heads 103 / 106, 256, 400 heads 111 / 114; 4096, 16
 // heads 307 / 358, 24 415 / 393; bidirectional, 2048, 16 heads 160 / 200, 24 239 / 199, 64 521 / 441; 1024, 96 heads 243 / 248;
-// 512, 300 heads 256 / 246; 256, 256 heads 71 / 64, 300 heads 108 / 110.  S_head 64 is faster here (4 x 1024 tokens, 16
-// heads, bidirectional 91 / 83; 8 x 1024 causal 108 / 99; 2048, 8 heads, causal 84 / 71; 256, 64 to 512 heads 1 to 4 % less), but not in launches
-// of more than 256 blocks that have two query tiles each, most of whose time are the loads and stores at either end, better hidden
-// by 16 waves to a unit than by 8 (128, 256 heads level, causal 400 heads 29.9 / 30.9, 512 30.7 / 31.4, bidirectional 512 30.8 / 31.7, 1024 56.1 / 57.6).
+// 512, 300 heads 256 / 246; 256, 256 heads 71 / 64, 300 heads 108 / 110.  S_head 64, eight waves in pairs / here: 4 x 1024 tokens, 16 heads,
+// bidirectional 89 / 84; 2048, 8 heads, causal 84 / 73; from S_seq 640 on 2 to 10 % less in launches of 32 to 1536 blocks of 128 keys, 512 1 to 5 %
+// less, 384 level to 4 % less (causal, 768 blocks 2 % more).  Rows of two and four query tiles, most of whose time are the loads and stores at
+// either end, better hidden by 16 waves to a unit than by 8: 128 3 to 4 % more up to 256 blocks, level above, 256 level up to 256, 1 to 4 % more above.
 bool attention_bwd_dkv_wide_better(int S_mb, int S_seq, int N_heads, int S_head, int causal) {
-  if (S_head == 64) return S_seq > 128 || (long)N_heads * S_mb <= 256;
+  if (S_head == 64) return S_seq > 256;
   if (S_seq % 256 || (causal && S_seq < 1024)) return false;
   const double n = S_seq / 128, hb = (double)N_heads * S_mb;  // tiles of a whole block: 2 n
   double narrow, wide;

@@ -706,12 +706,38 @@ def test_attention_backward_with_one_and_two_query_groups(d, causal, S_mb, S_seq
         assert np.isfinite(x).all() and rel_err(x, y) <= 2.0 ** -7, i
 
 
+@pytest.mark.parametrize("d,causal,S_mb,S_seq,a", [(128, 1, 6, 1024, 16), (128, 1, 4, 2048, 12), (128, 0, 4, 256, 64), (128, 0, 3, 768, 22)])
+def test_attention_backward_is_the_same_bits_in_batches(d, causal, S_mb, S_seq, a):
+    """dK / dV of a batch run on 256 keys a workgroup, of its sequences one by one on 128: the same roundings and sums, so the same
+    bits; and the column sums' partial rows, in the batch's order, too."""
+    h = a * d
+    assert S_seq % 256 == 0
+    qkv, dctx = (to_dev(bf_inputs.normal(67, i, (S_mb, S_seq, n * h), bf16=True), True) for i, n in ((0, 3), (1, 1)))
+    ctx, lse = torch.empty_like(dctx), torch.empty((S_mb, a, S_seq), device="cuda")
+    bf.bf_op_attention_fwd(bf.BF_BF16, 0, S_mb, S_seq, a, d, causal, qkv, ctx, lse)
+
+    def backward(m0, m1):
+        n = m1 - m0
+        dqkv, delta = torch.empty_like(qkv[m0:m1]), torch.empty((n, a, S_seq), device="cuda")
+        part = torch.zeros(bf.bf_op_attention_bwd_part_elems(n, S_seq, a, d), device="cuda")
+        db = torch.empty(3 * h, device="cuda")
+        bf.bf_op_attention_bwd_bias(bf.BF_BF16, 0, n, S_seq, a, d, causal, qkv[m0:m1], ctx[m0:m1], lse[m0:m1], dctx[m0:m1], dqkv, delta, db, part, 0)
+        return dqkv, part
+
+    dqkv, part = backward(0, S_mb)
+    rows = S_mb * S_seq // 128                      # of [dK | dV], at the end of the partial rows
+    kv = part[part.numel() - rows * 2 * h:].reshape(S_mb, -1)
+    for m in range(S_mb):
+        one, p1 = backward(m, m + 1)
+        assert torch.equal(one[0, :, h:], dqkv[m, :, h:]), m
+        assert torch.equal(p1[p1.numel() - kv.shape[1]:], kv[m]), m
+
+
 @pytest.mark.parametrize("causal,S_mb,S_seq,a", [(1, 1, 384, 90), (1, 1, 640, 60), (1, 2, 1024, 20), (0, 2, 384, 50), (0, 3, 1024, 12), (1, 4, 128, 64),
                                                  (1, 5, 128, 52), (0, 5, 128, 52), (0, 4, 128, 64)])
 def test_attention_backward_of_heads_of_64_in_large_launches(causal, S_mb, S_seq, a):
-    """256 to 340 blocks of 128 keys: the dK / dV kernel of 32 keys a wave, and, above 256 blocks of a single one per head, the one
-    of eight waves in pairs.  A handful of heads against the oracle, and the bias gradient's partial rows against the sums of what
-    was stored."""
+    """256 to 340 blocks of 128 keys: the dK / dV kernel of 32 keys a wave, and, in short rows, the one of eight waves in pairs.  A
+    handful of heads against the oracle, and the bias gradient's partial rows against the sums of what was stored."""
     d, h = 64, a * 64
     qkv, dctx = (bf_inputs.normal(43, i, (S_mb, S_seq, n * h), bf16=True) for i, n in ((0, 3), (1, 1)))
     dQKV, dDC = to_dev(qkv, True), to_dev(dctx, True)
