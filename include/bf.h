@@ -84,9 +84,16 @@ typedef struct {
                            With stored activations (BF_CKPT_NONE) the micro-batches of a stage also share launches, as
                            many of them as it takes for the layer's narrowest product to fill the chip (2^24 outputs:
                            8192 rows at S_hidden 2048, one 2048-row micro-batch at 8192); their rows are then those of
-                           one larger micro-batch, so that bias and LayerNorm gradients are the same sums in another
-                           order, and outputs agree with DF's to the rounding of the outputs where the larger product
-                           or attention launch is not split as the smaller one is (else bitwise).
+                           one larger micro-batch.  Bias and LayerNorm gradients are then the same sums in another
+                           order.  How a sum is cut depends on the rows of a launch: a contraction into slices or
+                           between groups of waves, an attention row's keys between groups of waves and, for S_seq that
+                           is no multiple of 128, a key's queries.  Where a group's launches cut as a micro-batch's
+                           do, outputs are DF's bit for bit, elsewhere they agree to the rounding of the outputs.
+                           Micro-batches do not share launches (and cost what they did one by one) with mb_chains = 2,
+                           with kernels = BF_KERNELS_PLAIN, in steps of S_mb < S_mb_max (their rows do not follow each
+                           other in the workspace: lay a stack out for the S_mb it runs), and where the bytes of a
+                           micro-batch's [S_mb_max, S_seq, S_hidden] or [S_mb_max, S_seq, S_mlp] tensor are no
+                           multiple of 256.
                            The per-micro-batch operands of one stage are kept until then (with
                            BF_CKPT_LAYER: the recomputed ones).  0: accumulate per micro-batch. */
   int32_t N_loop_min;   /* smallest N_loop bf_run_step will be called with (0 or 1: any).  Sizes the per-stage
@@ -115,20 +122,20 @@ typedef struct {
                            even micro-batches run on the caller's stream, odd ones on a second stream of the stack's,
                            each chain with its own backward temporaries; the chains meet once per stage, for the
                            stage-wide weight-gradient products and the optimizer step.  Pays where one micro-batch's
-                           kernels do not fill the chip (a 2048-wide model: step 43 -> 36 ms); costs an 8192-wide one
+                           kernels do not fill the chip and micro-batches do not share launches (see fuse_wgrad; a
+                           2048-wide model with per-layer checkpoints: step 53 -> 44 ms); costs an 8192-wide one
                            2 to 7 %.  The workspace grows by a second set of backward temporaries and a second fp32
                            gradient arena of the layers' size (with BF_CKPT_LAYER also by a second recomputation
                            record).  Needs fuse_wgrad = 1, dp_fs = 0, queue_depth = 0, S_voc = 0, and y and
                            dx given to bf_run_step / bf_run_rank_step; depth-first steps and steps of
                            one micro-batch run as with 1.  A two-chain step runs every micro-batch in launches of its
-                           own (a one-chain step shares them, see fuse_wgrad, and is the faster of the two where
-                           activations are stored: 2048-wide, 32 ms).  It splits no contraction and, with whole blocks
-                           of 128 rows and more than 128 of them, no row's keys (the one-chain step does where a product or an
-                           attention launch leaves the chip idle; results then differ by the rounding of the outputs,
-                           otherwise outputs and weight-matrix gradients are the same bits).  Bias and LayerNorm
-                           gradients are then (sum over even) + (sum over odd micro-batches): equal to the one-chain
-                           result to fp32 rounding, and the same bits from run to run.  0 or 1: one micro-batch at
-                           a time. */
+                           own (a one-chain step shares them where activations are stored, and is then the faster of
+                           the two: 2048-wide, 33 ms against 36).  It cuts no contraction into slices and, with whole blocks
+                           of 128 rows and more than 128 of them, no row's keys, as the one-chain step does where a product
+                           or an attention launch leaves the chip idle.  Where both cut their sums alike (see fuse_wgrad),
+                           outputs and weight-matrix gradients are the same bits, elsewhere they agree to the rounding
+                           of the outputs.  Bias and LayerNorm gradients are then (sum over even) + (sum over odd micro-batches): equal to the one-chain
+                           result to fp32 rounding, and the same bits from run to run.  0 or 1: one chain. */
 } bf_config;
 
 /* Integer event trace of a step. op: 0 forward, 1 backward, 2 optimizer (mb = -1).
@@ -261,7 +268,11 @@ bf_status bf_run_step(bf_stack* s, int schedule, int N_loop, int N_mb, int S_mb,
  *           gradient arriving at that stage's output
  *   y, dx   device outputs of the same shape (either may be NULL): the stage's output and the gradient
  *           leaving its input
- * so the rank's stages do not feed each other (at N_PP = 1 bf_run_step chains them instead).  Everything
+ * so the rank's stages do not feed each other (at N_PP = 1 bf_run_step chains them instead).  Micro-batches of a
+ * stage that share launches (bf_config.fuse_wgrad) do so here too: x of all of them has to be there (in stream order)
+ * when the first one's op starts, and y and dx of all are there when the last one's ends.  A rank that receives
+ * micro-batches one by one waits for a group's last, which the times of bf_schedule_trace, micro-batch by
+ * micro-batch, do not show; with fuse_wgrad = 0 every op is a micro-batch's own.  Everything
  * else (optimizer per stage when its gradient is final, fuse_wgrad in breadth-first order, dp_fs, timing,
  * report, trace with GLOBAL stage indices, error codes) is as for bf_run_step; BF_EINVAL also for a rank
  * outside 0..N_PP-1 or an N_mb the order does not allow. */

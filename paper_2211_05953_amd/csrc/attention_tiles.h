@@ -134,9 +134,9 @@ __device__ __forceinline__ void pack8_parts(const f32x16& a, int kk, bf16x8& hi,
 // infinite key would.  These lengths used to run on fp32 kernels, so probabilities and their gradients keep their 24 bits:
 // they enter the products as three bf16 operands.  (Two, 16 bits, are 4 % faster at S_head 128 and 10-20 % at 64, but nearly
 // uniform rows over values that cancel were 10 to 30 % further from the exact results than those kernels'.)
-// 2 x 1000 tokens, 16 heads of 128, causal, forward / backward: 422 / 911 us on fp32 matrix instructions, 44 / 149 here (bound
-// by the chain score -> exponential -> three-part product of one or two waves per SIMD; the longest key block sets the
-// end); 4 x 1000, 16 heads of 64, bidirectional: 52 / 218.
+// 2 x 1000 tokens, 16 heads of 128, causal, forward / backward: 422 / 911 us on fp32 matrix instructions, 45 / 126 here (bound
+// by the chain score -> exponential -> three-part product of one or two waves per SIMD); 4 x 1000, 16 heads of 64,
+// bidirectional: 51 / 175.
 // A zero times an infinity is a NaN in a matrix instruction, but a masked pair must not touch its row, and neither must the
 // smaller parts of a probability (zero or negative) take an infinity's sign: where a tile holds non-finite values, or a score
 // gradient is past what bf16 holds, the tile's rows are added element by element, allowed pairs only.

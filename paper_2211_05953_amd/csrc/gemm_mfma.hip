@@ -825,6 +825,7 @@ void gemm_mfma_tile(int layout, int epi, int M, int N, int* bm, int* bn) {
 // 50304 x 2048 393 / 365 (256 x 192 tiles), x 512 138 / 130, 1024 x 50304 x 1024 115 / 108, 2048 x 8320 x 2048 89 / 79; forward 431 / 409; weight gradient
 // 50304 x 2048 x 2048 436 / 393, 50304 x 1024 x 2048 236 / 212, 9216 x 2048 x 4096 187 / 147; not taken: 50304 x 512 x 2048 116 / 126, dgrad 2048 x
 // 9216 x 8192 270 / 278 (1.5 rounds of 256 x 192), 2048 x 32000 x 1024 123 / 126.
+// Sizes whose 256-wide tiles across do not divide 256 (1536, 3072, 6144) keep one grid: a round of theirs is no rectangle.
 // 0, or the rows / columns of the whole rounds.
 static int whole_rounds(int layout, int epi, int M, int N, int K, bool shared_chip) {
   const int fixed = layout == L_TN ? N : M, var = layout == L_TN ? M : N, across = fixed / 256;

@@ -137,8 +137,9 @@ struct WsLayout {
   size_t total;
 };
 
-// How many micro-batches of a stage one launch of a breadth-first step serves.  They are all there when the stage starts
-// and do not depend on each other (Sec. 4.1), their rows follow each other in memory, and every kernel of a layer treats its
+// How many micro-batches of a stage one launch of a breadth-first step serves.  They do not depend on each other and, on a rank
+// that holds all stages, are all there when the stage starts (Sec. 4.1; a rank of a deeper pipeline has them one after the other and
+// waits for a group's last), their rows follow each other in memory, and every kernel of a layer treats its
 // rows (or its sequences) alike, so g of them are simply g times the rows.  As many as it takes for the layer's narrowest
 // product, T x h, to be one whole round of 256 x 256 tiles over the 256 compute units, 2^24 output elements: below that
 // the launches leave compute units idle or do not outlast their own latency, above it nothing is gained (an 8192-wide

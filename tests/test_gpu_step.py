@@ -244,9 +244,9 @@ def test_micro_batches_of_a_stage_share_launches(mode, dtype, Lyr, N_loop, h, a,
 
 
 def test_grouped_micro_batches_on_other_kernels_than_single_ones():
-    """Four micro-batches of six causal sequences of 1024, 4 heads of 128: dK / dV of one runs on 128 keys a workgroup, of the
-    group of four, 96 blocks' worth of heads, on 256, which rounds a probability to another bf16 neighbour now and then.
-    Both against the oracle at the bf16 bars."""
+    """Four micro-batches of six causal sequences of 1024, 4 heads of 128: the forward of one shares a row's keys between two groups of
+    waves and its dK / dV runs on 128 keys a workgroup; of the group of four, 96 heads' worth, a row has one group and dK / dV
+    256 keys.  Both against the oracle at the bf16 bars."""
     Lyr, N_loop, h, a, f, S_seq, S_mb, N_mb = 1, 1, 512, 4, 512, 1024, 6, 4
     params = bf_inputs.make_params(61, Lyr, h, f, bf16=True)
     x, dy = bf_inputs.make_batch(61, N_mb, S_mb, S_seq, h, bf16=True)
